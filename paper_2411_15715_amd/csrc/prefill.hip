@@ -9,17 +9,22 @@
 // stages filled by direct global->LDS loads (global_load_lds_dwordx4, no VGPR staging), wave tile
 // (BM/2) x 64.  A row tile holds up to 256 rows, the last one of an expert up to 320 (si_internal.h: n_row_tiles);
 // the block runs the body instantiated for BM = 64, 128, 192, 256 or 320, the smallest that covers the rows the
-// tile really has.
+// tile really has.  Three main loops: ping-pong of two wave groups (PingPong, v_mfma_f32_16x16x32_bf16) for tiles that
+// share their weights with others, a streaming loop (StreamShape) for tiles bound by HBM, and one that converts 4-bit
+// weights on their way into LDS (SI_GEMM_MAIN_LOOP_REGB); the last two use v_mfma_f32_32x32x16_bf16.
 // LDS rows hold 64 contraction elements (128 bytes); the 16-byte piece c of row r sits at piece
 // c ^ ((r >> 1) & 7): gfx950's LDS has 64 banks, so 16 consecutive rows x 16 bytes must cover 256
 // distinct bytes of bank space for the 128-bit MFMA operand reads to be conflict free (measured:
 // SQ_LDS_BANK_CONFLICT = 0).
 #include "si_internal.h"
 
+#include <type_traits>
+
 namespace si {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 #define SI_GPTR(p) ((const void __attribute__((address_space(1)))*)(p))
@@ -32,8 +37,8 @@ constexpr int BK = 64;
 constexpr int B_BYTES = BN * BK * 2;  // 32 KB
 constexpr int KERNEL_LDS = 144 * 1024;  // the largest body
 
-// Body shapes.  With few rows the GEMM only streams its weights: the smaller A tiles then leave LDS for a
-// deeper ring of stages, i.e. more weight bytes in flight per CU.
+// Body shapes of the 32 x 32 x 16 loops.  With few rows the GEMM only streams its weights: the smaller A tiles then
+// leave LDS for a deeper ring of stages, i.e. more weight bytes in flight per CU.
 template <int BM> struct Shape {
   static constexpr int NST = BM >= 192 ? 2 : 3;           // LDS stages
   static constexpr int STAGE = BM * 128 + B_BYTES;        // bytes per stage
@@ -77,6 +82,14 @@ __device__ inline uint16_t f32_to_bf16(float f) {
 __device__ inline float silu_f(float z) { return z / (1.f + __expf(-z)); }
 
 __device__ inline bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
+
+// direct global -> LDS load of 16 bytes per lane: uniform base (scalar registers) + 32-bit byte offset of the lane
+__device__ inline void load_lds16(const void* base, uint32_t& off, unsigned char* l) {
+  typedef const unsigned char __attribute__((address_space(1))) gchar;
+  // (both opaque, so that no 64-bit address or zero-extended offset per lane is kept through the loop instead)
+  asm volatile("" : "+s"(base), "+v"(off));
+  __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)((gchar*)base + off), SI_LPTR(l), 16, 0, 0);
+}
 
 // swizzled byte offset of 16-byte piece c of row r in a [rows][64] bf16 tile
 __device__ inline int swz(int r, int c) { return r * 128 + ((c ^ ((r >> 1) & 7)) << 4); }
@@ -202,13 +215,162 @@ __device__ inline bool block_tile(const Plan& p, int expert_sel, int x2_only, in
 }
 
 // ---------------------------------------------------------------------------------------------
-// The two GEMM kernels share their main loop.  8 waves as 2 (rows) x 4 (B-row quarters of 64);
-// wave tile (BM/2) x 64: FA A-fragments x 2 B-fragments of v_mfma_f32_32x32x16_bf16.
-// Ring of NST stages holding k-tiles it .. it+NST-1.  The one barrier of an iteration sits before
-// its last k-step: by then every fragment of stage `st` is in registers, so after the barrier the
-// stage is refilled (tile it+NST) and the first fragments of the next stage are fetched while the
-// last 8 MFMAs of this iteration run; the wait before the barrier leaves the NST-2 youngest tiles in
-// flight.
+// Main loop of the matrix-bound bf16 tiles: ping-pong of two wave groups.
+// 8 waves as 2 (rows) x 4 (B-row quarters of 64), wave tile (BM/2) x 64 in v_mfma_f32_16x16x32_bf16 tiles.  Waves w and
+// w + 4 share a SIMD; the second row group runs one barrier behind the first, so that in every slot between two
+// barriers one wave of each SIMD issues matrix instructions and nothing else while the other reads its next fragments
+// from LDS, issues tile loads and waits.  A k-tile of 64 is cut into phases of up to 64 rows per group (2 loads per wave,
+// 4 fragments, 32 matrix instructions of 16 cycles); B is read in the first phase and kept in registers.
+// A region of a stage (the rows of one phase, with B in the first) is free once both groups have read it, i.e. one phase
+// later, and is refilled then with tile it + NST: at BM = 256 a load has three phases = 3072 matrix cycles to land.
+// What bounds it: the power limit.  Counters of a 1024 x 65536 x 8192 product: matrix cores busy 0.90 of the time at a
+// shader clock of 1.68 GHz (the loop with one barrier per k-tile that it replaces: 0.65 at 1.84 GHz): 1461 TFLOP/s against
+// 1181.  The 16 x 16 x 32 instruction is part of it: register-resident on random operands it sustains 2.06 PFLOP/s under
+// the power limit where the 32 x 32 x 16 one sustains 1.81 (its accumulators cost twice the register traffic).  Four
+// phases of 16 matrix instructions (64 x 32 quadrants) measured 1378, one wave per SIMD with 128 x 128 tiles 1064.
+// ---------------------------------------------------------------------------------------------
+template <int BM> struct PingPong {
+  static constexpr int NST = BM >= 192 ? 2 : 3;     // LDS stages
+  static constexpr int STAGE = BM * 128 + B_BYTES;  // bytes per stage
+  static constexpr int LDS = NST * STAGE;           // 120, 144, 112, 128, 144 KB for BM = 64, 128, 192, 256, 320
+  static constexpr int FA = BM / 32;                // A fragments (16 rows each) per wave
+  static constexpr int ALD = BM / 64;               // A load instructions (8 rows each) per wave and k-tile
+  static constexpr int NP = (ALD + 1) / 2;          // phases per k-tile
+  static constexpr int LPW = ALD + 4;               // load instructions per wave and k-tile
+  static constexpr int aloads(int p) { return ALD - 2 * p < 2 ? ALD - 2 * p : 2; }
+  static constexpr int loads(int p) { return aloads(p) + (p == 0 ? 4 : 0); }
+  // loads of a wave that may still be in flight when the data of the phase after phase q of tile `it` must have landed:
+  // those issued later than it, in the order (tile, phase region), when `rem` tiles follow tile `it`
+  static constexpr int younger(int q, int rem) {
+    int n = 0;
+    if (q < NP - 1) {
+      for (int p = q + 2; p < NP; ++p) n += loads(p);
+      for (int t = 1; t < NST && t <= rem; ++t) n += LPW;
+    } else {
+      if (rem >= 1) for (int p = 1; p < NP; ++p) n += loads(p);
+      for (int t = 2; t < NST && t <= rem; ++t) n += LPW;
+    }
+    if (rem >= NST) for (int p = 0; p < q; ++p) n += loads(p);
+    return n;
+  }
+  static_assert(LDS <= KERNEL_LDS && (NST + 1) * LPW < 64, "ring does not fit");
+};
+
+// first LDS row of the 8 rows that wave w's i-th A load of a k-tile fills (region p = i / 2 of both row groups)
+template <int BM> __device__ inline int pp_a_row(int w, int i) {
+  using P = PingPong<BM>;
+  const int p = i >> 1;
+  if (P::ALD - 2 * p >= 2) {
+    const int u = w * 2 + (i & 1);
+    return (u >> 3) * (BM / 2) + p * 64 + (u & 7) * 8;
+  }
+  return (w >> 2) * (BM / 2) + p * 64 + (w & 3) * 8;
+}
+
+template <int R, int BM, int Q> __device__ __forceinline__ void pp_wait(int rem) {
+  if constexpr (R == 0) {
+    wait_vmcnt<PingPong<BM>::younger(Q, 0)>();
+  } else {
+    if (rem >= R) wait_vmcnt<PingPong<BM>::younger(Q, R)>();
+    else pp_wait<R - 1, BM, Q>(rem);
+  }
+}
+
+// acc[i][j] += the 16 x 16 tile (rows i*16.., B rows j*16..) of the wave over nk k-tiles.
+//   issue_a(i, stage, kt): wave's i-th A load of tile kt into LDS stage `stage` (rows pp_a_row);  issue_b(stage, kt): its 4 B
+//   loads;  boff[ks]: byte offset of the lane's piece of B fragment 0 in k-step ks inside the B part of a stage, BJ: bytes
+//   between fragments.  (Fragment addresses are one lane offset per k-step and operand plus constants: the swizzle of
+//   row r is that of r + 16.  Left to the compiler they were 16 registers.)
+template <int BM, int BJ, class IA, class IB>
+__device__ __forceinline__ void gemm_pingpong(unsigned char* lds, int nk, int lane, int wr, f32x4 (&acc)[BM / 32][4],
+                                              IA issue_a, IB issue_b, const uint32_t (&boff)[2]) {
+  using P = PingPong<BM>;
+  constexpr int FP = P::ALD >= 2 ? 4 : 2;  // fragments of a phase
+  bf16x8 fa[FP][2], fb[4][2];
+  const uint32_t aoff[2] = {(uint32_t)swz(wr * (BM / 2) + (lane & 15), lane >> 4), (uint32_t)swz(wr * (BM / 2) + (lane & 15), 4 + (lane >> 4))};
+  auto issue = [&](auto pc, int stage, int kt) {
+    constexpr int p = decltype(pc)::value;
+#pragma unroll
+    for (int i = 0; i < P::aloads(p); ++i) issue_a(2 * p + i, stage, kt);
+    if constexpr (p == 0) issue_b(stage, kt);
+  };
+  auto next = [&](int st) { return st + 1 == P::NST ? 0 : st + 1; };
+  auto phase = [&](auto qc, int it, int st) {
+    constexpr int q = decltype(qc)::value;
+    constexpr int nf = 2 * P::aloads(q);
+    const unsigned char* sa = lds + st * P::STAGE;
+    if constexpr (q == 0) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          fb[j][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(sa + boff[ks] + (BM * 128 + j * BJ)));
+    }
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < nf; ++i)
+        fa[i][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(sa + aoff[ks] + (q * 64 + i * 16) * 128));
+    // refill the region that both groups have read: that of the previous phase
+    if constexpr (q == 0) {
+      if (it > 0 && it - 1 + P::NST < nk) issue(std::integral_constant<int, P::NP - 1>{}, st == 0 ? P::NST - 1 : st - 1, it - 1 + P::NST);
+    } else {
+      if (it + P::NST < nk) issue(std::integral_constant<int, q - 1>{}, st, it + P::NST);
+    }
+    pp_wait<P::NST, BM, q>(nk - 1 - it);
+    wait_lgkmcnt0();
+    __builtin_amdgcn_sched_barrier(0);
+    block_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < nf; ++i)
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+          const int j = (i & 1) ? 3 - jj : jj;
+          acc[q * 4 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i][ks], fb[j][ks], acc[q * 4 + i][j], 0, 0, 0);
+        }
+    __builtin_amdgcn_sched_barrier(0);
+    block_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int i = 0; i < BM / 32; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  using C0 = std::integral_constant<int, 0>;
+  using C1 = std::integral_constant<int, 1>;
+  using C2 = std::integral_constant<int, 2>;
+#pragma unroll
+  for (int t = 0; t < P::NST; ++t)
+    if (t < nk) {
+      issue(C0{}, t, t);
+      if constexpr (P::NP > 1) issue(C1{}, t, t);
+      if constexpr (P::NP > 2) issue(C2{}, t, t);
+    }
+  if (nk >= P::NST) wait_vmcnt<P::NST * P::LPW - P::loads(0)>();  // the first region of tile 0
+  else wait_vmcnt<0>();
+  block_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  if (wr == 1) block_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  int st = 0;
+  for (int it = 0; it < nk; ++it) {
+    phase(C0{}, it, st);
+    if constexpr (P::NP > 1) phase(C1{}, it, st);
+    if constexpr (P::NP > 2) phase(C2{}, it, st);
+    st = next(st);
+  }
+  if (wr == 0) block_barrier();  // the second group's last slot
+}
+
+// ---------------------------------------------------------------------------------------------
+// The loops below: 8 waves as 2 (rows) x 4 (B-row quarters of 64); wave tile (BM/2) x 64: FA A-fragments x 2
+// B-fragments of v_mfma_f32_32x32x16_bf16.  The one barrier of an iteration sits before its last k-step: by then every
+// fragment of stage `st` is in registers, so after the barrier the stage is refilled and the first fragments of the
+// next stage are fetched while the last 8 MFMAs of this iteration run; the wait before the barrier leaves the younger
+// tiles in flight.
 // ---------------------------------------------------------------------------------------------
 // accumulators, operand fragments and the two lambdas every variant of the main loop uses
 #define SI_GEMM_DECLS(BFRAG_OFF)                                                                                 \
@@ -239,33 +401,6 @@ __device__ inline void gload_u16(uint32_t& z, const void* p) {
 }
 struct BRegs { u32x4 q[4]; };  // one lane's share of a bf16 B tile
 __device__ inline void bready(BRegs& r) { asm volatile("" : "+v"(r.q[0]), "+v"(r.q[1]), "+v"(r.q[2]), "+v"(r.q[3])::"memory"); }
-
-#define SI_GEMM_MAIN_LOOP(NK, ISSUE)                                                                  \
-  {                                                                                                              \
-    const int nk_ = (NK);                                                                                        \
-    _Pragma("unroll") for (int s0 = 0; s0 < S::NST; ++s0) if (s0 < nk_) ISSUE(s0, s0);                           \
-    if (S::NST - 1 < nk_) wait_vmcnt<(S::NST - 1) * S::LPW>(); else wait_vmcnt<0>();                             \
-    block_barrier();                                                                                             \
-    ldfrag(0, 0, 0);                                                                                             \
-    int st = 0;                                                                                                  \
-    for (int it = 0; it < nk_; ++it) {                                                                           \
-      const int nx = st + 1 == S::NST ? 0 : st + 1;                                                              \
-      ldfrag(st, 1, 1); mma(0);                                                                                  \
-      ldfrag(st, 2, 0); mma(1);                                                                                  \
-      ldfrag(st, 3, 1); mma(0);                                                                                  \
-      /* tile it+1 must have landed for every wave and every read of stage st must be complete before the   */   \
-      /* barrier: after it stage nx is read and stage st is refilled with tile it+NST                       */   \
-      if (it + S::NST - 1 < nk_) wait_vmcnt<(S::NST - 2) * S::LPW>(); else wait_vmcnt<0>();                      \
-      wait_lgkmcnt0();                                                                                           \
-      block_barrier();                                                                                           \
-      if (it + 1 < nk_) ldfrag(nx, 0, 0);                                                                        \
-      if (it + S::NST < nk_) ISSUE(st, it + S::NST);                                                             \
-      __builtin_amdgcn_s_setprio(1);                                                                             \
-      mma(1);                                                                                                    \
-      __builtin_amdgcn_s_setprio(0);                                                                             \
-      st = nx;                                                                                                   \
-    }                                                                                                            \
-  }
 
 struct Q4Regs { u32x4 q; uint32_t z; };  // codes and scale of one lane's share of a B tile
 
@@ -450,10 +585,11 @@ __device__ __forceinline__ void gateup_body(const uint16_t* __restrict__ x, int 
   uint32_t a_src[S::ALD];  // element offsets from x (the host checks that x spans less than 2^31 elements)
 #pragma unroll
   for (int i = 0; i < S::ALD; ++i) {
-    const int lr = w * (BM / 8) + i * 8 + lrow;  // LDS row of the A tile
+    const int lr = (STREAM ? w * (BM / 8) + i * 8 : pp_a_row<BM>(w, i)) + lrow;  // LDS row of the A tile
     int row = ti.row0 + lr;
     row = row < ti.row_end ? row : ti.row_end - 1;
     a_src[i] = (uint32_t)p.row_token[row] * (uint32_t)M + ((lpp ^ ((lr >> 1) & 7)) * 8);
+    if (!STREAM) a_src[i] *= 2;  // bytes
   }
   // B: LDS row w*32 + i*8 + lrow  ->  chunk 2*tc + w/4, f = w%2 (gate / up block), column-in-chunk
   // jc = ((w/2)%2)*32 + i*8 + lrow.  Blocks are [M/PW panels][64 j][PW m] (cc_worker.h).
@@ -463,35 +599,6 @@ __device__ __forceinline__ void gateup_body(const uint16_t* __restrict__ x, int 
   const int PW = panel_width(M);
   const int lc0 = lpp ^ (lrow >> 1);  // B piece for even i; odd i uses lc0 ^ 4
 
-  auto issue = [&](int stage, int kt) {
-    unsigned char* sa = lds + stage * S::STAGE + w * (BM / 8) * 128;
-    unsigned char* sb = lds + stage * S::STAGE + BM * 128 + w * 4096;
-    const int k0 = kt * BK;
-#pragma unroll
-    for (int i = 0; i < S::ALD; ++i)
-      __builtin_amdgcn_global_load_lds(SI_GPTR(x + (a_src[i] + (uint32_t)k0)), SI_LPTR(sa + i * 1024), 16, 0, 0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int m0 = k0 + (((i & 1) ? (lc0 ^ 4) : lc0) * 8);
-      __builtin_amdgcn_global_load_lds(SI_GPTR(b_blk + ((size_t)(m0 / PW) * CHUNK_J + jc0 + i * 8) * PW + (m0 % PW)),
-                                       SI_LPTR(sb + i * 1024), 16, 0, 0);
-    }
-  };
-  // epilogue: element (row 8*(r/4) + 4*(lane/32) + r%4, column lane%32) of each 32x32 tile;
-  // acc[i][0] is the gate tile and acc[i][1] the up tile of the same 32 hidden columns
-  auto epilogue = [&](const f32x16 (&acc)[S::FA][2]) {
-    const int jl = wc * 32 + (lane & 31);  // hidden column inside the 128-column tile
-    if (2 * tc + (jl >> 6) < wv.n_chunks) {
-      const int col = wv.col0 + tc * 128 + jl;
-#pragma unroll
-      for (int i = 0; i < S::FA; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = ti.row0 + wr * (BM / 2) + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-          if (row < ti.row_end) hact[(size_t)row * ldh + col] = f32_to_bf16(silu_f(acc[i][0][r]) * acc[i][1][r]);
-        }
-    }
-  };
   if constexpr (STREAM) {
     // the same loads, with B through registers: lane (lrow, lpp) of instruction i fetches the piece that the
     // direct load would have put at byte lane * 16 of the wave's KB i, and stores it there
@@ -514,11 +621,57 @@ __device__ __forceinline__ void gateup_body(const uint16_t* __restrict__ x, int 
     };
     SI_GEMM_DECLS_STREAM(SI_BOFF_SWZ)
     SI_GEMM_MAIN_LOOP_STREAM(M / BK, issue_a, bload, bstore)
-    epilogue(acc);
+    // element (row 8*(r/4) + 4*(lane/32) + r%4, column lane%32) of each 32x32 tile;
+    // acc[i][0] is the gate tile and acc[i][1] the up tile of the same 32 hidden columns
+    const int jl = wc * 32 + (lane & 31);  // hidden column inside the 128-column tile
+    if (2 * tc + (jl >> 6) < wv.n_chunks) {
+      const int col = wv.col0 + tc * 128 + jl;
+#pragma unroll
+      for (int i = 0; i < S::FA; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int row = ti.row0 + wr * (BM / 2) + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+          if (row < ti.row_end) hact[(size_t)row * ldh + col] = f32_to_bf16(silu_f(acc[i][0][r]) * acc[i][1][r]);
+        }
+    }
   } else {
-    SI_GEMM_DECLS(SI_BOFF_SWZ)
-    SI_GEMM_MAIN_LOOP(M / BK, issue)
-    epilogue(acc);
+    using P = PingPong<BM>;
+    // uniform bases and 32-bit lane offsets: two vector registers for the B addresses instead of eight (a k-tile never
+    // crosses a panel, PW being a multiple of 64)
+    uint32_t b_lane[2] = {(uint32_t)(jc0 * PW + lc0 * 8) * 2u, (uint32_t)(jc0 * PW + (lc0 ^ 4) * 8) * 2u};
+    auto issue_a = [&](int i, int stage, int kt) {
+      load_lds16(x + kt * BK, a_src[i], lds + stage * P::STAGE + pp_a_row<BM>(w, i) * 128);
+    };
+    auto issue_b = [&](int stage, int kt) {
+      unsigned char* sb = lds + stage * P::STAGE + BM * 128 + w * 4096;
+      const int k0 = kt * BK;
+      const uint16_t* bk = b_blk + (size_t)(k0 / PW) * CHUNK_J * PW + k0 % PW;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) load_lds16(bk + i * 8 * PW, b_lane[i & 1], sb + i * 1024);
+    };
+    f32x4 acc[P::FA][4];
+    const uint32_t boff[2] = {(uint32_t)swz(wc * 64 + (lane & 15), lane >> 4), (uint32_t)swz(wc * 64 + (lane & 15), 4 + (lane >> 4))};
+    gemm_pingpong<BM, 2048>(lds, M / BK, lane, wr, acc, issue_a, issue_b, boff);
+    // element (row 4*(lane/16) + r, column lane%16) of each 16x16 tile; acc[i][j] is the gate tile and acc[i][j + 2] the
+    // up tile of the same 16 hidden columns
+    // (the lane index is made opaque here so that the output addresses are formed after the main loop: formed
+    // ahead of it they are live through it, which the 320-row body has no registers for)
+    int el = lane;
+    asm volatile("" : "+v"(el));
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int jl = wc * 32 + j * 16 + (el & 15);  // hidden column inside the 128-column tile
+      if (2 * tc + (jl >> 6) < wv.n_chunks) {
+        const int col = wv.col0 + tc * 128 + jl;
+#pragma unroll
+        for (int i = 0; i < P::FA; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int row = ti.row0 + wr * (BM / 2) + i * 16 + 4 * (el >> 4) + r;
+            if (row < ti.row_end) hact[(size_t)row * ldh + col] = f32_to_bf16(silu_f(acc[i][j][r]) * acc[i][j + 2][r]);
+          }
+      }
+    }
   }
 }
 
@@ -607,10 +760,11 @@ __device__ __forceinline__ void down_body(const uint16_t* __restrict__ hact, int
   uint32_t a_src[S::ALD];  // element offsets from hact (the host checks that it spans less than 2^31 elements)
 #pragma unroll
   for (int i = 0; i < S::ALD; ++i) {
-    const int lr = w * (BM / 8) + i * 8 + lrow;
+    const int lr = (STREAM ? w * (BM / 8) + i * 8 : pp_a_row<BM>(w, i)) + lrow;
     int row = ti.row0 + lr;
     row = row < ti.row_end ? row : ti.row_end - 1;
     a_src[i] = (uint32_t)row * (uint32_t)ldh + wv.col0 + ((lpp ^ ((lr >> 1) & 7)) * 8);
+    if (!STREAM) a_src[i] *= 2;  // bytes
   }
   // B: wave w loads group q = w of the chunk's down block ([M/NW tiles][8 q][NW m][8 i]), 4 x 64 output columns
   const int NW = ntile_width(M);
@@ -620,40 +774,9 @@ __device__ __forceinline__ void down_body(const uint16_t* __restrict__ hact, int
   for (int i = 0; i < 4; ++i) {
     const int n = min(n0 + i * 64 + lane, M - 1);
     b_off[i] = (((uint32_t)(n >> nw_shift) * 8 + w) * NW + (n & (NW - 1))) * 8;  // NW is a power of two
+    if (!STREAM) b_off[i] *= 2;  // bytes
   }
 
-  auto issue = [&](int stage, int kt) {
-    unsigned char* sa = lds + stage * S::STAGE + w * (BM / 8) * 128;
-    unsigned char* sb = lds + stage * S::STAGE + BM * 128 + w * 4096;
-    const int c = c_begin + kt;
-    const uint16_t* dblk = ebase + (size_t)(wv.chunk0 + c) * 3 * CHUNK_J * M + (size_t)2 * CHUNK_J * M;
-#pragma unroll
-    for (int i = 0; i < S::ALD; ++i)
-      __builtin_amdgcn_global_load_lds(SI_GPTR(hact + (a_src[i] + (uint32_t)(c * CHUNK_J))), SI_LPTR(sa + i * 1024), 16, 0, 0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      __builtin_amdgcn_global_load_lds(SI_GPTR(dblk + b_off[i]), SI_LPTR(sb + i * 1024), 16, 0, 0);
-  };
-  auto epilogue = [&](const f32x16 (&acc)[S::FA][2]) {
-    // (the lane index is made opaque here so that the output addresses are formed after the main loop: formed
-    // ahead of it they are live through it, which the 320-row body has no registers for)
-    int el = lane;
-    asm volatile("" : "+v"(el));
-#pragma unroll
-    for (int i = 0; i < S::FA; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int m = n0 + wc * 64 + j * 32 + (el & 31);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = ti.row0 + wr * (BM / 2) + i * 32 + 8 * (r >> 2) + 4 * (el >> 5) + (r & 3);
-          if (row < ti.row_end && m < M) {
-            float* dst = out + (size_t)row * M + m;
-            *dst = accumulate ? *dst + acc[i][j][r] : acc[i][j][r];
-          }
-        }
-      }
-  };
   if (c_begin < c_end) {
     if constexpr (STREAM) {
       auto issue_a = [&](int sta, int kt) {
@@ -672,11 +795,51 @@ __device__ __forceinline__ void down_body(const uint16_t* __restrict__ hact, int
       };
       SI_GEMM_DECLS_STREAM(SI_BOFF_K8)
       SI_GEMM_MAIN_LOOP_STREAM(c_end - c_begin, issue_a, bload, bstore)
-      epilogue(acc);
+#pragma unroll
+      for (int i = 0; i < S::FA; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int m = n0 + wc * 64 + j * 32 + (lane & 31);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int row = ti.row0 + wr * (BM / 2) + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+            if (row < ti.row_end && m < M) {
+              float* dst = out + (size_t)row * M + m;
+              *dst = accumulate ? *dst + acc[i][j][r] : acc[i][j][r];
+            }
+          }
+        }
     } else {
-      SI_GEMM_DECLS(SI_BOFF_K8)
-      SI_GEMM_MAIN_LOOP(c_end - c_begin, issue)
-      epilogue(acc);
+      using P = PingPong<BM>;
+      auto issue_a = [&](int i, int stage, int kt) {
+        load_lds16(hact + (c_begin + kt) * CHUNK_J, a_src[i], lds + stage * P::STAGE + pp_a_row<BM>(w, i) * 128);
+      };
+      auto issue_b = [&](int stage, int kt) {
+        unsigned char* sb = lds + stage * P::STAGE + BM * 128 + w * 4096;
+        const uint16_t* dblk = ebase + (size_t)(wv.chunk0 + c_begin + kt) * 3 * CHUNK_J * M + (size_t)2 * CHUNK_J * M;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) load_lds16(dblk, b_off[i], sb + i * 1024);
+      };
+      f32x4 acc[P::FA][4];
+      const uint32_t b0 = SI_BOFF_K8(wc * 64 + (lane & 15), lane >> 4);
+      const uint32_t boff[2] = {b0, b0 + 4 * BN * 16};
+      gemm_pingpong<BM, 256>(lds, c_end - c_begin, lane, wr, acc, issue_a, issue_b, boff);
+      int el = lane;  // opaque, as in gateup_body
+      asm volatile("" : "+v"(el));
+#pragma unroll
+      for (int i = 0; i < P::FA; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int m = n0 + wc * 64 + j * 16 + (el & 15);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int row = ti.row0 + wr * (BM / 2) + i * 16 + 4 * (el >> 4) + r;
+            if (row < ti.row_end && m < M) {
+              float* dst = out + (size_t)row * M + m;
+              *dst = accumulate ? *dst + acc[i][j][r] : acc[i][j][r];
+            }
+          }
+        }
     }
   } else {
     // an empty k-split of an overwriting launch still has to define its slab
