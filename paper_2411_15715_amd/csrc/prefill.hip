@@ -9,9 +9,8 @@
 // stages filled by direct global->LDS loads (global_load_lds_dwordx4, no VGPR staging), wave tile
 // (BM/2) x 64.  A row tile holds up to 256 rows, the last one of an expert up to 320 (si_internal.h: n_row_tiles);
 // the block runs the body instantiated for BM = 64, 128, 192, 256 or 320, the smallest that covers the rows the
-// tile really has.  Three main loops: ping-pong of two wave groups (PingPong, v_mfma_f32_16x16x32_bf16) for tiles that
-// share their weights with others, a streaming loop (StreamShape) for tiles bound by HBM, and one that converts 4-bit
-// weights on their way into LDS (SI_GEMM_MAIN_LOOP_REGB); the last two use v_mfma_f32_32x32x16_bf16.
+// tile really has.  Two main loops: ping-pong of two wave groups on v_mfma_f32_16x16x32_bf16 (PingPong), and one
+// on v_mfma_f32_32x32x16_bf16 that converts 4-bit weights on their way into LDS (SI_GEMM_MAIN_LOOP_REGB).
 // LDS rows hold 64 contraction elements (128 bytes); the 16-byte piece c of row r sits at piece
 // c ^ ((r >> 1) & 7): gfx950's LDS has 64 banks, so 16 consecutive rows x 16 bytes must cover 256
 // distinct bytes of bank space for the 128-bit MFMA operand reads to be conflict free (measured:
@@ -37,7 +36,7 @@ constexpr int BK = 64;
 constexpr int B_BYTES = BN * BK * 2;  // 32 KB
 constexpr int KERNEL_LDS = 144 * 1024;  // the largest body
 
-// Body shapes of the 32 x 32 x 16 loops.  With few rows the GEMM only streams its weights: the smaller A tiles then
+// Body shapes of the 4-bit loop.  With few rows the GEMM only streams its weights: the smaller A tiles then
 // leave LDS for a deeper ring of stages, i.e. more weight bytes in flight per CU.
 template <int BM> struct Shape {
   static constexpr int NST = BM >= 192 ? 2 : 3;           // LDS stages
@@ -51,26 +50,6 @@ template <int BM> struct Shape {
   // loop needs from global memory besides the tiles is fetched before it starts).  ensure_lds_attr() refuses a
   // build whose kernels use scratch memory, and the GPU tests run every body with fewer, as many and more k-tiles
   // than stages.
-};
-
-// Ring shapes of the streaming loop, which tiles of at most 192 rows run.  Such a tile is latency bound, not
-// matrix-core bound: what it needs is weight bytes in flight, and the LDS ring above holds at most two k-tiles
-// of them (64 KB per CU; the chip needs about 25 MB in flight to saturate its HBM, i.e. 100 KB per CU).  Here only
-// the A operand keeps a ring of DA stages in LDS; the B operand (the weights) travels through registers, R = DA - 1
-// k-tiles of it in flight per wave, and is written into one of two B stages in LDS one iteration before it is read.
-template <int BM> struct StreamShape {
-  static constexpr int DA = BM <= 64 ? 6 : BM <= 128 ? 5 : 3;  // A stages = prefetch distance in k-tiles
-  static constexpr int R = DA - 1;                              // register sets holding B tiles in flight
-  static constexpr int A_STAGE = BM * 128;
-  static constexpr int B0 = DA * A_STAGE;                       // offset of the two B stages
-  static constexpr int LDS = B0 + 2 * B_BYTES;                  // 112, 144, 136 KB for BM = 64, 128, 192
-  static constexpr int GL = 4;                                  // B register loads per wave and k-tile
-  static constexpr int ALD = BM / 64;                           // A load instructions per wave and k-tile
-  // waits of the steady state: a wave issues, per k-tile and in this order, GL register loads (B) and ALD
-  // direct-to-LDS loads (A); younger than B of tile t+1 are A of tile t+1 and the tiles t+2 .. t+DA-1
-  static constexpr int WAIT_B = (DA - 2) * (GL + ALD) + ALD;
-  static constexpr int WAIT_A = (DA - 2) * (GL + ALD);
-  static_assert(LDS <= KERNEL_LDS && WAIT_B < 64, "ring does not fit");
 };
 
 __device__ inline uint16_t f32_to_bf16(float f) {
@@ -144,9 +123,8 @@ __device__ inline bool map_block(int b, int N, int n_cu, int interleave, int& L,
   return true;
 }
 
-// se: index of the expert inside the launch's weight storage; solo: the tile holds all rows of its expert, so
-// nobody else reads its weight tiles (they come from HBM, not from a sibling's trail in the L2)
-struct TileInfo { int e, row0, row_end, se, solo; };
+// se: index of the expert inside the launch's weight storage
+struct TileInfo { int e, row0, row_end, se; };
 
 // Number of logical tile ids with work in this launch (row tiles x inner tiles); single: no expert of the launch
 // has more than one row tile.
@@ -190,7 +168,6 @@ __device__ inline bool decode_tile(const Plan& p, int expert_sel, int x2_only, i
   ti.e = e;
   ti.row0 = start + r * TILE_ROWS;
   ti.row_end = r == nrt - 1 ? end : ti.row0 + TILE_ROWS;
-  ti.solo = nrt == 1;
   return true;
 }
 
@@ -205,7 +182,6 @@ __device__ inline bool block_tile(const Plan& p, int expert_sel, int x2_only, in
   if (halves == 2) {
     const int rows = ti.row_end - ti.row0;
     if (rows <= 128) return half == 0;  // too few rows to share: the first block takes them all
-    ti.solo = 0;
     const int hs = ((rows + 1) / 2 + 31) / 32 * 32;
     ti.row0 += half * hs;
     ti.row_end = min(ti.row_end, ti.row0 + hs);
@@ -215,7 +191,7 @@ __device__ inline bool block_tile(const Plan& p, int expert_sel, int x2_only, in
 }
 
 // ---------------------------------------------------------------------------------------------
-// Main loop of the matrix-bound bf16 tiles: ping-pong of two wave groups.
+// Main loop of the bf16 tiles: ping-pong of two wave groups.
 // 8 waves as 2 (rows) x 4 (B-row quarters of 64), wave tile (BM/2) x 64 in v_mfma_f32_16x16x32_bf16 tiles.  Waves w and
 // w + 4 share a SIMD; the second row group runs one barrier behind the first, so that in every slot between two
 // barriers one wave of each SIMD issues matrix instructions and nothing else while the other reads its next fragments
@@ -366,7 +342,7 @@ __device__ __forceinline__ void gemm_pingpong(unsigned char* lds, int nk, int la
 }
 
 // ---------------------------------------------------------------------------------------------
-// The loops below: 8 waves as 2 (rows) x 4 (B-row quarters of 64); wave tile (BM/2) x 64: FA A-fragments x 2
+// The 4-bit loop: 8 waves as 2 (rows) x 4 (B-row quarters of 64); wave tile (BM/2) x 64: FA A-fragments x 2
 // B-fragments of v_mfma_f32_32x32x16_bf16.  The one barrier of an iteration sits before its last k-step: by then every
 // fragment of stage `st` is in registers, so after the barrier the stage is refilled and the first fragments of the
 // next stage are fetched while the last 8 MFMAs of this iteration run; the wait before the barrier leaves the younger
@@ -399,82 +375,10 @@ __device__ inline void gload_b128(u32x4& q, const void* p) {
 __device__ inline void gload_u16(uint32_t& z, const void* p) {
   asm volatile("global_load_ushort %0, %1, off" : "=v"(z) : "v"(p) : "memory");
 }
-struct BRegs { u32x4 q[4]; };  // one lane's share of a bf16 B tile
-__device__ inline void bready(BRegs& r) { asm volatile("" : "+v"(r.q[0]), "+v"(r.q[1]), "+v"(r.q[2]), "+v"(r.q[3])::"memory"); }
 
 struct Q4Regs { u32x4 q; uint32_t z; };  // codes and scale of one lane's share of a B tile
 
-// The streaming loop (StreamShape).  ISSUE_A(a_stage, kt): direct-to-LDS loads of A tile kt; BLOAD(kt, regs): register
-// loads of B tile kt; BSTORE(b_stage, regs, i): 16-byte LDS store of the i-th of them.  Iteration `it` computes tile
-// `it` (A stage it % DA, B stage it % 2), writes B of tile it+1 (fetched DA-1 iterations earlier) into the other B
-// stage between its matrix instructions, and after its barrier fetches tile it+DA into the A stage and the register
-// set it has just released.  The loop is unrolled by R so that every register set is named statically.  Near the end
-// of the contraction (fewer than DA-1 tiles ahead) the hand-counted waits no longer hold and the loop drains instead.
-#define SI_GEMM_DECLS_STREAM(BFRAG_OFF)                                                                          \
-  using SS = StreamShape<BM>;                                                                                    \
-  f32x16 acc[S::FA][2];                                                                                          \
-  _Pragma("unroll") for (int i = 0; i < S::FA; ++i) _Pragma("unroll") for (int j = 0; j < 2; ++j)                \
-      _Pragma("unroll") for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;                                         \
-  bf16x8 fa[2][S::FA], fb[2][2];                                                                                 \
-  auto ldfrag = [&](int sta, int stb, int ks, int buf) {                                                         \
-    const unsigned char* sa = lds + sta * SS::A_STAGE;                                                           \
-    const unsigned char* sb = lds + SS::B0 + stb * B_BYTES;                                                      \
-    const int pc = ks * 2 + (lane >> 5);                                                                         \
-    _Pragma("unroll") for (int i = 0; i < S::FA; ++i) fa[buf][i] = as_bf16x8(                                    \
-        *reinterpret_cast<const u32x4*>(sa + swz(wr * (BM / 2) + i * 32 + (lane & 31), pc)));                    \
-    _Pragma("unroll") for (int j = 0; j < 2; ++j) fb[buf][j] = as_bf16x8(                                        \
-        *reinterpret_cast<const u32x4*>(sb + BFRAG_OFF(wc * 64 + j * 32 + (lane & 31), pc)));                    \
-  };                                                                                                             \
-  auto mma = [&](int buf) {                                                                                      \
-    _Pragma("unroll") for (int i = 0; i < S::FA; ++i) _Pragma("unroll") for (int j = 0; j < 2; ++j)              \
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf][i], fb[buf][j], acc[i][j], 0, 0, 0);         \
-  };
-
-#define SI_GEMM_MAIN_LOOP_STREAM(NK, ISSUE_A, BLOAD, BSTORE)                                                     \
-  {                                                                                                              \
-    const int nk_ = (NK);                                                                                        \
-    BRegs rs[SS::R];                                                                                             \
-    /* tile 0 goes straight through; then the tiles 1 .. DA-1 are set off */                                     \
-    BLOAD(0, rs[0]); ISSUE_A(0, 0);                                                                              \
-    wait_vmcnt<SS::ALD>(); bready(rs[0]);                                                                        \
-    _Pragma("unroll") for (int i = 0; i < 4; ++i) BSTORE(0, rs[0], i);                                           \
-    _Pragma("unroll") for (int t = 1; t < SS::DA; ++t) if (t < nk_) { BLOAD(t, rs[t % SS::R]); ISSUE_A(t, t); }  \
-    if (SS::DA - 1 < nk_) wait_vmcnt<(SS::DA - 1) * (SS::GL + SS::ALD)>(); else wait_vmcnt<0>(); /* A of tile 0 */ \
-    wait_lgkmcnt0();                                                                                             \
-    block_barrier();                                                                                             \
-    ldfrag(0, 0, 0, 0);                                                                                          \
-    int sta = 0;                                                                                                 \
-    auto step = [&](int it, BRegs& rc) { /* rc: B of tile it+1 */                                                \
-      const int stb = it & 1;                                                                                    \
-      const int nsta = sta + 1 == SS::DA ? 0 : sta + 1;                                                          \
-      const bool full = it + SS::DA - 1 < nk_; /* the tiles it+1 .. it+DA-1 have all been set off */             \
-      const bool more = it + 1 < nk_;                                                                            \
-      ldfrag(sta, stb, 1, 1); mma(0);                                                                            \
-      if (full) wait_vmcnt<SS::WAIT_B>(); else wait_vmcnt<0>();                                                  \
-      bready(rc);                                                                                                \
-      if (more) BSTORE(stb ^ 1, rc, 0);                                                                          \
-      ldfrag(sta, stb, 2, 0); mma(1);                                                                            \
-      if (more) BSTORE(stb ^ 1, rc, 1);                                                                          \
-      ldfrag(sta, stb, 3, 1); mma(0);                                                                            \
-      if (more) { BSTORE(stb ^ 1, rc, 2); BSTORE(stb ^ 1, rc, 3); }                                              \
-      /* A of tile it+1 landed, B of tile it+1 written, every read of the two stages complete */                 \
-      if (full) wait_vmcnt<SS::WAIT_A>(); else wait_vmcnt<0>();                                                  \
-      wait_lgkmcnt0();                                                                                           \
-      block_barrier();                                                                                           \
-      if (more) ldfrag(nsta, stb ^ 1, 0, 0);                                                                     \
-      if (it + SS::DA < nk_) { BLOAD(it + SS::DA, rc); ISSUE_A(sta, it + SS::DA); }                              \
-      __builtin_amdgcn_s_setprio(1);                                                                             \
-      mma(1);                                                                                                    \
-      __builtin_amdgcn_s_setprio(0);                                                                             \
-      sta = nsta;                                                                                                \
-    };                                                                                                           \
-    for (int it = 0; it < nk_; it += SS::R) {                                                                    \
-      _Pragma("unroll") for (int u = 0; u < SS::R; ++u) if (it + u < nk_) step(it + u, rs[(u + 1) % SS::R]);     \
-    }                                                                                                            \
-  }
-
-
-// The same loop for weights in the 4-bit storage form.  The A operand still arrives by direct global->LDS loads;
+// The loop for weights in the 4-bit storage form.  The A operand arrives by direct global->LDS loads;
 // the B operand cannot (it has to be turned into bf16 on the way), so every lane fetches 16 bytes of codes (32
 // weights) and their group scale into registers one iteration ahead (BLOAD), and turns them into four 16-byte
 // pieces of bf16((code - 8) * scale) that it writes into the stage freed by the previous iteration's barrier,
@@ -570,11 +474,11 @@ __device__ inline uint32_t q4_pair(uint32_t bytes, int b0, int b1, float sc, flo
 // f = 0 the gate row and f = 1 the up row of column 32 wc + jj; SiLU(gate)*up is then formed in
 // registers from the two accumulator tiles of a wave.
 // ---------------------------------------------------------------------------------------------
-template <int BM, bool STREAM>
+template <int BM>
 __device__ __forceinline__ void gateup_body(const uint16_t* __restrict__ x, int M, const Plan& p, int tc, const TileInfo& ti,
                                             const WeightView& wv, uint16_t* __restrict__ hact, int ldh,
                                             unsigned char* lds) {
-  using S = Shape<BM>;
+  using P = PingPong<BM>;
   const int tid = threadIdx.x, lane = tid % WAVE, w = __builtin_amdgcn_readfirstlane(tid / WAVE);  // wave index, known to be uniform
   const int wr = w >> 2, wc = w & 3;
   const uint16_t* ebase = wv.base + (size_t)ti.se * wv.expert_stride;
@@ -582,14 +486,13 @@ __device__ __forceinline__ void gateup_body(const uint16_t* __restrict__ x, int 
   // loader: a wave instruction fills 8 LDS rows (1 KB); lane/8 is the row, lane%8 the slot inside the
   // 128-byte row, which holds logical piece slot ^ ((row >> 1) & 7)
   const int lrow = lane >> 3, lpp = lane & 7;
-  uint32_t a_src[S::ALD];  // element offsets from x (the host checks that x spans less than 2^31 elements)
+  uint32_t a_src[P::ALD];  // byte offsets from x (the host checks that x spans less than 2^31 elements)
 #pragma unroll
-  for (int i = 0; i < S::ALD; ++i) {
-    const int lr = (STREAM ? w * (BM / 8) + i * 8 : pp_a_row<BM>(w, i)) + lrow;  // LDS row of the A tile
+  for (int i = 0; i < P::ALD; ++i) {
+    const int lr = pp_a_row<BM>(w, i) + lrow;  // LDS row of the A tile
     int row = ti.row0 + lr;
     row = row < ti.row_end ? row : ti.row_end - 1;
-    a_src[i] = (uint32_t)p.row_token[row] * (uint32_t)M + ((lpp ^ ((lr >> 1) & 7)) * 8);
-    if (!STREAM) a_src[i] *= 2;  // bytes
+    a_src[i] = ((uint32_t)p.row_token[row] * (uint32_t)M + ((lpp ^ ((lr >> 1) & 7)) * 8)) * 2;
   }
   // B: LDS row w*32 + i*8 + lrow  ->  chunk 2*tc + w/4, f = w%2 (gate / up block), column-in-chunk
   // jc = ((w/2)%2)*32 + i*8 + lrow.  Blocks are [M/PW panels][64 j][PW m] (cc_worker.h).
@@ -599,112 +502,58 @@ __device__ __forceinline__ void gateup_body(const uint16_t* __restrict__ x, int 
   const int PW = panel_width(M);
   const int lc0 = lpp ^ (lrow >> 1);  // B piece for even i; odd i uses lc0 ^ 4
 
-  if constexpr (STREAM) {
-    // the same loads, with B through registers: lane (lrow, lpp) of instruction i fetches the piece that the
-    // direct load would have put at byte lane * 16 of the wave's KB i, and stores it there
-    auto issue_a = [&](int sta, int kt) {
-      unsigned char* sa = lds + sta * StreamShape<BM>::A_STAGE + w * (BM / 8) * 128;
+  // uniform bases and 32-bit lane offsets: two vector registers for the B addresses instead of eight (a k-tile never
+  // crosses a panel, PW being a multiple of 64)
+  uint32_t b_lane[2] = {(uint32_t)(jc0 * PW + lc0 * 8) * 2u, (uint32_t)(jc0 * PW + (lc0 ^ 4) * 8) * 2u};
+  auto issue_a = [&](int i, int stage, int kt) {
+    load_lds16(x + kt * BK, a_src[i], lds + stage * P::STAGE + pp_a_row<BM>(w, i) * 128);
+  };
+  auto issue_b = [&](int stage, int kt) {
+    unsigned char* sb = lds + stage * P::STAGE + BM * 128 + w * 4096;
+    const int k0 = kt * BK;
+    const uint16_t* bk = b_blk + (size_t)(k0 / PW) * CHUNK_J * PW + k0 % PW;
 #pragma unroll
-      for (int i = 0; i < S::ALD; ++i)
-        __builtin_amdgcn_global_load_lds(SI_GPTR(x + (a_src[i] + (uint32_t)(kt * BK))), SI_LPTR(sa + i * 1024), 16, 0, 0);
-    };
-    auto bload = [&](int kt, BRegs& r) {
-      const int k0 = kt * BK;
+    for (int i = 0; i < 4; ++i) load_lds16(bk + i * 8 * PW, b_lane[i & 1], sb + i * 1024);
+  };
+  f32x4 acc[P::FA][4];
+  const uint32_t boff[2] = {(uint32_t)swz(wc * 64 + (lane & 15), lane >> 4), (uint32_t)swz(wc * 64 + (lane & 15), 4 + (lane >> 4))};
+  gemm_pingpong<BM, 2048>(lds, M / BK, lane, wr, acc, issue_a, issue_b, boff);
+  // element (row 4*(lane/16) + r, column lane%16) of each 16x16 tile; acc[i][j] is the gate tile and acc[i][j + 2] the
+  // up tile of the same 16 hidden columns
+  // (the lane index is made opaque here so that the output addresses are formed after the main loop: formed
+  // ahead of it they are live through it, which the 320-row body has no registers for)
+  int el = lane;
+  asm volatile("" : "+v"(el));
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int m0 = k0 + (((i & 1) ? (lc0 ^ 4) : lc0) * 8);
-        gload_b128(r.q[i], b_blk + ((size_t)(m0 / PW) * CHUNK_J + jc0 + i * 8) * PW + (m0 % PW));
-      }
-    };
-    auto bstore = [&](int stb, const BRegs& r, int i) {
-      lds_store_b128(lds + StreamShape<BM>::B0 + stb * B_BYTES + w * 4096 + i * 1024 + lane * 16, r.q[i]);
-    };
-    SI_GEMM_DECLS_STREAM(SI_BOFF_SWZ)
-    SI_GEMM_MAIN_LOOP_STREAM(M / BK, issue_a, bload, bstore)
-    // element (row 8*(r/4) + 4*(lane/32) + r%4, column lane%32) of each 32x32 tile;
-    // acc[i][0] is the gate tile and acc[i][1] the up tile of the same 32 hidden columns
-    const int jl = wc * 32 + (lane & 31);  // hidden column inside the 128-column tile
+  for (int j = 0; j < 2; ++j) {
+    const int jl = wc * 32 + j * 16 + (el & 15);  // hidden column inside the 128-column tile
     if (2 * tc + (jl >> 6) < wv.n_chunks) {
       const int col = wv.col0 + tc * 128 + jl;
 #pragma unroll
-      for (int i = 0; i < S::FA; ++i)
+      for (int i = 0; i < P::FA; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = ti.row0 + wr * (BM / 2) + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-          if (row < ti.row_end) hact[(size_t)row * ldh + col] = f32_to_bf16(silu_f(acc[i][0][r]) * acc[i][1][r]);
+        for (int r = 0; r < 4; ++r) {
+          const int row = ti.row0 + wr * (BM / 2) + i * 16 + 4 * (el >> 4) + r;
+          if (row < ti.row_end) hact[(size_t)row * ldh + col] = f32_to_bf16(silu_f(acc[i][j][r]) * acc[i][j + 2][r]);
         }
-    }
-  } else {
-    using P = PingPong<BM>;
-    // uniform bases and 32-bit lane offsets: two vector registers for the B addresses instead of eight (a k-tile never
-    // crosses a panel, PW being a multiple of 64)
-    uint32_t b_lane[2] = {(uint32_t)(jc0 * PW + lc0 * 8) * 2u, (uint32_t)(jc0 * PW + (lc0 ^ 4) * 8) * 2u};
-    auto issue_a = [&](int i, int stage, int kt) {
-      load_lds16(x + kt * BK, a_src[i], lds + stage * P::STAGE + pp_a_row<BM>(w, i) * 128);
-    };
-    auto issue_b = [&](int stage, int kt) {
-      unsigned char* sb = lds + stage * P::STAGE + BM * 128 + w * 4096;
-      const int k0 = kt * BK;
-      const uint16_t* bk = b_blk + (size_t)(k0 / PW) * CHUNK_J * PW + k0 % PW;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) load_lds16(bk + i * 8 * PW, b_lane[i & 1], sb + i * 1024);
-    };
-    f32x4 acc[P::FA][4];
-    const uint32_t boff[2] = {(uint32_t)swz(wc * 64 + (lane & 15), lane >> 4), (uint32_t)swz(wc * 64 + (lane & 15), 4 + (lane >> 4))};
-    gemm_pingpong<BM, 2048>(lds, M / BK, lane, wr, acc, issue_a, issue_b, boff);
-    // element (row 4*(lane/16) + r, column lane%16) of each 16x16 tile; acc[i][j] is the gate tile and acc[i][j + 2] the
-    // up tile of the same 16 hidden columns
-    // (the lane index is made opaque here so that the output addresses are formed after the main loop: formed
-    // ahead of it they are live through it, which the 320-row body has no registers for)
-    int el = lane;
-    asm volatile("" : "+v"(el));
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int jl = wc * 32 + j * 16 + (el & 15);  // hidden column inside the 128-column tile
-      if (2 * tc + (jl >> 6) < wv.n_chunks) {
-        const int col = wv.col0 + tc * 128 + jl;
-#pragma unroll
-        for (int i = 0; i < P::FA; ++i)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int row = ti.row0 + wr * (BM / 2) + i * 16 + 4 * (el >> 4) + r;
-            if (row < ti.row_end) hact[(size_t)row * ldh + col] = f32_to_bf16(silu_f(acc[i][j][r]) * acc[i][j + 2][r]);
-          }
-      }
     }
   }
 }
 
 // A block picks the body for the rows its tile really has (whole-block branch), so a 40-row tile costs a 64-row
-// body and a 140-row tile a 192-row one.  The 320-row body (five A fragments per wave, 144 KB of LDS, every one of
-// the 256 registers a wave may have at two waves per SIMD) exists for the last tile of an expert only.  A tile that
-// holds all rows of its expert, at most 192, runs the streaming loop (StreamShape): its weights come from HBM.
-// (Two spellings of the same choice: with the 320-row body at the very limit of the register file, the order of the
-// tests decides where the compiler places what several bodies have in common, and each kernel has one order that
-// leaves it without a spill; ensure_lds_attr() refuses a build that has one.)
-#define SI_PICK_BODY_GU(ti, CALL)                               \
-  {                                                             \
-    const int rows_ = (ti).row_end - (ti).row0;                 \
-    if (rows_ <= 64) CALL(64, true);                            \
-    else if ((ti).solo && rows_ <= 192) {                       \
-      if (rows_ <= 128) CALL(128, true);                        \
-      else CALL(192, true);                                     \
-    } else if (rows_ <= 128) CALL(128, false);                  \
-    else if (rows_ <= 192) CALL(192, false);                    \
-    else if (rows_ <= 256) CALL(256, false);                    \
-    else CALL(320, false);                                      \
-  }
-#define SI_PICK_BODY_DN(ti, CALL)                               \
-  {                                                             \
-    const int rows_ = (ti).row_end - (ti).row0;                 \
-    if (rows_ > 256) CALL(320, false);                          \
-    else if (rows_ > 192) CALL(256, false);                     \
-    else if (rows_ <= 64) CALL(64, true);                       \
-    else if ((ti).solo) {                                       \
-      if (rows_ <= 128) CALL(128, true);                        \
-      else CALL(192, true);                                     \
-    } else if (rows_ <= 128) CALL(128, false);                  \
-    else CALL(192, false);                                      \
+// body and a 140-row tile a 192-row one.  The 320-row body (160 accumulator registers, 144 KB of LDS) exists for the last
+// tile of an expert only.  Tiles of at most 192 rows that hold all rows of their expert are bound by HBM: they ran a loop
+// of their own before (weights through registers, four k-tiles ahead), which the ping-pong loop overtook because an
+// iteration of it is shorter, not because more bytes are in flight (Mixtral-8x7B-shaped prompt of 512 tokens, about
+// 128 rows per expert: gate/up 398 -> 366 us, down 205 -> 165 us; 24 tokens, 6 rows per expert: equal).
+#define SI_PICK_BODY(ti, CALL)                  \
+  {                                             \
+    const int rows_ = (ti).row_end - (ti).row0; \
+    if (rows_ > 256) CALL(320);                 \
+    else if (rows_ > 192) CALL(256);            \
+    else if (rows_ > 128) CALL(192);            \
+    else if (rows_ > 64) CALL(128);             \
+    else CALL(64);                              \
   }
 // The 4-bit bodies stop at 256 rows (their B operand passes through registers, which leaves no room for a fifth
 // A fragment): the rows a last tile holds beyond 256 take a second pass of the same block.  No wave still reads
@@ -730,8 +579,8 @@ __global__ __launch_bounds__(THREADS, 1) void k_prefill_gateup(const uint16_t* _
   TileInfo ti;
   if (!block_tile(p, expert_sel, x2_only, n_ctiles, n_cu, 1, tc, ti)) return;
   if (!storage_index(wv, ti.e, ti.se)) return;
-#define SI_CALL_GU(BMV, ST) gateup_body<BMV, ST>(x, M, p, tc, ti, wv, hact, ldh, lds)
-  SI_PICK_BODY_GU(ti, SI_CALL_GU)
+#define SI_CALL_GU(BMV) gateup_body<BMV>(x, M, p, tc, ti, wv, hact, ldh, lds)
+  SI_PICK_BODY(ti, SI_CALL_GU)
 #undef SI_CALL_GU
 }
 
@@ -742,11 +591,11 @@ __global__ __launch_bounds__(THREADS, 1) void k_prefill_gateup(const uint16_t* _
 // LDS ([group][256 m] x 16 bytes), read conflict free by consecutive lanes.
 // Output slab `split` of yp: rows x M fp32; overwritten or accumulated.
 // ---------------------------------------------------------------------------------------------
-template <int BM, bool STREAM>
+template <int BM>
 __device__ __forceinline__ void down_body(const uint16_t* __restrict__ hact, int ldh, int M, int inner, const TileInfo& ti,
                                           int n_ntiles, int n_split, const WeightView& wv, float* __restrict__ yp,
                                           size_t slab_stride, int accumulate, unsigned char* lds) {
-  using S = Shape<BM>;
+  using P = PingPong<BM>;
   const int nt = inner % n_ntiles, split = inner / n_ntiles;
   const int c_begin = (int)((long)wv.n_chunks * split / n_split), c_end = (int)((long)wv.n_chunks * (split + 1) / n_split);
   if (c_begin >= c_end && accumulate) return;  // nothing to add
@@ -757,90 +606,54 @@ __device__ __forceinline__ void down_body(const uint16_t* __restrict__ hact, int
   float* out = yp + (size_t)split * slab_stride;
 
   const int lrow = lane >> 3, lpp = lane & 7;
-  uint32_t a_src[S::ALD];  // element offsets from hact (the host checks that it spans less than 2^31 elements)
+  uint32_t a_src[P::ALD];  // byte offsets from hact (the host checks that it spans less than 2^31 elements)
 #pragma unroll
-  for (int i = 0; i < S::ALD; ++i) {
-    const int lr = (STREAM ? w * (BM / 8) + i * 8 : pp_a_row<BM>(w, i)) + lrow;
+  for (int i = 0; i < P::ALD; ++i) {
+    const int lr = pp_a_row<BM>(w, i) + lrow;
     int row = ti.row0 + lr;
     row = row < ti.row_end ? row : ti.row_end - 1;
-    a_src[i] = (uint32_t)row * (uint32_t)ldh + wv.col0 + ((lpp ^ ((lr >> 1) & 7)) * 8);
-    if (!STREAM) a_src[i] *= 2;  // bytes
+    a_src[i] = ((uint32_t)row * (uint32_t)ldh + wv.col0 + ((lpp ^ ((lr >> 1) & 7)) * 8)) * 2;
   }
   // B: wave w loads group q = w of the chunk's down block ([M/NW tiles][8 q][NW m][8 i]), 4 x 64 output columns
   const int NW = ntile_width(M);
   const int nw_shift = __builtin_ctz(NW);
-  uint32_t b_off[4];  // inside one chunk's down block: below 64 * M elements
+  uint32_t b_off[4];  // bytes, inside one chunk's down block
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int n = min(n0 + i * 64 + lane, M - 1);
-    b_off[i] = (((uint32_t)(n >> nw_shift) * 8 + w) * NW + (n & (NW - 1))) * 8;  // NW is a power of two
-    if (!STREAM) b_off[i] *= 2;  // bytes
+    b_off[i] = (((uint32_t)(n >> nw_shift) * 8 + w) * NW + (n & (NW - 1))) * 16;  // NW is a power of two
   }
 
   if (c_begin < c_end) {
-    if constexpr (STREAM) {
-      auto issue_a = [&](int sta, int kt) {
-        unsigned char* sa = lds + sta * StreamShape<BM>::A_STAGE + w * (BM / 8) * 128;
+    auto issue_a = [&](int i, int stage, int kt) {
+      load_lds16(hact + (c_begin + kt) * CHUNK_J, a_src[i], lds + stage * P::STAGE + pp_a_row<BM>(w, i) * 128);
+    };
+    auto issue_b = [&](int stage, int kt) {
+      unsigned char* sb = lds + stage * P::STAGE + BM * 128 + w * 4096;
+      const uint16_t* dblk = ebase + (size_t)(wv.chunk0 + c_begin + kt) * 3 * CHUNK_J * M + (size_t)2 * CHUNK_J * M;
 #pragma unroll
-        for (int i = 0; i < S::ALD; ++i)
-          __builtin_amdgcn_global_load_lds(SI_GPTR(hact + (a_src[i] + (uint32_t)((c_begin + kt) * CHUNK_J))), SI_LPTR(sa + i * 1024), 16, 0, 0);
-      };
-      auto bload = [&](int kt, BRegs& r) {
-        const uint16_t* dblk = ebase + (size_t)(wv.chunk0 + c_begin + kt) * 3 * CHUNK_J * M + (size_t)2 * CHUNK_J * M;
+      for (int i = 0; i < 4; ++i) load_lds16(dblk, b_off[i], sb + i * 1024);
+    };
+    f32x4 acc[P::FA][4];
+    const uint32_t b0 = SI_BOFF_K8(wc * 64 + (lane & 15), lane >> 4);
+    const uint32_t boff[2] = {b0, b0 + 4 * BN * 16};
+    gemm_pingpong<BM, 256>(lds, c_end - c_begin, lane, wr, acc, issue_a, issue_b, boff);
+    int el = lane;  // opaque, as in gateup_body
+    asm volatile("" : "+v"(el));
 #pragma unroll
-        for (int i = 0; i < 4; ++i) gload_b128(r.q[i], dblk + b_off[i]);
-      };
-      auto bstore = [&](int stb, const BRegs& r, int i) {
-        lds_store_b128(lds + StreamShape<BM>::B0 + stb * B_BYTES + w * 4096 + i * 1024 + lane * 16, r.q[i]);
-      };
-      SI_GEMM_DECLS_STREAM(SI_BOFF_K8)
-      SI_GEMM_MAIN_LOOP_STREAM(c_end - c_begin, issue_a, bload, bstore)
+    for (int i = 0; i < P::FA; ++i)
 #pragma unroll
-      for (int i = 0; i < S::FA; ++i)
+      for (int j = 0; j < 4; ++j) {
+        const int m = n0 + wc * 64 + j * 16 + (el & 15);
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int m = n0 + wc * 64 + j * 32 + (lane & 31);
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int row = ti.row0 + wr * (BM / 2) + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-            if (row < ti.row_end && m < M) {
-              float* dst = out + (size_t)row * M + m;
-              *dst = accumulate ? *dst + acc[i][j][r] : acc[i][j][r];
-            }
+        for (int r = 0; r < 4; ++r) {
+          const int row = ti.row0 + wr * (BM / 2) + i * 16 + 4 * (el >> 4) + r;
+          if (row < ti.row_end && m < M) {
+            float* dst = out + (size_t)row * M + m;
+            *dst = accumulate ? *dst + acc[i][j][r] : acc[i][j][r];
           }
         }
-    } else {
-      using P = PingPong<BM>;
-      auto issue_a = [&](int i, int stage, int kt) {
-        load_lds16(hact + (c_begin + kt) * CHUNK_J, a_src[i], lds + stage * P::STAGE + pp_a_row<BM>(w, i) * 128);
-      };
-      auto issue_b = [&](int stage, int kt) {
-        unsigned char* sb = lds + stage * P::STAGE + BM * 128 + w * 4096;
-        const uint16_t* dblk = ebase + (size_t)(wv.chunk0 + c_begin + kt) * 3 * CHUNK_J * M + (size_t)2 * CHUNK_J * M;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) load_lds16(dblk, b_off[i], sb + i * 1024);
-      };
-      f32x4 acc[P::FA][4];
-      const uint32_t b0 = SI_BOFF_K8(wc * 64 + (lane & 15), lane >> 4);
-      const uint32_t boff[2] = {b0, b0 + 4 * BN * 16};
-      gemm_pingpong<BM, 256>(lds, c_end - c_begin, lane, wr, acc, issue_a, issue_b, boff);
-      int el = lane;  // opaque, as in gateup_body
-      asm volatile("" : "+v"(el));
-#pragma unroll
-      for (int i = 0; i < P::FA; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int m = n0 + wc * 64 + j * 16 + (el & 15);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int row = ti.row0 + wr * (BM / 2) + i * 16 + 4 * (el >> 4) + r;
-            if (row < ti.row_end && m < M) {
-              float* dst = out + (size_t)row * M + m;
-              *dst = accumulate ? *dst + acc[i][j][r] : acc[i][j][r];
-            }
-          }
-        }
-    }
+      }
   } else {
     // an empty k-split of an overwriting launch still has to define its slab
     for (int i = tid; i < BM * BN; i += THREADS) {
@@ -863,8 +676,8 @@ __global__ __launch_bounds__(THREADS, 1) void k_prefill_down(const uint16_t* __r
   // which measured 3 % slower although the XCDs finish together)
   if (!block_tile(p, expert_sel, x2_only, n_ntiles * n_split, n_cu, 0, inner, ti)) return;
   if (!storage_index(wv, ti.e, ti.se)) return;
-#define SI_CALL_DN(BMV, ST) down_body<BMV, ST>(hact, ldh, M, inner, ti, n_ntiles, n_split, wv, yp, slab_stride, accumulate, lds)
-  SI_PICK_BODY_DN(ti, SI_CALL_DN)
+#define SI_CALL_DN(BMV) down_body<BMV>(hact, ldh, M, inner, ti, n_ntiles, n_split, wv, yp, slab_stride, accumulate, lds)
+  SI_PICK_BODY(ti, SI_CALL_DN)
 #undef SI_CALL_DN
 }
 

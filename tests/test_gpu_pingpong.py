@@ -1,6 +1,5 @@
 """The ping-pong main loop of the prompt-phase GEMMs waits on hand-counted loads, per phase and per tiles that remain:
-row tiles that share an expert's weights (they never run the streaming loop), one for every body (128, 192, 256 and 320
-rows, full and partly filled), with fewer k-tiles than LDS stages, as many and more, against the oracle."""
+one and two row tiles of an expert, for every body (64 to 320 rows, full and partly filled), with fewer k-tiles than LDS stages, as many and more, against the oracle."""
 import pytest
 
 import paper_2411_15715_amd as si
@@ -9,8 +8,8 @@ from gpu_helpers import GpuLayer, assert_parity
 
 pytestmark = pytest.mark.gpu
 
-# 256 + 65, 256 + 128, 256 + 129, 256 + 192, 256 + 256, 256 + 257, 256 + 320
-ROWS = (321, 384, 385, 448, 512, 513, 576)
+# one tile on both sides of each body, then 256 + 65, 256 + 128, 256 + 129, 256 + 192, 256 + 256, 256 + 257, 256 + 320
+ROWS = (64, 65, 128, 129, 192, 193, 321, 384, 385, 448, 512, 513, 576)
 
 
 @pytest.mark.parametrize("d_model,d_ff", [(64, 64), (128, 512), (192, 768), (256, 1088), (320, 1600), (448, 2048)])
