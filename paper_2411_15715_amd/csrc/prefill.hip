@@ -9,8 +9,8 @@
 // stages filled by direct global->LDS loads (global_load_lds_dwordx4, no VGPR staging), wave tile
 // (BM/2) x 64.  A row tile holds up to 256 rows, the last one of an expert up to 320 (si_internal.h: n_row_tiles);
 // the block runs the body instantiated for BM = 64, 128, 192, 256 or 320, the smallest that covers the rows the
-// tile really has.  Two main loops: ping-pong of two wave groups on v_mfma_f32_16x16x32_bf16 (PingPong), and one
-// on v_mfma_f32_32x32x16_bf16 that converts 4-bit weights on their way into LDS (SI_GEMM_MAIN_LOOP_REGB).
+// tile really has.  The main loop is a ping-pong of two wave groups on v_mfma_f32_16x16x32_bf16 (gemm_pingpong;
+// gemm_pingpong_q4 converts 4-bit weights on their way into LDS).
 // LDS rows hold 64 contraction elements (128 bytes); the 16-byte piece c of row r sits at piece
 // c ^ ((r >> 1) & 7): gfx950's LDS has 64 banks, so 16 consecutive rows x 16 bytes must cover 256
 // distinct bytes of bank space for the 128-bit MFMA operand reads to be conflict free (measured:
@@ -24,7 +24,6 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 #define SI_GPTR(p) ((const void __attribute__((address_space(1)))*)(p))
 #define SI_LPTR(p) ((void __attribute__((address_space(3)))*)(p))
@@ -35,22 +34,6 @@ constexpr int BN = 256;  // B rows per tile: 128 hidden columns (gate+up) or 256
 constexpr int BK = 64;
 constexpr int B_BYTES = BN * BK * 2;  // 32 KB
 constexpr int KERNEL_LDS = 144 * 1024;  // the largest body
-
-// Body shapes of the 4-bit loop.  With few rows the GEMM only streams its weights: the smaller A tiles then
-// leave LDS for a deeper ring of stages, i.e. more weight bytes in flight per CU.
-template <int BM> struct Shape {
-  static constexpr int NST = BM >= 192 ? 2 : 3;           // LDS stages
-  static constexpr int STAGE = BM * 128 + B_BYTES;        // bytes per stage
-  static constexpr int LDS = NST * STAGE;                 // 120, 144, 112, 128, 144 KB for BM = 64, 128, 192, 256, 320
-  static constexpr int FA = BM / 64;                      // A fragments (32 rows each) per wave
-  static constexpr int ALD = BM / 64;                     // A load instructions per wave per stage
-  static constexpr int LPW = ALD + 4;                     // load instructions per wave per stage
-  // Invariant behind every wait_vmcnt<N> of the main loops: between two barriers a wave issues exactly these
-  // vector-memory instructions, in program order, and no others (no spill, no hoisted table load: everything a
-  // loop needs from global memory besides the tiles is fetched before it starts).  ensure_lds_attr() refuses a
-  // build whose kernels use scratch memory, and the GPU tests run every body with fewer, as many and more k-tiles
-  // than stages.
-};
 
 __device__ inline uint16_t f32_to_bf16(float f) {
   uint32_t u = __float_as_uint(f);
@@ -205,16 +188,16 @@ __device__ inline bool block_tile(const Plan& p, int expert_sel, int x2_only, in
 // the power limit where the 32 x 32 x 16 one sustains 1.81 (its accumulators cost twice the register traffic).  Four
 // phases of 16 matrix instructions (64 x 32 quadrants) measured 1378, one wave per SIMD with 128 x 128 tiles 1064.
 // ---------------------------------------------------------------------------------------------
-template <int BM> struct PingPong {
+template <int BM, int BL = 4> struct PingPong {  // BL: direct-to-LDS loads of B per wave and k-tile (0: B travels through registers)
   static constexpr int NST = BM >= 192 ? 2 : 3;     // LDS stages
   static constexpr int STAGE = BM * 128 + B_BYTES;  // bytes per stage
   static constexpr int LDS = NST * STAGE;           // 120, 144, 112, 128, 144 KB for BM = 64, 128, 192, 256, 320
   static constexpr int FA = BM / 32;                // A fragments (16 rows each) per wave
   static constexpr int ALD = BM / 64;               // A load instructions (8 rows each) per wave and k-tile
   static constexpr int NP = (ALD + 1) / 2;          // phases per k-tile
-  static constexpr int LPW = ALD + 4;               // load instructions per wave and k-tile
+  static constexpr int LPW = ALD + BL;              // direct-to-LDS load instructions per wave and k-tile
   static constexpr int aloads(int p) { return ALD - 2 * p < 2 ? ALD - 2 * p : 2; }
-  static constexpr int loads(int p) { return aloads(p) + (p == 0 ? 4 : 0); }
+  static constexpr int loads(int p) { return aloads(p) + (p == 0 ? BL : 0); }
   // loads of a wave that may still be in flight when the data of the phase after phase q of tile `it` must have landed:
   // those issued later than it, in the order (tile, phase region), when `rem` tiles follow tile `it`
   static constexpr int younger(int q, int rem) {
@@ -243,12 +226,13 @@ template <int BM> __device__ inline int pp_a_row(int w, int i) {
   return (w >> 2) * (BM / 2) + p * 64 + (w & 3) * 8;
 }
 
-template <int R, int BM, int Q> __device__ __forceinline__ void pp_wait(int rem) {
+// P: PingPong; X: register loads of B that are younger than what is waited for as well
+template <int R, class P, int Q, int X> __device__ __forceinline__ void pp_wait(int rem) {
   if constexpr (R == 0) {
-    wait_vmcnt<PingPong<BM>::younger(Q, 0)>();
+    wait_vmcnt<P::younger(Q, 0) + X>();
   } else {
-    if (rem >= R) wait_vmcnt<PingPong<BM>::younger(Q, R)>();
-    else pp_wait<R - 1, BM, Q>(rem);
+    if (rem >= R) wait_vmcnt<P::younger(Q, R) + X>();
+    else pp_wait<R - 1, P, Q, X>(rem);
   }
 }
 
@@ -293,7 +277,7 @@ __device__ __forceinline__ void gemm_pingpong(unsigned char* lds, int nk, int la
     } else {
       if (it + P::NST < nk) issue(std::integral_constant<int, q - 1>{}, st, it + P::NST);
     }
-    pp_wait<P::NST, BM, q>(nk - 1 - it);
+    pp_wait<P::NST, P, q, 0>(nk - 1 - it);
     wait_lgkmcnt0();
     __builtin_amdgcn_sched_barrier(0);
     block_barrier();
@@ -341,33 +325,6 @@ __device__ __forceinline__ void gemm_pingpong(unsigned char* lds, int nk, int la
   if (wr == 0) block_barrier();  // the second group's last slot
 }
 
-// ---------------------------------------------------------------------------------------------
-// The 4-bit loop: 8 waves as 2 (rows) x 4 (B-row quarters of 64); wave tile (BM/2) x 64: FA A-fragments x 2
-// B-fragments of v_mfma_f32_32x32x16_bf16.  The one barrier of an iteration sits before its last k-step: by then every
-// fragment of stage `st` is in registers, so after the barrier the stage is refilled and the first fragments of the
-// next stage are fetched while the last 8 MFMAs of this iteration run; the wait before the barrier leaves the younger
-// tiles in flight.
-// ---------------------------------------------------------------------------------------------
-// accumulators, operand fragments and the two lambdas every variant of the main loop uses
-#define SI_GEMM_DECLS(BFRAG_OFF)                                                                                 \
-  f32x16 acc[S::FA][2];                                                                                          \
-  _Pragma("unroll") for (int i = 0; i < S::FA; ++i) _Pragma("unroll") for (int j = 0; j < 2; ++j)                \
-      _Pragma("unroll") for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;                                         \
-  bf16x8 fa[2][S::FA], fb[2][2];                                                                                 \
-  auto ldfrag = [&](int stage, int ks, int buf) {                                                                \
-    const unsigned char* sa = lds + stage * S::STAGE;                                                            \
-    const unsigned char* sb = sa + BM * 128;                                                                     \
-    const int pc = ks * 2 + (lane >> 5);                                                                         \
-    _Pragma("unroll") for (int i = 0; i < S::FA; ++i) fa[buf][i] = as_bf16x8(                                    \
-        *reinterpret_cast<const u32x4*>(sa + swz(wr * (BM / 2) + i * 32 + (lane & 31), pc)));                    \
-    _Pragma("unroll") for (int j = 0; j < 2; ++j) fb[buf][j] = as_bf16x8(                                        \
-        *reinterpret_cast<const u32x4*>(sb + BFRAG_OFF(wc * 64 + j * 32 + (lane & 31), pc)));                    \
-  };                                                                                                             \
-  auto mma = [&](int buf) {                                                                                      \
-    _Pragma("unroll") for (int i = 0; i < S::FA; ++i) _Pragma("unroll") for (int j = 0; j < 2; ++j)              \
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf][i], fb[buf][j], acc[i][j], 0, 0, 0);         \
-  };
-
 // register loads and the dependency tie used by the loops whose B operand travels through registers
 __device__ inline void gload_b128(u32x4& q, const void* p) {
   asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(q) : "v"(p) : "memory");
@@ -377,72 +334,7 @@ __device__ inline void gload_u16(uint32_t& z, const void* p) {
 }
 
 struct Q4Regs { u32x4 q; uint32_t z; };  // codes and scale of one lane's share of a B tile
-
-// The loop for weights in the 4-bit storage form.  The A operand arrives by direct global->LDS loads;
-// the B operand cannot (it has to be turned into bf16 on the way), so every lane fetches 16 bytes of codes (32
-// weights) and their group scale into registers one iteration ahead (BLOAD), and turns them into four 16-byte
-// pieces of bf16((code - 8) * scale) that it writes into the stage freed by the previous iteration's barrier,
-// one piece after each k-step's matrix instructions (BCONV), so that the conversion arithmetic runs under the
-// matrix core's work.  A k-tile of 64 is one scale group of either projection.
-// Order of the vector-memory operations of a wave, which the wait counts rely on: iteration j issues the
-// register loads of tile j+NST (GL instructions, at the top of the iteration) and, after its barrier, the A loads
-// of tile j+NST (ALD instructions).  The register loads are inline assembly and their waits explicit: with
-// direct-to-LDS loads in flight the compiler's own wait before the first use of a loaded register is vmcnt(0),
-// which would drain the ring every iteration; BREADY ties the registers to the explicit wait so that no use is
-// scheduled above it.
-#define SI_GEMM_MAIN_LOOP_REGB(NK, GLN, BREGS, ISSUE_A, BLOAD, BREADY, BCONV)                                    \
-  {                                                                                                              \
-    constexpr int GL = (GLN); /* register loads per B tile and lane */                                           \
-    const int nk_ = (NK);                                                                                        \
-    BREGS ra, rb;                                                                                                \
-    _Pragma("unroll") for (int s0 = 0; s0 < S::NST; ++s0) if (s0 < nk_) ISSUE_A(s0, s0);                         \
-    _Pragma("unroll") for (int s0 = 0; s0 < S::NST - 1; ++s0) if (s0 < nk_) {                                    \
-      BLOAD(s0, ra);                                                                                             \
-      wait_vmcnt<0>();                                                                                           \
-      BREADY(ra);                                                                                                \
-      _Pragma("unroll") for (int i = 0; i < 4; ++i) BCONV(s0, ra, i);                                            \
-    }                                                                                                            \
-    BLOAD(min(S::NST - 1, nk_ - 1), ra);                                                                         \
-    wait_vmcnt<0>();                                                                                             \
-    BREADY(ra);                                                                                                  \
-    wait_lgkmcnt0();                                                                                             \
-    block_barrier();                                                                                             \
-    ldfrag(0, 0, 0);                                                                                             \
-    int st = 0;                                                                                                  \
-    /* one iteration; the registers it converts are rc, those it fetches go to rn: the loop below            */ \
-    /* alternates two register sets, so that no fetched register is copied while its load is in flight        */ \
-    auto step = [&](int it, BREGS& rc, BREGS& rn) {                                                              \
-      const int nx = st + 1 == S::NST ? 0 : st + 1;                                                              \
-      const int pv = st == 0 ? S::NST - 1 : st - 1;                                                              \
-      const bool fill = it + S::NST - 1 < nk_; /* B of tile it+NST-1 goes into stage pv during this iteration */ \
-      /* always issued (index clamped), so that the wait below sees the same number of younger operations */     \
-      BLOAD(min(it + S::NST, nk_ - 1), rn);                                                                      \
-      ldfrag(st, 1, 1); mma(0);                                                                                  \
-      /* rc was fetched at the top of the previous iteration; younger: that iteration's A loads, the          */ \
-      /* fetch above.  Past the last tile the conversion runs on whatever the clamped fetch brought and      */ \
-      /* writes a stage nobody reads again: straight-line code, so that the scheduler can place the          */ \
-      /* conversion arithmetic between the matrix instructions                                               */ \
-      wait_vmcnt<S::ALD + GL>(); BREADY(rc); BCONV(pv, rc, 0);                                                   \
-      ldfrag(st, 2, 0); mma(1); BCONV(pv, rc, 1);                                                                \
-      ldfrag(st, 3, 1); mma(0); BCONV(pv, rc, 2); BCONV(pv, rc, 3);                                              \
-      /* the A loads of tile it+1 must have landed, the B pieces written above and every read of stage st  */    \
-      /* must be complete before the barrier; younger than those A loads are the operations of NST-2 whole  */    \
-      /* iterations and this iteration's register loads                                                     */    \
-      if (fill) wait_vmcnt<(S::NST - 2) * (S::ALD + GL) + GL>(); else wait_vmcnt<0>();                           \
-      wait_lgkmcnt0();                                                                                           \
-      block_barrier();                                                                                           \
-      if (it + 1 < nk_) ldfrag(nx, 0, 0);                                                                        \
-      if (it + S::NST < nk_) ISSUE_A(st, it + S::NST);                                                           \
-      __builtin_amdgcn_s_setprio(1);                                                                             \
-      mma(1);                                                                                                    \
-      __builtin_amdgcn_s_setprio(0);                                                                             \
-      st = nx;                                                                                                   \
-    };                                                                                                           \
-    for (int it = 0; it < nk_; it += 2) {                                                                        \
-      step(it, ra, rb);                                                                                          \
-      if (it + 1 < nk_) step(it + 1, rb, ra);                                                                    \
-    }                                                                                                            \
-  }
+constexpr int Q4_GL = 2;                 // register loads of a Q4Regs
 
 // 16-byte LDS store the compiler does not see as one: with a direct-to-LDS load in flight it would otherwise wait
 // for ALL vector-memory operations (vmcnt(0)) before any LDS store it cannot prove disjoint from the load's
@@ -465,7 +357,173 @@ __device__ inline uint32_t q4_pair(uint32_t bytes, int b0, int b1, float sc, flo
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));  // round to nearest even
 }
 
-#define SI_BOFF_SWZ(row, pc) swz((row), (pc))
+// The ping-pong loop for weights in the 4-bit storage form.  The A operand arrives by direct global->LDS loads as above;
+// the B operand cannot (it has to be turned into bf16 on the way), so every lane fetches 16 bytes of codes (32 weights)
+// and their group scale into registers, and turns them into four 16-byte pieces of bf16((code - 8) * scale) that it
+// writes into the B part of a stage.  A k-tile of 64 is one scale group of either projection.
+// A wave converts B of tile it+1 in the memory slots of tile it, four pieces over its phases, while its partner on the
+// SIMD issues matrix instructions; the registers that frees are refilled in the last phase with tile it+3 (two register
+// sets, the loop unrolled by two, so that no fetched register is copied while its load is in flight).
+// Order of a wave's vector-memory operations, which the wait counts rely on: per phase its A loads, and in the last phase
+// of a tile, after them, the Q4_GL register loads (always issued, tile index clamped).  The register loads are inline
+// assembly and their waits explicit: with direct-to-LDS loads in flight the compiler's own wait before the first use
+// of a loaded register is vmcnt(0), which would drain the ring every iteration; bready ties the registers to the wait.
+//   bload(kt, regs), bconv(stage, regs, i): fetch / convert-and-store piece i
+template <int BM, int BJ, class IA, class BL, class BC>
+__device__ __forceinline__ void gemm_pingpong_q4(unsigned char* lds, int nk, int lane, int wr, f32x4 (&acc)[BM / 32][4],
+                                                 IA issue_a, BL bload, BC bconv, const uint32_t (&boff)[2]) {
+  using P = PingPong<BM, 0>;
+  constexpr int FP = P::ALD >= 2 ? 4 : 2;  // fragments of a phase
+  bf16x8 fa[FP][2], fb[4][2];
+  const uint32_t aoff[2] = {(uint32_t)swz(wr * (BM / 2) + (lane & 15), lane >> 4), (uint32_t)swz(wr * (BM / 2) + (lane & 15), 4 + (lane >> 4))};
+  auto bready = [](Q4Regs& r) { asm volatile("" : "+v"(r.q), "+v"(r.z)::"memory"); };
+  auto issue = [&](auto pc, int stage, int kt) {
+    constexpr int p = decltype(pc)::value;
+#pragma unroll
+    for (int i = 0; i < P::aloads(p); ++i) issue_a(2 * p + i, stage, kt);
+  };
+  auto phase = [&](auto qc, int it, int st, Q4Regs& rg) {
+    constexpr int q = decltype(qc)::value;
+    constexpr int nf = 2 * P::aloads(q);
+    constexpr int XB = Q4_GL * ((q + 1) % P::NP == P::NP - 1 ? P::NST - 1 : P::NST);  // register loads younger than the A region waited for
+    constexpr int NB = P::ALD + P::aloads(P::NP - 1) + Q4_GL;           // operations younger than the codes of tile it+1
+    const unsigned char* sa = lds + st * P::STAGE;
+    const int nst = st + 1 == P::NST ? 0 : st + 1;
+    if constexpr (q == 0) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          fb[j][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(sa + boff[ks] + (BM * 128 + j * BJ)));
+    }
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < nf; ++i)
+        fa[i][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(sa + aoff[ks] + (q * 64 + i * 16) * 128));
+    if constexpr (q == 0) {
+      if (it > 0 && it - 1 + P::NST < nk) issue(std::integral_constant<int, P::NP - 1>{}, st == 0 ? P::NST - 1 : st - 1, it - 1 + P::NST);
+      // (near the end, where A loads are no longer issued, the A part of the count is dropped)
+      if (it - 1 + P::NST < nk) wait_vmcnt<NB>(); else wait_vmcnt<Q4_GL>();
+      bready(rg);
+    } else {
+      if (it + P::NST < nk) issue(std::integral_constant<int, q - 1>{}, st, it + P::NST);
+    }
+#pragma unroll
+    for (int i = 4 * q / P::NP; i < 4 * (q + 1) / P::NP; ++i) bconv(nst, rg, i);
+    if constexpr (q == P::NP - 1) bload(min(it + 3, nk - 1), rg);
+    pp_wait<P::NST, P, q, XB>(nk - 1 - it);
+    wait_lgkmcnt0();
+    __builtin_amdgcn_sched_barrier(0);
+    block_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < nf; ++i)
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+          const int j = (i & 1) ? 3 - jj : jj;
+          acc[q * 4 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i][ks], fb[j][ks], acc[q * 4 + i][j], 0, 0, 0);
+        }
+    __builtin_amdgcn_sched_barrier(0);
+    block_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int i = 0; i < BM / 32; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  using C0 = std::integral_constant<int, 0>;
+  using C1 = std::integral_constant<int, 1>;
+  Q4Regs ra, rb;
+#pragma unroll
+  for (int t = 0; t < P::NST; ++t)
+    if (t < nk) {
+      issue(C0{}, t, t);
+      if constexpr (P::NP > 1) issue(C1{}, t, t);
+    }
+  Q4Regs r0;
+  bload(0, r0);
+  bload(min(1, nk - 1), ra);
+  bload(min(2, nk - 1), rb);
+  wait_vmcnt<0>();
+  bready(r0);
+  bready(ra);
+  bready(rb);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) bconv(0, r0, i);
+  wait_lgkmcnt0();
+  block_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  if (wr == 1) block_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  int st = 0;
+  auto tile = [&](int it, Q4Regs& rg) {
+    phase(C0{}, it, st, rg);
+    if constexpr (P::NP > 1) phase(C1{}, it, st, rg);
+    st = st + 1 == P::NST ? 0 : st + 1;
+  };
+  for (int it = 0; it < nk; it += 2) {
+    tile(it, ra);
+    if (it + 1 < nk) tile(it + 1, rb);
+  }
+  if (wr == 0) block_barrier();  // the second group's last slot
+  wait_vmcnt<0>();  // the clamped fetches past the last tile
+  bready(ra);
+  bready(rb);
+}
+
+// epilogue of FC1: SiLU(gate) * up of the wave's 32 hidden columns -> bf16 Hact
+template <int BM>
+__device__ __forceinline__ void gateup_store(const f32x4 (&acc)[BM / 32][4], const TileInfo& ti, const WeightView& wv, int tc, int wr,
+                                             int wc, int lane, uint16_t* __restrict__ hact, int ldh) {
+  using P = PingPong<BM>;
+  // element (row 4*(lane/16) + r, column lane%16) of each 16x16 tile; acc[i][j] is the gate tile and acc[i][j + 2] the
+  // up tile of the same 16 hidden columns
+  // (the lane index is made opaque here so that the output addresses are formed after the main loop: formed
+  // ahead of it they are live through it, which the 320-row body has no registers for)
+  int el = lane;
+  asm volatile("" : "+v"(el));
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int jl = wc * 32 + j * 16 + (el & 15);  // hidden column inside the 128-column tile
+    if (2 * tc + (jl >> 6) < wv.n_chunks) {
+      const int col = wv.col0 + tc * 128 + jl;
+#pragma unroll
+      for (int i = 0; i < P::FA; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = ti.row0 + wr * (BM / 2) + i * 16 + 4 * (el >> 4) + r;
+          if (row < ti.row_end) hact[(size_t)row * ldh + col] = f32_to_bf16(silu_f(acc[i][j][r]) * acc[i][j + 2][r]);
+        }
+    }
+  }
+}
+
+// epilogue of FC2: the wave's 64 output columns, overwritten or accumulated
+template <int BM>
+__device__ __forceinline__ void down_store(const f32x4 (&acc)[BM / 32][4], const TileInfo& ti, int n0, int wr, int wc, int lane, int M,
+                                           float* __restrict__ out, int accumulate) {
+  using P = PingPong<BM>;
+  int el = lane;  // opaque, as in gateup_store
+  asm volatile("" : "+v"(el));
+#pragma unroll
+  for (int i = 0; i < P::FA; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int m = n0 + wc * 64 + j * 16 + (el & 15);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = ti.row0 + wr * (BM / 2) + i * 16 + 4 * (el >> 4) + r;
+        if (row < ti.row_end && m < M) {
+          float* dst = out + (size_t)row * M + m;
+          *dst = accumulate ? *dst + acc[i][j][r] : acc[i][j][r];
+        }
+      }
+    }
+}
+
 #define SI_BOFF_K8(col, pc) (((pc) * BN + (col)) * 16)
 
 // ---------------------------------------------------------------------------------------------
@@ -518,26 +576,7 @@ __device__ __forceinline__ void gateup_body(const uint16_t* __restrict__ x, int 
   f32x4 acc[P::FA][4];
   const uint32_t boff[2] = {(uint32_t)swz(wc * 64 + (lane & 15), lane >> 4), (uint32_t)swz(wc * 64 + (lane & 15), 4 + (lane >> 4))};
   gemm_pingpong<BM, 2048>(lds, M / BK, lane, wr, acc, issue_a, issue_b, boff);
-  // element (row 4*(lane/16) + r, column lane%16) of each 16x16 tile; acc[i][j] is the gate tile and acc[i][j + 2] the
-  // up tile of the same 16 hidden columns
-  // (the lane index is made opaque here so that the output addresses are formed after the main loop: formed
-  // ahead of it they are live through it, which the 320-row body has no registers for)
-  int el = lane;
-  asm volatile("" : "+v"(el));
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int jl = wc * 32 + j * 16 + (el & 15);  // hidden column inside the 128-column tile
-    if (2 * tc + (jl >> 6) < wv.n_chunks) {
-      const int col = wv.col0 + tc * 128 + jl;
-#pragma unroll
-      for (int i = 0; i < P::FA; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = ti.row0 + wr * (BM / 2) + i * 16 + 4 * (el >> 4) + r;
-          if (row < ti.row_end) hact[(size_t)row * ldh + col] = f32_to_bf16(silu_f(acc[i][j][r]) * acc[i][j + 2][r]);
-        }
-    }
-  }
+  gateup_store<BM>(acc, ti, wv, tc, wr, wc, lane, hact, ldh);
 }
 
 // A block picks the body for the rows its tile really has (whole-block branch), so a 40-row tile costs a 64-row
@@ -638,22 +677,7 @@ __device__ __forceinline__ void down_body(const uint16_t* __restrict__ hact, int
     const uint32_t b0 = SI_BOFF_K8(wc * 64 + (lane & 15), lane >> 4);
     const uint32_t boff[2] = {b0, b0 + 4 * BN * 16};
     gemm_pingpong<BM, 256>(lds, c_end - c_begin, lane, wr, acc, issue_a, issue_b, boff);
-    int el = lane;  // opaque, as in gateup_body
-    asm volatile("" : "+v"(el));
-#pragma unroll
-    for (int i = 0; i < P::FA; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int m = n0 + wc * 64 + j * 16 + (el & 15);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = ti.row0 + wr * (BM / 2) + i * 16 + 4 * (el >> 4) + r;
-          if (row < ti.row_end && m < M) {
-            float* dst = out + (size_t)row * M + m;
-            *dst = accumulate ? *dst + acc[i][j][r] : acc[i][j][r];
-          }
-        }
-      }
+    down_store<BM>(acc, ti, n0, wr, wc, lane, M, out, accumulate);
   } else {
     // an empty k-split of an overwriting launch still has to define its slab
     for (int i = tid; i < BM * BN; i += THREADS) {
@@ -689,25 +713,22 @@ template <int BM>
 __device__ __forceinline__ void gateup_body_q4(const uint16_t* __restrict__ x, int M, const Plan& p, int tc, const TileInfo& ti,
                                                const WeightView& wv, uint16_t* __restrict__ hact, int ldh,
                                                unsigned char* lds) {
-  using S = Shape<BM>;
+  using P = PingPong<BM, 0>;
   const int tid = threadIdx.x, lane = tid % WAVE, w = __builtin_amdgcn_readfirstlane(tid / WAVE);  // wave index, known to be uniform
   const int wr = w >> 2, wc = w & 3;
   const unsigned char* ebase = reinterpret_cast<const unsigned char*>(wv.base + (size_t)ti.se * wv.expert_stride);
 
   const int lrow = lane >> 3, lpp = lane & 7;
-  const uint16_t* a_src[S::ALD];
+  uint32_t a_src[P::ALD];  // byte offsets from x
 #pragma unroll
-  for (int i = 0; i < S::ALD; ++i) {
-    const int lr = w * (BM / 8) + i * 8 + lrow;
+  for (int i = 0; i < P::ALD; ++i) {
+    const int lr = pp_a_row<BM>(w, i) + lrow;
     int row = ti.row0 + lr;
     row = row < ti.row_end ? row : ti.row_end - 1;
-    a_src[i] = x + (size_t)p.row_token[row] * M + ((lpp ^ ((lr >> 1) & 7)) * 8);
+    a_src[i] = ((uint32_t)p.row_token[row] * (uint32_t)M + ((lpp ^ ((lr >> 1) & 7)) * 8)) * 2;
   }
-  auto issue_a = [&](int stage, int kt) {
-    unsigned char* sa = lds + stage * S::STAGE + w * (BM / 8) * 128;
-#pragma unroll
-    for (int i = 0; i < S::ALD; ++i)
-      __builtin_amdgcn_global_load_lds(SI_GPTR(a_src[i] + kt * BK), SI_LPTR(sa + i * 1024), 16, 0, 0);
+  auto issue_a = [&](int i, int stage, int kt) {
+    load_lds16(x + kt * BK, a_src[i], lds + stage * P::STAGE + pp_a_row<BM>(w, i) * 128);
   };
   // B: wave w fills LDS rows [32 w, 32 w + 32) = (chunk 2*tc + w/4, gate (w even) or up block, columns
   // ((w/2)%2)*32 .. +31 of the chunk); lane = (row lane/2, k-half lane%2): the 32 weights of its half row are
@@ -723,7 +744,6 @@ __device__ __forceinline__ void gateup_body_q4(const uint16_t* __restrict__ x, i
     gload_b128(r.q, qrow + (size_t)kt * 32);
     gload_u16(r.z, zrow + kt);
   };
-  auto bready = [&](Q4Regs& r) { asm volatile("" : "+v"(r.q), "+v"(r.z)::"memory"); };
   // word i of the lane's codes = elements 8i .. 8i+7 of its half row; even nibbles hold elements 0 4 1 5, odd
   // nibbles 2 6 3 7 (cc_worker.h)
   auto bconv = [&](int stage, const Q4Regs& r, int i) {
@@ -734,21 +754,12 @@ __device__ __forceinline__ void gateup_body_q4(const uint16_t* __restrict__ x, i
     o.y = q4_pair(od, 0, 2, sc, s8);
     o.z = q4_pair(ev, 1, 3, sc, s8);
     o.w = q4_pair(od, 1, 3, sc, s8);
-    lds_store_b128(lds + stage * S::STAGE + BM * 128 + brow * 128 + (((kh * 4 + i) ^ bsw) << 4), o);
+    lds_store_b128(lds + stage * P::STAGE + BM * 128 + brow * 128 + (((kh * 4 + i) ^ bsw) << 4), o);
   };
-  SI_GEMM_DECLS(SI_BOFF_SWZ)
-  SI_GEMM_MAIN_LOOP_REGB(M / BK, 2, Q4Regs, issue_a, bload, bready, bconv)
-  const int jl = wc * 32 + (lane & 31);
-  if (2 * tc + (jl >> 6) < wv.n_chunks) {
-    const int col = wv.col0 + tc * 128 + jl;
-#pragma unroll
-    for (int i = 0; i < S::FA; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = ti.row0 + wr * (BM / 2) + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (row < ti.row_end) hact[(size_t)row * ldh + col] = f32_to_bf16(silu_f(acc[i][0][r]) * acc[i][1][r]);
-      }
-  }
+  f32x4 acc[P::FA][4];
+  const uint32_t boff[2] = {(uint32_t)swz(wc * 64 + (lane & 15), lane >> 4), (uint32_t)swz(wc * 64 + (lane & 15), 4 + (lane >> 4))};
+  gemm_pingpong_q4<BM, 2048>(lds, M / BK, lane, wr, acc, issue_a, bload, bconv, boff);
+  gateup_store<BM>(acc, ti, wv, tc, wr, wc, lane, hact, ldh);
 }
 
 __global__ __launch_bounds__(THREADS, 1) void k_prefill_gateup_q4(const uint16_t* __restrict__ x, int M, Plan p,
@@ -769,7 +780,7 @@ template <int BM>
 __device__ __forceinline__ void down_body_q4(const uint16_t* __restrict__ hact, int ldh, int M, int inner, const TileInfo& ti,
                                              int n_ntiles, int n_split, const WeightView& wv, float* __restrict__ yp,
                                              size_t slab_stride, int accumulate, unsigned char* lds) {
-  using S = Shape<BM>;
+  using P = PingPong<BM, 0>;
   const int nt = inner % n_ntiles, split = inner / n_ntiles;
   const int c_begin = (int)((long)wv.n_chunks * split / n_split), c_end = (int)((long)wv.n_chunks * (split + 1) / n_split);
   if (c_begin >= c_end && accumulate) return;
@@ -780,19 +791,16 @@ __device__ __forceinline__ void down_body_q4(const uint16_t* __restrict__ hact, 
   float* out = yp + (size_t)split * slab_stride;
 
   const int lrow = lane >> 3, lpp = lane & 7;
-  const uint16_t* a_src[S::ALD];
+  uint32_t a_src[P::ALD];  // byte offsets from hact
 #pragma unroll
-  for (int i = 0; i < S::ALD; ++i) {
-    const int lr = w * (BM / 8) + i * 8 + lrow;
+  for (int i = 0; i < P::ALD; ++i) {
+    const int lr = pp_a_row<BM>(w, i) + lrow;
     int row = ti.row0 + lr;
     row = row < ti.row_end ? row : ti.row_end - 1;
-    a_src[i] = hact + (size_t)row * ldh + wv.col0 + ((lpp ^ ((lr >> 1) & 7)) * 8);
+    a_src[i] = ((uint32_t)row * (uint32_t)ldh + wv.col0 + ((lpp ^ ((lr >> 1) & 7)) * 8)) * 2;
   }
-  auto issue_a = [&](int stage, int kt) {
-    unsigned char* sa = lds + stage * S::STAGE + w * (BM / 8) * 128;
-#pragma unroll
-    for (int i = 0; i < S::ALD; ++i)
-      __builtin_amdgcn_global_load_lds(SI_GPTR(a_src[i] + (c_begin + kt) * CHUNK_J), SI_LPTR(sa + i * 1024), 16, 0, 0);
+  auto issue_a = [&](int i, int stage, int kt) {
+    load_lds16(hact + (c_begin + kt) * CHUNK_J, a_src[i], lds + stage * P::STAGE + pp_a_row<BM>(w, i) * 128);
   };
   // B: thread = (output column n0 + (w%4)*64 + lane, j-half w/4): its 16 bytes of codes are the 32 hidden columns
   // of the half for that output column, i.e. the pieces 4*half .. +3 of the column in the [piece][column] B stage
@@ -807,7 +815,6 @@ __device__ __forceinline__ void down_body_q4(const uint16_t* __restrict__ hact, 
     gload_b128(r.q, cb + qoff);
     gload_u16(r.z, cb + zoff);
   };
-  auto bready = [&](Q4Regs& r) { asm volatile("" : "+v"(r.q), "+v"(r.z)::"memory"); };
   // word i = hidden columns 8i .. 8i+7 of the half; even nibbles hold elements 0 1 2 3, odd nibbles 4 5 6 7
   auto bconv = [&](int stage, const Q4Regs& r, int i) {
     const float sc = __uint_as_float(r.z << 16), s8 = -8.f * sc;
@@ -817,25 +824,14 @@ __device__ __forceinline__ void down_body_q4(const uint16_t* __restrict__ hact, 
     o.y = q4_pair(ev, 2, 3, sc, s8);
     o.z = q4_pair(od, 0, 1, sc, s8);
     o.w = q4_pair(od, 2, 3, sc, s8);
-    lds_store_b128(lds + stage * S::STAGE + BM * 128 + ((half * 4 + i) * BN + col) * 16, o);
+    lds_store_b128(lds + stage * P::STAGE + BM * 128 + ((half * 4 + i) * BN + col) * 16, o);
   };
   if (c_begin < c_end) {
-    SI_GEMM_DECLS(SI_BOFF_K8)
-    SI_GEMM_MAIN_LOOP_REGB(c_end - c_begin, 2, Q4Regs, issue_a, bload, bready, bconv)
-#pragma unroll
-    for (int i = 0; i < S::FA; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int m = n0 + wc * 64 + j * 32 + (lane & 31);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = ti.row0 + wr * (BM / 2) + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-          if (row < ti.row_end && m < M) {
-            float* dst = out + (size_t)row * M + m;
-            *dst = accumulate ? *dst + acc[i][j][r] : acc[i][j][r];
-          }
-        }
-      }
+    f32x4 acc[P::FA][4];
+    const uint32_t b0 = SI_BOFF_K8(wc * 64 + (lane & 15), lane >> 4);
+    const uint32_t boff[2] = {b0, b0 + 4 * BN * 16};
+    gemm_pingpong_q4<BM, 256>(lds, c_end - c_begin, lane, wr, acc, issue_a, bload, bconv, boff);
+    down_store<BM>(acc, ti, n0, wr, wc, lane, M, out, accumulate);
   } else {
     for (int i = tid; i < BM * BN; i += THREADS) {
       const int row = ti.row0 + i / BN, m = n0 + i % BN;
@@ -899,9 +895,6 @@ __global__ void k_fill_zero(float* __restrict__ p, size_t n) {
 
 }  // namespace
 
-static_assert(Shape<64>::LDS <= KERNEL_LDS && Shape<128>::LDS <= KERNEL_LDS && Shape<192>::LDS <= KERNEL_LDS &&
-              Shape<256>::LDS <= KERNEL_LDS, "a body does not fit the launch's LDS");
-
 // compute units of the current device (a round of the tail split)
 static int cu_count() {
   static int n = [] {
@@ -924,7 +917,7 @@ static hipError_t ensure_lds_attr() {
     for (const void* k : kernels) {
       hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, KERNEL_LDS);
       if (e != hipSuccess) return e;
-      // The main loops count their own vector-memory operations (wait_vmcnt<N> against Shape<>::LPW / ALD): a
+      // The main loops count their own vector-memory operations (wait_vmcnt<N> against PingPong<>::younger): a
       // register spill would add scratch loads and stores to that count and let a barrier pass before a tile has
       // landed.  A build whose GEMM kernels use scratch memory is refused here instead of computing wrong results.
       hipFuncAttributes fa{};
