@@ -35,13 +35,15 @@ constexpr int BK = 64;
 constexpr int B_BYTES = BN * BK * 2;  // 32 KB
 constexpr int KERNEL_LDS = 144 * 1024;  // the largest body
 
-__device__ inline uint16_t f32_to_bf16(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
+// (the reciprocal instruction is accurate to one unit in the last place of fp32; the product is rounded to bf16 next)
+__device__ inline float silu_f(float z) { return z * __builtin_amdgcn_rcpf(1.f + __expf(-z)); }
 
-__device__ inline float silu_f(float z) { return z / (1.f + __expf(-z)); }
+// two floats -> two bf16 (round to nearest even) in one register, a in the low half
+__device__ inline uint32_t pack_bf16(float a, float b) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+}
 
 __device__ inline bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
@@ -236,7 +238,8 @@ template <int R, class P, int Q, int X> __device__ __forceinline__ void pp_wait(
   }
 }
 
-// acc[i][j] += the 16 x 16 tile (rows i*16.., B rows j*16..) of the wave over nk k-tiles.
+// acc[i][j] += the 16 x 16 tile (rows i*16.., B rows j*16..) of the wave over nk k-tiles, transposed: lane l holds row
+// l%16 and the four consecutive B rows 4*(l/16) .. +3, i.e. output columns that are adjacent in memory.
 //   issue_a(i, stage, kt): wave's i-th A load of tile kt into LDS stage `stage` (rows pp_a_row);  issue_b(stage, kt): its 4 B
 //   loads;  boff[ks]: byte offset of the lane's piece of B fragment 0 in k-step ks inside the B part of a stage, BJ: bytes
 //   between fragments.  (Fragment addresses are one lane offset per k-step and operand plus constants: the swizzle of
@@ -289,7 +292,7 @@ __device__ __forceinline__ void gemm_pingpong(unsigned char* lds, int nk, int la
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
           const int j = (i & 1) ? 3 - jj : jj;
-          acc[q * 4 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i][ks], fb[j][ks], acc[q * 4 + i][j], 0, 0, 0);
+          acc[q * 4 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][ks], fa[i][ks], acc[q * 4 + i][j], 0, 0, 0);
         }
     __builtin_amdgcn_sched_barrier(0);
     block_barrier();
@@ -351,10 +354,7 @@ __device__ inline void lds_store_b128(unsigned char* p, const u32x4& v) {
 __device__ inline uint32_t q4_pair(uint32_t bytes, int b0, int b1, float sc, float s8) {
   // (the compiler turns byte extraction + conversion into one v_cvt_f32_ubyteN)
   const float c0 = (float)((bytes >> (8 * b0)) & 0xffu), c1 = (float)((bytes >> (8 * b1)) & 0xffu);
-  typedef float f32x2 __attribute__((ext_vector_type(2)));
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  const f32x2 v = {__builtin_fmaf(c0, sc, s8), __builtin_fmaf(c1, sc, s8)};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));  // round to nearest even
+  return pack_bf16(__builtin_fmaf(c0, sc, s8), __builtin_fmaf(c1, sc, s8));
 }
 
 // The ping-pong loop for weights in the 4-bit storage form.  The A operand arrives by direct global->LDS loads as above;
@@ -424,7 +424,7 @@ __device__ __forceinline__ void gemm_pingpong_q4(unsigned char* lds, int nk, int
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
           const int j = (i & 1) ? 3 - jj : jj;
-          acc[q * 4 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i][ks], fb[j][ks], acc[q * 4 + i][j], 0, 0, 0);
+          acc[q * 4 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][ks], fa[i][ks], acc[q * 4 + i][j], 0, 0, 0);
         }
     __builtin_amdgcn_sched_barrier(0);
     block_barrier();
@@ -474,54 +474,55 @@ __device__ __forceinline__ void gemm_pingpong_q4(unsigned char* lds, int nk, int
   bready(rb);
 }
 
-// epilogue of FC1: SiLU(gate) * up of the wave's 32 hidden columns -> bf16 Hact
+// Epilogue of FC1: SiLU(gate) * up of the wave's 32 hidden columns -> bf16 Hact.  The loader puts the hidden columns of a
+// wave into LDS in an order (gu_col) that leaves 8 adjacent columns in a lane, for one 16-byte store per fragment row: with
+// the plain order, 2-byte stores and a full division this epilogue was 1180 vector instructions per wave, 5 us of a tile.
 template <int BM>
 __device__ __forceinline__ void gateup_store(const f32x4 (&acc)[BM / 32][4], const TileInfo& ti, const WeightView& wv, int tc, int wr,
                                              int wc, int lane, uint16_t* __restrict__ hact, int ldh) {
   using P = PingPong<BM>;
-  // element (row 4*(lane/16) + r, column lane%16) of each 16x16 tile; acc[i][j] is the gate tile and acc[i][j + 2] the
-  // up tile of the same 16 hidden columns
+  if (2 * tc + (wc >> 1) >= wv.n_chunks) return;
   // (the lane index is made opaque here so that the output addresses are formed after the main loop: formed
   // ahead of it they are live through it, which the 320-row body has no registers for)
   int el = lane;
   asm volatile("" : "+v"(el));
+  const int row0 = ti.row0 + wr * (BM / 2) + (el & 15);
+  uint16_t* dst = hact + (size_t)row0 * ldh + (wv.col0 + tc * 128 + wc * 32 + (el >> 4) * 8);
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int jl = wc * 32 + j * 16 + (el & 15);  // hidden column inside the 128-column tile
-    if (2 * tc + (jl >> 6) < wv.n_chunks) {
-      const int col = wv.col0 + tc * 128 + jl;
+  for (int i = 0; i < P::FA; ++i) {
+    u32x4 o;
 #pragma unroll
-      for (int i = 0; i < P::FA; ++i)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = ti.row0 + wr * (BM / 2) + i * 16 + 4 * (el >> 4) + r;
-          if (row < ti.row_end) hact[(size_t)row * ldh + col] = f32_to_bf16(silu_f(acc[i][j][r]) * acc[i][j + 2][r]);
-        }
-    }
+      for (int r = 0; r < 2; ++r)
+        o[j * 2 + r] = pack_bf16(silu_f(acc[i][j][2 * r]) * acc[i][j + 2][2 * r], silu_f(acc[i][j][2 * r + 1]) * acc[i][j + 2][2 * r + 1]);
+    if (row0 + i * 16 < ti.row_end) *reinterpret_cast<u32x4*>(dst + (size_t)(i * 16) * ldh) = o;
   }
 }
+// hidden column (of the 32 of a wave) whose gate / up row sits at LDS row r of the wave's 32: fragment j = r / 16, row
+// n = r % 16 of it holds column 8*(n/4) + 4*j + n%4
+__device__ inline int gu_col(int r) { return ((r & 12) << 1) + ((r >> 4) << 2) + (r & 3); }
 
-// epilogue of FC2: the wave's 64 output columns, overwritten or accumulated
+// Epilogue of FC2: the wave's 64 output columns, overwritten or accumulated, 16 bytes per lane
 template <int BM>
 __device__ __forceinline__ void down_store(const f32x4 (&acc)[BM / 32][4], const TileInfo& ti, int n0, int wr, int wc, int lane, int M,
                                            float* __restrict__ out, int accumulate) {
   using P = PingPong<BM>;
   int el = lane;  // opaque, as in gateup_store
   asm volatile("" : "+v"(el));
+  const int row0 = ti.row0 + wr * (BM / 2) + (el & 15), m0 = n0 + wc * 64 + (el >> 4) * 4;
+  float* dst = out + (size_t)row0 * M + m0;
 #pragma unroll
-  for (int i = 0; i < P::FA; ++i)
+  for (int i = 0; i < P::FA; ++i) {
+    if (row0 + i * 16 < ti.row_end) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = n0 + wc * 64 + j * 16 + (el & 15);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = ti.row0 + wr * (BM / 2) + i * 16 + 4 * (el >> 4) + r;
-        if (row < ti.row_end && m < M) {
-          float* dst = out + (size_t)row * M + m;
-          *dst = accumulate ? *dst + acc[i][j][r] : acc[i][j][r];
+      for (int j = 0; j < 4; ++j)
+        if (m0 + j * 16 < M) {
+          f32x4* d = reinterpret_cast<f32x4*>(dst + (size_t)(i * 16) * M + j * 16);
+          *d = accumulate ? *d + acc[i][j] : acc[i][j];
         }
-      }
     }
+  }
 }
 
 #define SI_BOFF_K8(col, pc) (((pc) * BN + (col)) * 16)
@@ -553,10 +554,10 @@ __device__ __forceinline__ void gateup_body(const uint16_t* __restrict__ x, int 
     a_src[i] = ((uint32_t)p.row_token[row] * (uint32_t)M + ((lpp ^ ((lr >> 1) & 7)) * 8)) * 2;
   }
   // B: LDS row w*32 + i*8 + lrow  ->  chunk 2*tc + w/4, f = w%2 (gate / up block), column-in-chunk
-  // jc = ((w/2)%2)*32 + i*8 + lrow.  Blocks are [M/PW panels][64 j][PW m] (cc_worker.h).
+  // jc = ((w/2)%2)*32 + gu_col(i*8 + lrow).  Blocks are [M/PW panels][64 j][PW m] (cc_worker.h).
   const int chunk_rel = min(2 * tc + (w >> 2), wv.n_chunks - 1);
   const uint16_t* b_blk = ebase + (size_t)(wv.chunk0 + chunk_rel) * 3 * CHUNK_J * M + (size_t)(w & 1) * CHUNK_J * M;
-  const int jc0 = ((w >> 1) & 1) * 32 + lrow;
+  const int jc0 = ((w >> 1) & 1) * 32 + gu_col(lrow);
   const int PW = panel_width(M);
   const int lc0 = lpp ^ (lrow >> 1);  // B piece for even i; odd i uses lc0 ^ 4
 
@@ -571,7 +572,7 @@ __device__ __forceinline__ void gateup_body(const uint16_t* __restrict__ x, int 
     const int k0 = kt * BK;
     const uint16_t* bk = b_blk + (size_t)(k0 / PW) * CHUNK_J * PW + k0 % PW;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) load_lds16(bk + i * 8 * PW, b_lane[i & 1], sb + i * 1024);
+    for (int i = 0; i < 4; ++i) load_lds16(bk + gu_col(i * 8) * PW, b_lane[i & 1], sb + i * 1024);
   };
   f32x4 acc[P::FA][4];
   const uint32_t boff[2] = {(uint32_t)swz(wc * 64 + (lane & 15), lane >> 4), (uint32_t)swz(wc * 64 + (lane & 15), 4 + (lane >> 4))};
@@ -731,11 +732,11 @@ __device__ __forceinline__ void gateup_body_q4(const uint16_t* __restrict__ x, i
     load_lds16(x + kt * BK, a_src[i], lds + stage * P::STAGE + pp_a_row<BM>(w, i) * 128);
   };
   // B: wave w fills LDS rows [32 w, 32 w + 32) = (chunk 2*tc + w/4, gate (w even) or up block, columns
-  // ((w/2)%2)*32 .. +31 of the chunk); lane = (row lane/2, k-half lane%2): the 32 weights of its half row are
+  // ((w/2)%2)*32 + gu_col(row) of the chunk); lane = (row lane/2, k-half lane%2): the 32 weights of its half row are
   // 16 bytes of codes, i.e. the pieces 4*(lane%2) .. +3 of the LDS row
   const int chunk_rel = min(2 * tc + (w >> 2), wv.n_chunks - 1);
   const unsigned char* cb = ebase + (size_t)(wv.chunk0 + chunk_rel) * q4_chunk_u16(M) * 2;
-  const int jc = ((w >> 1) & 1) * 32 + (lane >> 1), kh = lane & 1;
+  const int jc = ((w >> 1) & 1) * 32 + gu_col(lane >> 1), kh = lane & 1;
   const unsigned char* qrow = cb + q4_off_codes(w & 1, M) + (size_t)jc * (M / 2) + kh * 16;
   const uint16_t* zrow = reinterpret_cast<const uint16_t*>(cb + q4_off_scales(w & 1, M)) + (size_t)jc * (M / 64);
   const int brow = w * 32 + (lane >> 1);
