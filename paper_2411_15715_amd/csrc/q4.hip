@@ -1,32 +1,26 @@
 // Kernels for the 4-bit storage form of the weights (codes 0..15 standing for (code - 8) * scale, bf16 group
 // scales; chunk layout in cc_worker.h).
-//   k_decode_gateup_q4 / k_decode_down_q4 : the generation-phase GEMVs straight from the codes (fp32, exact
-//       products; 4x fewer weight bytes than bf16, so the integer unpacking has to stay below ~2 VALU
-//       operations per weight for the kernels to remain bound by HBM)
+//   k_decode_gateup_q4 / k_decode_down_q4 : the generation-phase GEMVs straight from the codes (exact products, fp32
+//       sums; 4x fewer weight bytes than bf16, so the unpacking, about 1.5 vector instructions per weight, and not the
+//       multiplication, which the matrix cores do, has to stay below the time the bytes take)
 //   k_dequant_q4 : codes -> bf16 chunks (the layout the MFMA GEMMs read), piece by piece, for the prompt phase
 #include "si_internal.h"
+
+#include <algorithm>
 
 namespace si {
 namespace {
 
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 constexpr int WAVE = 64;
-constexpr int QGU_THREADS = 256;
-constexpr int QGU_JPW = 4;                                   // hidden columns per wave
-constexpr int QGU_JPB = QGU_JPW * (QGU_THREADS / WAVE);      // per block (16)
+constexpr int QGU_THREADS = 512;
+constexpr int QGU_JPB = 32;  // hidden columns per block
 constexpr int QDN_THREADS = 256;
 
-__device__ inline float bf_lo(uint32_t u) { return __uint_as_float(u << 16); }
-__device__ inline float bf_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
 __device__ inline float bf16_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 __device__ inline float silu_f(float z) { return z / (1.f + __expf(-z)); }
-
-__device__ inline float wave_sum(float v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, WAVE);
-  return v;
-}
 
 // expert handled by this block and its row range; false when there is nothing to do
 __device__ inline bool block_rows(const Plan& p, int expert_sel, int x2_only, int slot, int& e, int& r0, int& r1) {
@@ -42,195 +36,300 @@ __device__ inline bool block_rows(const Plan& p, int expert_sel, int x2_only, in
   return r1 > r0;
 }
 
-// sum over the 32 weights of one 16-byte load of x[m] * (128 + code[m]): the pair (codes 2p, 2p+1) of a word is
-// (word >> 4p) & 0x000F000F; putting 0x4300 into the other bits of both halves makes the two bf16 values
-// 128 + code (exact: bf16 has 8 significant bits), and one dot-product instruction multiplies them with the bf16
-// pair of x.  mask / magic arrive in registers so that select-bits-and-merge is one bit-field-insert
-// instruction: shift, insert, dot product = 3 operations per 2 weights.
-__device__ inline float dot_codes(const u32x4& w, const uint32_t* xv, uint32_t mask, uint32_t magic) {
-  float d = 0.f;
-  const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+// The generation-phase GEMVs on the matrix cores.  A code c turns into the bf16 value 128 + c by inserting its nibble
+// into 0x4300 (exact), so a 32-bit word of 8 codes is matrix operand data after 3 shifts and 4 and-or instructions,
+// whatever the number of tokens: the rows of the other operand are the tokens (or the bf16 parts of fp32 activations).
+// Per scale group: acc = -136 sum(x) + sum x (128 + c), total += scale * acc, in fp32.  The dot-product kernels this
+// replaces (shift, insert and one dot instruction per pair and token) were bound by the vector units: LLaMA-shaped layer,
+// 3 tokens, gate/up 107 us and down 77 us for 250 and 125 MB of codes.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// the 8 codes of a word as bf16(128 + c): register i holds the nibbles i and i + 4.  mask / magic arrive in registers, so
+// that and-then-or is one instruction.  (Not inline assembly: a matrix instruction may read a register that a vector
+// instruction wrote only two wait states later, and the compiler inserts those for instructions it knows.)
+__device__ __forceinline__ u32x4 expand_codes(uint32_t w, uint32_t mask, uint32_t magic) {
+  u32x4 o;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int pp = 0; pp < 4; ++pp) {
-      const uint32_t sh = ws[i] >> (4 * pp);
-      uint32_t pair;  // (mask & sh) | (~mask & magic)
-      asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(pair) : "v"(mask), "v"(sh), "s"(magic));
-      d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), __builtin_bit_cast(bf16x2, xv[i * 4 + pp]), d, false);
-    }
-  return d;
+  for (int i = 0; i < 4; ++i) o[i] = ((w >> (4 * i)) & mask) | magic;
+  return o;
 }
 
-// h[row][j] = SiLU(x . Wg[j]) * (x . Wu[j]) with W = (code - 8) * scale:
-//   x . W[j] = sum over groups of 64 m of scale * ( sum x (128 + code) - 136 * sum x ).
-// A lane owns 32 consecutive m of a row per pass (one 16-byte load per row), i.e. half a scale group.
-template <int TB>
-__global__ __launch_bounds__(QGU_THREADS) void k_decode_gateup_q4(const uint16_t* __restrict__ x, int M, Plan p,
-                                                                  int expert_sel, int x2_only, WeightView wv,
-                                                                  float* __restrict__ h, int ldh) {
-  extern __shared__ uint32_t s_xq[];  // [TB][M/2] bf16 pairs of x
-  int e, r0, r1;
+// FC2: a lane's 16-byte load holds 32 codes of a column, i.e. half a scale group: lanes of quarter q = lane/16 hold half q%2 of group q/2.
+// Exchanging between the lane halves leaves words of one group in all four quarters, which one matrix instruction needs:
+// g[0][i], g[1][i]: word pair i of group 0 / 1.  Quarter q then covers the contraction offset unit_k(q) + 8 i.
+__device__ __forceinline__ void split_groups(const u32x4& w, uint32_t (&g)[2][2]) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const auto r = __builtin_amdgcn_permlane32_swap(w[i], w[i + 2], false, false);
+    g[0][i] = r[0];
+    g[1][i] = r[1];
+  }
+}
+__device__ inline int unit_k(int q) { return ((q & 1) << 5) | ((q >> 1) << 4); }
+
+// h[row][j] = SiLU(x . Wg[j]) * (x . Wu[j]).  A wave owns 4 hidden columns over the whole contraction: v_mfma_f32_4x4x4_16b
+// multiplies 16 independent 4 x 4 x 4 blocks, and block b = lane / 4 takes the 32 codes of piece b (16 bytes) of a row, so
+// that one load covers 256 contiguous bytes of 4 rows and a lane's codes lie in one scale group.  (With the 16 x 16 x 32
+// instruction a load covers 64 bytes of 16 rows: the same loads without any arithmetic then took 57 us for 250 MB where
+// 1 KB runs took 43.)  A lane ends up with 4 tokens of its column and piece, scaled and summed over the row in fp32;
+// -136 sum(x) is the product of x with a constant operand.  LDS: x of up to 4 tokens.
+// LLaMA-shaped layer, 3 tokens: 107 -> 55 us (250 MB of codes).
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+constexpr int QU = 2;      // units (512 codes per row; 2 KB of gate and up codes per wave) in flight, refilled as they are consumed
+                           // (3 and 4 units: 62 and 67 us instead of 55, the registers cost waves)
+constexpr int QGU_TB = 4;  // tokens per pass over the weights
+__global__ __launch_bounds__(QGU_THREADS, 4) void k_decode_gateup_q4(const uint16_t* __restrict__ x, int M, Plan p,
+                                                                     int expert_sel, int x2_only, WeightView wv,
+                                                                     float* __restrict__ h, int ldh, int tb) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char s_q[];
+  int e, r0, r1, se;
   if (!block_rows(p, expert_sel, x2_only, blockIdx.y, e, r0, r1)) return;
-  const int tid = threadIdx.x, lane = tid % WAVE, wid = tid / WAVE;
-  const int M2 = M / 2, M32 = M / 32, MG = M / 64;
+  if (!storage_index(wv, e, se)) return;
+  const int tid = threadIdx.x, lane = tid % WAVE, wid = __builtin_amdgcn_readfirstlane(tid / WAVE), j = lane & 3, pc = lane >> 2;
   constexpr int blocks_per_chunk = CHUNK_J / QGU_JPB;
   const int chunk = wv.chunk0 + blockIdx.x / blocks_per_chunk;
-  const int jj0 = (blockIdx.x % blocks_per_chunk) * QGU_JPB + wid * QGU_JPW;
-  int se;
-  if (!storage_index(wv, e, se)) return;
+  const int jb = (blockIdx.x % blocks_per_chunk) * QGU_JPB, jj0 = jb + wid * 4;
   const unsigned char* cb = reinterpret_cast<const unsigned char*>(wv.base + (size_t)se * wv.expert_stride + (size_t)chunk * q4_chunk_u16(M));
-  const u32x4* gq = reinterpret_cast<const u32x4*>(cb + q4_off_codes(0, M));
-  const u32x4* uq = reinterpret_cast<const u32x4*>(cb + q4_off_codes(1, M));
-  const uint16_t* gs = reinterpret_cast<const uint16_t*>(cb + q4_off_scales(0, M));
-  const uint16_t* us = reinterpret_cast<const uint16_t*>(cb + q4_off_scales(1, M));
-  const int jcol = wv.col0 + (blockIdx.x / blocks_per_chunk) * CHUNK_J + jj0;
-  const u32x4* gp = gq + (size_t)jj0 * M32;
-  const u32x4* up = uq + (size_t)jj0 * M32;
-  const uint16_t* gsp = gs + (size_t)jj0 * MG;
-  const uint16_t* usp = us + (size_t)jj0 * MG;
-  u32x4 wg[QGU_JPW], wu[QGU_JPW];
-  float sg[QGU_JPW], su[QGU_JPW];
-  auto load_w = [&](int slot) {
-#pragma unroll
-    for (int j = 0; j < QGU_JPW; ++j) {
-      wg[j] = __builtin_nontemporal_load(gp + j * M32 + slot);
-      wu[j] = __builtin_nontemporal_load(up + j * M32 + slot);
-      sg[j] = bf16_f32(gsp[j * MG + (slot >> 1)]);
-      su[j] = bf16_f32(usp[j * MG + (slot >> 1)]);
-    }
-  };
+  const unsigned char* gq = cb + q4_off_codes(0, M) + (size_t)(jj0 + j) * (M / 2);
+  const unsigned char* uq = cb + q4_off_codes(1, M) + (size_t)(jj0 + j) * (M / 2);
+  const int n_pieces = M / 32, n_units = (n_pieces + 15) / 16;
+  const int MG = M / 64, GS = MG + 2, xstride = 2 * M + 16;     // (padded: the 4 tokens of 4 pieces then cover all banks)
+  uint16_t* s_sc = reinterpret_cast<uint16_t*>(s_q);           // [2][32][GS]
+  unsigned char* s_x = s_q + 2 * QGU_JPB * GS * 2;             // [tb][xstride]
+  uint32_t mask = 0x000F000Fu, magic = 0x43004300u, m136 = 0xC308C308u;  // (m136: two bf16 values -136)
+  asm volatile("" : "+v"(mask), "+s"(magic), "+v"(m136));  // kept out of the optimiser's sight (see expand_codes)
+  const s16x4 neg136 = __builtin_bit_cast(s16x4, (u32x2{m136, m136}));
 
-  for (int rb = r0; rb < r1; rb += TB) {
-    const int nt = min(TB, r1 - rb);
-    __syncthreads();
-    for (int i = tid; i < nt * (M2 / 4); i += QGU_THREADS) {
-      const int tb = i / (M2 / 4), c = i % (M2 / 4);
-      const int tok = p.row_token[rb + tb];
-      reinterpret_cast<u32x4*>(s_xq)[tb * (M2 / 4) + c] = reinterpret_cast<const u32x4*>(x + (size_t)tok * M)[c];
+  u32x4 wg[QU], wu[QU];
+  auto fetch1 = [&](int i, int u) {
+    const int pp = min(u * 16 + pc, n_pieces - 1);  // (a piece past the row is fetched from its end and not used)
+    wg[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(gq + (size_t)pp * 16));
+    wu[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(uq + (size_t)pp * 16));
+  };
+  auto fetch = [&]() {
+#pragma unroll
+    for (int i = 0; i < QU; ++i) fetch1(i, i);
+  };
+  fetch();
+  // the scales of the 32 rows are contiguous: 8 per load (32 * MG of them, so no load crosses the section).  Fetched by
+  // each wave as it needs them, 16 bytes of a row at a time, they cost 7 us.
+  for (int i = tid; i < 2 * 4 * MG; i += QGU_THREADS) {
+    const int f = i >= 4 * MG, pos = (f ? i - 4 * MG : i) * 8;
+    const u32x4 v = *reinterpret_cast<const u32x4*>(cb + q4_off_scales(f, M) + ((size_t)jb * MG + pos) * 2);
+    int r = pos / MG, g = pos - r * MG;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      s_sc[(f * QGU_JPB + r) * GS + g] = (uint16_t)(v[k >> 1] >> (16 * (k & 1)));
+      if (++g == MG) { g = 0; ++r; }
+    }
+  }
+  const uint16_t* sc = s_sc + (wid * 4 + j) * GS;
+  for (int rb = r0; rb < r1; rb += tb) {
+    const int nt = min(tb, r1 - rb);
+    if (rb != r0) {
+      __syncthreads();
+      fetch();
+    }
+    // x in batches of XB pieces of 16 bytes per thread, whose loads are in flight together
+    constexpr int XB = 6;
+    const int M8 = M / 8;
+    for (int i0 = tid; i0 < nt * M8; i0 += XB * QGU_THREADS) {
+      u32x4 v[XB];
+#pragma unroll
+      for (int b = 0; b < XB; ++b) {
+        const int i = min(i0 + b * QGU_THREADS, nt * M8 - 1), t = i / M8;
+        v[b] = reinterpret_cast<const u32x4*>(x + (size_t)p.row_token[rb + t] * M)[i - t * M8];
+      }
+#pragma unroll
+      for (int b = 0; b < XB; ++b) {
+        const int i = i0 + b * QGU_THREADS, t = i / M8, c = i - t * M8;
+        if (i < nt * M8) *reinterpret_cast<u32x4*>(s_x + t * xstride + c * 16) = v[b];
+      }
     }
     __syncthreads();
-    float ag[QGU_JPW][TB], au[QGU_JPW][TB];
+    // operand rows past the last token repeat it, their results are not read
+    const unsigned char* xrow = s_x + min(j, nt - 1) * xstride;
+    f32x4 tg = {0.f, 0.f, 0.f, 0.f}, tu = tg;
+    auto use = [&](int i, int u) {
+      const int pp = min(u * 16 + pc, n_pieces - 1);
+      const bool in = u * 16 + pc < n_pieces;
+      const unsigned char* xp = xrow + pp * 64;
+      f32x4 ag = {0.f, 0.f, 0.f, 0.f}, au = ag, as = ag;
 #pragma unroll
-    for (int j = 0; j < QGU_JPW; ++j)
+      for (int w = 0; w < 4; ++w) {
+        const u32x4 xv = *reinterpret_cast<const u32x4*>(xp + w * 16);
+        const u32x4 cg = expand_codes(wg[i][w], mask, magic), cu = expand_codes(wu[i][w], mask, magic);
 #pragma unroll
-      for (int tb = 0; tb < TB; ++tb) { ag[j][tb] = 0.f; au[j][tb] = 0.f; }
-    // constants kept out of the optimiser's sight (see dot_codes)
-    uint32_t mask = 0x000F000Fu, magic = 0x43004300u, ones = 0x3F803F80u;
-    asm volatile("" : "+v"(mask), "+s"(magic), "+s"(ones));
-    for (int slot = lane; slot < M32; slot += WAVE) {
-      load_w(slot);
-#pragma unroll
-      for (int tb = 0; tb < TB; ++tb) {
-        if (tb < nt) {
-          uint32_t xv[16];
-          const u32x4* xs4 = reinterpret_cast<const u32x4*>(s_xq + tb * M2 + slot * 16);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const u32x4 v = xs4[i];
-            xv[4 * i] = v.x; xv[4 * i + 1] = v.y; xv[4 * i + 2] = v.z; xv[4 * i + 3] = v.w;
-          }
-          float xsum = 0.f;  // sum of the lane's 32 x values: pairs times (1, 1)
-#pragma unroll
-          for (int i = 0; i < 16; ++i)
-            xsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, xv[i]), __builtin_bit_cast(bf16x2, ones), xsum, false);
-          const float off = 136.f * xsum;
-#pragma unroll
-          for (int j = 0; j < QGU_JPW; ++j) {
-            ag[j][tb] = fmaf(sg[j], dot_codes(wg[j], xv, mask, magic) - off, ag[j][tb]);
-            au[j][tb] = fmaf(su[j], dot_codes(wu[j], xv, mask, magic) - off, au[j][tb]);
-          }
+        for (int f = 0; f < 2; ++f) {
+          const s16x4 xa = __builtin_bit_cast(s16x4, (u32x2{xv[2 * f], xv[2 * f + 1]}));
+          as = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(xa, neg136, as, 0, 0, 0);
+          ag = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(xa, __builtin_bit_cast(s16x4, (u32x2{cg[2 * f], cg[2 * f + 1]})), ag, 0, 0, 0);
+          au = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(xa, __builtin_bit_cast(s16x4, (u32x2{cu[2 * f], cu[2 * f + 1]})), au, 0, 0, 0);
         }
+      }
+      const float sg = in ? bf16_f32(sc[pp >> 1]) : 0.f, su = in ? bf16_f32(sc[QGU_JPB * GS + (pp >> 1)]) : 0.f;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) { tg[r] = fmaf(sg, ag[r] + as[r], tg[r]); tu[r] = fmaf(su, au[r] + as[r], tu[r]); }
+    };
+    int u0 = 0;
+    for (; u0 + QU < n_units; u0 += QU) {
+#pragma unroll
+      for (int i = 0; i < QU; ++i) {
+        use(i, u0 + i);
+        fetch1(i, u0 + QU + i);
       }
     }
 #pragma unroll
-    for (int j = 0; j < QGU_JPW; ++j)
+    for (int i = 0; i < QU; ++i)
+      if (u0 + i < n_units) use(i, u0 + i);
+    // sum over the 16 pieces; then lanes 0..3 hold the tokens of columns 0..3
 #pragma unroll
-      for (int tb = 0; tb < TB; ++tb) {
-        if (tb < nt) {
-          const float g = wave_sum(ag[j][tb]);
-          const float u = wave_sum(au[j][tb]);
-          if (lane == 0) h[(size_t)(rb + tb) * ldh + jcol + j] = silu_f(g) * u;
-        }
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int d = 4; d < WAVE; d <<= 1) {
+        tg[r] += __shfl_xor(tg[r], d, WAVE);
+        tu[r] += __shfl_xor(tu[r], d, WAVE);
       }
+    if (lane < 4) {
+#pragma unroll
+      for (int t = 0; t < QGU_TB; ++t)
+        if (t < nt) h[(size_t)(rb + t) * ldh + wv.col0 + (blockIdx.x / blocks_per_chunk) * CHUNK_J + jj0 + j] = silu_f(tg[t]) * tu[t];
+    }
   }
 }
 
-// part[slot][row][m] = sum over the chunks of the slot of scale_c[m] * ( sum_j h_j code[j][m] - 8 * sum_j h_j ).
-// One thread per output column; a chunk's 64 codes of a column are two 16-byte loads.
-template <int TB>
+// part[slot][row][m] = sum over the chunks of the slot of scale_c[m] * sum_j h_j (code[j][m] - 8).  Block: 128 output
+// columns (32 per wave) of one slot; a load covers 256 contiguous bytes of two halves of two chunks.  LLaMA-shaped layer,
+// 3 tokens: 77 -> 25 us (125 MB of codes, 5 TB/s; four pairs of chunks in flight instead of two cost waves: 29 us).  The fp32 activations are split into three bf16 parts (8 significant bits each, i.e.
+// exactly), which are three operand rows: rows 4t .. 4t+2 belong to token t, so a lane ends up with the parts of one token.
+constexpr int QDN_COLS = 128, QDN_TB = 4;
 __global__ __launch_bounds__(QDN_THREADS) void k_decode_down_q4(const float* __restrict__ h, int ldh, int M, Plan p,
                                                                 int expert_sel, int x2_only, WeightView wv, int slot0,
                                                                 int chunks_per_slot, float* __restrict__ part,
-                                                                size_t slot_stride) {
-  int e, r0, r1;
+                                                                size_t slot_stride, int tb) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char s_h[];
+  int e, r0, r1, se;
   if (!block_rows(p, expert_sel, x2_only, blockIdx.z, e, r0, r1)) return;
   const int s = blockIdx.y;
   const int c_begin = s * chunks_per_slot;
-  const int c_end = min(c_begin + chunks_per_slot, wv.n_chunks);
-  if (c_begin >= c_end) return;
-  const int m = blockIdx.x * QDN_THREADS + threadIdx.x;
-  const bool active = m < M;
-  const int mm = active ? m : 0;
-  const int NW = ntile_width(M);
-  int se;
+  const int n_c = min(chunks_per_slot, wv.n_chunks - c_begin);
+  if (n_c <= 0) return;
   if (!storage_index(wv, e, se)) return;
-  const uint16_t* ebase = wv.base + (size_t)se * wv.expert_stride;
+  const int tid = threadIdx.x, lane = tid % WAVE, wid = __builtin_amdgcn_readfirstlane(tid / WAVE), q = lane >> 4;
+  const int NW = ntile_width(M);
+  const size_t cbytes = q4_chunk_u16(M) * 2;
+  const unsigned char* base = reinterpret_cast<const unsigned char*>(wv.base + (size_t)se * wv.expert_stride) + (size_t)(wv.chunk0 + c_begin) * cbytes;
   float* out = part + (size_t)(slot0 + s) * slot_stride;
+  int m[2];
+  size_t qo[2], zo[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    m[i] = blockIdx.x * QDN_COLS + wid * 32 + i * 16 + (lane & 15);
+    const int mm = min(m[i], M - 1);
+    qo[i] = q4_off_codes(2, M) + (((size_t)(mm / NW) * 2 + (q & 1)) * NW + mm % NW) * 16;
+    zo[i] = q4_off_scales(2, M) + (size_t)mm * 2;
+  }
+  const int n_j = n_c * CHUNK_J, hstride = 2 * n_j + 16;
+  float* s_sum = reinterpret_cast<float*>(s_h + (size_t)tb * 3 * hstride);  // [n_c][tb][4]: -136 * (chunk sums of the parts)
+  uint32_t mask = 0x000F000Fu, magic = 0x43004300u;
+  asm volatile("" : "+v"(mask), "+s"(magic));
 
-  extern __shared__ float s_hq[];  // [TB][n_j] activations of this slot, then [TB][n_c] their sums per chunk
-  const int n_c = c_end - c_begin, n_j = n_c * CHUNK_J;
-  float* s_sum = s_hq + TB * n_j;
-  const int jbase = wv.col0 + c_begin * CHUNK_J;
-
-  for (int rb = r0; rb < r1; rb += TB) {
-    const int nt = min(TB, r1 - rb);
-    __syncthreads();
-    for (int i = threadIdx.x; i < nt * n_j; i += QDN_THREADS) {
-      const int tb = i / n_j, j = i % n_j;
-      s_hq[tb * n_j + j] = h[(size_t)(rb + tb) * ldh + jbase + j];
+  constexpr int DU = 2;  // pairs of chunks fetched ahead
+  u32x4 wd[DU][2];
+  uint32_t zd[DU][2];
+  auto fetch = [&](int c0) {
+#pragma unroll
+    for (int d = 0; d < DU; ++d)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const unsigned char* cb = base + (size_t)min(c0 + 2 * d + (q >> 1), n_c - 1) * cbytes;
+        wd[d][i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(cb + qo[i]));
+        zd[d][i] = *reinterpret_cast<const uint16_t*>(cb + zo[i]);
+      }
+  };
+  fetch(0);
+  for (int rb = r0; rb < r1; rb += tb) {
+    const int nt = min(tb, r1 - rb);
+    if (rb != r0) {
+      __syncthreads();
+      fetch(0);
     }
-    __syncthreads();
-    for (int i = threadIdx.x; i < nt * n_c; i += QDN_THREADS) {
-      const int tb = i / n_c, c = i % n_c;
-      float a = 0.f;
-      for (int j = 0; j < CHUNK_J; ++j) a += s_hq[tb * n_j + c * CHUNK_J + j];
-      s_sum[tb * n_c + c] = a;
-    }
-    __syncthreads();
-    float acc[TB];
+    // eight activations per thread, stored in the order in which a word delivers its codes: 0 2 4 6 1 3 5 7
+    for (int i = tid; i < nt * (n_j / 8); i += QDN_THREADS) {
+      const int t = i / (n_j / 8), c8 = i % (n_j / 8);
+      const f32x4* src = reinterpret_cast<const f32x4*>(h + (size_t)(rb + t) * ldh + wv.col0 + c_begin * CHUNK_J + c8 * 8);
+      const f32x4 lo = src[0], hi = src[1];
+      const float v[8] = {lo[0], lo[2], hi[0], hi[2], lo[1], lo[3], hi[1], hi[3]};
+      u32x4 o[3];
+      float sum[3] = {0.f, 0.f, 0.f};
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb) acc[tb] = 0.f;
-    for (int c = c_begin; c < c_end; ++c) {
-      const unsigned char* cb = reinterpret_cast<const unsigned char*>(ebase + (size_t)(wv.chunk0 + c) * q4_chunk_u16(M));
-      const u32x4* dq = reinterpret_cast<const u32x4*>(cb + q4_off_codes(2, M));
-      const size_t i0 = ((size_t)(mm / NW) * 2) * NW + (mm % NW);
-      const u32x4 w0 = __builtin_nontemporal_load(dq + i0), w1 = __builtin_nontemporal_load(dq + i0 + NW);
-      const float sd = bf16_f32(reinterpret_cast<const uint16_t*>(cb + q4_off_scales(2, M))[mm]);
-      const uint32_t ws[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+      for (int w = 0; w < 4; ++w)
 #pragma unroll
-      for (int tb = 0; tb < TB; ++tb) {
-        if (tb < nt) {
-          const float4* hr = reinterpret_cast<const float4*>(s_hq + tb * n_j + (c - c_begin) * CHUNK_J);
-          float a = 0.f;
+        for (int f = 0; f < 2; ++f) {
+          float rest = v[2 * w + f];
 #pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            const uint32_t lo = ws[q] & 0x0F0F0F0Fu, hi = (ws[q] >> 4) & 0x0F0F0F0Fu;
-            const float4 h0 = hr[q * 2], h1 = hr[q * 2 + 1];
-            a = fmaf(h0.x, (float)(lo & 0xffu), a); a = fmaf(h0.y, (float)((lo >> 8) & 0xffu), a);
-            a = fmaf(h0.z, (float)((lo >> 16) & 0xffu), a); a = fmaf(h0.w, (float)(lo >> 24), a);
-            a = fmaf(h1.x, (float)(hi & 0xffu), a); a = fmaf(h1.y, (float)((hi >> 8) & 0xffu), a);
-            a = fmaf(h1.z, (float)((hi >> 16) & 0xffu), a); a = fmaf(h1.w, (float)(hi >> 24), a);
+          for (int a = 0; a < 3; ++a) {
+            const uint32_t bits = __float_as_uint(rest) & 0xffff0000u;
+            const float pv = __uint_as_float(bits);
+            rest -= pv;
+            sum[a] += pv;
+            if (f == 0) o[a][w] = bits >> 16; else o[a][w] |= bits;
           }
-          acc[tb] = fmaf(sd, a - 8.f * s_sum[tb * n_c + (c - c_begin)], acc[tb]);
+        }
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        *reinterpret_cast<u32x4*>(s_h + (t * 3 + a) * hstride + c8 * 16) = o[a];
+#pragma unroll
+        for (int d = 1; d < 8; d <<= 1) sum[a] += __shfl_xor(sum[a], d, WAVE);
+      }
+      if ((c8 & 7) == 0) *reinterpret_cast<f32x4*>(s_sum + ((size_t)(c8 >> 3) * tb + t) * 4) = f32x4{-136.f * sum[0], -136.f * sum[1], -136.f * sum[2], 0.f};
+    }
+    __syncthreads();
+    const unsigned char* hrow = s_h + (min((lane & 15) >> 2, nt - 1) * 3 + min(lane & 3, 2)) * hstride + unit_k(q) * 2;
+    const float* srow = s_sum + min(q, nt - 1) * 4;
+    float tot[2] = {0.f, 0.f};
+    for (int c0 = 0; c0 < n_c; c0 += 2 * DU) {
+      u32x4 cd[DU][2];
+      uint32_t cz[DU][2];
+#pragma unroll
+      for (int d = 0; d < DU; ++d)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) { cd[d][i] = wd[d][i]; cz[d][i] = zd[d][i]; }
+      if (c0 + 2 * DU < n_c) fetch(c0 + 2 * DU);
+#pragma unroll
+      for (int d = 0; d < DU; ++d) {
+        uint32_t g[2][2][2];
+        float sc[2][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          split_groups(cd[d][i], g[i]);
+          const auto z = __builtin_amdgcn_permlane32_swap(cz[d][i], cz[d][i], false, false);
+          sc[0][i] = __uint_as_float(z[0] << 16);
+          sc[1][i] = __uint_as_float(z[1] << 16);
+        }
+#pragma unroll
+        for (int gi = 0; gi < 2; ++gi) {
+          const int c = c0 + 2 * d + gi;
+          if (c < n_c) {
+            const f32x4 off = *reinterpret_cast<const f32x4*>(srow + (size_t)c * tb * 4);
+            f32x4 acc[2] = {off, off};
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+              const bf16x8 hv = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(hrow + c * 128 + k * 16));
+#pragma unroll
+              for (int i = 0; i < 2; ++i)
+                acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hv, __builtin_bit_cast(bf16x8, expand_codes(g[i][gi][k], mask, magic)), acc[i], 0, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) tot[i] = fmaf(sc[gi][i], acc[i][0] + (acc[i][1] + acc[i][2]), tot[i]);
+          }
         }
       }
     }
-    if (active) {
 #pragma unroll
-      for (int tb = 0; tb < TB; ++tb)
-        if (tb < nt) out[(size_t)(rb + tb) * M + m] = acc[tb];
-    }
+    for (int i = 0; i < 2; ++i)
+      if (q < nt && m[i] < M) out[(size_t)(rb + q) * M + m[i]] = tot[i];
   }
 }
 
@@ -292,19 +391,31 @@ __global__ __launch_bounds__(256) void k_dequant_q4(const uint16_t* __restrict__
   }
 }
 
-int pick_tb(int tb_hint) { return tb_hint <= 1 ? 1 : (tb_hint <= 2 ? 2 : 4); }
+size_t gateup_lds(int tb, int M) { return (size_t)2 * QGU_JPB * (M / 64 + 2) * 2 + (size_t)tb * (2 * M + 16); }
+size_t down_lds(int tb, int cps) { return (size_t)tb * 3 * (2 * cps * CHUNK_J + 16) + (size_t)cps * tb * 16; }
+constexpr size_t Q4_LDS = 81 * 1024;  // two blocks per compute unit
+
+hipError_t ensure_q4_lds() {
+  static hipError_t st = [] {
+    const void* kernels[] = {(const void*)k_decode_gateup_q4, (const void*)k_decode_down_q4};
+    for (const void* k : kernels) {
+      const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)Q4_LDS);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }();
+  return st;
+}
 
 }  // namespace
 
 hipError_t launch_decode_gateup_q4(const uint16_t* x, int M, const Plan& plan, int tb_hint, int expert_sel, int x2_only,
                                    int max_touched, const WeightView& wv, float* h, int ldh, hipStream_t stream) {
   if (wv.n_chunks <= 0) return hipSuccess;
+  if (hipError_t e = ensure_q4_lds(); e != hipSuccess) return e;
   dim3 grid(wv.n_chunks * (CHUNK_J / QGU_JPB), expert_sel >= 0 ? 1 : max_touched);
-  const int tb = pick_tb(tb_hint);
-  const size_t lds = (size_t)tb * M * 2;
-  if (tb == 1) hipLaunchKernelGGL(k_decode_gateup_q4<1>, grid, dim3(QGU_THREADS), lds, stream, x, M, plan, expert_sel, x2_only, wv, h, ldh);
-  else if (tb == 2) hipLaunchKernelGGL(k_decode_gateup_q4<2>, grid, dim3(QGU_THREADS), lds, stream, x, M, plan, expert_sel, x2_only, wv, h, ldh);
-  else hipLaunchKernelGGL(k_decode_gateup_q4<4>, grid, dim3(QGU_THREADS), lds, stream, x, M, plan, expert_sel, x2_only, wv, h, ldh);
+  const int tb = std::max(1, std::min(tb_hint, QGU_TB));  // (80 KB of LDS at most: two blocks per CU)
+  hipLaunchKernelGGL(k_decode_gateup_q4, grid, dim3(QGU_THREADS), gateup_lds(tb, M), stream, x, M, plan, expert_sel, x2_only, wv, h, ldh, tb);
   return hipGetLastError();
 }
 
@@ -312,17 +423,12 @@ hipError_t launch_decode_down_q4(const float* h, int ldh, int M, const Plan& pla
                                  int max_touched, const WeightView& wv, int slot0, int chunks_per_slot, float* part,
                                  size_t slot_stride, hipStream_t stream) {
   if (wv.n_chunks <= 0) return hipSuccess;
+  if (hipError_t e = ensure_q4_lds(); e != hipSuccess) return e;
   const int n_slots = (wv.n_chunks + chunks_per_slot - 1) / chunks_per_slot;
-  dim3 grid((M + QDN_THREADS - 1) / QDN_THREADS, n_slots, expert_sel >= 0 ? 1 : max_touched);
-  int tb = pick_tb(tb_hint);
-  size_t lds = (size_t)tb * chunks_per_slot * (CHUNK_J + 1) * sizeof(float);
-  while (lds > 65536 && tb > 1) {  // stay inside the default dynamic LDS limit: fewer tokens per weight pass
-    tb >>= 1;
-    lds = (size_t)tb * chunks_per_slot * (CHUNK_J + 1) * sizeof(float);
-  }
-  if (tb == 1) hipLaunchKernelGGL(k_decode_down_q4<1>, grid, dim3(QDN_THREADS), lds, stream, h, ldh, M, plan, expert_sel, x2_only, wv, slot0, chunks_per_slot, part, slot_stride);
-  else if (tb == 2) hipLaunchKernelGGL(k_decode_down_q4<2>, grid, dim3(QDN_THREADS), lds, stream, h, ldh, M, plan, expert_sel, x2_only, wv, slot0, chunks_per_slot, part, slot_stride);
-  else hipLaunchKernelGGL(k_decode_down_q4<4>, grid, dim3(QDN_THREADS), lds, stream, h, ldh, M, plan, expert_sel, x2_only, wv, slot0, chunks_per_slot, part, slot_stride);
+  dim3 grid((M + QDN_COLS - 1) / QDN_COLS, n_slots, expert_sel >= 0 ? 1 : max_touched);
+  int tb = std::max(1, std::min(tb_hint, QDN_TB));
+  while (tb > 1 && down_lds(tb, chunks_per_slot) > Q4_LDS) --tb;
+  hipLaunchKernelGGL(k_decode_down_q4, grid, dim3(QDN_THREADS), down_lds(tb, chunks_per_slot), stream, h, ldh, M, plan, expert_sel, x2_only, wv, slot0, chunks_per_slot, part, slot_stride, tb);
   return hipGetLastError();
 }
 
