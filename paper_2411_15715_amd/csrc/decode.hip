@@ -8,6 +8,7 @@
 #include "si_internal.h"
 #include "route_device.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace si {
@@ -32,8 +33,11 @@ __device__ inline float wave_sum(float v) {
 __device__ inline float silu_f(float z) { return z / (1.f + __expf(-z)); }
 
 // expert handled by this block and its row range; returns false when there is nothing to do
+// (slot < 0: the shared expert, entry n_routed, of a launch that covers it along with the routed ones)
 __device__ inline bool block_rows(const Plan& p, int expert_sel, int x2_only, int slot, int& e, int& r0, int& r1) {
-  if (expert_sel >= 0) {
+  if (slot < 0) {
+    e = p.n_routed;
+  } else if (expert_sel >= 0) {
     e = expert_sel;
   } else {
     if (slot >= *p.n_touched) return false;
@@ -140,11 +144,15 @@ __device__ inline void block_route(const FusedRoute& fr, BlockRoute& br, const P
 
 template <int TB, int FUSED>
 __global__ __launch_bounds__(GU_THREADS) void k_decode_gateup(const uint16_t* __restrict__ x, int M, Plan p,
-                                                              int expert_sel, int x2_only, WeightView wv,
-                                                              float* __restrict__ h, int ldh, FusedRoute fr) {
+                                                              int expert_sel, int x2_only, WeightView wv_r, WeightView wv_s,
+                                                              int shared_y, float* __restrict__ h, int ldh, FusedRoute fr) {
   extern __shared__ u32x4 s_x[];  // [TB][M/8] bf16 x 8
   __shared__ typename std::conditional<FUSED != 0, BlockRoute, int>::type s_br;  // (4 bytes when the tables are given)
   int e, r0, r1;
+  // the first shared_y rows of the grid are the blocks of the shared expert 
+  const int slot = (int)blockIdx.y - shared_y;
+  const int bx = slot < 0 ? blockIdx.y * gridDim.x + blockIdx.x : blockIdx.x;
+  const WeightView wv = slot < 0 ? wv_s : wv_r;
   const int* row_token = p.row_token;
   constexpr int X_EARLY_MAX = 4;  // 16-byte pieces per thread: d_model <= 8192
   u32x4 x_reg[X_EARLY_MAX];
@@ -159,26 +167,31 @@ __global__ __launch_bounds__(GU_THREADS) void k_decode_gateup(const uint16_t* __
     }
     BlockRoute& br = s_br;
     block_route(fr, br, p, blockIdx.x == 0 && blockIdx.y == 0);
-    if (expert_sel >= 0) {
+    if (slot < 0) {
+      e = fr.E;
+      r0 = fr.T * fr.k;
+      r1 = r0 + fr.T;
+    } else if (expert_sel >= 0) {
       // one given expert: the routed expert of a dense layer (every pair is its row)
       e = expert_sel;
       r0 = 0;
       r1 = fr.T * fr.k;
     } else {
-      if ((int)blockIdx.y >= br.n_touched) return;
-      e = br.t_expert[blockIdx.y];
-      r0 = br.t_off[blockIdx.y];
-      r1 = r0 + br.t_cnt[blockIdx.y];
+      if (slot >= br.n_touched) return;
+      e = br.t_expert[slot];
+      r0 = br.t_off[slot];
+      r1 = r0 + br.t_cnt[slot];
     }
     row_token = br.row_token;
   } else {
-    if (!block_rows(p, expert_sel, x2_only, blockIdx.y, e, r0, r1)) return;
+    if (!block_rows(p, expert_sel, x2_only, slot, e, r0, r1)) return;
   }
   const int tid = threadIdx.x, lane = tid % WAVE, wid = tid / WAVE;
   const int M8 = M / 8;
   const int blocks_per_chunk = CHUNK_J / GU_JPB;
-  const int chunk = wv.chunk0 + blockIdx.x / blocks_per_chunk;
-  const int jj0 = (blockIdx.x % blocks_per_chunk) * GU_JPB + wid * GU_JPW;  // first j of this wave in the chunk
+  if (bx >= wv.n_chunks * blocks_per_chunk) return;
+  const int chunk = wv.chunk0 + bx / blocks_per_chunk;
+  const int jj0 = (bx % blocks_per_chunk) * GU_JPB + wid * GU_JPW;  // first j of this wave in the chunk
   int se;
   if (!storage_index(wv, e, se)) return;
   const uint16_t* cbase = wv.base + (size_t)se * wv.expert_stride + (size_t)chunk * 3 * CHUNK_J * M;
@@ -186,7 +199,7 @@ __global__ __launch_bounds__(GU_THREADS) void k_decode_gateup(const uint16_t* __
   const u32x4* gblk = reinterpret_cast<const u32x4*>(cbase);
   const u32x4* ublk = reinterpret_cast<const u32x4*>(cbase + (size_t)CHUNK_J * M);
   const int PW = panel_width(M), PW8 = PW / 8;
-  const int jcol = wv.col0 + (blockIdx.x / blocks_per_chunk) * CHUNK_J + jj0;
+  const int jcol = wv.col0 + (bx / blocks_per_chunk) * CHUNK_J + jj0;
 
   // One-row launches (TB == 1, the generation phase proper): the weights of a wave's first step are fetched before
   // the row of x is staged (and, with a single token, x before the token assignment is derived), so that a block's
@@ -277,12 +290,16 @@ __global__ __launch_bounds__(GU_THREADS) void k_decode_gateup(const uint16_t* __
 
 template <int TB>
 __global__ __launch_bounds__(DN_THREADS) void k_decode_down(const float* __restrict__ h, int ldh, int M, Plan p,
-                                                            int expert_sel, int x2_only, WeightView wv, int slot0,
-                                                            int chunks_per_slot, float* __restrict__ part,
-                                                            size_t slot_stride) {
+                                                            int expert_sel, int x2_only, WeightView wv_r, WeightView wv_s,
+                                                            int shared_z, int cps_s, int slot0, int chunks_per_slot,
+                                                            float* __restrict__ part, size_t slot_stride) {
   int e, r0, r1;
-  if (!block_rows(p, expert_sel, x2_only, blockIdx.z, e, r0, r1)) return;
-  const int s = blockIdx.y;
+  // the first shared_z layers of the grid are the j-slots of the shared expert
+  const int slot = (int)blockIdx.z - shared_z;
+  if (!block_rows(p, expert_sel, x2_only, slot, e, r0, r1)) return;
+  const WeightView wv = slot < 0 ? wv_s : wv_r;
+  if (slot < 0) chunks_per_slot = cps_s;
+  const int s = slot < 0 ? blockIdx.z * gridDim.y + blockIdx.y : blockIdx.y;
   const int c_begin = s * chunks_per_slot;
   const int c_end = min(c_begin + chunks_per_slot, wv.n_chunks);
   if (c_begin >= c_end) return;
@@ -387,45 +404,46 @@ __global__ __launch_bounds__(64) void k_decode_combine(DecodeCombineArgs a, Plan
 static int pick_tb(int tb_hint) { return tb_hint <= 1 ? 1 : (tb_hint <= 2 ? 2 : 4); }
 
 hipError_t launch_decode_gateup(const uint16_t* x, int M, const Plan& plan, int tb_hint, int expert_sel, int x2_only,
-                                int max_touched, const WeightView& wv, float* h, int ldh, hipStream_t stream,
-                                const FusedRoute* fused_route) {
+                                int max_touched, const WeightView& wv, const WeightView& ws, float* h, int ldh,
+                                hipStream_t stream, const FusedRoute* fused_route) {
   if (wv.n_chunks <= 0) return hipSuccess;
   if (wv.q4) {
     if (fused_route) return hipErrorInvalidValue;  // the 4-bit kernels take the assignment from the tables
-    return launch_decode_gateup_q4(x, M, plan, tb_hint, expert_sel, x2_only, max_touched, wv, h, ldh, stream);
+    return launch_decode_gateup_q4(x, M, plan, tb_hint, expert_sel, x2_only, max_touched, wv, ws, h, ldh, stream);
   }
-  dim3 grid(wv.n_chunks * (CHUNK_J / GU_JPB), expert_sel >= 0 ? 1 : max_touched);
+  const int shared_y = (ws.n_chunks + wv.n_chunks - 1) / wv.n_chunks;
+  dim3 grid(wv.n_chunks * (CHUNK_J / GU_JPB), shared_y + (expert_sel >= 0 ? 1 : max_touched));
   const int tb = pick_tb(tb_hint);
   size_t lds = (size_t)tb * M * 2;
-  if (fused_route) {
-    const FusedRoute& fr = *fused_route;
-    if (fr.T < 1 || fr.T > FUSED_ROUTE_MAX_T || fr.T * fr.k > FUSED_ROUTE_MAX_PAIRS || fr.E > MAX_EXPERTS || x2_only) return hipErrorInvalidValue;
-    if (tb == 1) hipLaunchKernelGGL((k_decode_gateup<1, 1>), grid, dim3(GU_THREADS), lds, stream, x, M, plan, expert_sel, x2_only, wv, h, ldh, fr);
-    else if (tb == 2) hipLaunchKernelGGL((k_decode_gateup<2, 1>), grid, dim3(GU_THREADS), lds, stream, x, M, plan, expert_sel, x2_only, wv, h, ldh, fr);
-    else hipLaunchKernelGGL((k_decode_gateup<4, 1>), grid, dim3(GU_THREADS), lds, stream, x, M, plan, expert_sel, x2_only, wv, h, ldh, fr);
-    return hipGetLastError();
-  }
   const FusedRoute none{};
-  if (tb == 1) hipLaunchKernelGGL((k_decode_gateup<1, 0>), grid, dim3(GU_THREADS), lds, stream, x, M, plan, expert_sel, x2_only, wv, h, ldh, none);
-  else if (tb == 2) hipLaunchKernelGGL((k_decode_gateup<2, 0>), grid, dim3(GU_THREADS), lds, stream, x, M, plan, expert_sel, x2_only, wv, h, ldh, none);
-  else hipLaunchKernelGGL((k_decode_gateup<4, 0>), grid, dim3(GU_THREADS), lds, stream, x, M, plan, expert_sel, x2_only, wv, h, ldh, none);
+  const FusedRoute& fr = fused_route ? *fused_route : none;
+  if (fused_route && (fr.T < 1 || fr.T > FUSED_ROUTE_MAX_T || fr.T * fr.k > FUSED_ROUTE_MAX_PAIRS || fr.E > MAX_EXPERTS || x2_only))
+    return hipErrorInvalidValue;
+#define SI_GU(TBV, F) hipLaunchKernelGGL((k_decode_gateup<TBV, F>), grid, dim3(GU_THREADS), lds, stream, x, M, plan, expert_sel, x2_only, wv, ws, shared_y, h, ldh, fr)
+  if (fused_route) {
+    if (tb == 1) SI_GU(1, 1); else if (tb == 2) SI_GU(2, 1); else SI_GU(4, 1);
+  } else {
+    if (tb == 1) SI_GU(1, 0); else if (tb == 2) SI_GU(2, 0); else SI_GU(4, 0);
+  }
+#undef SI_GU
   return hipGetLastError();
 }
 
 hipError_t launch_decode_down(const float* h, int ldh, int M, const Plan& plan, int tb_hint, int expert_sel, int x2_only,
-                              int max_touched, const WeightView& wv, int slot0, int chunks_per_slot, float* part,
-                              size_t slot_stride, hipStream_t stream) {
+                              int max_touched, const WeightView& wv, const WeightView& ws, int cps_s, int slot0, int chunks_per_slot,
+                              float* part, size_t slot_stride, hipStream_t stream) {
   if (wv.n_chunks <= 0) return hipSuccess;
   if (wv.q4)
-    return launch_decode_down_q4(h, ldh, M, plan, tb_hint, expert_sel, x2_only, max_touched, wv, slot0, chunks_per_slot, part,
-                                 slot_stride, stream);
-  int n_slots = (wv.n_chunks + chunks_per_slot - 1) / chunks_per_slot;
-  dim3 grid((M + DN_THREADS - 1) / DN_THREADS, n_slots, expert_sel >= 0 ? 1 : max_touched);
+    return launch_decode_down_q4(h, ldh, M, plan, tb_hint, expert_sel, x2_only, max_touched, wv, ws, cps_s, slot0, chunks_per_slot,
+                                 part, slot_stride, stream);
+  const int n_slots = (wv.n_chunks + chunks_per_slot - 1) / chunks_per_slot;
+  const int slots_s = ws.n_chunks > 0 ? (ws.n_chunks + cps_s - 1) / cps_s : 0, shared_z = (slots_s + n_slots - 1) / n_slots;
+  dim3 grid((M + DN_THREADS - 1) / DN_THREADS, n_slots, shared_z + (expert_sel >= 0 ? 1 : max_touched));
   const int tb = pick_tb(tb_hint);
-  size_t lds = (size_t)tb * chunks_per_slot * CHUNK_J * sizeof(float);
-  if (tb == 1) hipLaunchKernelGGL(k_decode_down<1>, grid, dim3(DN_THREADS), lds, stream, h, ldh, M, plan, expert_sel, x2_only, wv, slot0, chunks_per_slot, part, slot_stride);
-  else if (tb == 2) hipLaunchKernelGGL(k_decode_down<2>, grid, dim3(DN_THREADS), lds, stream, h, ldh, M, plan, expert_sel, x2_only, wv, slot0, chunks_per_slot, part, slot_stride);
-  else hipLaunchKernelGGL(k_decode_down<4>, grid, dim3(DN_THREADS), lds, stream, h, ldh, M, plan, expert_sel, x2_only, wv, slot0, chunks_per_slot, part, slot_stride);
+  size_t lds = (size_t)tb * std::max(chunks_per_slot, slots_s ? cps_s : 0) * CHUNK_J * sizeof(float);
+#define SI_DN(TBV) hipLaunchKernelGGL(k_decode_down<TBV>, grid, dim3(DN_THREADS), lds, stream, h, ldh, M, plan, expert_sel, x2_only, wv, ws, shared_z, cps_s, slot0, chunks_per_slot, part, slot_stride)
+  if (tb == 1) SI_DN(1); else if (tb == 2) SI_DN(2); else SI_DN(4);
+#undef SI_DN
   return hipGetLastError();
 }
 

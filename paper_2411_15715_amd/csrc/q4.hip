@@ -23,8 +23,11 @@ __device__ inline float bf16_f32(uint16_t b) { return __uint_as_float((uint32_t)
 __device__ inline float silu_f(float z) { return z / (1.f + __expf(-z)); }
 
 // expert handled by this block and its row range; false when there is nothing to do
+// (slot < 0: the shared expert, entry n_routed, of a launch that covers it along with the routed ones)
 __device__ inline bool block_rows(const Plan& p, int expert_sel, int x2_only, int slot, int& e, int& r0, int& r1) {
-  if (expert_sel >= 0) {
+  if (slot < 0) {
+    e = p.n_routed;
+  } else if (expert_sel >= 0) {
     e = expert_sel;
   } else {
     if (slot >= *p.n_touched) return false;
@@ -80,16 +83,21 @@ constexpr int QU = 2;      // units (512 codes per row; 2 KB of gate and up code
                            // (3 and 4 units: 62 and 67 us instead of 55, the registers cost waves)
 constexpr int QGU_TB = 4;  // tokens per pass over the weights
 __global__ __launch_bounds__(QGU_THREADS, 4) void k_decode_gateup_q4(const uint16_t* __restrict__ x, int M, Plan p,
-                                                                     int expert_sel, int x2_only, WeightView wv,
-                                                                     float* __restrict__ h, int ldh, int tb) {
+                                                                     int expert_sel, int x2_only, WeightView wv_r, WeightView wv_s,
+                                                                     int shared_y, float* __restrict__ h, int ldh, int tb) {
   extern __shared__ __attribute__((aligned(16))) unsigned char s_q[];
   int e, r0, r1, se;
-  if (!block_rows(p, expert_sel, x2_only, blockIdx.y, e, r0, r1)) return;
+  // the first shared_y rows of the grid are the blocks of the shared expert
+  const int slot = (int)blockIdx.y - shared_y;
+  const int bx = slot < 0 ? blockIdx.y * gridDim.x + blockIdx.x : blockIdx.x;
+  const WeightView wv = slot < 0 ? wv_s : wv_r;
+  if (!block_rows(p, expert_sel, x2_only, slot, e, r0, r1)) return;
   if (!storage_index(wv, e, se)) return;
   const int tid = threadIdx.x, lane = tid % WAVE, wid = __builtin_amdgcn_readfirstlane(tid / WAVE), j = lane & 3, pc = lane >> 2;
   constexpr int blocks_per_chunk = CHUNK_J / QGU_JPB;
-  const int chunk = wv.chunk0 + blockIdx.x / blocks_per_chunk;
-  const int jb = (blockIdx.x % blocks_per_chunk) * QGU_JPB, jj0 = jb + wid * 4;
+  if (bx >= wv.n_chunks * blocks_per_chunk) return;
+  const int chunk = wv.chunk0 + bx / blocks_per_chunk;
+  const int jb = (bx % blocks_per_chunk) * QGU_JPB, jj0 = jb + wid * 4;
   const unsigned char* cb = reinterpret_cast<const unsigned char*>(wv.base + (size_t)se * wv.expert_stride + (size_t)chunk * q4_chunk_u16(M));
   const unsigned char* gq = cb + q4_off_codes(0, M) + (size_t)(jj0 + j) * (M / 2);
   const unsigned char* uq = cb + q4_off_codes(1, M) + (size_t)(jj0 + j) * (M / 2);
@@ -194,7 +202,7 @@ __global__ __launch_bounds__(QGU_THREADS, 4) void k_decode_gateup_q4(const uint1
     if (lane < 4) {
 #pragma unroll
       for (int t = 0; t < QGU_TB; ++t)
-        if (t < nt) h[(size_t)(rb + t) * ldh + wv.col0 + (blockIdx.x / blocks_per_chunk) * CHUNK_J + jj0 + j] = silu_f(tg[t]) * tu[t];
+        if (t < nt) h[(size_t)(rb + t) * ldh + wv.col0 + (bx / blocks_per_chunk) * CHUNK_J + jj0 + j] = silu_f(tg[t]) * tu[t];
     }
   }
 }
@@ -205,13 +213,17 @@ __global__ __launch_bounds__(QGU_THREADS, 4) void k_decode_gateup_q4(const uint1
 // exactly), which are three operand rows: rows 4t .. 4t+2 belong to token t, so a lane ends up with the parts of one token.
 constexpr int QDN_COLS = 128, QDN_TB = 4;
 __global__ __launch_bounds__(QDN_THREADS) void k_decode_down_q4(const float* __restrict__ h, int ldh, int M, Plan p,
-                                                                int expert_sel, int x2_only, WeightView wv, int slot0,
-                                                                int chunks_per_slot, float* __restrict__ part,
-                                                                size_t slot_stride, int tb) {
+                                                                int expert_sel, int x2_only, WeightView wv_r, WeightView wv_s,
+                                                                int shared_z, int cps_s, int slot0, int chunks_per_slot,
+                                                                float* __restrict__ part, size_t slot_stride, int tb) {
   extern __shared__ __attribute__((aligned(16))) unsigned char s_h[];
   int e, r0, r1, se;
-  if (!block_rows(p, expert_sel, x2_only, blockIdx.z, e, r0, r1)) return;
-  const int s = blockIdx.y;
+  // the first shared_z layers of the grid are the j-slots of the shared expert
+  const int slot = (int)blockIdx.z - shared_z;
+  if (!block_rows(p, expert_sel, x2_only, slot, e, r0, r1)) return;
+  const WeightView wv = slot < 0 ? wv_s : wv_r;
+  if (slot < 0) chunks_per_slot = cps_s;
+  const int s = slot < 0 ? blockIdx.z * gridDim.y + blockIdx.y : blockIdx.y;
   const int c_begin = s * chunks_per_slot;
   const int n_c = min(chunks_per_slot, wv.n_chunks - c_begin);
   if (n_c <= 0) return;
@@ -410,25 +422,28 @@ hipError_t ensure_q4_lds() {
 }  // namespace
 
 hipError_t launch_decode_gateup_q4(const uint16_t* x, int M, const Plan& plan, int tb_hint, int expert_sel, int x2_only,
-                                   int max_touched, const WeightView& wv, float* h, int ldh, hipStream_t stream) {
+                                   int max_touched, const WeightView& wv, const WeightView& ws, float* h, int ldh, hipStream_t stream) {
   if (wv.n_chunks <= 0) return hipSuccess;
   if (hipError_t e = ensure_q4_lds(); e != hipSuccess) return e;
-  dim3 grid(wv.n_chunks * (CHUNK_J / QGU_JPB), expert_sel >= 0 ? 1 : max_touched);
+  const int shared_y = (ws.n_chunks + wv.n_chunks - 1) / wv.n_chunks;
+  dim3 grid(wv.n_chunks * (CHUNK_J / QGU_JPB), shared_y + (expert_sel >= 0 ? 1 : max_touched));
   const int tb = std::max(1, std::min(tb_hint, QGU_TB));  // (80 KB of LDS at most: two blocks per CU)
-  hipLaunchKernelGGL(k_decode_gateup_q4, grid, dim3(QGU_THREADS), gateup_lds(tb, M), stream, x, M, plan, expert_sel, x2_only, wv, h, ldh, tb);
+  hipLaunchKernelGGL(k_decode_gateup_q4, grid, dim3(QGU_THREADS), gateup_lds(tb, M), stream, x, M, plan, expert_sel, x2_only, wv, ws, shared_y, h, ldh, tb);
   return hipGetLastError();
 }
 
 hipError_t launch_decode_down_q4(const float* h, int ldh, int M, const Plan& plan, int tb_hint, int expert_sel, int x2_only,
-                                 int max_touched, const WeightView& wv, int slot0, int chunks_per_slot, float* part,
-                                 size_t slot_stride, hipStream_t stream) {
+                                 int max_touched, const WeightView& wv, const WeightView& ws, int cps_s, int slot0,
+                                 int chunks_per_slot, float* part, size_t slot_stride, hipStream_t stream) {
   if (wv.n_chunks <= 0) return hipSuccess;
   if (hipError_t e = ensure_q4_lds(); e != hipSuccess) return e;
   const int n_slots = (wv.n_chunks + chunks_per_slot - 1) / chunks_per_slot;
-  dim3 grid((M + QDN_COLS - 1) / QDN_COLS, n_slots, expert_sel >= 0 ? 1 : max_touched);
+  const int slots_s = ws.n_chunks > 0 ? (ws.n_chunks + cps_s - 1) / cps_s : 0, shared_z = (slots_s + n_slots - 1) / n_slots;
+  const int cps_max = std::max(chunks_per_slot, slots_s ? cps_s : 0);
+  dim3 grid((M + QDN_COLS - 1) / QDN_COLS, n_slots, shared_z + (expert_sel >= 0 ? 1 : max_touched));
   int tb = std::max(1, std::min(tb_hint, QDN_TB));
-  while (tb > 1 && down_lds(tb, chunks_per_slot) > Q4_LDS) --tb;
-  hipLaunchKernelGGL(k_decode_down_q4, grid, dim3(QDN_THREADS), down_lds(tb, chunks_per_slot), stream, h, ldh, M, plan, expert_sel, x2_only, wv, slot0, chunks_per_slot, part, slot_stride, tb);
+  while (tb > 1 && down_lds(tb, cps_max) > Q4_LDS) --tb;
+  hipLaunchKernelGGL(k_decode_down_q4, grid, dim3(QDN_THREADS), down_lds(tb, cps_max), stream, h, ldh, M, plan, expert_sel, x2_only, wv, ws, shared_z, cps_s, slot0, chunks_per_slot, part, slot_stride, tb);
   return hipGetLastError();
 }
 

@@ -93,6 +93,7 @@ __device__ inline bool storage_index(const WeightView& wv, int e, int& se) {
 // h[row][j] = SiLU(x_row . Wg[j]) * (x_row . Wu[j]) for the rows of the selected experts.
 //  expert_sel < 0: all touched experts (table lookup);  >= 0: only that expert.
 //  x2_only: restrict to rows of X2 tokens (CG').
+//  ws: the shared expert's weights, covered by the same launch (n_chunks == 0: not); its blocks come first in the grid.
 //  tb_hint: upper bound on the rows of one expert (T); picks the tokens-per-pass instantiation (1, 2 or 4).
 // Token assignment folded into the first gate/up launch of a generation-phase call with few tokens (the launch of a
 // separate assignment kernel costs as much as reading tens of megabytes): every block derives the assignment of
@@ -106,8 +107,8 @@ struct FusedRoute {
   RouteOut user;
 };
 hipError_t launch_decode_gateup(const uint16_t* x, int M, const Plan& plan, int tb_hint, int expert_sel, int x2_only,
-                                int max_touched, const WeightView& wv, float* h, int ldh, hipStream_t stream,
-                                const FusedRoute* fused_route = nullptr);
+                                int max_touched, const WeightView& wv, const WeightView& ws, float* h, int ldh,
+                                hipStream_t stream, const FusedRoute* fused_route = nullptr);
 // part[slot][row][m] = sum over the j of the slot of h[row][j] * Wd[j][m]
 // y[t][m] = sum_s w[t][s] * sum_slots part[slot][inv[t*k+s]][m] + shared rows + ycc[t][m]
 struct DecodeCombineArgs {
@@ -118,8 +119,9 @@ struct DecodeCombineArgs {
   int T, k, M, n_x1, has_shared;
 };
 // part[slot][row][m] = sum over the j of the slot of h[row][j] * Wd[j][m]
+// (ws, cps_s: the shared expert's weights and chunks per slot, as above)
 hipError_t launch_decode_down(const float* h, int ldh, int M, const Plan& plan, int tb_hint, int expert_sel, int x2_only,
-                              int max_touched, const WeightView& wv, int slot0, int chunks_per_slot,
+                              int max_touched, const WeightView& wv, const WeightView& ws, int cps_s, int slot0, int chunks_per_slot,
                               float* part, size_t slot_stride, hipStream_t stream);
 hipError_t launch_decode_combine(const DecodeCombineArgs& a, const Plan& plan, float* y, hipStream_t stream);
 
@@ -142,10 +144,10 @@ hipError_t launch_fill_zero(float* p, size_t n, hipStream_t stream);
 // q4.hip -------------------------------------------------------------------------------------
 // the GEMV launchers of decode.hip hand over to these when wv.q4 is set
 hipError_t launch_decode_gateup_q4(const uint16_t* x, int M, const Plan& plan, int tb_hint, int expert_sel, int x2_only,
-                                   int max_touched, const WeightView& wv, float* h, int ldh, hipStream_t stream);
+                                   int max_touched, const WeightView& wv, const WeightView& ws, float* h, int ldh, hipStream_t stream);
 hipError_t launch_decode_down_q4(const float* h, int ldh, int M, const Plan& plan, int tb_hint, int expert_sel, int x2_only,
-                                 int max_touched, const WeightView& wv, int slot0, int chunks_per_slot, float* part,
-                                 size_t slot_stride, hipStream_t stream);
+                                 int max_touched, const WeightView& wv, const WeightView& ws, int cps_s, int slot0,
+                                 int chunks_per_slot, float* part, size_t slot_stride, hipStream_t stream);
 // 4-bit chunks [wv.chunk0, +wv.n_chunks) of one expert (expert_sel >= 0) or of every routed expert that has rows
 // -> bf16 chunks 0..n_chunks at dst (+ e * dst_estride)
 hipError_t launch_dequant_q4(const WeightView& wv, int M, const Plan& plan, int expert_sel, int x2_only, int n_experts,
