@@ -953,6 +953,14 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
   const int n_ntiles = ceil_div(M, 256);
   const int rt_guess = std::max(ceil_div(T * k, TILE_ROWS), std::min(E, T * k));  // row tiles if the rows spread evenly
   const int split_call = std::min(MAX_KSPLIT, std::max(1, 256 / (std::max(1, rt_guess) * n_ntiles)));
+  // The routed and the shared expert share their launches where both have a resident part: with launches of their own
+  // the chip drains and fills twice more per call (64 experts of 2560 columns, top-8, a shared one of 20480: 4 tokens
+  // 255 -> 237 us, 2011 tokens 1829 -> 1761 us).
+  const bool joint = L->has_shared && L->sch_gg > 0 && L->ch_gg > 0 && !(path == SI_PREFILL && L->q4 && L->d_deq);
+  // k-splits of the shared expert's down projection: alone it has to fill the chip; beside the routed experts its tiles
+  // only have to be short against the whole: at most four times the k-tiles of a routed tile (twice: equal).
+  const int sh_tiles = n_row_tiles(T) * n_ntiles;
+  const int split_s = std::min(MAX_KSPLIT, std::max(1, joint ? std::max(split_call, ceil_div(L->sch_gg, 4 * L->ch_gg)) : 256 / sh_tiles));
   hipError_t ke = hipSuccess;
 #define K_TRY(expr) do { ke = (expr); if (ke != hipSuccess) return fail(SI_EHIP, "%s failed: %s", #expr, hipGetErrorString(ke)); } while (0)
 
@@ -1004,15 +1012,18 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
           }
           wg = WeightView{L->d_deq, dst_stride, 0, ns, 0, 0, nullptr};
         }
-        const int ldh = ns * CHUNK_J;
+        const int ldh = ns * CHUNK_J, ldh_s = ws.n_chunks * CHUNK_J;
+        // (the activations of the T*k routed rows, then those of the shared expert's rows)
+        const SharedPart sp{ws, n_row_tiles(T), ldh_s, (long)T * k * (ldh - ldh_s), split_s};
         {
           SegScope sc(L, stream, SI_K_PREFILL_GATEUP);
-          K_TRY(launch_prefill_gateup(x, M, L->plan, esel, x2_only, n_rt, wg, L->d_hact, ldh, stream));
+          K_TRY(launch_prefill_gateup(x, M, L->plan, esel, x2_only, n_rt, wg, L->d_hact, ldh, sp, stream));
         }
         SegScope sc(L, stream, SI_K_PREFILL_DOWN);
-        const int split = first ? split_call : std::min(split_call, std::max(1, ns / 8));
+        const int split_max = is_shared ? split_s : split_call;
+        const int split = first ? split_max : std::min(split_max, std::max(1, ns / 8));
         K_TRY(launch_prefill_down(L->d_hact, ldh, M, L->plan, esel, x2_only, n_rt, wg, L->d_yp, L->yp_slab, split,
-                                  first ? 0 : 1, stream));
+                                  first ? 0 : 1, sp, stream));
       }
     }
     return SI_OK;
@@ -1025,10 +1036,10 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
     int rc;
     if (path == SI_PREFILL) {
       SegScope sc(L, stream, SI_K_FILL);
-      for (int q = 0; q < split_call; ++q) {
+      for (int q = 0; q < split_call; ++q)
         if (L->ch_gg == 0 || L->placed) K_TRY(launch_fill_zero(L->d_yp + q * L->yp_slab, (size_t)T * k * M, stream));
+      for (int q = 0; q < split_s; ++q)
         if (L->has_shared && L->sch_gg == 0) K_TRY(launch_fill_zero(L->d_yp + q * L->yp_slab + (size_t)T * k * M, (size_t)T * M, stream));
-      }
     }
     if (path == SI_DECODE && L->placed) {
       // rows of experts that no launch of this call writes (CC experts of X1 tokens) must read as zero in the merge
@@ -1036,10 +1047,6 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
       const int n_slots = ceil_div(L->H / CHUNK_J, cps_of(L->H / CHUNK_J, one, M));
       for (int q = 0; q < n_slots; ++q) K_TRY(launch_fill_zero(L->d_part + (size_t)q * slot_stride, (size_t)T * k * M, stream));
     }
-    // The routed and the shared expert of a generation-phase call share their launches where both have a resident part:
-    // with launches of their own the chip drains and fills twice more per call (64 experts of 2560 columns, top-8, a
-    // shared one of 20480, 4 tokens: 255 -> 237 us).
-    const bool joint = L->has_shared && L->sch_gg > 0 && L->ch_gg > 0 && path == SI_DECODE;
     WeightView ws{};
     if (joint) ws = WeightView{L->d_sgg, 0, 0, L->sch_gg, (L->sch_cc + L->sch_cg) * CHUNK_J, L->q4, nullptr};
     if (E == 1) rc = run_part(L->d_gg, 0, 0, 0, 0, L->ch_gg, hch * CHUNK_J, 0, 0, 0, true, ws);
@@ -1141,7 +1148,7 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
       a.ycc = ycc_dev; a.T = T; a.k = k; a.M = M; a.n_x1 = n_x1; a.has_shared = L->has_shared;
       K_TRY(launch_decode_combine(a, L->plan, y_dev, stream));
     } else {
-      K_TRY(launch_prefill_combine(L->d_yp, L->yp_slab, split_call, ycc_dev, T, k, M, n_x1, L->has_shared, L->plan, y_dev, stream));
+      K_TRY(launch_prefill_combine(L->d_yp, L->yp_slab, split_call, split_s, ycc_dev, T, k, M, n_x1, L->has_shared, L->plan, y_dev, stream));
     }
   }
   if (L->profiling) HIP_TRY(hipEventRecord(L->ev_t1, stream));

@@ -108,8 +108,8 @@ __device__ inline bool map_block(int b, int N, int n_cu, int interleave, int& L,
   return true;
 }
 
-// se: index of the expert inside the launch's weight storage
-struct TileInfo { int e, row0, row_end, se; };
+// se: index of the expert inside the launch's weight storage; sh: the shared expert in a launch that covers it as well
+struct TileInfo { int e, row0, row_end, se, sh; };
 
 // Number of logical tile ids with work in this launch (row tiles x inner tiles); single: no expert of the launch
 // has more than one row tile.
@@ -156,10 +156,33 @@ __device__ inline bool decode_tile(const Plan& p, int expert_sel, int x2_only, i
   return true;
 }
 
+// Launch over the routed experts and the shared one: every XCD gets a contiguous eighth of either kind's ids, the shared
+// expert's first: its tiles are the longest of the down projection and alike, and the smaller ones of the routed experts
+// even out the end (a split tail as in map_block is not needed).  2011 tokens, 64 experts of 2560 columns, top-8, a
+// shared one of 20480: 1829 us with two launches, 1761 like this, 1790 with the routed tiles first, 1827 with the two
+// kinds in turn (their operands then share the L2s).
+__device__ inline bool joint_tile(const Plan& p, int expert_sel, int n_inner, int n_inner_s, int spread, int& inner, TileInfo& ti) {
+  int single;
+  const int n_r = launch_extent(p, expert_sel, 0, n_inner, single);
+  const int n_s = n_row_tiles(p.off[p.n_routed + 1] - p.off[p.n_routed]) * n_inner_s;
+  const int per_r = (n_r + 7) / 8, per_s = (n_s + 7) / 8;
+  const int xcd = blockIdx.x % 8, i = blockIdx.x / 8;
+  const bool sh = i < per_s;
+  const int idx = sh ? i : i - per_s, per = sh ? per_s : per_r;
+  if (idx >= per) return false;
+  const int L = !sh && single && spread ? idx * 8 + xcd : xcd * per + idx;
+  if (L >= (sh ? n_s : n_r)) return false;
+  ti.sh = sh;
+  return decode_tile(p, sh ? p.n_routed : expert_sel, 0, L, sh ? n_inner_s : n_inner, inner, ti);
+}
+
 // block id -> tile of this block (false: nothing to do)
+// n_inner_s: inner tiles of the shared expert when the launch covers it along with the routed ones, else 0
 // spread: deal single-tile launches round-robin over the XCDs (see map_block)
-__device__ inline bool block_tile(const Plan& p, int expert_sel, int x2_only, int n_inner, int n_cu, int spread,
+__device__ inline bool block_tile(const Plan& p, int expert_sel, int x2_only, int n_inner, int n_inner_s, int n_cu, int spread,
                                   int& inner, TileInfo& ti) {
+  ti.sh = 0;
+  if (n_inner_s) return joint_tile(p, expert_sel, n_inner, n_inner_s, spread, inner, ti);
   int L, half, halves, single;
   const int extent = launch_extent(p, expert_sel, x2_only, n_inner, single);
   if (!map_block(blockIdx.x, extent, n_cu, single && spread, L, half, halves)) return false;
@@ -612,12 +635,15 @@ __device__ __forceinline__ void gateup_body(const uint16_t* __restrict__ x, int 
 
 __global__ __launch_bounds__(THREADS, 1) void k_prefill_gateup(const uint16_t* __restrict__ x, int M, Plan p,
                                                                int expert_sel, int x2_only, int n_cu,
-                                                               int n_ctiles, WeightView wv,
-                                                               uint16_t* __restrict__ hact, int ldh) {
+                                                               int n_ctiles, WeightView wv_r, WeightView wv_s,
+                                                               uint16_t* __restrict__ hact, int ldh_r, long hact_s, int ldh_s) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   int tc;
   TileInfo ti;
-  if (!block_tile(p, expert_sel, x2_only, n_ctiles, n_cu, 1, tc, ti)) return;
+  if (!block_tile(p, expert_sel, x2_only, n_ctiles, (wv_s.n_chunks + 1) / 2, n_cu, 1, tc, ti)) return;
+  const WeightView wv = ti.sh ? wv_s : wv_r;
+  const int ldh = ti.sh ? ldh_s : ldh_r;
+  hact += ti.sh ? hact_s : 0;
   if (!storage_index(wv, ti.e, ti.se)) return;
 #define SI_CALL_GU(BMV) gateup_body<BMV>(x, M, p, tc, ti, wv, hact, ldh, lds)
   SI_PICK_BODY(ti, SI_CALL_GU)
@@ -688,18 +714,21 @@ __device__ __forceinline__ void down_body(const uint16_t* __restrict__ hact, int
   }
 }
 
-__global__ __launch_bounds__(THREADS, 1) void k_prefill_down(const uint16_t* __restrict__ hact, int ldh, int M, Plan p,
+__global__ __launch_bounds__(THREADS, 1) void k_prefill_down(const uint16_t* __restrict__ hact, int ldh_r, int M, Plan p,
                                                              int expert_sel, int x2_only, int n_cu,
-                                                             int n_ntiles, int n_split, WeightView wv,
-                                                             float* __restrict__ yp, size_t slab_stride,
-                                                             int accumulate) {
+                                                             int n_ntiles, int split_r, WeightView wv_r, WeightView wv_s,
+                                                             int ldh_s, long hact_s, int split_s, float* __restrict__ yp,
+                                                             size_t slab_stride, int accumulate) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   int inner;
   TileInfo ti;
   // (XCD ranges also when every expert has a single row tile: one expert's Hact rows, the A operand, a few MB,
   // then stay in one L2; dealt round-robin every XCD re-reads every expert's rows for each of its column tiles,
   // which measured 3 % slower although the XCDs finish together)
-  if (!block_tile(p, expert_sel, x2_only, n_ntiles * n_split, n_cu, 0, inner, ti)) return;
+  if (!block_tile(p, expert_sel, x2_only, n_ntiles * split_r, wv_s.n_chunks ? n_ntiles * split_s : 0, n_cu, 0, inner, ti)) return;
+  const WeightView wv = ti.sh ? wv_s : wv_r;
+  const int ldh = ti.sh ? ldh_s : ldh_r, n_split = ti.sh ? split_s : split_r;
+  hact += ti.sh ? hact_s : 0;
   if (!storage_index(wv, ti.e, ti.se)) return;
 #define SI_CALL_DN(BMV) down_body<BMV>(hact, ldh, M, inner, ti, n_ntiles, n_split, wv, yp, slab_stride, accumulate, lds)
   SI_PICK_BODY(ti, SI_CALL_DN)
@@ -765,12 +794,15 @@ __device__ __forceinline__ void gateup_body_q4(const uint16_t* __restrict__ x, i
 
 __global__ __launch_bounds__(THREADS, 1) void k_prefill_gateup_q4(const uint16_t* __restrict__ x, int M, Plan p,
                                                                   int expert_sel, int x2_only, int n_cu,
-                                                                  int n_ctiles, WeightView wv,
-                                                                  uint16_t* __restrict__ hact, int ldh) {
+                                                                  int n_ctiles, WeightView wv_r, WeightView wv_s,
+                                                                  uint16_t* __restrict__ hact, int ldh_r, long hact_s, int ldh_s) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   int tc;
   TileInfo ti;
-  if (!block_tile(p, expert_sel, x2_only, n_ctiles, n_cu, 1, tc, ti)) return;
+  if (!block_tile(p, expert_sel, x2_only, n_ctiles, (wv_s.n_chunks + 1) / 2, n_cu, 1, tc, ti)) return;
+  const WeightView wv = ti.sh ? wv_s : wv_r;
+  const int ldh = ti.sh ? ldh_s : ldh_r;
+  hact += ti.sh ? hact_s : 0;
   if (!storage_index(wv, ti.e, ti.se)) return;
 #define SI_CALL_GU(BMV) gateup_body_q4<BMV>(x, M, p, tc, ti, wv, hact, ldh, lds)
   SI_PICK_BODY_2PASS(ti, SI_CALL_GU);
@@ -841,22 +873,25 @@ __device__ __forceinline__ void down_body_q4(const uint16_t* __restrict__ hact, 
   }
 }
 
-__global__ __launch_bounds__(THREADS, 1) void k_prefill_down_q4(const uint16_t* __restrict__ hact, int ldh, int M, Plan p,
+__global__ __launch_bounds__(THREADS, 1) void k_prefill_down_q4(const uint16_t* __restrict__ hact, int ldh_r, int M, Plan p,
                                                                 int expert_sel, int x2_only, int n_cu,
-                                                                int n_ntiles, int n_split, WeightView wv,
-                                                                float* __restrict__ yp, size_t slab_stride,
-                                                                int accumulate) {
+                                                                int n_ntiles, int split_r, WeightView wv_r, WeightView wv_s,
+                                                                int ldh_s, long hact_s, int split_s, float* __restrict__ yp,
+                                                                size_t slab_stride, int accumulate) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   int inner;
   TileInfo ti;
-  if (!block_tile(p, expert_sel, x2_only, n_ntiles * n_split, n_cu, 0, inner, ti)) return;
+  if (!block_tile(p, expert_sel, x2_only, n_ntiles * split_r, wv_s.n_chunks ? n_ntiles * split_s : 0, n_cu, 0, inner, ti)) return;
+  const WeightView wv = ti.sh ? wv_s : wv_r;
+  const int ldh = ti.sh ? ldh_s : ldh_r, n_split = ti.sh ? split_s : split_r;
+  hact += ti.sh ? hact_s : 0;
   if (!storage_index(wv, ti.e, ti.se)) return;
 #define SI_CALL_DN(BMV) down_body_q4<BMV>(hact, ldh, M, inner, ti, n_ntiles, n_split, wv, yp, slab_stride, accumulate, lds)
   SI_PICK_BODY_2PASS(ti, SI_CALL_DN);
 #undef SI_CALL_DN
 }
 
-__global__ __launch_bounds__(256) void k_prefill_combine(const float* __restrict__ yp, size_t slab_stride, int n_split,
+__global__ __launch_bounds__(256) void k_prefill_combine(const float* __restrict__ yp, size_t slab_stride, int n_split, int split_s,
                                                          const float* __restrict__ ycc, int T, int k, int M, int n_x1,
                                                          int has_shared, Plan p, float* __restrict__ y) {
   const int t = blockIdx.y;
@@ -876,7 +911,7 @@ __global__ __launch_bounds__(256) void k_prefill_combine(const float* __restrict
   }
   if (has_shared) {
     const float* row = yp + (size_t)(T * k + t) * M;
-    for (int q = 0; q < n_split; ++q) {
+    for (int q = 0; q < split_s; ++q) {
       const float4 v = reinterpret_cast<const float4*>(row + (size_t)q * slab_stride)[m4];
       acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
     }
@@ -932,44 +967,44 @@ static hipError_t ensure_lds_attr() {
 }
 
 hipError_t launch_prefill_gateup(const uint16_t* x, int M, const Plan& plan, int expert_sel, int x2_only,
-                                 int n_row_tiles, const WeightView& wv, uint16_t* hact, int ldh,
+                                 int n_row_tiles, const WeightView& wv, uint16_t* hact, int ldh, const SharedPart& sp,
                                  hipStream_t stream) {
   if (wv.n_chunks <= 0 || n_row_tiles <= 0) return hipSuccess;
   hipError_t e = ensure_lds_attr();
   if (e != hipSuccess) return e;
   const int n_ctiles = (wv.n_chunks + 1) / 2;
-  const int total = grid_blocks(n_row_tiles * n_ctiles);
+  const int total = grid_blocks(n_row_tiles * n_ctiles) + (sp.row_tiles * ((sp.wv.n_chunks + 1) / 2) + 7) / 8 * 8;
   if (wv.q4)
     hipLaunchKernelGGL(k_prefill_gateup_q4, dim3(total), dim3(THREADS), KERNEL_LDS, stream, x, M, plan, expert_sel, x2_only,
-                       cu_count(), n_ctiles, wv, hact, ldh);
+                       cu_count(), n_ctiles, wv, sp.wv, hact, ldh, sp.hact, sp.ldh);
   else
     hipLaunchKernelGGL(k_prefill_gateup, dim3(total), dim3(THREADS), KERNEL_LDS, stream, x, M, plan, expert_sel, x2_only,
-                       cu_count(), n_ctiles, wv, hact, ldh);
+                       cu_count(), n_ctiles, wv, sp.wv, hact, ldh, sp.hact, sp.ldh);
   return hipGetLastError();
 }
 
 hipError_t launch_prefill_down(const uint16_t* hact, int ldh, int M, const Plan& plan, int expert_sel,
                                int x2_only, int n_row_tiles, const WeightView& wv, float* yp, size_t slab_stride,
-                               int n_split, int accumulate, hipStream_t stream) {
+                               int n_split, int accumulate, const SharedPart& sp, hipStream_t stream) {
   if (wv.n_chunks <= 0 || n_row_tiles <= 0) return hipSuccess;
   hipError_t e = ensure_lds_attr();
   if (e != hipSuccess) return e;
   const int n_ntiles = (M + BN - 1) / BN;
-  const int total = grid_blocks(n_row_tiles * n_ntiles * n_split);
+  const int total = grid_blocks(n_row_tiles * n_ntiles * n_split) + (sp.wv.n_chunks ? (sp.row_tiles * n_ntiles * sp.split + 7) / 8 * 8 : 0);
   if (wv.q4)
     hipLaunchKernelGGL(k_prefill_down_q4, dim3(total), dim3(THREADS), KERNEL_LDS, stream, hact, ldh, M, plan, expert_sel,
-                       x2_only, cu_count(), n_ntiles, n_split, wv, yp, slab_stride, accumulate);
+                       x2_only, cu_count(), n_ntiles, n_split, wv, sp.wv, sp.ldh, sp.hact, sp.split, yp, slab_stride, accumulate);
   else
     hipLaunchKernelGGL(k_prefill_down, dim3(total), dim3(THREADS), KERNEL_LDS, stream, hact, ldh, M, plan, expert_sel,
-                       x2_only, cu_count(), n_ntiles, n_split, wv, yp, slab_stride, accumulate);
+                       x2_only, cu_count(), n_ntiles, n_split, wv, sp.wv, sp.ldh, sp.hact, sp.split, yp, slab_stride, accumulate);
   return hipGetLastError();
 }
 
-hipError_t launch_prefill_combine(const float* yp, size_t slab_stride, int n_split, const float* ycc, int T, int k, int M,
+hipError_t launch_prefill_combine(const float* yp, size_t slab_stride, int n_split, int split_s, const float* ycc, int T, int k, int M,
                                   int n_x1, int has_shared, const Plan& plan, float* y, hipStream_t stream) {
   if (T <= 0) return hipSuccess;
   dim3 grid((M / 4 + 255) / 256, T);
-  hipLaunchKernelGGL(k_prefill_combine, grid, dim3(256), 0, stream, yp, slab_stride, n_split, ycc, T, k, M, n_x1,
+  hipLaunchKernelGGL(k_prefill_combine, grid, dim3(256), 0, stream, yp, slab_stride, n_split, split_s, ycc, T, k, M, n_x1,
                      has_shared, plan, y);
   return hipGetLastError();
 }

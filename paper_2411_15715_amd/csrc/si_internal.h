@@ -126,18 +126,26 @@ hipError_t launch_decode_down(const float* h, int ldh, int M, const Plan& plan, 
 hipError_t launch_decode_combine(const DecodeCombineArgs& a, const Plan& plan, float* y, hipStream_t stream);
 
 // prefill.hip --------------------------------------------------------------------------------
+// The shared expert's part of a launch that covers it along with the routed experts (wv.n_chunks == 0: it does not).
+struct SharedPart {
+  WeightView wv;
+  int row_tiles;  // of its T rows
+  int ldh;        // its activations: row r (an expert-sorted row index) at Hact + hact + r * ldh
+  long hact;
+  int split;      // k-splits of its down projection
+};
 // Hact[row][c] (bf16) for c in [0, 64*n_chunks): SwiGLU of the gate/up products (MFMA, fp32 acc).
 // n_row_tiles: (an upper bound on) the row tiles of the launch, for the grid; the kernels find the real ones
 hipError_t launch_prefill_gateup(const uint16_t* x, int M, const Plan& plan, int expert_sel, int x2_only,
-                                 int n_row_tiles, const WeightView& wv, uint16_t* hact, int ldh,
+                                 int n_row_tiles, const WeightView& wv, uint16_t* hact, int ldh, const SharedPart& sp,
                                  hipStream_t stream);
 // Yp[split][row][m] (fp32) (+)= Hact[row][chunks of the split] . Wd[chunks][m]; the chunk range of the launch is
 // cut into n_split equal parts, each with its own output slab (summed by the combine kernel)
 hipError_t launch_prefill_down(const uint16_t* hact, int ldh, int M, const Plan& plan, int expert_sel,
                                int x2_only, int n_row_tiles, const WeightView& wv, float* yp, size_t slab_stride,
-                               int n_split, int accumulate, hipStream_t stream);
-// y[t][m] = sum_s w[t][s]*Yp[inv[t*k+s]][m] + Yp[T*k+t][m] (shared) + ycc[t][m] (X1 rows)
-hipError_t launch_prefill_combine(const float* yp, size_t slab_stride, int n_split, const float* ycc, int T, int k,
+                               int n_split, int accumulate, const SharedPart& sp, hipStream_t stream);
+// y[t][m] = sum_s w[t][s]*Yp[inv[t*k+s]][m] (n_split slabs) + Yp[T*k+t][m] (shared: split_s slabs) + ycc[t][m] (X1 rows)
+hipError_t launch_prefill_combine(const float* yp, size_t slab_stride, int n_split, int split_s, const float* ycc, int T, int k,
                                   int M, int n_x1, int has_shared, const Plan& plan, float* y, hipStream_t stream);
 hipError_t launch_fill_zero(float* p, size_t n, hipStream_t stream);
 

@@ -15,14 +15,14 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("E,k,d_ff,d_ff_shared,split", [
     (4, 2, 192, 64, (1.0, 0.0, 0.0)), (4, 2, 192, 192, (1.0, 0.0, 0.0)), (12, 3, 128, 1088, (1.0, 0.0, 0.0)),
     (2, 1, 64, 4160, (1.0, 0.0, 0.0)), (4, 1, 576, 320, (0.5, 0.5, 0.0)), (4, 2, 64, 320, (0.3, 0.4, 0.3))])
-def test_joint_decode(oracle, q4, E, k, d_ff, d_ff_shared, split):
+def test_joint(oracle, q4, E, k, d_ff, d_ff_shared, split):
     cfg = synth.scaled(synth.CONFIGS["qwen_moe"], d_model=320, d_ff=d_ff, d_ff_shared=d_ff_shared, n_experts=E, top_k=k)
     wq = synth.make_weights_q4(cfg) if q4 else None
     w = None if q4 else synth.make_weights(cfg)
-    L = Q4Layer(cfg, wq, split, max_tokens=16) if q4 else GpuLayer(cfg, w, split, max_tokens=16)
+    L = Q4Layer(cfg, wq, split, max_tokens=577) if q4 else GpuLayer(cfg, w, split, max_tokens=577)
     try:
-        for T in (1, 2, 4, 9):
-            print("joint decode E=%d H=%d Hs=%d T=%d" % (E, d_ff, d_ff_shared, T), flush=True)
+        for T in (1, 2, 4, 9, 65, 321, 577):
+            print("joint launch E=%d H=%d Hs=%d T=%d" % (E, d_ff, d_ff_shared, T), flush=True)
             xb = synth.make_tokens(cfg, T)
             lg = synth.make_router_logits(cfg, xb)
             if q4:
@@ -30,7 +30,10 @@ def test_joint_decode(oracle, q4, E, k, d_ff, d_ff_shared, split):
             else:
                 yo = oracle.layer_forward(xb, w["w_gate"], w["w_up"], w["w_down"], logits=lg, top_k=k,
                                           shared=(w["s_gate"], w["s_up"], w["s_down"]))
-            # fp32 sums of exact products; the host's share splits the activations into two bf16 parts
-            assert_parity(L.forward(xb, lg, mode=si.SI_DECODE), yo, tol=1e-4 if split[2] == 0 else 1e-3)
+            if T < 16:
+                # fp32 sums of exact products; the host's share splits the activations into two bf16 parts
+                assert_parity(L.forward(xb, lg, mode=si.SI_DECODE), yo, tol=1e-4 if split[2] == 0 else 1e-3)
+            for n_g in {0, T}:
+                assert_parity(L.forward(xb, lg, mode=si.SI_PREFILL, n_g=n_g), yo)
     finally:
         L.close()
