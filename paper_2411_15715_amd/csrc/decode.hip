@@ -143,7 +143,7 @@ __device__ inline void block_route(const FusedRoute& fr, BlockRoute& br, const P
 }
 
 template <int TB, int FUSED>
-__global__ __launch_bounds__(GU_THREADS) void k_decode_gateup(const uint16_t* __restrict__ x, int M, Plan p,
+__global__ __launch_bounds__(GU_THREADS, 4) void k_decode_gateup(const uint16_t* __restrict__ x, int M, Plan p,
                                                               int expert_sel, int x2_only, WeightView wv_r, WeightView wv_s,
                                                               int shared_y, float* __restrict__ h, int ldh, FusedRoute fr) {
   extern __shared__ u32x4 s_x[];  // [TB][M/8] bf16 x 8
@@ -182,11 +182,13 @@ __global__ __launch_bounds__(GU_THREADS) void k_decode_gateup(const uint16_t* __
       r0 = br.t_off[slot];
       r1 = r0 + br.t_cnt[slot];
     }
+    // (uniform, but read from LDS: into scalar registers)
+    e = __builtin_amdgcn_readfirstlane(e); r0 = __builtin_amdgcn_readfirstlane(r0); r1 = __builtin_amdgcn_readfirstlane(r1);
     row_token = br.row_token;
   } else {
     if (!block_rows(p, expert_sel, x2_only, slot, e, r0, r1)) return;
   }
-  const int tid = threadIdx.x, lane = tid % WAVE, wid = tid / WAVE;
+  const int tid = threadIdx.x, lane = tid % WAVE, wid = __builtin_amdgcn_readfirstlane(tid / WAVE);
   const int M8 = M / 8;
   const int blocks_per_chunk = CHUNK_J / GU_JPB;
   if (bx >= wv.n_chunks * blocks_per_chunk) return;
@@ -207,12 +209,17 @@ __global__ __launch_bounds__(GU_THREADS) void k_decode_gateup(const uint16_t* __
   // registers, i.e. waves per SIMD, and the plain loop stays.
   constexpr bool EARLY = TB == 1;
   u32x4 wg[GU_JPW], wu[GU_JPW];
+  // uniform row bases and one 32-bit lane offset: with a 64-bit address per load the four-token kernel had no registers
+  // to keep the eight loads of a step in flight together (experts of 2048 columns, d_model 7680, top-6 of 32, 7 tokens:
+  // call 428 -> 367 us; 4 experts of 17344, d_model 7680, 8 tokens: 479 -> 399)
   auto wload = [&](int c) {
-    const size_t poff = (size_t)(c / PW8) * CHUNK_J * PW8 + (c % PW8);  // panel base + position in the row segment
+    const uint32_t poff = ((uint32_t)(c / PW8) * CHUNK_J * PW8 + c % PW8) * 16u;  // panel base + position in the row segment
 #pragma unroll
     for (int j = 0; j < GU_JPW; ++j) {
-      wg[j] = __builtin_nontemporal_load(gblk + poff + (size_t)(jj0 + j) * PW8);
-      wu[j] = __builtin_nontemporal_load(ublk + poff + (size_t)(jj0 + j) * PW8);
+      const char* gr = reinterpret_cast<const char*>(gblk + (size_t)(jj0 + j) * PW8);
+      const char* ur = reinterpret_cast<const char*>(ublk + (size_t)(jj0 + j) * PW8);
+      wg[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(gr + poff));
+      wu[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ur + poff));
     }
   };
   if (EARLY && lane < M8) wload(lane);
@@ -225,10 +232,26 @@ __global__ __launch_bounds__(GU_THREADS) void k_decode_gateup(const uint16_t* __
       for (int i = 0; i < X_EARLY_MAX; ++i)
         if (tid + i * GU_THREADS < M8) s_x[tid + i * GU_THREADS] = x_reg[i];
     } else {
-      for (int i = tid; i < nt * M8; i += GU_THREADS) {
-        int tb = i / M8, c = i % M8;
-        int tok = row_token[rb + tb];
-        s_x[tb * M8 + c] = reinterpret_cast<const u32x4*>(x + (size_t)tok * M)[c];
+      // batches of XB pieces per thread whose loads are in flight together: one at a time, each behind the load of its
+      // row's token, they were 14 round trips at 4 rows of 7168
+      constexpr int XB = 4;
+      int tok[TB];
+#pragma unroll
+      for (int tb = 0; tb < TB; ++tb) tok[tb] = __builtin_amdgcn_readfirstlane(row_token[rb + min(tb, nt - 1)]);
+      for (int i0 = tid; i0 < nt * M8; i0 += XB * GU_THREADS) {
+        u32x4 v[XB];
+#pragma unroll
+        for (int b = 0; b < XB; ++b) {
+          const int i = min(i0 + b * GU_THREADS, nt * M8 - 1);
+          int t = tok[0], c = i;
+#pragma unroll
+          for (int tb = 1; tb < TB; ++tb)
+            if (i >= tb * M8) { t = tok[tb]; c = i - tb * M8; }
+          v[b] = reinterpret_cast<const u32x4*>(x + (size_t)t * M)[c];
+        }
+#pragma unroll
+        for (int b = 0; b < XB; ++b)
+          if (i0 + b * GU_THREADS < nt * M8) s_x[i0 + b * GU_THREADS] = v[b];
       }
     }
     __syncthreads();
@@ -289,7 +312,7 @@ __global__ __launch_bounds__(GU_THREADS) void k_decode_gateup(const uint16_t* __
 }
 
 template <int TB>
-__global__ __launch_bounds__(DN_THREADS) void k_decode_down(const float* __restrict__ h, int ldh, int M, Plan p,
+__global__ __launch_bounds__(DN_THREADS, 5) void k_decode_down(const float* __restrict__ h, int ldh, int M, Plan p,
                                                             int expert_sel, int x2_only, WeightView wv_r, WeightView wv_s,
                                                             int shared_z, int cps_s, int slot0, int chunks_per_slot,
                                                             float* __restrict__ part, size_t slot_stride) {
@@ -307,6 +330,7 @@ __global__ __launch_bounds__(DN_THREADS) void k_decode_down(const float* __restr
   const bool active = m < M;
   const int mm = active ? m : 0;
   const int NW = ntile_width(M);
+  const uint32_t moff = ((uint32_t)(mm / NW) * 8 * NW + mm % NW) * 16u;  // of the lane's column inside a chunk's down block, bytes
   int se;
   if (!storage_index(wv, e, se)) return;
   const uint16_t* ebase = wv.base + (size_t)se * wv.expert_stride;
@@ -319,20 +343,18 @@ __global__ __launch_bounds__(DN_THREADS) void k_decode_down(const float* __restr
   for (int rb = r0; rb < r1; rb += TB) {
     const int nt = min(TB, r1 - rb);
     __syncthreads();
-    for (int i = threadIdx.x; i < nt * n_j; i += DN_THREADS) {
-      int tb = i / n_j, j = i % n_j;
-      s_h[tb * n_j + j] = h[(size_t)(rb + tb) * ldh + jbase + j];
-    }
+    for (int tb = 0; tb < nt; ++tb)
+      for (int j = threadIdx.x * 4; j < n_j; j += DN_THREADS * 4)
+        *reinterpret_cast<float4*>(s_h + tb * n_j + j) = *reinterpret_cast<const float4*>(h + (size_t)(rb + tb) * ldh + jbase + j);
     __syncthreads();
     float acc[TB];
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) acc[tb] = 0.f;
     for (int c = c_begin; c < c_end; ++c) {
-      const u32x4* dblk = reinterpret_cast<const u32x4*>(ebase + (size_t)(wv.chunk0 + c) * 3 * CHUNK_J * M +
-                                                         (size_t)2 * CHUNK_J * M);
+      const char* dblk = reinterpret_cast<const char*>(ebase + (size_t)(wv.chunk0 + c) * 3 * CHUNK_J * M + (size_t)2 * CHUNK_J * M);
       u32x4 wd[8];  // down block [M/NW tiles][8 q][NW m][8 i]: 16 bytes per (q, m)
 #pragma unroll
-      for (int q = 0; q < 8; ++q) wd[q] = __builtin_nontemporal_load(dblk + ((size_t)(mm / NW) * 8 + q) * NW + (mm % NW));
+      for (int q = 0; q < 8; ++q) wd[q] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(dblk + (size_t)q * NW * 16 + moff));
 #pragma unroll
       for (int tb = 0; tb < TB; ++tb) {
         if (tb < nt) {

@@ -781,6 +781,17 @@ int cps_of(int ch, bool single_expert, int M) {
   return std::max(1, std::max(ceil_div(ch, slots), std::min(8, ch)));
 }
 
+// The same for the resident part of the routed bf16 experts (its cut is nobody else's concern): where that leaves hardly
+// more than a block per compute unit in a launch over n_e experts, more and shorter slots, down to 1 chunk: a dense
+// layer of 3328 x 2240, 1 token, has 65 blocks of 8 chunks; with 234 of 2 the call takes 21.3 instead of 27.6 us.
+// With 416 blocks (6400 columns, 2 experts of d_model 4096) the longer merge already costs more: 60.6 against 63.7 us.
+// (The 4-bit kernels lost 5 to 12 % by it and keep the cut above.)
+int cps_resident(int ch, bool single_expert, int M, int n_e) {
+  const int cps = cps_of(ch, single_expert, M), per_slot = ceil_div(M, 256) * n_e;
+  if (ch <= 0 || per_slot * ceil_div(ch, cps) >= 320) return cps;
+  return std::min(cps, ceil_div(ch, std::min(DOWN_SLOTS, ceil_div(1024, per_slot))));
+}
+
 // chunks per staged piece of a part with `cps` chunks per j-slot
 int piece_chunks(const si_layer* L, int path, int cps) {
   return path == SI_DECODE ? std::max(cps, L->stage_chunks / cps * cps) : L->stage_chunks;
@@ -945,7 +956,8 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
   const int tiles_upper = (T * k) / TILE_ROWS + std::min(E, T * k);  // bound on the routed row tiles
   // (whole-expert placement: every routed expert has H/64 chunks wherever it lives)
   const bool one = E == 1;
-  const int cps_gg = cps_of(L->placed ? L->H / CHUNK_J : L->ch_gg, one, M), cps_cg = cps_of(L->placed ? L->H / CHUNK_J : L->ch_cg, one, M),
+  const int n_e = std::min(E, T * k);  // (an upper bound on the experts of a launch)
+  const int cps_gg = L->placed ? cps_of(L->H / CHUNK_J, one, M) : L->q4 ? cps_of(L->ch_gg, one, M) : cps_resident(L->ch_gg, one, M, n_e), cps_cg = cps_of(L->placed ? L->H / CHUNK_J : L->ch_cg, one, M),
             cps_cc = cps_of(L->placed ? L->H / CHUNK_J : L->ch_cc, one, M);
   const int scps_gg = cps_of(L->sch_gg, true, M), scps_cg = cps_of(L->sch_cg, true, M), scps_cc = cps_of(L->sch_cc, true, M);
   const size_t slot_stride = (size_t)L->rows_dec * M;
