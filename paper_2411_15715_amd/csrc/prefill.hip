@@ -272,6 +272,11 @@ __device__ __forceinline__ void gemm_pingpong(unsigned char* lds, int nk, int la
                                               IA issue_a, IB issue_b, const uint32_t (&boff)[2]) {
   using P = PingPong<BM>;
   constexpr int FP = P::ALD >= 2 ? 4 : 2;  // fragments of a phase
+  // With a 64-row body a slot of matrix instructions is far shorter than one of loads and LDS reads, and the groups in turn
+  // only add their latencies: there all waves read, pass one barrier per k-tile and multiply.  (What is read was waited for
+  // before that barrier, and what is refilled after it was read before it.)  Dense layers of 13 to 61 tokens: 4352 x 7232
+  // 62.3 -> 59.2 us, 3328 x 1472 41.4 -> 39.0, 2816 x 4928 47.3 -> 45.9; the 128-row body loses 2 to 12 % by it.
+  constexpr bool PONG = BM > 64;
   bf16x8 fa[FP][2], fb[4][2];
   const uint32_t aoff[2] = {(uint32_t)swz(wr * (BM / 2) + (lane & 15), lane >> 4), (uint32_t)swz(wr * (BM / 2) + (lane & 15), 4 + (lane >> 4))};
   auto issue = [&](auto pc, int stage, int kt) {
@@ -317,9 +322,11 @@ __device__ __forceinline__ void gemm_pingpong(unsigned char* lds, int nk, int la
           const int j = (i & 1) ? 3 - jj : jj;
           acc[q * 4 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][ks], fa[i][ks], acc[q * 4 + i][j], 0, 0, 0);
         }
-    __builtin_amdgcn_sched_barrier(0);
-    block_barrier();
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (PONG) {
+      __builtin_amdgcn_sched_barrier(0);
+      block_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
 #pragma unroll
   for (int i = 0; i < BM / 32; ++i)
@@ -339,7 +346,7 @@ __device__ __forceinline__ void gemm_pingpong(unsigned char* lds, int nk, int la
   else wait_vmcnt<0>();
   block_barrier();
   __builtin_amdgcn_sched_barrier(0);
-  if (wr == 1) block_barrier();
+  if (PONG && wr == 1) block_barrier();
   __builtin_amdgcn_sched_barrier(0);
   int st = 0;
   for (int it = 0; it < nk; ++it) {
@@ -348,7 +355,7 @@ __device__ __forceinline__ void gemm_pingpong(unsigned char* lds, int nk, int la
     if constexpr (P::NP > 2) phase(C2{}, it, st);
     st = next(st);
   }
-  if (wr == 0) block_barrier();  // the second group's last slot
+  if (!PONG || wr == 0) block_barrier();  // the second group's last slot
 }
 
 // register loads and the dependency tie used by the loops whose B operand travels through registers
@@ -380,7 +387,7 @@ __device__ inline uint32_t q4_pair(uint32_t bytes, int b0, int b1, float sc, flo
   return pack_bf16(__builtin_fmaf(c0, sc, s8), __builtin_fmaf(c1, sc, s8));
 }
 
-// The ping-pong loop for weights in the 4-bit storage form.  The A operand arrives by direct global->LDS loads as above;
+// The same loop for weights in the 4-bit storage form.  The A operand arrives by direct global->LDS loads as above;
 // the B operand cannot (it has to be turned into bf16 on the way), so every lane fetches 16 bytes of codes (32 weights)
 // and their group scale into registers, and turns them into four 16-byte pieces of bf16((code - 8) * scale) that it
 // writes into the B part of a stage.  A k-tile of 64 is one scale group of either projection.
@@ -397,6 +404,10 @@ __device__ __forceinline__ void gemm_pingpong_q4(unsigned char* lds, int nk, int
                                                  IA issue_a, BL bload, BC bconv, const uint32_t (&boff)[2]) {
   using P = PingPong<BM, 0>;
   constexpr int FP = P::ALD >= 2 ? 4 : 2;  // fragments of a phase
+  // Bodies of up to 128 rows: one barrier per k-tile, as in gemm_pingpong; here the conversion makes the memory slot the
+  // longer one up to 128 rows (12 experts of 3200 columns, d_model 5632, top-6, 62 tokens: 326 -> 268 us; dense
+  // 5376 x 1472, 89 tokens: 118 -> 112; the 192- and 256-row bodies keep the two groups).
+  constexpr bool PONG = BM > 128;
   bf16x8 fa[FP][2], fb[4][2];
   const uint32_t aoff[2] = {(uint32_t)swz(wr * (BM / 2) + (lane & 15), lane >> 4), (uint32_t)swz(wr * (BM / 2) + (lane & 15), 4 + (lane >> 4))};
   auto bready = [](Q4Regs& r) { asm volatile("" : "+v"(r.q), "+v"(r.z)::"memory"); };
@@ -449,9 +460,11 @@ __device__ __forceinline__ void gemm_pingpong_q4(unsigned char* lds, int nk, int
           const int j = (i & 1) ? 3 - jj : jj;
           acc[q * 4 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][ks], fa[i][ks], acc[q * 4 + i][j], 0, 0, 0);
         }
-    __builtin_amdgcn_sched_barrier(0);
-    block_barrier();
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (PONG) {
+      __builtin_amdgcn_sched_barrier(0);
+      block_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
 #pragma unroll
   for (int i = 0; i < BM / 32; ++i)
@@ -479,7 +492,7 @@ __device__ __forceinline__ void gemm_pingpong_q4(unsigned char* lds, int nk, int
   wait_lgkmcnt0();
   block_barrier();
   __builtin_amdgcn_sched_barrier(0);
-  if (wr == 1) block_barrier();
+  if (PONG && wr == 1) block_barrier();
   __builtin_amdgcn_sched_barrier(0);
   int st = 0;
   auto tile = [&](int it, Q4Regs& rg) {
@@ -491,7 +504,7 @@ __device__ __forceinline__ void gemm_pingpong_q4(unsigned char* lds, int nk, int
     tile(it, ra);
     if (it + 1 < nk) tile(it + 1, rb);
   }
-  if (wr == 0) block_barrier();  // the second group's last slot
+  if (!PONG || wr == 0) block_barrier();  // the second group's last slot
   wait_vmcnt<0>();  // the clamped fetches past the last tile
   bready(ra);
   bready(rb);
