@@ -792,6 +792,10 @@ int cps_resident(int ch, bool single_expert, int M, int n_e) {
   return std::min(cps, ceil_div(ch, std::min(DOWN_SLOTS, ceil_div(1024, per_slot))));
 }
 
+// Rows handed to the host and its results are moved by kernels up to this size, above by the copy engine (whose start
+// costs as much as some 256 KB on the link).
+constexpr size_t HANDOFF_DIRECT_BYTES = 256 << 10;
+
 // chunks per staged piece of a part with `cps` chunks per j-slot
 int piece_chunks(const si_layer* L, int path, int cps) {
   return path == SI_DECODE ? std::max(cps, L->stage_chunks / cps * cps) : L->stage_chunks;
@@ -912,46 +916,23 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
     if (e != hipSuccess) return fail(SI_EHIP, "route launch failed: %s", hipGetErrorString(e));
   }
   // ---- hand-off to the host: the rows of X1 and the assignment go to the CPU for the CC part (Section III-B),
-  //      and with them the per-expert counts the copy scheduler needs
+  //      and with them the per-expert counts the copy scheduler needs.  One kernel writes them into pinned memory (five
+  //      small copies took longer than a tiny layer's kernels); only large x rows go through the copy engine.  The
+  //      host waits for them after it has enqueued the resident part.
+  std::chrono::steady_clock::time_point h0;
   if (need_sync) {
-    if (need_cc) {
-      HIP_TRY(hipMemcpyAsync(L->hx, x, (size_t)n_x1 * M * 2, hipMemcpyDeviceToHost, stream));
-      HIP_TRY(hipMemcpyAsync(L->hidx, L->plan.idx, (size_t)T * k * 4, hipMemcpyDeviceToHost, stream));
-      HIP_TRY(hipMemcpyAsync(L->hw, L->plan.w, (size_t)T * k * 4, hipMemcpyDeviceToHost, stream));
-    }
-    HIP_TRY(hipMemcpyAsync(L->hcount, L->plan.count, (size_t)EX * 4, hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipMemcpyAsync(L->hcount + EX, L->plan.count1, (size_t)EX * 4, hipMemcpyDeviceToHost, stream));
+    const size_t x_bytes = need_cc ? (size_t)n_x1 * M * 2 : 0;
+    const bool x_copy = x_bytes > HANDOFF_DIRECT_BYTES;
+    h0 = std::chrono::steady_clock::now();
+    if (x_copy) HIP_TRY(hipMemcpyAsync(L->hx, x, x_bytes, hipMemcpyDeviceToHost, stream));
+    HIP_TRY(launch_handoff(L->plan, x, x_copy ? 0 : x_bytes, need_cc ? T * k : 0, EX, L->hx, L->hidx, L->hw, L->hcount, stream));
     HIP_TRY(hipEventRecord(L->ev_host, stream));
-    const auto h0 = std::chrono::steady_clock::now();
-    HIP_TRY(hipEventSynchronize(L->ev_host));
-    st.handoff_ms = std::chrono::duration<float, std::milli>(std::chrono::steady_clock::now() - h0).count();
-    int nt = 0;
-    for (int e = 0; e < EX; ++e) nt += L->hcount[e] > 0;
-    st.n_touched = nt;
   } else if (E == 1) {
     st.n_touched = EX;
   }
-  std::chrono::steady_clock::time_point cc0;
-  if (need_cc) {
-    CcJob job{};
-    job.x = L->hx; job.idx = L->hidx; job.w = L->hw; job.T1 = n_x1; job.k = k; job.M = M; job.E = E;
-    job.routed = L->h_routed; job.expert_stride = (size_t)hch * ce; job.n_cc_chunks = L->ch_cc;
-    if (L->placed) { job.e_off = L->h_off.data(); job.e_cc_chunks = L->e_cc.data(); }
-    job.shared = (L->has_shared && L->sch_cc > 0) ? L->h_shared : nullptr; job.s_cc_chunks = L->sch_cc;
-    job.ycc = L->hycc;
-    job.q4 = L->q4;
-    if (L->ch_cc == 0 && !job.shared) {
-      std::memset(L->hycc, 0, (size_t)n_x1 * M * 4);
-    } else {
-      cc0 = std::chrono::steady_clock::now();
-      cc_pool_start(L->pool, job);
-      L->cc_inflight = true;
-    }
-  }
-
-  // counts per expert as known on the host (dense layers need no copy)
-  auto rows_all = [&](int e) { return need_sync ? L->hcount[e] : T; };
-  auto rows_x2 = [&](int e) { return need_sync ? L->hcount[e] - L->hcount[EX + e] : n_g; };
+  // rows per expert as known on the host: of a routed expert among several only once the hand-off has arrived
+  auto rows_all = [&](int e) { return E > 1 && e < E ? L->hcount[e] : T; };
+  auto rows_x2 = [&](int e) { return E > 1 && e < E ? L->hcount[e] - L->hcount[EX + e] : n_g; };
   const int max_touched = std::min(EX, T * k + L->has_shared);
   const int tiles_upper = (T * k) / TILE_ROWS + std::min(E, T * k);  // bound on the routed row tiles
   // (whole-expert placement: every routed expert has H/64 chunks wherever it lives)
@@ -1068,13 +1049,39 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
       rc = run_part(L->d_sgg, 0, 0, 1, 0, L->sch_gg, (L->sch_cc + L->sch_cg) * CHUNK_J, 0, 0, 0, true, no_ws);
       if (rc) return rc;
     }
-    st.bytes_gg = 0;
-    for (int e = 0; e < EX; ++e) {
-      const bool touched = need_sync ? L->hcount[e] > 0 : true;
-      if (touched) st.bytes_gg += (double)L->e_chunks(e, 0) * ce * 2;
-    }
-    if (!need_sync && E > 1) st.bytes_gg = -1;  // not known on the host without the counts
   }
+
+  // ---- the host takes over its share
+  if (need_sync) {
+    HIP_TRY(hipEventSynchronize(L->ev_host));
+    st.handoff_ms = std::chrono::duration<float, std::milli>(std::chrono::steady_clock::now() - h0).count();
+    int nt = 0;
+    for (int e = 0; e < EX; ++e) nt += L->hcount[e] > 0;
+    st.n_touched = nt;
+  }
+  std::chrono::steady_clock::time_point cc0;
+  if (need_cc) {
+    CcJob job{};
+    job.x = L->hx; job.idx = L->hidx; job.w = L->hw; job.T1 = n_x1; job.k = k; job.M = M; job.E = E;
+    job.routed = L->h_routed; job.expert_stride = (size_t)hch * ce; job.n_cc_chunks = L->ch_cc;
+    if (L->placed) { job.e_off = L->h_off.data(); job.e_cc_chunks = L->e_cc.data(); }
+    job.shared = (L->has_shared && L->sch_cc > 0) ? L->h_shared : nullptr; job.s_cc_chunks = L->sch_cc;
+    job.ycc = L->hycc;
+    job.q4 = L->q4;
+    if (L->ch_cc == 0 && !job.shared) {
+      std::memset(L->hycc, 0, (size_t)n_x1 * M * 4);
+    } else {
+      cc0 = std::chrono::steady_clock::now();
+      cc_pool_start(L->pool, job);
+      L->cc_inflight = true;
+    }
+  }
+  st.bytes_gg = 0;
+  for (int e = 0; e < EX; ++e) {
+    const bool touched = need_sync ? L->hcount[e] > 0 : true;
+    if (touched) st.bytes_gg += (double)L->e_chunks(e, 0) * ce * 2;
+  }
+  if (!need_sync && E > 1) st.bytes_gg = -1;  // not known on the host without the counts
 
   // ---- CG and CG' parts: copy (Stream-C) double-buffered against compute (Stream-D)
   if (any_cg || need_cgp) {
@@ -1141,8 +1148,12 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
       for (int e = 0; e < EX; ++e) if (L->hcount[EX + e] > 0) b += (double)L->e_chunks(e, 2) * ce * 2;
       st.bytes_cc = b;
     }
-    HIP_TRY(hipMemcpyAsync(L->d_ycc, L->hycc, (size_t)n_x1 * M * 4, hipMemcpyHostToDevice, stream));
-    ycc_dev = L->d_ycc;
+    if ((size_t)n_x1 * M * 4 <= HANDOFF_DIRECT_BYTES) {
+      ycc_dev = L->hycc;  // (pinned: the merge reads it over the link; the next call's hand-off follows on the stream)
+    } else {
+      HIP_TRY(hipMemcpyAsync(L->d_ycc, L->hycc, (size_t)n_x1 * M * 4, hipMemcpyHostToDevice, stream));
+      ycc_dev = L->d_ycc;
+    }
   }
 
   // ---- merge: Y = Y^CC (or Y^CG') + Y^CG + Y^GG (Eq. 2) and the weighted sum over experts

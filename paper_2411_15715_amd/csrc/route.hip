@@ -6,6 +6,8 @@
 #include "si_internal.h"
 #include "route_device.h"
 
+#include <algorithm>
+
 namespace si {
 
 namespace {
@@ -239,7 +241,25 @@ __global__ __launch_bounds__(ROUTE_THREADS) void k_route_small(const float* __re
   assign_body(s, T, E, k, has_shared, n_x1, p, u, 0, T * k, true);
 }
 
+// (rows of x are multiples of 128 bytes, x and the pinned buffer aligned to 16)
+__global__ __launch_bounds__(256) void k_handoff(Plan p, const uint4* __restrict__ x, uint4* __restrict__ hx, int n16, int n_pairs,
+                                                 int EX, int32_t* __restrict__ hidx, float* __restrict__ hw,
+                                                 int32_t* __restrict__ hcount) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n16) hx[i] = x[i];
+  if (i < n_pairs) { hidx[i] = p.idx[i]; hw[i] = p.w[i]; }
+  if (i < EX) { hcount[i] = p.count[i]; hcount[EX + i] = p.count1[i]; }
+}
+
 }  // namespace
+
+hipError_t launch_handoff(const Plan& plan, const uint16_t* x, size_t x_bytes, int n_pairs, int EX, uint16_t* hx, int32_t* hidx,
+                          float* hw, int32_t* hcount, hipStream_t stream) {
+  const int n16 = (int)(x_bytes / 16), n = std::max(std::max(n16, n_pairs), EX);
+  hipLaunchKernelGGL(k_handoff, dim3((n + 255) / 256), dim3(256), 0, stream, plan, reinterpret_cast<const uint4*>(x),
+                     reinterpret_cast<uint4*>(hx), n16, n_pairs, EX, hidx, hw, hcount);
+  return hipGetLastError();
+}
 
 hipError_t launch_route(const float* logits, int T, int E, int k, int has_shared, int n_g,
                         const Plan& plan, const RouteOut& user, hipStream_t stream) {

@@ -69,6 +69,11 @@ struct RouteOut {
 hipError_t launch_route(const float* logits, int T, int E, int k, int has_shared, int n_g,
                         const Plan& plan, const RouteOut& user, hipStream_t stream);
 
+// Hand-off to the host (layer.hip): the first x_bytes of x, the first n_pairs idx / w and the EX counts and X1 counts of
+// the plan into pinned host memory (hcount: count, then count1).
+hipError_t launch_handoff(const Plan& plan, const uint16_t* x, size_t x_bytes, int n_pairs, int EX, uint16_t* hx, int32_t* hidx,
+                          float* hw, int32_t* hcount, hipStream_t stream);
+
 // Description of the weights one kernel launch works on.
 struct WeightView {
   const uint16_t* base;   // chunk-major storage
