@@ -1,4 +1,4 @@
-// Prompt-phase grouped GEMMs on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16), fp32 accumulate.
+// Prompt-phase grouped GEMMs on the bf16 matrix cores (v_mfma_f32_16x16x32_bf16), fp32 accumulate.
 //   gateup : Hact[row][j] = SiLU(X_e . Wg_e[j]) * (X_e . Wu_e[j])   (FC1 + activation, Eq. 1)
 //   down   : Yp[row][m] (+)= Hact[row][:] . Wd_e[:, m]              (FC2, one term of Eq. 2)
 //   combine: y[t] = sum_s w[t][s] Yp[row(t,s)] (+ shared expert row) (+ Y^CC for X1 rows)
