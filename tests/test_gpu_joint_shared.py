@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("q4", [False, True])
 @pytest.mark.parametrize("E,k,d_ff,d_ff_shared,split", [
-    (4, 2, 192, 64, (1.0, 0.0, 0.0)), (4, 2, 192, 192, (1.0, 0.0, 0.0)), (12, 3, 128, 1088, (1.0, 0.0, 0.0)),
+    (1, 1, 192, 320, (1.0, 0.0, 0.0)), (1, 1, 320, 192, (0.4, 0.3, 0.3)), (4, 2, 192, 64, (1.0, 0.0, 0.0)), (4, 2, 192, 192, (1.0, 0.0, 0.0)), (12, 3, 128, 1088, (1.0, 0.0, 0.0)),
     (2, 1, 64, 4160, (1.0, 0.0, 0.0)), (4, 1, 576, 320, (0.5, 0.5, 0.0)), (4, 2, 64, 320, (0.3, 0.4, 0.3))])
 def test_joint(oracle, q4, E, k, d_ff, d_ff_shared, split):
     cfg = synth.scaled(synth.CONFIGS["qwen_moe"], d_model=320, d_ff=d_ff, d_ff_shared=d_ff_shared, n_experts=E, top_k=k)
