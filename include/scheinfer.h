@@ -175,9 +175,12 @@ int si_place_experts(const double* freq, int32_t n_experts, int32_t n_gg, double
  * `placement`: NULL (slice by the rates) or HOST [n_experts] as for si_layer_create_placed.
  * Everything else (slicing, placement, forward, stats) is as for si_layer_create; the parts keep the 4-bit
  * form in HBM, in pinned memory and on the host link (102*d_model bytes per 64 hidden columns instead of
- * 384*d_model).  Generation-phase kernels and the host workers multiply codes and scales in fp32 (exact); the
- * prompt-phase GEMMs read the same chunks and feed the matrix cores (c - 8) * scale rounded to bf16, converted
- * on the way into LDS (or, with desc->deq_mib > 0, by a separate pass into a bf16 scratch).
+ * 384*d_model).  Generation-phase kernels form exact products and fp32 sums: FC2 of h * (c - 8), whose rounding is
+ * bounded by the |h * (c - 8)| summed; FC1 of x * (128 + c) less 136 * x, whose partial sums within a scale group
+ * reach 143 * sum |x| before the offset cancels.  The host workers sum in fp32 too; where the CPU has bf16 dot products
+ * they take h as two bf16 parts (16 bits) and both products in the 128 + c form.  The prompt-phase GEMMs read the
+ * same chunks and feed the matrix cores (c - 8) * scale rounded to bf16, converted on the way into LDS (or, with
+ * desc->deq_mib > 0, by a separate pass into a bf16 scratch).
  */
 typedef struct {
   const uint8_t* q_gate;

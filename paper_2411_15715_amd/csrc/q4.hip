@@ -39,13 +39,15 @@ __device__ inline bool block_rows(const Plan& p, int expert_sel, int x2_only, in
   return r1 > r0;
 }
 
-// The generation-phase GEMVs on the matrix cores.  A code c turns into the bf16 value 128 + c by inserting its nibble
-// into 0x4300 (exact), so a 32-bit word of 8 codes is matrix operand data after 3 shifts and 4 and-or instructions,
-// whatever the number of tokens: the rows of the other operand are the tokens (or the bf16 parts of fp32 activations).
-// Per scale group: acc = -136 sum(x) + sum x (128 + c), total += scale * acc, in fp32.  The dot-product kernels this
-// replaces (shift, insert and one dot instruction per pair and token) were bound by the vector units: LLaMA-shaped layer,
-// 3 tokens, gate/up 107 us and down 77 us for 250 and 125 MB of codes.
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+// The generation-phase GEMVs on the matrix cores.  A 32-bit word of 8 codes becomes matrix operand data with one or two
+// instructions per pair of codes, whatever the number of tokens: the rows of the other operand are the tokens (FC1) or
+// the fp16 parts of fp32 activations (FC2).  FC1 inserts a nibble into 0x4300, the bf16 value 128 + c (3 shifts and 4 and-or
+// per word), and per scale group forms acc = -136 sum(x) + sum x (128 + c), total += scale * acc, in fp32; FC2 sums
+// h (c - 8) directly (SignedCodes).  The dot-product kernels these replaced (shift, insert and one dot instruction per pair
+// and token) were bound by the vector units: LLaMA-shaped layer, 3 tokens, gate/up 107 us and down 77 us for 250 and
+// 125 MB of codes; now 53 and 26.5 us.
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // the 8 codes of a word as bf16(128 + c): register i holds the nibbles i and i + 4.  mask / magic arrive in registers, so
@@ -207,10 +209,30 @@ __global__ __launch_bounds__(QGU_THREADS, 4) void k_decode_gateup_q4(const uint1
   }
 }
 
+// 8 codes as the fp16 values c - 8 (exact), in the order of expand_codes.  A nibble inserted into 0x6400 is 1024 + c at bit 0
+// and 1024 + 16 c at bit 4, which a packed addition and a packed multiply-add turn into c - 8.
+struct SignedCodes {
+  uint32_t lo = 0x000F000Fu, hi = 0x00F000F0u, magic = 0x64006400u, m1032 = 0xE408E408u, r16 = 0x2C002C00u, m72 = 0xD480D480u;
+  __device__ __forceinline__ void hide() { asm volatile("" : "+v"(lo), "+v"(hi), "+s"(magic), "+v"(m1032), "+s"(r16), "+v"(m72)); }
+  __device__ __forceinline__ f16x8 operator()(uint32_t w) const {
+    const uint32_t w8 = w >> 8;
+    const f16x2 a = __builtin_bit_cast(f16x2, (w & lo) | magic) + __builtin_bit_cast(f16x2, m1032);
+    const f16x2 b = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, (w & hi) | magic), __builtin_bit_cast(f16x2, r16), __builtin_bit_cast(f16x2, m72));
+    const f16x2 c = __builtin_bit_cast(f16x2, (w8 & lo) | magic) + __builtin_bit_cast(f16x2, m1032);
+    const f16x2 d = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, (w8 & hi) | magic), __builtin_bit_cast(f16x2, r16), __builtin_bit_cast(f16x2, m72));
+    return __builtin_shufflevector(__builtin_shufflevector(a, b, 0, 1, 2, 3), __builtin_shufflevector(c, d, 0, 1, 2, 3), 0, 1, 2, 3, 4, 5, 6, 7);
+  }
+};
+
 // part[slot][row][m] = sum over the chunks of the slot of scale_c[m] * sum_j h_j (code[j][m] - 8).  Block: 128 output
-// columns (32 per wave) of one slot; a load covers 256 contiguous bytes of two halves of two chunks.  LLaMA-shaped layer,
-// 3 tokens: 77 -> 25 us (125 MB of codes, 5 TB/s; four pairs of chunks in flight instead of two cost waves: 29 us).  The fp32 activations are split into three bf16 parts (8 significant bits each, i.e.
-// exactly), which are three operand rows: rows 4t .. 4t+2 belong to token t, so a lane ends up with the parts of one token.
+// columns (32 per wave) of one slot; a load covers 256 contiguous bytes of two halves of two chunks.
+// The fp32 activations of a chunk are scaled by a power of two that brings the largest to [2^14, 2^15) and split into three
+// fp16 parts (11 bits each; what a part of an element 2^15 times smaller than that still drops is below 2^-39 of the
+// largest), which are three operand rows: rows 4t .. 4t+2 belong to token t, so a lane ends up with the parts of one token.
+// The products h (c - 8) are exact and at most 8 |h|, and a weight of 0 adds nothing.  LLaMA-shaped layer, 3 tokens: 26.5 us
+// (125 MB of codes, 4.7 TB/s; four pairs of chunks in flight instead of two cost waves).  bf16 parts against 128 + c and
+// -136 sum(h) took 24.4 us, but their sums carried 136 |h| until the offset cancelled: 10 to 20 times the rounding error,
+// against 64 bits 2.5e-6 instead of 1.5e-6 of a whole call.
 constexpr int QDN_COLS = 128, QDN_TB = 4;
 __global__ __launch_bounds__(QDN_THREADS) void k_decode_down_q4(const float* __restrict__ h, int ldh, int M, Plan p,
                                                                 int expert_sel, int x2_only, WeightView wv_r, WeightView wv_s,
@@ -243,9 +265,9 @@ __global__ __launch_bounds__(QDN_THREADS) void k_decode_down_q4(const float* __r
     zo[i] = q4_off_scales(2, M) + (size_t)mm * 2;
   }
   const int n_j = n_c * CHUNK_J, hstride = 2 * n_j + 16;
-  float* s_sum = reinterpret_cast<float*>(s_h + (size_t)tb * 3 * hstride);  // [n_c][tb][4]: -136 * (chunk sums of the parts)
-  uint32_t mask = 0x000F000Fu, magic = 0x43004300u;
-  asm volatile("" : "+v"(mask), "+s"(magic));
+  float* s_inv = reinterpret_cast<float*>(s_h + (size_t)tb * 3 * hstride);  // [n_c][tb]: 1 / scale of the chunk's activations
+  SignedCodes signed_codes;
+  signed_codes.hide();
 
   constexpr int DU = 2;  // pairs of chunks fetched ahead
   u32x4 wd[DU][2];
@@ -272,34 +294,33 @@ __global__ __launch_bounds__(QDN_THREADS) void k_decode_down_q4(const float* __r
       const int t = i / (n_j / 8), c8 = i % (n_j / 8);
       const f32x4* src = reinterpret_cast<const f32x4*>(h + (size_t)(rb + t) * ldh + wv.col0 + c_begin * CHUNK_J + c8 * 8);
       const f32x4 lo = src[0], hi = src[1];
-      const float v[8] = {lo[0], lo[2], hi[0], hi[2], lo[1], lo[3], hi[1], hi[3]};
-      u32x4 o[3];
-      float sum[3] = {0.f, 0.f, 0.f};
+      float v[8] = {lo[0], lo[2], hi[0], hi[2], lo[1], lo[3], hi[1], hi[3]};
+      float top = 0.f;
 #pragma unroll
-      for (int w = 0; w < 4; ++w)
+      for (int e = 0; e < 8; ++e) top = fmaxf(top, fabsf(v[e]));
 #pragma unroll
-        for (int f = 0; f < 2; ++f) {
-          float rest = v[2 * w + f];
+      for (int d = 1; d < 8; d <<= 1) top = fmaxf(top, __shfl_xor(top, d, WAVE));  // (the 8 threads of a chunk are adjacent lanes)
+      // biased exponent; from 15 up the scale and its reciprocal are normal numbers
+      const uint32_t ex = max(__float_as_uint(top) >> 23, 15u);
+      const float up = __uint_as_float((268u - ex) << 23);
+      f16x2 o[3][4];
 #pragma unroll
-          for (int a = 0; a < 3; ++a) {
-            const uint32_t bits = __float_as_uint(rest) & 0xffff0000u;
-            const float pv = __uint_as_float(bits);
-            rest -= pv;
-            sum[a] += pv;
-            if (f == 0) o[a][w] = bits >> 16; else o[a][w] |= bits;
-          }
+      for (int e = 0; e < 8; ++e) {
+        float rest = v[e] * up;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          const _Float16 pv = (_Float16)rest;
+          rest -= (float)pv;
+          o[a][e >> 1][e & 1] = pv;
         }
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        *reinterpret_cast<u32x4*>(s_h + (t * 3 + a) * hstride + c8 * 16) = o[a];
-#pragma unroll
-        for (int d = 1; d < 8; d <<= 1) sum[a] += __shfl_xor(sum[a], d, WAVE);
       }
-      if ((c8 & 7) == 0) *reinterpret_cast<f32x4*>(s_sum + ((size_t)(c8 >> 3) * tb + t) * 4) = f32x4{-136.f * sum[0], -136.f * sum[1], -136.f * sum[2], 0.f};
+#pragma unroll
+      for (int a = 0; a < 3; ++a) *reinterpret_cast<u32x4*>(s_h + (t * 3 + a) * hstride + c8 * 16) = __builtin_bit_cast(u32x4, o[a]);
+      if ((c8 & 7) == 0) s_inv[(size_t)(c8 >> 3) * tb + t] = __uint_as_float((ex - 14u) << 23);
     }
     __syncthreads();
     const unsigned char* hrow = s_h + (min((lane & 15) >> 2, nt - 1) * 3 + min(lane & 3, 2)) * hstride + unit_k(q) * 2;
-    const float* srow = s_sum + min(q, nt - 1) * 4;
+    const float* irow = s_inv + min(q, nt - 1);
     float tot[2] = {0.f, 0.f};
     for (int c0 = 0; c0 < n_c; c0 += 2 * DU) {
       u32x4 cd[DU][2];
@@ -324,17 +345,17 @@ __global__ __launch_bounds__(QDN_THREADS) void k_decode_down_q4(const float* __r
         for (int gi = 0; gi < 2; ++gi) {
           const int c = c0 + 2 * d + gi;
           if (c < n_c) {
-            const f32x4 off = *reinterpret_cast<const f32x4*>(srow + (size_t)c * tb * 4);
-            f32x4 acc[2] = {off, off};
+            const float inv = irow[(size_t)c * tb];
+            f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
-              const bf16x8 hv = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(hrow + c * 128 + k * 16));
+              const f16x8 hv = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(hrow + c * 128 + k * 16));
 #pragma unroll
               for (int i = 0; i < 2; ++i)
-                acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hv, __builtin_bit_cast(bf16x8, expand_codes(g[i][gi][k], mask, magic)), acc[i], 0, 0, 0);
+                acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hv, signed_codes(g[i][gi][k]), acc[i], 0, 0, 0);
             }
 #pragma unroll
-            for (int i = 0; i < 2; ++i) tot[i] = fmaf(sc[gi][i], acc[i][0] + (acc[i][1] + acc[i][2]), tot[i]);
+            for (int i = 0; i < 2; ++i) tot[i] = fmaf(sc[gi][i], (acc[i][0] + (acc[i][1] + acc[i][2])) * inv, tot[i]);
           }
         }
       }
@@ -404,7 +425,7 @@ __global__ __launch_bounds__(256) void k_dequant_q4(const uint16_t* __restrict__
 }
 
 size_t gateup_lds(int tb, int M) { return (size_t)2 * QGU_JPB * (M / 64 + 2) * 2 + (size_t)tb * (2 * M + 16); }
-size_t down_lds(int tb, int cps) { return (size_t)tb * 3 * (2 * cps * CHUNK_J + 16) + (size_t)cps * tb * 16; }
+size_t down_lds(int tb, int cps) { return (size_t)tb * 3 * (2 * cps * CHUNK_J + 16) + (size_t)cps * tb * 4; }
 constexpr size_t Q4_LDS = 81 * 1024;  // two blocks per compute unit
 
 hipError_t ensure_q4_lds() {
