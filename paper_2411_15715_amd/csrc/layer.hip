@@ -782,14 +782,19 @@ int cps_of(int ch, bool single_expert, int M) {
 }
 
 // The same for the resident part of the routed bf16 experts (its cut is nobody else's concern): where that leaves hardly
-// more than a block per compute unit in a launch over n_e experts, more and shorter slots, down to 1 chunk: a dense
+// more than a block per compute unit for the n_e experts of one token, more and shorter slots, down to 1 chunk: a dense
 // layer of 3328 x 2240, 1 token, has 65 blocks of 8 chunks; with 234 of 2 the call takes 21.3 instead of 27.6 us.
 // With 416 blocks (6400 columns, 2 experts of d_model 4096) the longer merge already costs more: 60.6 against 63.7 us.
+// n_e counts one token's experts whatever the call holds, so that a token is summed in the same order in every batch.
+// As calls of several tokens then have more blocks and a longer merge, several experts aim at 512 blocks, a single one at
+// 1024: 60 experts of 1408 columns, top-4, d_model 2048, 1 / 8 tokens: 26.4 / 90.9 us with 512, 27.2 / 94.3 with 1024, 31.5 /
+// 90.9 with the cut above; 16 of 768, top-3, 4096: 24.3 / 56.6, 24.2 / 56.5, 30.1 / 61.6; 16 of 1024, top-2, 2304: 20.5 / 42.4,
+// 21.0 / 42.2, 25.5 / 47.8; dense 1408 x 8192, 4 tokens: 45.3 with 512, 44.1 with 1024.
 // (The 4-bit kernels lost 5 to 12 % by it and keep the cut above.)
 int cps_resident(int ch, bool single_expert, int M, int n_e) {
   const int cps = cps_of(ch, single_expert, M), per_slot = ceil_div(M, 256) * n_e;
   if (ch <= 0 || per_slot * ceil_div(ch, cps) >= 320) return cps;
-  return std::min(cps, ceil_div(ch, std::min(DOWN_SLOTS, ceil_div(1024, per_slot))));
+  return std::min(cps, ceil_div(ch, std::min(DOWN_SLOTS, ceil_div(single_expert ? 1024 : 512, per_slot))));
 }
 
 // Rows handed to the host and its results are moved by kernels up to this size, above by the copy engine (whose start
@@ -937,8 +942,8 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
   const int tiles_upper = (T * k) / TILE_ROWS + std::min(E, T * k);  // bound on the routed row tiles
   // (whole-expert placement: every routed expert has H/64 chunks wherever it lives)
   const bool one = E == 1;
-  const int n_e = std::min(E, T * k);  // (an upper bound on the experts of a launch)
-  const int cps_gg = L->placed ? cps_of(L->H / CHUNK_J, one, M) : L->q4 ? cps_of(L->ch_gg, one, M) : cps_resident(L->ch_gg, one, M, n_e), cps_cg = cps_of(L->placed ? L->H / CHUNK_J : L->ch_cg, one, M),
+  const int cps_gg = L->placed ? cps_of(L->H / CHUNK_J, one, M) : L->q4 ? cps_of(L->ch_gg, one, M) : cps_resident(L->ch_gg, one, M, k),
+            cps_cg = cps_of(L->placed ? L->H / CHUNK_J : L->ch_cg, one, M),
             cps_cc = cps_of(L->placed ? L->H / CHUNK_J : L->ch_cc, one, M);
   const int scps_gg = cps_of(L->sch_gg, true, M), scps_cg = cps_of(L->sch_cg, true, M), scps_cc = cps_of(L->sch_cc, true, M);
   const size_t slot_stride = (size_t)L->rows_dec * M;
