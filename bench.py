@@ -274,19 +274,21 @@ def eq6_prediction(st):
         tau_L^i   = tau_L^(i-1) + t_L
         tau_C2G^i = max(tau_L^i, tau_C2G^(i-1)) + t_C2G
         tau_G^i   = max(tau_C2G^i, tau_G^(i-1)) + t_G
-    with tau^0 = the hand-off wait, tau_G^0 additionally the assignment kernels and the resident (GG) part, which
-    are enqueued before the first copy is waited for; t_fin = max(tau_G^n + merge, tau_C)."""
+    The host enqueues the assignment, the hand-off and the resident (GG) part, then waits for the hand-off, then starts the
+    CPU part and the n pieces: tau_L^0 = tau_C2G^0 = one share of the launch time plus the wait, where tau_C starts as well,
+    and tau_G^0 = the assignment kernels and the resident part, which run from the start of the call;
+    t_fin = max(tau_G^n + merge, tau_C)."""
     n = st["n_copies"]
-    t0 = st["handoff_ms"]
+    t_l = max(0.0, st["enqueue_ms"] - st["handoff_ms"] - st["cc_ms"]) / (n + 1)
+    t0 = t_l + st["handoff_ms"]
     merge = st["kernel_ms"][3] + st["kernel_ms"][6]
     gg = st["gpu_ms"] - st["staged_ms"] - merge
     tau_c = t0 + st["cc_ms"]
     if n == 0:
-        return max(t0 + gg + merge, tau_c)
+        return max(gg + merge, tau_c)
     t_c2g, t_g = st["copy_ms"] / n, st["staged_ms"] / n
-    t_l = max(0.0, st["enqueue_ms"] - st["handoff_ms"] - st["cc_ms"]) / (n + 1)
     tau_l = tau_c2g = t0
-    tau_g = t0 + gg
+    tau_g = gg
     for _ in range(n):
         tau_l += t_l
         tau_c2g = max(tau_l, tau_c2g) + t_c2g

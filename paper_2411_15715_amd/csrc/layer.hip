@@ -924,11 +924,9 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
   //      and with them the per-expert counts the copy scheduler needs.  One kernel writes them into pinned memory (five
   //      small copies took longer than a tiny layer's kernels); only large x rows go through the copy engine.  The
   //      host waits for them after it has enqueued the resident part.
-  std::chrono::steady_clock::time_point h0;
   if (need_sync) {
     const size_t x_bytes = need_cc ? (size_t)n_x1 * M * 2 : 0;
     const bool x_copy = x_bytes > HANDOFF_DIRECT_BYTES;
-    h0 = std::chrono::steady_clock::now();
     if (x_copy) HIP_TRY(hipMemcpyAsync(L->hx, x, x_bytes, hipMemcpyDeviceToHost, stream));
     HIP_TRY(launch_handoff(L->plan, x, x_copy ? 0 : x_bytes, need_cc ? T * k : 0, EX, L->hx, L->hidx, L->hw, L->hcount, stream));
     HIP_TRY(hipEventRecord(L->ev_host, stream));
@@ -1058,6 +1056,7 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
 
   // ---- the host takes over its share
   if (need_sync) {
+    const auto h0 = std::chrono::steady_clock::now();
     HIP_TRY(hipEventSynchronize(L->ev_host));
     st.handoff_ms = std::chrono::duration<float, std::milli>(std::chrono::steady_clock::now() - h0).count();
     int nt = 0;
