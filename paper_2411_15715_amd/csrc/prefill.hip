@@ -942,7 +942,9 @@ __global__ __launch_bounds__(256) void k_prefill_combine(const float* __restrict
   reinterpret_cast<float4*>(y + (size_t)t * M)[m4] = acc;
 }
 
-__global__ void k_fill_zero(float* __restrict__ p, size_t n) {
+// grid: (blocks over the n elements, slabs)
+__global__ void k_fill_zero(float* __restrict__ p, size_t n, size_t slab_stride) {
+  p += blockIdx.y * slab_stride;
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const size_t stride = (size_t)gridDim.x * blockDim.x;
   for (; i < n; i += stride) p[i] = 0.f;
@@ -1028,10 +1030,10 @@ hipError_t launch_prefill_combine(const float* yp, size_t slab_stride, int n_spl
   return hipGetLastError();
 }
 
-hipError_t launch_fill_zero(float* p, size_t n, hipStream_t stream) {
-  if (n == 0) return hipSuccess;
+hipError_t launch_fill_zero(float* p, size_t n, int n_slabs, size_t slab_stride, hipStream_t stream) {
+  if (n == 0 || n_slabs <= 0) return hipSuccess;
   int blocks = (int)std::min<size_t>((n + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_fill_zero, dim3(blocks), dim3(256), 0, stream, p, n);
+  hipLaunchKernelGGL(k_fill_zero, dim3(blocks, n_slabs), dim3(256), 0, stream, p, n, slab_stride);
   return hipGetLastError();
 }
 

@@ -152,7 +152,8 @@ hipError_t launch_prefill_down(const uint16_t* hact, int ldh, int M, const Plan&
 // y[t][m] = sum_s w[t][s]*Yp[inv[t*k+s]][m] (n_split slabs) + Yp[T*k+t][m] (shared: split_s slabs) + ycc[t][m] (X1 rows)
 hipError_t launch_prefill_combine(const float* yp, size_t slab_stride, int n_split, int split_s, const float* ycc, int T, int k,
                                   int M, int n_x1, int has_shared, const Plan& plan, float* y, hipStream_t stream);
-hipError_t launch_fill_zero(float* p, size_t n, hipStream_t stream);
+// n elements at p, p + slab_stride, ... of n_slabs slabs
+hipError_t launch_fill_zero(float* p, size_t n, int n_slabs, size_t slab_stride, hipStream_t stream);
 
 // q4.hip -------------------------------------------------------------------------------------
 // the GEMV launchers of decode.hip hand over to these when wv.q4 is set
