@@ -1046,7 +1046,8 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
       K_TRY(launch_fill_zero(L->d_part, (size_t)T * k * M, n_slots, slot_stride, stream));
     }
     WeightView ws{};
-    if (joint) ws = WeightView{L->d_sgg, 0, 0, L->sch_gg, (L->sch_cc + L->sch_cg) * CHUNK_J, L->q4, nullptr};
+    // (col0 as in run_part: the generation phase keeps h by the column of the expert, the prompt phase by that of the launch)
+    if (joint) ws = WeightView{L->d_sgg, 0, 0, L->sch_gg, path == SI_DECODE ? (L->sch_cc + L->sch_cg) * CHUNK_J : 0, L->q4, nullptr};
     if (E == 1) rc = run_part(L->d_gg, 0, 0, 0, 0, L->ch_gg, hch * CHUNK_J, 0, 0, 0, true, ws);
     else rc = run_part(L->d_gg, (size_t)L->ch_gg * ce, -1, 0, 0, L->ch_gg, hch * CHUNK_J, 0, 0, 0, true, ws);
     if (rc) return rc;
