@@ -3,9 +3,10 @@
 //   gateup : h[row][j] = SiLU(x . Wg[j]) * (x . Wu[j])         (FC1 + activation, Eq. 1)
 //   down   : part[slot][row][m] = sum_{j in slot} h[row][j] Wd[j][m]   (FC2, one term of Eq. 2)
 //   combine: y[t] = sum_s w[t][s] sum_slots part[..][row(t,s)] (+ shared expert, + Y^CC)
-// Every weight byte is read once per pass of up to DECODE_TB tokens, with 128-bit loads that are
+// Every weight byte is read once per pass of up to 4 tokens (pick_tb), with 128-bit loads that are
 // contiguous across the lanes of a wave.
 #include "si_internal.h"
+#include "decode_device.h"
 #include "route_device.h"
 
 #include <algorithm>
@@ -28,25 +29,6 @@ __device__ inline float wave_sum(float v) {
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, WAVE);
   return v;
-}
-
-__device__ inline float silu_f(float z) { return z / (1.f + __expf(-z)); }
-
-// expert handled by this block and its row range; returns false when there is nothing to do
-// (slot < 0: the shared expert, entry n_routed, of a launch that covers it along with the routed ones)
-__device__ inline bool block_rows(const Plan& p, int expert_sel, int x2_only, int slot, int& e, int& r0, int& r1) {
-  if (slot < 0) {
-    e = p.n_routed;
-  } else if (expert_sel >= 0) {
-    e = expert_sel;
-  } else {
-    if (slot >= *p.n_touched) return false;
-    e = p.touched[slot];
-    if (e >= p.n_routed) return false;
-  }
-  r0 = p.off[e] + (x2_only ? p.count1[e] : 0);
-  r1 = p.off[e + 1];
-  return r1 > r0;
 }
 
 // Token assignment of a few tokens inside a block (FusedRoute): the same result as route.hip's kernels, derived
@@ -149,7 +131,7 @@ __global__ __launch_bounds__(GU_THREADS, 4) void k_decode_gateup(const uint16_t*
   extern __shared__ u32x4 s_x[];  // [TB][M/8] bf16 x 8
   __shared__ typename std::conditional<FUSED != 0, BlockRoute, int>::type s_br;  // (4 bytes when the tables are given)
   int e, r0, r1;
-  // the first shared_y rows of the grid are the blocks of the shared expert 
+  // the first shared_y rows of the grid are the blocks of the shared expert
   const int slot = (int)blockIdx.y - shared_y;
   const int bx = slot < 0 ? blockIdx.y * gridDim.x + blockIdx.x : blockIdx.x;
   const WeightView wv = slot < 0 ? wv_s : wv_r;

@@ -25,7 +25,6 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-#define SI_GPTR(p) ((const void __attribute__((address_space(1)))*)(p))
 #define SI_LPTR(p) ((void __attribute__((address_space(3)))*)(p))
 
 constexpr int WAVE = 64;
@@ -571,8 +570,8 @@ __device__ __forceinline__ void down_store(const f32x4 (&acc)[BM / 32][4], const
 
 // ---------------------------------------------------------------------------------------------
 // FC1 + SwiGLU.  Tile: BM rows x 128 hidden columns (two chunks).  B rows in LDS are ordered so
-// that wave column wc owns hidden columns [32 wc, 32 wc + 32): LDS B row = wc*64 + f*32 + jj with
-// f = 0 the gate row and f = 1 the up row of column 32 wc + jj; SiLU(gate)*up is then formed in
+// that wave column wc owns hidden columns [32 wc, 32 wc + 32): LDS B row = wc*64 + f*32 + r with
+// f = 0 the gate row and f = 1 the up row of column 32 wc + gu_col(r); SiLU(gate)*up is then formed in
 // registers from the two accumulator tiles of a wave.
 // ---------------------------------------------------------------------------------------------
 template <int BM>

@@ -5,6 +5,7 @@
 //       multiplication, which the matrix cores do, has to stay below the time the bytes take)
 //   k_dequant_q4 : codes -> bf16 chunks (the layout the MFMA GEMMs read), piece by piece, for the prompt phase
 #include "si_internal.h"
+#include "decode_device.h"
 
 #include <algorithm>
 
@@ -13,32 +14,12 @@ namespace {
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 constexpr int WAVE = 64;
 constexpr int QGU_THREADS = 512;
 constexpr int QGU_JPB = 32;  // hidden columns per block
 constexpr int QDN_THREADS = 256;
 
 __device__ inline float bf16_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-__device__ inline float silu_f(float z) { return z / (1.f + __expf(-z)); }
-
-// expert handled by this block and its row range; false when there is nothing to do
-// (slot < 0: the shared expert, entry n_routed, of a launch that covers it along with the routed ones)
-__device__ inline bool block_rows(const Plan& p, int expert_sel, int x2_only, int slot, int& e, int& r0, int& r1) {
-  if (slot < 0) {
-    e = p.n_routed;
-  } else if (expert_sel >= 0) {
-    e = expert_sel;
-  } else {
-    if (slot >= *p.n_touched) return false;
-    e = p.touched[slot];
-    if (e >= p.n_routed) return false;
-  }
-  r0 = p.off[e] + (x2_only ? p.count1[e] : 0);
-  r1 = p.off[e + 1];
-  return r1 > r0;
-}
-
 // The generation-phase GEMVs on the matrix cores.  A 32-bit word of 8 codes becomes matrix operand data with one or two
 // instructions per pair of codes, whatever the number of tokens: the rows of the other operand are the tokens (FC1) or
 // the fp16 parts of fp32 activations (FC2).  FC1 inserts a nibble into 0x4300, the bf16 value 128 + c (3 shifts and 4 and-or

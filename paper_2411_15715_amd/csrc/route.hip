@@ -128,7 +128,7 @@ __device__ __forceinline__ void assign_body(AssignLds& s, int T, int E, int k, i
       if (p.off) p.off[EX] = s.off[EX];
       if (u.off) u.off[E] = s.off[E];
       if (p.n_touched) *p.n_touched = s.touch[EX];
-      // launches over "all experts" cover the routed experts only (the shared expert, entry E, gets its own)
+      // the tiles of the routed experts only (the shared expert, entry E, is found through its offset)
       if (p.n_tiles) *p.n_tiles = s.tile[0][E];
       if (p.n_tiles_x2) *p.n_tiles_x2 = s.tile[1][E];
       if (p.tile_flags) *p.tile_flags = (s.multi[0] ? 0 : 1) | (s.multi[1] ? 0 : 2);

@@ -19,7 +19,6 @@ constexpr int MAX_EXPERTS = 256;      // routed experts (a shared expert adds on
 constexpr int ROUTE_THREADS = 1024;   // block size of the assignment kernel
 constexpr int TILE_ROWS = 256;        // rows per row tile of the prefill GEMMs (the last tile of an expert: see n_row_tiles)
 constexpr int MAX_KSPLIT = 4;         // k-splits (output slabs) of the prefill down projection
-constexpr int DECODE_TB = 4;          // most tokens handled per weight pass in the GEMV kernels
 constexpr int DOWN_SLOTS = 32;        // j-splits of the decode down projection per part
 
 // Row tiles of an expert (or of its X2 rows) with `rows` rows.  The GEMM kernels run, per tile, the body
@@ -56,8 +55,8 @@ struct Plan {
   int32_t* tile_r_x2;
   int32_t* n_tiles_x2;  // [1]
   int32_t* tile_flags;  // [1] bit 0: no routed expert has more than one row tile; bit 1: the same for the X2 rows
-  int32_t n_routed;    // E: launches over "all experts" cover entries < n_routed only (the shared
-                       // expert's weights live in their own buffer and get their own launch)
+  int32_t n_routed;    // E: the tables of a launch over "all experts" cover entries < n_routed only (the shared expert's
+                       // weights live in their own buffer: a view of their own in the same launch, or one of its own)
 };
 
 // user-visible copies (first E entries), any pointer may be null
