@@ -13,10 +13,12 @@ the timed region.
 Without --config the run covers every workload shape at full size in one process.  The headline
 (``value``, ``ms_per_step``, ``roofline``, ``cpu_baseline``) is the largest one, the Mixtral-8x22B-shaped
 layer with all weights resident, timed over exactly K steps after W warm-up steps; ``configs`` holds one
-entry per shape and quoted split (the PhiMoE- and Mixtral-8x22B-shaped layers: all seven splits of the
-sweep 100/0/0 ... 20/60/20) with the step time, tokens/s per phase, every weight kernel against its
-roofline, host-link rate, overlap and the Eq. 6 prediction next to the measured call time; those
-entries are timed over min(K, 3) steps of min(decode calls, 4) decode calls each.
+row per shape and quoted split (the PhiMoE- and Mixtral-8x22B-shaped layers: all seven splits of the
+sweep 100/0/0 ... 20/60/20) with the step and call times; those of splits with a streamed or host part are
+timed over min(K, 3) steps of min(decode calls, 4) decode calls each.  The full entries (tokens/s per phase,
+every weight kernel against its roofline, host-link rate, overlap and the Eq. 6 prediction next to the
+measured call time) are too long for a line that tools keep only the end of: they go to the file given
+with --detail, or as one JSON line to stderr.
 
 The printed JSON line carries
   value / ms_per_step   whole-step throughput of the headline workload
@@ -74,6 +76,7 @@ def parse_args():
                          "default: all five full-size shapes, headline on the Mixtral-8x22B-shaped layer")
     ap.add_argument("--split", default=None, help="r_gg,r_cg,r_cc (default: the config's)")
     ap.add_argument("--decode-calls", type=int, default=16)
+    ap.add_argument("--detail", default=None, help="without --config: file for the full entries of all shapes (default: stderr)")
     ap.add_argument("--n-g", type=int, default=-1, help="prefill tokens on CG' (default: all when r_cc > 0)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-peaks", action="store_true", help="skip the measurement of this machine's own HBM / MFMA / link peaks")
@@ -817,12 +820,20 @@ def all_configs_line(args, si, torch, synth):
         "config": {"workload": workload_text(cfg, args.decode_calls), "split_gg_cg_cc": [1.0, 0.0, 0.0],
                    "columns": head["info"], "n_g": 0, "tokens_per_step": tokens_per_step},
         "roofline": head["roofline"],
-        "configs": entries,
+        "configs": {"fields": ["shape", "split", "ms_per_step", "prefill_call_ms", "decode_call_us"],
+                    "rows": [[e["config"], "/".join("%g" % (100 * v) for v in e["split_gg_cg_cc"]), e["ms_per_step"],
+                              e["prefill_call_ms"], e["decode_call_us"]] for e in entries]},
         "measured_peaks": {k: (round(v, 1) if isinstance(v, float) else v) for k, v in MEASURED_PEAKS.items()} if MEASURED_PEAKS else None,
         "bench_wall_s": round(time.perf_counter() - t_all, 1),
     }
     if "cpu_baseline" in head:
         out["cpu_baseline"] = head["cpu_baseline"]
+    detail = json.dumps({"detail": "all shapes", "configs": entries})
+    if args.detail:
+        with open(args.detail, "w") as f:
+            f.write(detail + "\n")
+    else:
+        print(detail, file=sys.stderr, flush=True)
     print(json.dumps(out))
 
 
