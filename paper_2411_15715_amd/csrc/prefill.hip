@@ -5,12 +5,12 @@
 // Rows are the expert-sorted (token, slot) pairs of the token assignment; a row tile never
 // crosses an expert.  The gather of x rows is fused into the A-operand load of the first GEMM.
 //
-// Both GEMMs: one 512-thread block (8 waves, 2 per SIMD) per BM x 256 output tile, BK = 64, a ring of LDS
-// stages filled by direct global->LDS loads (global_load_lds_dwordx4, no VGPR staging), wave tile
-// (BM/2) x 64.  A row tile holds up to 256 rows, the last one of an expert up to 320 (si_internal.h: n_row_tiles);
-// the block runs the body instantiated for BM = 64, 128, 192, 256 or 320, the smallest that covers the rows the
-// tile really has.  The main loop is a ping-pong of two wave groups on v_mfma_f32_16x16x32_bf16 (gemm_pingpong;
-// gemm_pingpong_q4 converts 4-bit weights on their way into LDS).
+// Both GEMMs: one 512-thread block (8 waves, 2 per SIMD) per compute unit, which takes tile after tile of BM x 256 outputs
+// (TileQueues), BK = 64, rings of LDS stages filled by direct global->LDS loads (global_load_lds_dwordx4, no VGPR staging), wave
+// tile (BM/2) x 64.  A row tile holds up to 256 rows, the last one of an expert up to 320 (si_internal.h: n_row_tiles);
+// the block runs the body instantiated for the next multiple of 32 rows that covers the tile's (4-bit: 64, 128, 192 or 256).
+// The main loop is a ping-pong of two wave groups on v_mfma_f32_16x16x32_bf16 (gemm_pingpong; gemm_pingpong_q4 converts
+// 4-bit weights on their way into LDS).
 // LDS rows hold 64 contraction elements (128 bytes); the 16-byte piece c of row r sits at piece
 // c ^ ((r >> 1) & 7): gfx950's LDS has 64 banks, so 16 consecutive rows x 16 bytes must cover 256
 // distinct bytes of bank space for the 128-bit MFMA operand reads to be conflict free (measured:
@@ -32,7 +32,8 @@ constexpr int THREADS = 512;
 constexpr int BN = 256;  // B rows per tile: 128 hidden columns (gate+up) or 256 output columns
 constexpr int BK = 64;
 constexpr int B_BYTES = BN * BK * 2;  // 32 KB
-constexpr int KERNEL_LDS = 144 * 1024;  // the largest body
+constexpr int KERNEL_LDS = 156 * 1024;  // the largest body
+constexpr int NEXT_LDS = 16;            // after it: the block's next item (run_items)
 
 // z / (1 + exp(-z)), the division by one residual step on the reciprocal instruction, whose own error is up to 1 ulp and whose
 // denormal results are flushed (hence the factor 1/4).  Equal to the division bit for bit on 4 M arguments in [-100, 100] and
@@ -52,6 +53,27 @@ __device__ inline uint32_t pack_bf16(float a, float b) {
 }
 
 __device__ inline bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
+
+// thread index, opaque, so that what a body derives from it is formed per tile: hoisted out of the loop over the tiles the lane
+// offsets of all bodies are live through every main loop (9 registers spilled)
+__device__ __forceinline__ int thread_of_item() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
+// the same for uniform values (the conditions on the number of k-tiles of all bodies filled the scalar registers)
+__device__ __forceinline__ int scalar_of_item(int v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+
+// Entry i (uniform) of a table that kernels before this one wrote, as a scalar load.  (Left to the compiler, which has to assume
+// that the stores of earlier tiles reach it, it is a vector load and a wait for all of them.)
+__device__ __forceinline__ int table(const int32_t* t, int i) {
+  typedef const int32_t __attribute__((address_space(4))) constant_t;
+  return ((constant_t*)(uintptr_t)t)[i];
+}
 
 // direct global -> LDS load of 16 bytes per lane: uniform base (scalar registers) + 32-bit byte offset of the lane
 __device__ inline void load_lds16(const void* base, uint32_t& off, unsigned char* l) {
@@ -82,143 +104,377 @@ __device__ inline void block_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// Hardware block id -> logical tile id.
-//  * XCD-aware remap: consecutive hardware block ids go round-robin over the 8 XCDs; give each XCD a
-//    contiguous range of logical ids so that the row tiles that read the same weights share an L2.  The
-//    ranges are cut from the number of ids that really have work (known on the device only), so that no
-//    XCD is handed a range of empty ids (with ranges cut from the grid's upper bound the remap cost more than
-//    it saved on small tiles: the last XCD idled while the others carried its share).
-//    When no expert of the launch has more than one row tile nothing is shared through the L2 but the few rows
-//    of x, and tiles of different experts differ in cost (a 192-row tile streams its weights a quarter slower than
-//    a 128-row one): the ids are then dealt round-robin (`interleave`), every XCD gets the same mix, and the launch
-//    takes the mean of the experts' times instead of the slowest XCD's.
-//  * Tail split: N tiles on n_cu compute units run in ceil(N / n_cu) rounds; when the last round is at most
-//    half full each of its tiles gets two blocks, which share its rows if it has more than 128 (LLaMA-shaped
-//    gate/up GEMM: 896 tiles = 3.5 rounds; the last round then costs about half a round).
-__device__ inline bool map_block(int b, int N, int n_cu, int interleave, int& L, int& half, int& halves) {
-  int r = N % n_cu;
-  if (2 * r > n_cu) r = 0;
-  const int main_n = N - r;
-  const int per = (main_n + 7) / 8;
-  if (b < 8 * per) {
-    L = interleave ? b : (b % 8) * per + b / 8;
-    half = 0;
-    halves = 1;
-    return L < main_n;
-  }
-  const int bt = b - 8 * per;
-  if (bt >= 2 * r) return false;
-  L = main_n + (bt >> 1);
-  half = bt & 1;
-  halves = 2;
-  return true;
-}
-
 // se: index of the expert inside the launch's weight storage; sh: the shared expert in a launch that covers it as well
-struct TileInfo { int e, row0, row_end, se, sh; };
+// row_t0: row r is token r - row_t0 (the shared expert, a single routed one), -1: look it up
+struct TileInfo { int e, row0, row_end, se, sh, row_t0; };
 
-// Number of logical tile ids with work in this launch (row tiles x inner tiles); single: no expert of the launch
-// has more than one row tile.
-__device__ inline int launch_extent(const Plan& p, int expert_sel, int x2_only, int n_inner, int& single) {
-  if (expert_sel >= 0) {
-    const int start = p.off[expert_sel] + (x2_only ? p.count1[expert_sel] : 0);
-    const int nrt = n_row_tiles(p.off[expert_sel + 1] - start);
-    single = nrt <= 1;
-    return nrt * n_inner;
-  }
-  single = (*p.tile_flags >> (x2_only ? 1 : 0)) & 1;
-  return (x2_only ? *p.n_tiles_x2 : *p.n_tiles) * n_inner;  // row tiles of the routed experts
+// The tiles of a launch, in one queue per XCD (hardware block ids go round-robin over the 8 XCDs).
+//  * Three lists of ids: the shared expert's tiles, in a launch that covers it along with the routed ones (its tiles are the
+//    longest of the down projection); the routed experts' spill tiles (the last tile of an expert where it has more than
+//    TILE_ROWS rows), longer than all others; their other tiles in the order expert, inner index, row tile.  In a launch over one
+//    expert whose last tile is a short one the second list is of its full tiles, the third of the last.  A queue holds an eighth of
+//    each list, in this order: the longest tiles start first, the last round is of the shortest, and in between different
+//    XCDs work on experts of different sizes (sorted by rows altogether, the tiles bound by the matrix cores came first and
+//    those bound by the weights after them: 2011 tokens, 64 experts of 2560 columns, top-8, 1690 -> 1775 us).
+//    The eighth is a range, so that the row tiles that read the same weights share an L2; when no expert of the launch has more
+//    than one row tile nothing is shared but the few rows of x, and the ids are dealt one by one: every XCD gets the same mix.
+//  * One block per compute unit takes tile after tile from the queue of its XCD and, when that is empty, from the fullest other
+//    one: with ranges alone a launch took the time of the XCD with the fullest experts.
+//  * Where the last round of a queue (a tile per compute unit) is at most half full its tiles are cut in two.
+// A launch has 3 to 20 rounds, so a tile more than the mean is 5 to 30 %.  One block per tile in ranges of ids per XCD, tiles
+// computed for 64, 128, 192, 256 or 320 rows, against this: 2011 tokens, 64 experts of 2560 columns, top-8, a shared one of 20480:
+// 1757 -> 1694 us; 4096 tokens, 8 experts of 16384, d_model 6144, top-2: 3907 -> 3676 (3747 with the spill tiles in their place);
+// 512 tokens, 8 experts of 14336: 543 -> 530; dense 6656 x 1152, 20 tokens (9 tiles cut along their columns): 65 -> 45.
+constexpr int N_XCD = 8, XCD_CU = 32;  // XCDs, compute units of one
+constexpr int SHORT_ROWS = 128;        // a last tile up to here is a short one
+// a / b and the remainder of uniform numbers, 0 <= a < 2^24, b > 0: a tenth of the general division's instructions.  A launch
+// starts with cold instruction caches; 2 KB less code before the first load are 1 to 2 us.
+__device__ __forceinline__ int small_div(int a, int b, int& rem) {
+  int q = (int)((float)a * __builtin_amdgcn_rcpf((float)b));  // at most 1 off
+  int r = a - q * b;
+  if (r < 0) { --q; r += b; }
+  if (r >= b) { ++q; r -= b; }
+  rem = __builtin_amdgcn_readfirstlane(r);
+  return __builtin_amdgcn_readfirstlane(q);
 }
 
-// logical id L -> (expert, inner index, row tile) with the row tile varying fastest inside an
-// expert: L / n_inner indexes the row-tile table, which yields the expert.
-__device__ inline bool decode_tile(const Plan& p, int expert_sel, int x2_only, int L, int n_inner, int& inner,
-                                   TileInfo& ti) {
-  int e, first, nrt, start, end;
+struct TileQueues {
+  unsigned n0, n1, n2;        // ids of each list
+  int rows0, rows1, rows2;    // row tiles of an inner index in it (launch over one expert) or of all experts
+  int deal;
+  __device__ __forceinline__ int rows(int list) const { return rows0 * (list == 0) + rows1 * (list == 1) + rows2 * (list == 2); }
+  static __device__ __forceinline__ unsigned first(unsigned n, unsigned q) { return n * q / N_XCD; }
+  __device__ __forceinline__ unsigned count0(unsigned q) const { return first(n0, q + 1) - first(n0, q); }
+  __device__ __forceinline__ unsigned count(unsigned n, unsigned q) const { return deal ? (n + N_XCD - 1 - q) / N_XCD : first(n, q + 1) - first(n, q); }
+  __device__ __forceinline__ unsigned tiles(unsigned q) const { return count0(q) + count(n1, q) + count(n2, q); }
+  __device__ __forceinline__ unsigned most_tiles() const { return (n0 + 7) / N_XCD + (n1 + 7) / N_XCD + (n2 + 7) / N_XCD; }  // >= any tiles(q)
+  __device__ __forceinline__ unsigned cut(unsigned tiles) const { const unsigned r = tiles % XCD_CU; return 2 * r > XCD_CU ? 0 : r; }
+  __device__ __forceinline__ int items(unsigned q) const { const unsigned t = tiles(q); return t + cut(t); }
+  // item of queue q -> list and id in it, and which half of a cut tile (halves 2)
+  __device__ __forceinline__ int find(unsigned q, unsigned item, int& list, int& half, int& halves) const {
+    const unsigned t = tiles(q), whole = t - cut(t);
+    halves = item < whole ? 1 : 2;
+    half = item < whole ? 0 : (item - whole) & 1;
+    const unsigned i = item < whole ? item : whole + (item - whole) / 2, c0 = count0(q), c1 = c0 + count(n1, q);
+    list = i < c0 ? 0 : i < c1 ? 1 : 2;
+    const unsigned k = i - (list == 0 ? 0 : list == 1 ? c0 : c1), f0 = first(n0, q), f1 = first(n1, q), f2 = first(n2, q);
+    return list && deal ? k * N_XCD + q : (list == 0 ? f0 : list == 1 ? f1 : f2) + k;
+  }
+};
+
+__device__ __forceinline__ TileQueues tile_queues(const Plan& p, int expert_sel, int x2_only, int n_inner, int n_inner_s, bool deal) {
+  TileQueues t;
+  t.rows0 = n_inner_s ? n_row_tiles(table(p.off, p.n_routed + 1) - table(p.off, p.n_routed)) : 0;
+  int multi, n;
   if (expert_sel >= 0) {
-    e = expert_sel;
-    start = p.off[e] + (x2_only ? p.count1[e] : 0);
-    end = p.off[e + 1];
-    nrt = n_row_tiles(end - start);
-    if (L >= nrt * n_inner) return false;
-    first = 0;
+    const int rows = table(p.off, expert_sel + 1) - table(p.off, expert_sel) - (x2_only ? table(p.count1, expert_sel) : 0), last = rows & (TILE_ROWS - 1);
+    n = n_row_tiles(rows);
+    multi = n > 1;
+    t.rows1 = has_spill_tile(rows) ? 1 : multi && last && last <= SHORT_ROWS ? n - 1 : 0;
   } else {
-    const int n_tiles = x2_only ? *p.n_tiles_x2 : *p.n_tiles;
-    const int t = L / n_inner;
-    if (t >= n_tiles) return false;
-    e = x2_only ? p.tile_e_x2[t] : p.tile_e[t];
-    if (e >= p.n_routed) return false;
-    first = t - (x2_only ? p.tile_r_x2[t] : p.tile_r[t]);
-    start = p.off[e] + (x2_only ? p.count1[e] : 0);
-    end = p.off[e + 1];
-    nrt = n_row_tiles(end - start);
+    const int32_t* nt = p.n_tiles + 3 * x2_only;
+    n = table(nt, 0);
+    t.rows1 = table(nt, 1);
+    multi = !table(nt, 2);
   }
-  const int Le = L - first * n_inner;
-  inner = Le / nrt;
-  const int r = Le % nrt;
-  ti.e = e;
+  t.rows2 = n - t.rows1;
+  t.deal = deal && !multi;
+  t.n0 = t.rows0 * n_inner_s;
+  t.n1 = t.rows1 * n_inner;
+  t.n2 = t.rows2 * n_inner;
+  return t;
+}
+
+// item -> expert, inner index, rows
+__device__ __forceinline__ void item_tile(const TileQueues& tq, const Plan& p, int expert_sel, int x2_only, int q, int item, int n_inner,
+                                          int& inner, TileInfo& ti, int& half, int& halves) {
+  int list;
+  const int id = tq.find(q, item, list, half, halves);
+  ti.sh = list == 0;
+  // the group of row tiles that share an inner index: id inside it, its size, its first row tile
+  int in_group = id, size, r0 = 0, rem;
+  if (ti.sh || expert_sel >= 0) {
+    ti.e = ti.sh ? p.n_routed : expert_sel;
+    size = tq.rows(list);
+  } else {
+    const int t = small_div(id, n_inner, rem), at = t + (list == 2 ? tq.rows1 : 0);
+    const int32_t *te = x2_only ? p.tile_e_x2 : p.tile_e, *tr = x2_only ? p.tile_r_x2 : p.tile_r;
+    const unsigned e = table(te, at);
+    const int first = table(tr, at);
+    ti.e = e & TILE_E_MASK;
+    size = e / (TILE_E_MASK + 1);
+    in_group = rem;
+    if (list == 1) r0 = first;
+    else in_group += first * n_inner;
+  }
+  const int off = table(p.off, ti.e), start = off + (x2_only ? table(p.count1, ti.e) : 0), rows = table(p.off, ti.e + 1) - start, n = n_row_tiles(rows);
+  // one expert: the spill tile (list 1) or the short last tile (list 2) is the last one
+  if (expert_sel >= 0 && (has_spill_tile(rows) ? list == 1 : list == 2)) r0 = n - size;
+  inner = small_div(in_group, size, rem);
+  const int r = r0 + rem;
+  // (uniform, but partly formed in vector registers)
+  ti.sh = __builtin_amdgcn_readfirstlane(ti.sh);
+  ti.e = __builtin_amdgcn_readfirstlane(ti.e);
+  half = __builtin_amdgcn_readfirstlane(half);
+  ti.row_t0 = ti.e == p.n_routed || p.n_routed == 1 ? off : -1;
   ti.row0 = start + r * TILE_ROWS;
-  ti.row_end = r == nrt - 1 ? end : ti.row0 + TILE_ROWS;
-  return true;
+  ti.row_end = r == n - 1 ? start + rows : ti.row0 + TILE_ROWS;
 }
 
-// Launch over the routed experts and the shared one: every XCD gets a contiguous eighth of either kind's ids, the shared
-// expert's first: its tiles are the longest of the down projection and alike, and the smaller ones of the routed experts
-// even out the end (a split tail as in map_block is not needed).  2011 tokens, 64 experts of 2560 columns, top-8, a
-// shared one of 20480: 1829 us with two launches, 1761 like this, 1790 with the routed tiles first, 1827 with the two
-// kinds in turn (their operands then share the L2s).
-__device__ inline bool joint_tile(const Plan& p, int expert_sel, int n_inner, int n_inner_s, int spread, int& inner, TileInfo& ti) {
-  int single;
-  const int n_r = launch_extent(p, expert_sel, 0, n_inner, single);
-  const int n_s = n_row_tiles(p.off[p.n_routed + 1] - p.off[p.n_routed]) * n_inner_s;
-  const int per_r = (n_r + 7) / 8, per_s = (n_s + 7) / 8;
-  const int xcd = blockIdx.x % 8, i = blockIdx.x / 8;
-  const bool sh = i < per_s;
-  const int idx = sh ? i : i - per_s, per = sh ? per_s : per_r;
-  if (idx >= per) return false;
-  const int L = !sh && single && spread ? idx * 8 + xcd : xcd * per + idx;
-  if (L >= (sh ? n_s : n_r)) return false;
-  ti.sh = sh;
-  return decode_tile(p, sh ? p.n_routed : expert_sel, 0, L, sh ? n_inner_s : n_inner, inner, ti);
-}
-
-// block id -> tile of this block (false: nothing to do)
-// n_inner_s: inner tiles of the shared expert when the launch covers it along with the routed ones, else 0
-// spread: deal single-tile launches round-robin over the XCDs (see map_block)
-__device__ inline bool block_tile(const Plan& p, int expert_sel, int x2_only, int n_inner, int n_inner_s, int n_cu, int spread,
-                                  int& inner, TileInfo& ti) {
-  ti.sh = 0;
-  if (n_inner_s) return joint_tile(p, expert_sel, n_inner, n_inner_s, spread, inner, ti);
-  int L, half, halves, single;
-  const int extent = launch_extent(p, expert_sel, x2_only, n_inner, single);
-  if (!map_block(blockIdx.x, extent, n_cu, single && spread, L, half, halves)) return false;
-  if (!decode_tile(p, expert_sel, x2_only, L, n_inner, inner, ti)) return false;
-  if (halves == 2) {
-    const int rows = ti.row_end - ti.row0;
-    if (rows <= 128) return half == 0;  // too few rows to share: the first block takes them all
-    const int hs = ((rows + 1) / 2 + 31) / 32 * 32;
-    ti.row0 += half * hs;
-    ti.row_end = min(ti.row_end, ti.row0 + hs);
-    if (ti.row0 >= ti.row_end) return false;
+// Takes items until all queues are empty.  The first item of a block is given (block b: item b / 8 of queue b % 8), further ones
+// come from a counter per queue, which the kernel before this one on the stream has cleared (it clears the other launch's).
+//   body(queue, item, take): processes the item and calls take() once, when its last loads have been waited for: the answer of
+//   the counter then arrives under the epilogue.
+// Every block ends: a queue's counter never falls, so each of the 8 queues refuses a block at most once.
+template <class F>
+__device__ __forceinline__ void run_items(const TileQueues& tq, int32_t* head, int32_t* clear, unsigned char* lds, F body) {
+  volatile int __attribute__((address_space(3)))* s_next = (volatile int __attribute__((address_space(3)))*)SI_LPTR(lds + KERNEL_LDS);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  constexpr int first = XCD_CU;
+  if (blockIdx.x == 0 && threadIdx.x < N_XCD) clear[threadIdx.x * QUEUE_STRIDE] = 0;
+  const bool more = tq.most_tiles() > XCD_CU;  // some items are not given to a block (a cut round is at most full)
+  int q = blockIdx.x % N_XCD, cand = blockIdx.x / N_XCD, par = 0;
+  bool given = cand < tq.items(q);
+  for (;;) {
+    if (!given) {
+      if (!more) return;
+      if (w == 0) {
+        const int lane = thread_of_item();
+        cand = __builtin_amdgcn_readfirstlane(cand);
+        while (cand >= tq.items(q)) {
+          int best = 0;  // items left * 8 + queue
+          if (lane < N_XCD) best = max(0, tq.items(lane) - first - __hip_atomic_load(head + lane * QUEUE_STRIDE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) * N_XCD + lane;
+#pragma unroll
+          for (int d = 1; d < N_XCD; d <<= 1) best = max(best, __shfl_xor(best, d, WAVE));
+          best = __builtin_amdgcn_readfirstlane(best);
+          if (best < N_XCD) { q = -1; break; }
+          q = best % N_XCD;
+          int got = 0;
+          if (lane == 0) got = first + __hip_atomic_fetch_add(head + q * QUEUE_STRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          cand = __builtin_amdgcn_readfirstlane(got);
+        }
+        if (lane == 0) s_next[par] = q < 0 ? -1 : cand * N_XCD + q;
+        wait_lgkmcnt0();
+      }
+      block_barrier();
+      const int v = __builtin_amdgcn_readfirstlane(s_next[par]);
+      if (v < 0) return;
+      q = v % N_XCD;
+      cand = v / N_XCD;
+      par ^= 1;
+    }
+    given = false;
+    body(__builtin_amdgcn_readfirstlane(q), __builtin_amdgcn_readfirstlane(cand), [&]() {
+      if (more && thread_of_item() == 0) cand = first + __hip_atomic_fetch_add(head + q * QUEUE_STRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    });
   }
-  return true;
+}
+
+// the rows of half a tile; false: none (of few rows the first half takes all)
+__device__ __forceinline__ bool half_rows(TileInfo& ti, int half) {
+  const int rows = ti.row_end - ti.row0;
+  if (rows <= 128) return half == 0;
+  const int hs = ((rows + 1) / 2 + 31) / 32 * 32;
+  ti.row0 += half * hs;
+  ti.row_end = min(ti.row_end, ti.row0 + hs);
+  return ti.row0 < ti.row_end;
 }
 
 // ---------------------------------------------------------------------------------------------
-// Main loop of the bf16 tiles: ping-pong of two wave groups.
-// 8 waves as 2 (rows) x 4 (B-row quarters of 64), wave tile (BM/2) x 64 in v_mfma_f32_16x16x32_bf16 tiles.  Waves w and
-// w + 4 share a SIMD; the second row group runs one barrier behind the first, so that in every slot between two
-// barriers one wave of each SIMD issues matrix instructions and nothing else while the other reads its next fragments
-// from LDS, issues tile loads and waits.  A k-tile of 64 is cut into phases of up to 64 rows per group (2 loads per wave,
-// 4 fragments, 32 matrix instructions of 16 cycles); B is read in the first phase and kept in registers.
-// A region of a stage (the rows of one phase, with B in the first) is free once both groups have read it, i.e. one phase
-// later, and is refilled then with tile it + NST: at BM = 256 a load has three phases = 3072 matrix cycles to land.
+// Main loop of the tiles: ping-pong of two wave groups.
+// 8 waves as 2 (row groups) x 4 (B-row quarters of 64), wave tile (16 FA) x 64 in v_mfma_f32_16x16x32_bf16 tiles, FA = 1 .. 10
+// fragments of 16 rows: a tile is computed for the next multiple of 32 rows.  Waves w and w + 4 share a SIMD; the second row
+// group runs one barrier behind the first, so that in every slot between two barriers one wave of each SIMD issues matrix
+// instructions and nothing else while the other reads its next fragments from LDS, issues tile loads and waits.  A k-tile of
+// 64 is cut into phases of up to 4 fragments per group (32 matrix instructions of 16 cycles); B is read in the first phase and
+// kept in registers.  A region (the A rows of one phase; B) is free once both groups have read it, i.e. one phase later, and is
+// refilled then with the tile NA (A) or NB (B) further on: with 256 rows a load has three phases = 3072 matrix cycles to land.
 // What bounds it: the power limit.  Counters of a 1024 x 65536 x 8192 product: matrix cores busy 0.90 of the time at a
 // shader clock of 1.68 GHz (the loop with one barrier per k-tile that it replaces: 0.65 at 1.84 GHz): 1461 TFLOP/s against
 // 1181.  The 16 x 16 x 32 instruction is part of it: register-resident on random operands it sustains 2.06 PFLOP/s under
 // the power limit where the 32 x 32 x 16 one sustains 1.81 (its accumulators cost twice the register traffic).  Four
 // phases of 16 matrix instructions (64 x 32 quadrants) measured 1378, one wave per SIMD with 128 x 128 tiles 1064.
 // ---------------------------------------------------------------------------------------------
+template <int FAV, int NJV> struct Ring {
+  static constexpr int FA = FAV;
+  static constexpr int NJ = NJV;                                   // B fragments (16 rows) of a wave: 4, or 2 of a tile cut in two
+  static constexpr int BM = 32 * FA;                               // rows of the tile
+  static constexpr int BNW = 64 * NJ;                              // B rows
+  static constexpr int NP = FA <= 4 ? 1 : FA <= 8 ? 2 : 3;         // phases per k-tile
+  static constexpr int NA = FA <= 5 ? 3 : 2;                       // LDS stages of A
+  static constexpr int NB = FA <= 2 ? 4 : FA <= 5 ? 3 : 2;         // LDS stages of B
+  static constexpr int A_STAGE = BM * 128;
+  static constexpr int B_STAGE = BNW * 128;
+  static constexpr int B_OFF = NA * A_STAGE;
+  static constexpr int LDS = B_OFF + NB * B_STAGE;
+  static constexpr int BL = NJ;                                    // direct-to-LDS loads of B per wave and k-tile
+  static constexpr int R = NA > NB ? NA : NB;
+  // fragments of a phase, fragments before it
+  static constexpr int frags(int p) {
+    return NP == 1 ? FA : NP == 2 ? (p == 0 ? (FA + 1) / 2 : FA / 2) : p == 0 ? 4 : p == 1 ? FA - 6 : 2;
+  }
+  static constexpr int frag0(int p) { return p == 0 ? 0 : frag0(p - 1) + frags(p - 1); }
+  // A loads of a wave for a phase's region (32 rows per fragment, both groups): 8 rows each, for an odd number of fragments one
+  // of 4 rows (half the lanes); loads before the phase's
+  static constexpr int aloads(int p) { return (frags(p) + 1) / 2; }
+  static constexpr int aload0(int p) { return p == 0 ? 0 : aload0(p - 1) + aloads(p - 1); }
+  static constexpr int ALD = aload0(NP - 1) + aloads(NP - 1);
+  static constexpr int phase_of(int i) { int p = 0; while (i >= aload0(p) + aloads(p)) ++p; return p; }
+  static constexpr bool half(int i) { return frags(phase_of(i)) % 2 == 1 && i == aload0(phase_of(i)) + aloads(phase_of(i)) - 1; }
+
+  // Loads of a wave that may still be in flight when the data of the phase after phase q of tile `it` must have landed, with
+  // `rem` tiles after tile `it`: those issued later than the last load of that data.  The order of issue is the loop's.
+  static constexpr int younger_at(int it, int q, int rem) {
+    const int nk = it + 1 + rem;
+    int pos = 0, last = 0;
+    bool any = false;
+    for (int step = -1; step < it * NP + q + 1; ++step) {
+      const int t0 = step < 0 ? 0 : step / NP, q0 = step < 0 ? 0 : step % NP;
+      const int n_t = step < 0 ? R : 1;  // the prologue issues tiles 0 .. R-1
+      for (int t = 0; t < n_t; ++t)
+        for (int p = 0; p < NP; ++p) {
+          const int at = step < 0 ? (t < NA ? t : -1) : refill_a(t0, q0, p, nk), bt = p > 0 ? -1 : step < 0 ? (t < NB ? t : -1) : refill_b(t0, q0, nk);
+          if (at >= 0 && at < nk) { pos += aloads(p); if (q < NP - 1 ? at == it && p == q + 1 : at == it + 1 && p == 0) { last = pos; any = true; } }
+          if (bt >= 0 && bt < nk) { pos += BL; if (q == NP - 1 && bt == it + 1) { last = pos; any = true; } }
+        }
+    }
+    return any ? pos - last : pos;
+  }
+  // tile whose region p of A (whose B) is issued in phase q of tile `it`, -1: none
+  static constexpr int refill_a(int it, int q, int p, int nk) {
+    if (p != (q == 0 ? NP - 1 : q - 1)) return -1;
+    const int t = (q == 0 ? it - 1 : it) + NA;
+    return (q == 0 && it == 0) || t >= nk ? -1 : t;
+  }
+  static constexpr int refill_b(int it, int q, int nk) {
+    if (q != (NP == 1 ? 0 : 1)) return -1;
+    const int t = (NP == 1 ? it - 1 : it) + NB;
+    return (NP == 1 && it == 0) || t >= nk ? -1 : t;
+  }
+  static constexpr int younger(int q, int rem) {
+    int n = 63;
+    for (int it = 0; it < 2 * R + 2; ++it) { const int y = younger_at(it, q, rem); n = y < n ? y : n; }
+    return n;
+  }
+  static_assert(LDS <= KERNEL_LDS, "ring does not fit");
+};
+
+// first LDS row of the rows that wave w's i-th A load of a k-tile fills
+template <class P, int I> __device__ __forceinline__ int ring_a_row(int w) {
+  constexpr int p = P::phase_of(I), f = P::frags(p);
+  const int rr = P::half(I) ? f / 2 * 64 + w * 4 : (I - P::aload0(p)) * 64 + w * 8;  // row inside the phase's region of 2 x 16 f rows
+  const int g = rr >= 16 * f ? 1 : 0;
+  return g * 16 * P::FA + P::frag0(p) * 16 + rr - g * 16 * f;
+}
+template <int N, class F> __device__ __forceinline__ void unroll(F f) {
+  if constexpr (N > 0) {
+    unroll<N - 1>(f);
+    f(std::integral_constant<int, N - 1>{});
+  }
+}
+
+template <int R, class P, int Q> __device__ __forceinline__ void ring_wait(int rem) {
+  if constexpr (R == 0) {
+    wait_vmcnt<P::younger(Q, 0)>();
+  } else {
+    if (rem >= R) wait_vmcnt<P::younger(Q, R)>();
+    else ring_wait<R - 1, P, Q>(rem);
+  }
+}
+
+// acc[i][j] += the 16 x 16 tile (rows i*16.., B rows j*16..) of the wave over nk k-tiles, transposed: lane l holds row
+// l%16 and the four consecutive B rows 4*(l/16) .. +3, i.e. output columns that are adjacent in memory.
+//   issue_a(i, stage, kt): wave's i-th A load of tile kt into LDS at `stage` (rows ring_a_row);  issue_b(stage, kt): its 4 B
+//   loads;  boff[ks]: byte offset of the lane's piece of B fragment 0 in k-step ks inside a B stage, BJ: bytes
+//   between fragments.  (Fragment addresses are one lane offset per k-step and operand plus constants: the swizzle of
+//   row r is that of r + 16.  Left to the compiler they were 16 registers.)
+template <class P, int BJ, class IA, class IB>
+__device__ __forceinline__ void gemm_pingpong(unsigned char* lds, int nk, int lane, int wr, f32x4 (&acc)[P::FA][P::NJ],
+                                              IA issue_a, IB issue_b, const uint32_t (&boff)[2]) {
+  constexpr int FP = P::frags(0);
+  // With up to 64 rows a slot of matrix instructions is far shorter than one of loads and LDS reads, and the groups in turn
+  // only add their latencies: there all waves read, pass one barrier per k-tile and multiply.  (What is read was waited for
+  // before that barrier, and what is refilled after it was read before it.)  Dense layers of 13 to 61 tokens: 4352 x 7232
+  // 62.3 -> 59.2 us, 3328 x 1472 41.4 -> 39.0, 2816 x 4928 47.3 -> 45.9; the 128-row body loses 2 to 12 % by it.
+  constexpr bool PONG = P::FA > 2;
+  bf16x8 fa[FP][2], fb[P::NJ][2];
+  const uint32_t aoff[2] = {(uint32_t)swz(wr * 16 * P::FA + (lane & 15), lane >> 4), (uint32_t)swz(wr * 16 * P::FA + (lane & 15), 4 + (lane >> 4))};
+  auto issue_region = [&](auto pc, int stage, int kt) {
+    constexpr int p = decltype(pc)::value;
+    unroll<P::aloads(p)>([&](auto i) { issue_a(std::integral_constant<int, P::aload0(p) + decltype(i)::value>{}, lds + stage * P::A_STAGE, kt); });
+  };
+  auto b_stage = [&](int stage) { return lds + P::B_OFF + stage * P::B_STAGE; };
+  auto phase = [&](auto qc, int it, int sta, int stb) {
+    constexpr int q = decltype(qc)::value;
+    constexpr int nf = P::frags(q), f0 = P::frag0(q);
+    const unsigned char *sa = lds + sta * P::A_STAGE, *sb = b_stage(stb);
+    if constexpr (q == 0) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int j = 0; j < P::NJ; ++j) fb[j][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(sb + boff[ks] + j * BJ));
+    }
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < nf; ++i) fa[i][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(sa + aoff[ks] + (f0 + i) * 2048));
+    // refill the regions that both groups have read: those of the previous phase
+    if constexpr (q == 0) {
+      if (it > 0 && it - 1 + P::NA < nk) issue_region(std::integral_constant<int, P::NP - 1>{}, sta == 0 ? P::NA - 1 : sta - 1, it - 1 + P::NA);
+      if constexpr (P::NP == 1)
+        if (it > 0 && it - 1 + P::NB < nk) issue_b(b_stage(stb == 0 ? P::NB - 1 : stb - 1), it - 1 + P::NB);
+    } else {
+      if (it + P::NA < nk) issue_region(std::integral_constant<int, q - 1>{}, sta, it + P::NA);
+      if constexpr (q == 1)
+        if (it + P::NB < nk) issue_b(b_stage(stb), it + P::NB);
+    }
+    ring_wait<P::R, P, q>(nk - 1 - it);
+    wait_lgkmcnt0();
+    __builtin_amdgcn_sched_barrier(0);
+    block_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < nf; ++i)
+#pragma unroll
+        for (int jj = 0; jj < P::NJ; ++jj) {
+          const int j = (i & 1) ? P::NJ - 1 - jj : jj;
+          acc[f0 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][ks], fa[i][ks], acc[f0 + i][j], 0, 0, 0);
+        }
+    if constexpr (PONG) {
+      __builtin_amdgcn_sched_barrier(0);
+      block_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < P::FA; ++i)
+#pragma unroll
+    for (int j = 0; j < P::NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < P::R; ++t)
+    if (t < nk)
+      unroll<P::NP>([&](auto p) {
+        if (t < P::NA) issue_region(p, t, t);
+        if (p == 0 && t < P::NB) issue_b(b_stage(t), t);
+      });
+  if (nk >= P::R) wait_vmcnt<P::NA * P::ALD + P::NB * P::BL - P::aloads(0) - P::BL>();  // the first region of A and B of tile 0
+  else wait_vmcnt<0>();
+  block_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  if (PONG && wr == 1) block_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  int sta = 0, stb = 0;
+  for (int it = 0; it < nk; ++it) {
+    unroll<P::NP>([&](auto q) { phase(q, it, sta, stb); });
+    sta = sta + 1 == P::NA ? 0 : sta + 1;
+    stb = stb + 1 == P::NB ? 0 : stb + 1;
+  }
+  if (!PONG || wr == 0) block_barrier();  // the second group's last slot
+}
+
+// (4-bit bodies)
 template <int BM, int BL = 4> struct PingPong {  // BL: direct-to-LDS loads of B per wave and k-tile (0: B travels through registers)
   static constexpr int NST = BM >= 192 ? 2 : 3;     // LDS stages
   static constexpr int STAGE = BM * 128 + B_BYTES;  // bytes per stage
@@ -265,103 +521,6 @@ template <int R, class P, int Q, int X> __device__ __forceinline__ void pp_wait(
     if (rem >= R) wait_vmcnt<P::younger(Q, R) + X>();
     else pp_wait<R - 1, P, Q, X>(rem);
   }
-}
-
-// acc[i][j] += the 16 x 16 tile (rows i*16.., B rows j*16..) of the wave over nk k-tiles, transposed: lane l holds row
-// l%16 and the four consecutive B rows 4*(l/16) .. +3, i.e. output columns that are adjacent in memory.
-//   issue_a(i, stage, kt): wave's i-th A load of tile kt into LDS stage `stage` (rows pp_a_row);  issue_b(stage, kt): its 4 B
-//   loads;  boff[ks]: byte offset of the lane's piece of B fragment 0 in k-step ks inside the B part of a stage, BJ: bytes
-//   between fragments.  (Fragment addresses are one lane offset per k-step and operand plus constants: the swizzle of
-//   row r is that of r + 16.  Left to the compiler they were 16 registers.)
-template <int BM, int BJ, class IA, class IB>
-__device__ __forceinline__ void gemm_pingpong(unsigned char* lds, int nk, int lane, int wr, f32x4 (&acc)[BM / 32][4],
-                                              IA issue_a, IB issue_b, const uint32_t (&boff)[2]) {
-  using P = PingPong<BM>;
-  constexpr int FP = P::ALD >= 2 ? 4 : 2;  // fragments of a phase
-  // With a 64-row body a slot of matrix instructions is far shorter than one of loads and LDS reads, and the groups in turn
-  // only add their latencies: there all waves read, pass one barrier per k-tile and multiply.  (What is read was waited for
-  // before that barrier, and what is refilled after it was read before it.)  Dense layers of 13 to 61 tokens: 4352 x 7232
-  // 62.3 -> 59.2 us, 3328 x 1472 41.4 -> 39.0, 2816 x 4928 47.3 -> 45.9; the 128-row body loses 2 to 12 % by it.
-  constexpr bool PONG = BM > 64;
-  bf16x8 fa[FP][2], fb[4][2];
-  const uint32_t aoff[2] = {(uint32_t)swz(wr * (BM / 2) + (lane & 15), lane >> 4), (uint32_t)swz(wr * (BM / 2) + (lane & 15), 4 + (lane >> 4))};
-  auto issue = [&](auto pc, int stage, int kt) {
-    constexpr int p = decltype(pc)::value;
-#pragma unroll
-    for (int i = 0; i < P::aloads(p); ++i) issue_a(2 * p + i, stage, kt);
-    if constexpr (p == 0) issue_b(stage, kt);
-  };
-  auto next = [&](int st) { return st + 1 == P::NST ? 0 : st + 1; };
-  auto phase = [&](auto qc, int it, int st) {
-    constexpr int q = decltype(qc)::value;
-    constexpr int nf = 2 * P::aloads(q);
-    const unsigned char* sa = lds + st * P::STAGE;
-    if constexpr (q == 0) {
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          fb[j][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(sa + boff[ks] + (BM * 128 + j * BJ)));
-    }
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-      for (int i = 0; i < nf; ++i)
-        fa[i][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(sa + aoff[ks] + (q * 64 + i * 16) * 128));
-    // refill the region that both groups have read: that of the previous phase
-    if constexpr (q == 0) {
-      if (it > 0 && it - 1 + P::NST < nk) issue(std::integral_constant<int, P::NP - 1>{}, st == 0 ? P::NST - 1 : st - 1, it - 1 + P::NST);
-    } else {
-      if (it + P::NST < nk) issue(std::integral_constant<int, q - 1>{}, st, it + P::NST);
-    }
-    pp_wait<P::NST, P, q, 0>(nk - 1 - it);
-    wait_lgkmcnt0();
-    __builtin_amdgcn_sched_barrier(0);
-    block_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-      for (int i = 0; i < nf; ++i)
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          const int j = (i & 1) ? 3 - jj : jj;
-          acc[q * 4 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][ks], fa[i][ks], acc[q * 4 + i][j], 0, 0, 0);
-        }
-    if constexpr (PONG) {
-      __builtin_amdgcn_sched_barrier(0);
-      block_barrier();
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-#pragma unroll
-  for (int i = 0; i < BM / 32; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  using C0 = std::integral_constant<int, 0>;
-  using C1 = std::integral_constant<int, 1>;
-  using C2 = std::integral_constant<int, 2>;
-#pragma unroll
-  for (int t = 0; t < P::NST; ++t)
-    if (t < nk) {
-      issue(C0{}, t, t);
-      if constexpr (P::NP > 1) issue(C1{}, t, t);
-      if constexpr (P::NP > 2) issue(C2{}, t, t);
-    }
-  if (nk >= P::NST) wait_vmcnt<P::NST * P::LPW - P::loads(0)>();  // the first region of tile 0
-  else wait_vmcnt<0>();
-  block_barrier();
-  __builtin_amdgcn_sched_barrier(0);
-  if (PONG && wr == 1) block_barrier();
-  __builtin_amdgcn_sched_barrier(0);
-  int st = 0;
-  for (int it = 0; it < nk; ++it) {
-    phase(C0{}, it, st);
-    if constexpr (P::NP > 1) phase(C1{}, it, st);
-    if constexpr (P::NP > 2) phase(C2{}, it, st);
-    st = next(st);
-  }
-  if (!PONG || wr == 0) block_barrier();  // the second group's last slot
 }
 
 // register loads and the dependency tie used by the loops whose B operand travels through registers
@@ -519,26 +678,27 @@ __device__ __forceinline__ void gemm_pingpong_q4(unsigned char* lds, int nk, int
 // Epilogue of FC1: SiLU(gate) * up of the wave's 32 hidden columns -> bf16 Hact.  The loader puts the hidden columns of a
 // wave into LDS in an order (gu_col) that leaves 8 adjacent columns in a lane, for one 16-byte store per fragment row: with
 // the plain order, 2-byte stores and a full division this epilogue was 1180 vector instructions per wave, 5 us of a tile.
-template <int BM>
-__device__ __forceinline__ void gateup_store(const f32x4 (&acc)[BM / 32][4], const TileInfo& ti, const WeightView& wv, int tc, int wr,
-                                             int wc, int lane, uint16_t* __restrict__ hact, int ldh) {
-  using P = PingPong<BM>;
-  if (2 * tc + (wc >> 1) >= wv.n_chunks) return;
+// chunk: of the wave's columns; col: their first column inside the launch's range
+template <int FA, int NJ>
+__device__ __forceinline__ void gateup_store(const f32x4 (&acc)[FA][NJ], const TileInfo& ti, const WeightView& wv, int chunk, int col, int wr,
+                                             int lane, uint16_t* __restrict__ hact, int ldh) {
+  if (chunk >= wv.n_chunks) return;
   // (the lane index is made opaque here so that the output addresses are formed after the main loop: formed
   // ahead of it they are live through it, which the 320-row body has no registers for)
   int el = lane;
   asm volatile("" : "+v"(el));
-  const int row0 = ti.row0 + wr * (BM / 2) + (el & 15);
-  uint16_t* dst = hact + (size_t)row0 * ldh + (wv.col0 + tc * 128 + wc * 32 + (el >> 4) * 8);
+  const int row0 = ti.row0 + wr * (16 * FA) + (el & 15);
+  uint16_t* dst = hact + (size_t)row0 * ldh + (wv.col0 + col + (el >> 4) * 2 * NJ);
 #pragma unroll
-  for (int i = 0; i < P::FA; ++i) {
-    u32x4 o;
+  for (int i = 0; i < FA; ++i) {
+    typedef uint32_t out_t __attribute__((ext_vector_type(NJ)));
+    out_t o;
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NJ / 2; ++j)
 #pragma unroll
       for (int r = 0; r < 2; ++r)
-        o[j * 2 + r] = pack_bf16(silu_f(acc[i][j][2 * r]) * acc[i][j + 2][2 * r], silu_f(acc[i][j][2 * r + 1]) * acc[i][j + 2][2 * r + 1]);
-    if (row0 + i * 16 < ti.row_end) *reinterpret_cast<u32x4*>(dst + (size_t)(i * 16) * ldh) = o;
+        o[j * 2 + r] = pack_bf16(silu_f(acc[i][j][2 * r]) * acc[i][j + NJ / 2][2 * r], silu_f(acc[i][j][2 * r + 1]) * acc[i][j + NJ / 2][2 * r + 1]);
+    if (row0 + i * 16 < ti.row_end) *reinterpret_cast<out_t*>(dst + (size_t)(i * 16) * ldh) = o;
   }
 }
 // hidden column (of the 32 of a wave) whose gate / up row sits at LDS row r of the wave's 32: fragment j = r / 16, row
@@ -546,19 +706,18 @@ __device__ __forceinline__ void gateup_store(const f32x4 (&acc)[BM / 32][4], con
 __device__ inline int gu_col(int r) { return ((r & 12) << 1) + ((r >> 4) << 2) + (r & 3); }
 
 // Epilogue of FC2: the wave's 64 output columns, overwritten or accumulated, 16 bytes per lane
-template <int BM>
-__device__ __forceinline__ void down_store(const f32x4 (&acc)[BM / 32][4], const TileInfo& ti, int n0, int wr, int wc, int lane, int M,
+template <int FA, int NJ>
+__device__ __forceinline__ void down_store(const f32x4 (&acc)[FA][NJ], const TileInfo& ti, int n0, int wr, int lane, int M,
                                            float* __restrict__ out, int accumulate) {
-  using P = PingPong<BM>;
   int el = lane;  // opaque, as in gateup_store
   asm volatile("" : "+v"(el));
-  const int row0 = ti.row0 + wr * (BM / 2) + (el & 15), m0 = n0 + wc * 64 + (el >> 4) * 4;
+  const int row0 = ti.row0 + wr * (16 * FA) + (el & 15), m0 = n0 + (el >> 4) * 4;
   float* dst = out + (size_t)row0 * M + m0;
 #pragma unroll
-  for (int i = 0; i < P::FA; ++i) {
+  for (int i = 0; i < FA; ++i) {
     if (row0 + i * 16 < ti.row_end) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < NJ; ++j)
         if (m0 + j * 16 < M) {
           f32x4* d = reinterpret_cast<f32x4*>(dst + (size_t)(i * 16) * M + j * 16);
           *d = accumulate ? *d + acc[i][j] : acc[i][j];
@@ -575,12 +734,10 @@ __device__ __forceinline__ void down_store(const f32x4 (&acc)[BM / 32][4], const
 // f = 0 the gate row and f = 1 the up row of column 32 wc + gu_col(r); SiLU(gate)*up is then formed in
 // registers from the two accumulator tiles of a wave.
 // ---------------------------------------------------------------------------------------------
-template <int BM>
-__device__ __forceinline__ void gateup_body(const uint16_t* __restrict__ x, int M, const Plan& p, int tc, const TileInfo& ti,
-                                            const WeightView& wv, uint16_t* __restrict__ hact, int ldh,
-                                            unsigned char* lds) {
-  using P = PingPong<BM>;
-  const int tid = threadIdx.x, lane = tid % WAVE, w = __builtin_amdgcn_readfirstlane(tid / WAVE);  // wave index, known to be uniform
+template <class P, class Take>
+__device__ __forceinline__ void gateup_body(const uint16_t* __restrict__ x, int M, const Plan& p, int tc, int half, const TileInfo& ti,
+                                            const WeightView& wv, uint16_t* __restrict__ hact, int ldh, unsigned char* lds, Take take) {
+  const int tid = thread_of_item(), lane = tid % WAVE, w = __builtin_amdgcn_readfirstlane(tid / WAVE);  // wave index, known to be uniform
   const int wr = w >> 2, wc = w & 3;
   const uint16_t* ebase = wv.base + (size_t)ti.se * wv.expert_stride;
 
@@ -588,54 +745,72 @@ __device__ __forceinline__ void gateup_body(const uint16_t* __restrict__ x, int 
   // 128-byte row, which holds logical piece slot ^ ((row >> 1) & 7)
   const int lrow = lane >> 3, lpp = lane & 7;
   uint32_t a_src[P::ALD];  // byte offsets from x (the host checks that x spans less than 2^31 elements)
-#pragma unroll
-  for (int i = 0; i < P::ALD; ++i) {
-    const int lr = pp_a_row<BM>(w, i) + lrow;  // LDS row of the A tile
+  unroll<P::ALD>([&](auto i) {
+    const int lr = ring_a_row<P, i>(w) + lrow;  // LDS row of the A tile
     int row = ti.row0 + lr;
     row = row < ti.row_end ? row : ti.row_end - 1;
-    a_src[i] = ((uint32_t)p.row_token[row] * (uint32_t)M + ((lpp ^ ((lr >> 1) & 7)) * 8)) * 2;
-  }
-  // B: LDS row w*32 + i*8 + lrow  ->  chunk 2*tc + w/4, f = w%2 (gate / up block), column-in-chunk
-  // jc = ((w/2)%2)*32 + gu_col(i*8 + lrow).  Blocks are [M/PW panels][64 j][PW m] (cc_worker.h).
-  const int chunk_rel = min(2 * tc + (w >> 2), wv.n_chunks - 1);
+    a_src[i] = ((uint32_t)(ti.row_t0 >= 0 ? row - ti.row_t0 : p.row_token[row]) * (uint32_t)M + ((lpp ^ ((lr >> 1) & 7)) * 8)) * 2;
+  });
+  // B: LDS row w*8*NJ + i*8 + lrow.  A whole tile: chunk 2*tc + w/4, f = w%2 (gate / up block), column-in-chunk
+  // jc = ((w/2)%2)*32 + gu_col(i*8 + lrow); half a tile: chunk 2*tc + half, f = w%2, jc = (w/2)*16 + i*8 + lrow.
+  // Blocks are [M/PW panels][64 j][PW m] (cc_worker.h).
+  const int chunk = 2 * tc + (P::NJ == 4 ? wc >> 1 : half);
+  const int chunk_rel = __builtin_amdgcn_readfirstlane(min(2 * tc + (P::NJ == 4 ? w >> 2 : half), wv.n_chunks - 1));
   const uint16_t* b_blk = ebase + (size_t)(wv.chunk0 + chunk_rel) * 3 * CHUNK_J * M + (size_t)(w & 1) * CHUNK_J * M;
-  const int jc0 = ((w >> 1) & 1) * 32 + gu_col(lrow);
+  const int jc0 = P::NJ == 4 ? ((w >> 1) & 1) * 32 + gu_col(lrow) : (w >> 1) * 16 + lrow;
   const int PW = panel_width(M);
   const int lc0 = lpp ^ (lrow >> 1);  // B piece for even i; odd i uses lc0 ^ 4
 
   // uniform bases and 32-bit lane offsets: two vector registers for the B addresses instead of eight (a k-tile never
   // crosses a panel, PW being a multiple of 64)
   uint32_t b_lane[2] = {(uint32_t)(jc0 * PW + lc0 * 8) * 2u, (uint32_t)(jc0 * PW + (lc0 ^ 4) * 8) * 2u};
-  auto issue_a = [&](int i, int stage, int kt) {
-    load_lds16(x + kt * BK, a_src[i], lds + stage * P::STAGE + pp_a_row<BM>(w, i) * 128);
+  auto issue_a = [&](auto i, unsigned char* stage, int kt) {
+    if (!P::half(i) || lane < 32) load_lds16(x + kt * BK, a_src[i], stage + ring_a_row<P, i>(w) * 128);
   };
-  auto issue_b = [&](int stage, int kt) {
-    unsigned char* sb = lds + stage * P::STAGE + BM * 128 + w * 4096;
+  auto issue_b = [&](unsigned char* stage, int kt) {
+    unsigned char* sb = stage + w * (P::NJ * 1024);
     const int k0 = kt * BK;
     const uint16_t* bk = b_blk + (size_t)(k0 / PW) * CHUNK_J * PW + k0 % PW;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) load_lds16(bk + gu_col(i * 8) * PW, b_lane[i & 1], sb + i * 1024);
+    for (int i = 0; i < P::NJ; ++i) load_lds16(bk + (P::NJ == 4 ? gu_col(i * 8) : i * 8) * PW, b_lane[i & 1], sb + i * 1024);
   };
-  f32x4 acc[P::FA][4];
-  const uint32_t boff[2] = {(uint32_t)swz(wc * 64 + (lane & 15), lane >> 4), (uint32_t)swz(wc * 64 + (lane & 15), 4 + (lane >> 4))};
-  gemm_pingpong<BM, 2048>(lds, M / BK, lane, wr, acc, issue_a, issue_b, boff);
-  gateup_store<BM>(acc, ti, wv, tc, wr, wc, lane, hact, ldh);
+  f32x4 acc[P::FA][P::NJ];
+  const int br = wc * 16 * P::NJ + (lane & 15);
+  const uint32_t boff[2] = {(uint32_t)swz(br, lane >> 4), (uint32_t)swz(br, 4 + (lane >> 4))};
+  gemm_pingpong<P, 2048>(lds, M / BK, lane, wr, acc, issue_a, issue_b, boff);
+  take();
+  gateup_store<P::FA, P::NJ>(acc, ti, wv, chunk, tc * 128 + (P::NJ == 4 ? wc * 32 : half * 64 + wc * 16), wr, lane, hact, ldh);
 }
 
 // A block picks the body for the rows its tile really has (whole-block branch), so a 40-row tile costs a 64-row
-// body and a 140-row tile a 192-row one.  The 320-row body (160 accumulator registers, 144 KB of LDS) exists for the last
+// body and a 140-row tile a 160-row one.  The bodies above 256 rows (160 accumulator registers, 144 KB of LDS) exist for the last
 // tile of an expert only.  Tiles of at most 192 rows that hold all rows of their expert are bound by HBM: they ran a loop
 // of their own before (weights through registers, four k-tiles ahead), which the ping-pong loop overtook because an
 // iteration of it is shorter, not because more bytes are in flight (Mixtral-8x7B-shaped prompt of 512 tokens, about
 // 128 rows per expert: gate/up 398 -> 366 us, down 205 -> 165 us; 24 tokens, 6 rows per expert: equal).
-#define SI_PICK_BODY(ti, CALL)                  \
-  {                                             \
-    const int rows_ = (ti).row_end - (ti).row0; \
-    if (rows_ > 256) CALL(320);                 \
-    else if (rows_ > 192) CALL(256);            \
-    else if (rows_ > 128) CALL(192);            \
-    else if (rows_ > 64) CALL(128);             \
-    else CALL(64);                              \
+#define SI_PICK_BODY(ti, CALL)                         \
+  switch (((ti).row_end - (ti).row0 + 31) / 32) {      \
+    case 1: CALL(1, 4); break;                         \
+    case 2: CALL(2, 4); break;                         \
+    case 3: CALL(3, 4); break;                         \
+    case 4: CALL(4, 4); break;                         \
+    case 5: CALL(5, 4); break;                         \
+    case 6: CALL(6, 4); break;                         \
+    case 7: CALL(7, 4); break;                         \
+    case 8: CALL(8, 4); break;                         \
+    case 9: CALL(9, 4); break;                         \
+    default: CALL(10, 4); break;                       \
+  }
+// A tile of at most CUT_COLUMNS_ROWS rows is cut along its columns (such tiles are bound by the weights, which each half then
+// reads half of), others along their rows.
+constexpr int CUT_COLUMNS_ROWS = 160;
+#define SI_PICK_HALF_BODY(ti, CALL)                    \
+  switch (((ti).row_end - (ti).row0 + 31) / 32) {      \
+    case 1: CALL(1, 2); break;                         \
+    case 2: CALL(2, 2); break;                         \
+    case 3: CALL(3, 2); break;                         \
+    case 4: CALL(4, 2); break;                         \
+    default: CALL(5, 2); break;                        \
   }
 // The 4-bit bodies stop at 256 rows (their B operand passes through registers, which leaves no room for a fifth
 // A fragment): the rows a last tile holds beyond 256 take a second pass of the same block.  No wave still reads
@@ -653,20 +828,40 @@ __device__ __forceinline__ void gateup_body(const uint16_t* __restrict__ x, int 
   }
 
 __global__ __launch_bounds__(THREADS, 1) void k_prefill_gateup(const uint16_t* __restrict__ x, int M, Plan p,
-                                                               int expert_sel, int x2_only, int n_cu,
+                                                               int expert_sel, int x2_only,
                                                                int n_ctiles, WeightView wv_r, WeightView wv_s,
-                                                               uint16_t* __restrict__ hact, int ldh_r, long hact_s, int ldh_s) {
+                                                               uint16_t* __restrict__ hact_r, int ldh_r, long hact_s, int ldh_s) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  int tc;
-  TileInfo ti;
-  if (!block_tile(p, expert_sel, x2_only, n_ctiles, (wv_s.n_chunks + 1) / 2, n_cu, 1, tc, ti)) return;
-  const WeightView wv = ti.sh ? wv_s : wv_r;
-  const int ldh = ti.sh ? ldh_s : ldh_r;
-  hact += ti.sh ? hact_s : 0;
-  if (!storage_index(wv, ti.e, ti.se)) return;
-#define SI_CALL_GU(BMV) gateup_body<BMV>(x, M, p, tc, ti, wv, hact, ldh, lds)
-  SI_PICK_BODY(ti, SI_CALL_GU)
+  const int n_ctiles_s = (wv_s.n_chunks + 1) / 2;
+  const TileQueues tq = tile_queues(p, expert_sel, x2_only, n_ctiles, n_ctiles_s, true);
+  run_items(tq, p.queue, p.queue + N_XCD * QUEUE_STRIDE, lds, [&](int q, int item, auto take) {
+    int tc, half, halves;
+    TileInfo ti;
+    item_tile(tq, p, expert_sel, x2_only, q, item, n_ctiles, tc, ti, half, halves);
+    const WeightView wv = ti.sh ? wv_s : wv_r;
+    const int ldh = ti.sh ? ldh_s : ldh_r;
+    uint16_t* hact = hact_r + (ti.sh ? hact_s : 0);
+    if (!storage_index(wv, ti.e, ti.se)) return take();
+#define SI_CALL_GU(FAV, NJV) gateup_body<Ring<FAV, NJV>>(x, scalar_of_item(M), p, tc, half, ti, wv, hact, ldh, lds, take)
+    if (halves == 2 && ti.row_end - ti.row0 <= CUT_COLUMNS_ROWS) {
+      SI_PICK_HALF_BODY(ti, SI_CALL_GU)
+    } else {
+      if (halves == 2 && !half_rows(ti, half)) return take();
+      SI_PICK_BODY(ti, SI_CALL_GU)
+    }
 #undef SI_CALL_GU
+  });
+}
+
+// inner index of an FC2 tile -> output columns, k-split and its chunks
+struct DownRange { int nt, split, c_begin, c_end; };
+__device__ __forceinline__ DownRange down_range(int inner, int n_ntiles, int n_split, int n_chunks) {
+  DownRange d;
+  int rem;
+  d.split = small_div(inner, n_ntiles, d.nt);
+  d.c_begin = small_div(n_chunks * d.split, n_split, rem);
+  d.c_end = small_div(n_chunks * (d.split + 1), n_split, rem);
+  return d;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -676,82 +871,91 @@ __global__ __launch_bounds__(THREADS, 1) void k_prefill_gateup(const uint16_t* _
 // LDS ([group][256 m] x 16 bytes), read conflict free by consecutive lanes.
 // Output slab `split` of yp: rows x M fp32; overwritten or accumulated.
 // ---------------------------------------------------------------------------------------------
-template <int BM>
-__device__ __forceinline__ void down_body(const uint16_t* __restrict__ hact, int ldh, int M, int inner, const TileInfo& ti,
-                                          int n_ntiles, int n_split, const WeightView& wv, float* __restrict__ yp,
-                                          size_t slab_stride, int accumulate, unsigned char* lds) {
-  using P = PingPong<BM>;
-  const int nt = inner % n_ntiles, split = inner / n_ntiles;
-  const int c_begin = (int)((long)wv.n_chunks * split / n_split), c_end = (int)((long)wv.n_chunks * (split + 1) / n_split);
-  if (c_begin >= c_end && accumulate) return;  // nothing to add
-  const int tid = threadIdx.x, lane = tid % WAVE, w = __builtin_amdgcn_readfirstlane(tid / WAVE);  // wave index, known to be uniform
+template <class P, class Take>
+__device__ __forceinline__ void down_body(const uint16_t* __restrict__ hact, int ldh, int M, const DownRange& dr, int half, const TileInfo& ti,
+                                          const WeightView& wv, float* __restrict__ yp, size_t slab_stride, int accumulate,
+                                          unsigned char* lds, Take take) {
+  const int c_begin = dr.c_begin, c_end = dr.c_end;
+  if (c_begin >= c_end && accumulate) return take();  // nothing to add
+  const int tid = thread_of_item(), lane = tid % WAVE, w = __builtin_amdgcn_readfirstlane(tid / WAVE);  // wave index, known to be uniform
   const int wr = w >> 2, wc = w & 3;
-  const int n0 = nt * BN;
+  const int n0 = dr.nt * BN + (P::NJ == 4 ? 0 : half * P::BNW);
   const uint16_t* ebase = wv.base + (size_t)ti.se * wv.expert_stride;
-  float* out = yp + (size_t)split * slab_stride;
+  float* out = yp + (size_t)dr.split * slab_stride;
 
   const int lrow = lane >> 3, lpp = lane & 7;
   uint32_t a_src[P::ALD];  // byte offsets from hact (the host checks that it spans less than 2^31 elements)
-#pragma unroll
-  for (int i = 0; i < P::ALD; ++i) {
-    const int lr = pp_a_row<BM>(w, i) + lrow;
+  unroll<P::ALD>([&](auto i) {
+    const int lr = ring_a_row<P, i>(w) + lrow;
     int row = ti.row0 + lr;
     row = row < ti.row_end ? row : ti.row_end - 1;
     a_src[i] = ((uint32_t)row * (uint32_t)ldh + wv.col0 + ((lpp ^ ((lr >> 1) & 7)) * 8)) * 2;
-  }
-  // B: wave w loads group q = w of the chunk's down block ([M/NW tiles][8 q][NW m][8 i]), 4 x 64 output columns
+  });
+  // B: wave w loads group q = w of the chunk's down block ([M/NW tiles][8 q][NW m][8 i]), NJ x 64 output columns
   const int NW = ntile_width(M);
   const int nw_shift = __builtin_ctz(NW);
-  uint32_t b_off[4];  // bytes, inside one chunk's down block
+  uint32_t b_off[P::NJ];  // bytes, inside one chunk's down block
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < P::NJ; ++i) {
     const int n = min(n0 + i * 64 + lane, M - 1);
     b_off[i] = (((uint32_t)(n >> nw_shift) * 8 + w) * NW + (n & (NW - 1))) * 16;  // NW is a power of two
   }
 
   if (c_begin < c_end) {
-    auto issue_a = [&](int i, int stage, int kt) {
-      load_lds16(hact + (c_begin + kt) * CHUNK_J, a_src[i], lds + stage * P::STAGE + pp_a_row<BM>(w, i) * 128);
+    auto issue_a = [&](auto i, unsigned char* stage, int kt) {
+      if (!P::half(i) || lane < 32) load_lds16(hact + (c_begin + kt) * CHUNK_J, a_src[i], stage + ring_a_row<P, i>(w) * 128);
     };
-    auto issue_b = [&](int stage, int kt) {
-      unsigned char* sb = lds + stage * P::STAGE + BM * 128 + w * 4096;
+    auto issue_b = [&](unsigned char* stage, int kt) {
+      unsigned char* sb = stage + w * (P::NJ * 1024);
       const uint16_t* dblk = ebase + (size_t)(wv.chunk0 + c_begin + kt) * 3 * CHUNK_J * M + (size_t)2 * CHUNK_J * M;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) load_lds16(dblk, b_off[i], sb + i * 1024);
+      for (int i = 0; i < P::NJ; ++i) load_lds16(dblk, b_off[i], sb + i * 1024);
     };
-    f32x4 acc[P::FA][4];
-    const uint32_t b0 = SI_BOFF_K8(wc * 64 + (lane & 15), lane >> 4);
-    const uint32_t boff[2] = {b0, b0 + 4 * BN * 16};
-    gemm_pingpong<BM, 256>(lds, c_end - c_begin, lane, wr, acc, issue_a, issue_b, boff);
-    down_store<BM>(acc, ti, n0, wr, wc, lane, M, out, accumulate);
+    f32x4 acc[P::FA][P::NJ];
+    const uint32_t b0 = ((lane >> 4) * P::BNW + wc * 16 * P::NJ + (lane & 15)) * 16;
+    const uint32_t boff[2] = {b0, b0 + 4 * P::BNW * 16};
+    gemm_pingpong<P, 256>(lds, c_end - c_begin, lane, wr, acc, issue_a, issue_b, boff);
+    take();
+    down_store<P::FA, P::NJ>(acc, ti, n0 + wc * 16 * P::NJ, wr, lane, M, out, accumulate);
   } else {
     // an empty k-split of an overwriting launch still has to define its slab
-    for (int i = tid; i < BM * BN; i += THREADS) {
-      const int row = ti.row0 + i / BN, m = n0 + i % BN;
+    take();
+    for (int i = tid; i < P::BM * P::BNW; i += THREADS) {
+      const int row = ti.row0 + i / P::BNW, m = n0 + i % P::BNW;
       if (row < ti.row_end && m < M) out[(size_t)row * M + m] = 0.f;
     }
   }
 }
 
-__global__ __launch_bounds__(THREADS, 1) void k_prefill_down(const uint16_t* __restrict__ hact, int ldh_r, int M, Plan p,
-                                                             int expert_sel, int x2_only, int n_cu,
+__global__ __launch_bounds__(THREADS, 1) void k_prefill_down(const uint16_t* __restrict__ hact_r, int ldh_r, int M, Plan p,
+                                                             int expert_sel, int x2_only,
                                                              int n_ntiles, int split_r, WeightView wv_r, WeightView wv_s,
                                                              int ldh_s, long hact_s, int split_s, float* __restrict__ yp,
                                                              size_t slab_stride, int accumulate) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  int inner;
-  TileInfo ti;
-  // (XCD ranges also when every expert has a single row tile: one expert's Hact rows, the A operand, a few MB,
-  // then stay in one L2; dealt round-robin every XCD re-reads every expert's rows for each of its column tiles,
-  // which measured 3 % slower although the XCDs finish together)
-  if (!block_tile(p, expert_sel, x2_only, n_ntiles * split_r, wv_s.n_chunks ? n_ntiles * split_s : 0, n_cu, 0, inner, ti)) return;
-  const WeightView wv = ti.sh ? wv_s : wv_r;
-  const int ldh = ti.sh ? ldh_s : ldh_r, n_split = ti.sh ? split_s : split_r;
-  hact += ti.sh ? hact_s : 0;
-  if (!storage_index(wv, ti.e, ti.se)) return;
-#define SI_CALL_DN(BMV) down_body<BMV>(hact, ldh, M, inner, ti, n_ntiles, n_split, wv, yp, slab_stride, accumulate, lds)
-  SI_PICK_BODY(ti, SI_CALL_DN)
+  const int n_in_r = n_ntiles * split_r, n_in_s = wv_s.n_chunks ? n_ntiles * split_s : 0;
+  // (ids in ranges also when every expert has a single row tile: one expert's Hact rows, the A operand, a few MB,
+  // then stay in one L2; dealt one by one every XCD re-reads every expert's rows for each of its column tiles: 512 tokens over
+  // 8 experts of 14336 columns 540 -> 552 us)
+  const TileQueues tq = tile_queues(p, expert_sel, x2_only, n_in_r, n_in_s, false);
+  run_items(tq, p.queue + N_XCD * QUEUE_STRIDE, p.queue, lds, [&](int q, int item, auto take) {
+    int inner, half, halves;
+    TileInfo ti;
+    item_tile(tq, p, expert_sel, x2_only, q, item, n_in_r, inner, ti, half, halves);
+    const WeightView wv = ti.sh ? wv_s : wv_r;
+    const int ldh = ti.sh ? ldh_s : ldh_r, n_split = ti.sh ? split_s : split_r;
+    const uint16_t* hact = hact_r + (ti.sh ? hact_s : 0);
+    const DownRange dr = down_range(inner, n_ntiles, n_split, wv.n_chunks);
+    if (!storage_index(wv, ti.e, ti.se)) return take();
+#define SI_CALL_DN(FAV, NJV) down_body<Ring<FAV, NJV>>(hact, ldh, scalar_of_item(M), dr, half, ti, wv, yp, slab_stride, accumulate, lds, take)
+    if (halves == 2 && ti.row_end - ti.row0 <= CUT_COLUMNS_ROWS) {
+      SI_PICK_HALF_BODY(ti, SI_CALL_DN)
+    } else {
+      if (halves == 2 && !half_rows(ti, half)) return take();
+      SI_PICK_BODY(ti, SI_CALL_DN)
+    }
 #undef SI_CALL_DN
+  });
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -763,7 +967,7 @@ __device__ __forceinline__ void gateup_body_q4(const uint16_t* __restrict__ x, i
                                                const WeightView& wv, uint16_t* __restrict__ hact, int ldh,
                                                unsigned char* lds) {
   using P = PingPong<BM, 0>;
-  const int tid = threadIdx.x, lane = tid % WAVE, w = __builtin_amdgcn_readfirstlane(tid / WAVE);  // wave index, known to be uniform
+  const int tid = thread_of_item(), lane = tid % WAVE, w = __builtin_amdgcn_readfirstlane(tid / WAVE);  // wave index, known to be uniform
   const int wr = w >> 2, wc = w & 3;
   const unsigned char* ebase = reinterpret_cast<const unsigned char*>(wv.base + (size_t)ti.se * wv.expert_stride);
 
@@ -774,7 +978,7 @@ __device__ __forceinline__ void gateup_body_q4(const uint16_t* __restrict__ x, i
     const int lr = pp_a_row<BM>(w, i) + lrow;
     int row = ti.row0 + lr;
     row = row < ti.row_end ? row : ti.row_end - 1;
-    a_src[i] = ((uint32_t)p.row_token[row] * (uint32_t)M + ((lpp ^ ((lr >> 1) & 7)) * 8)) * 2;
+    a_src[i] = ((uint32_t)(ti.row_t0 >= 0 ? row - ti.row_t0 : p.row_token[row]) * (uint32_t)M + ((lpp ^ ((lr >> 1) & 7)) * 8)) * 2;
   }
   auto issue_a = [&](int i, int stage, int kt) {
     load_lds16(x + kt * BK, a_src[i], lds + stage * P::STAGE + pp_a_row<BM>(w, i) * 128);
@@ -808,39 +1012,43 @@ __device__ __forceinline__ void gateup_body_q4(const uint16_t* __restrict__ x, i
   f32x4 acc[P::FA][4];
   const uint32_t boff[2] = {(uint32_t)swz(wc * 64 + (lane & 15), lane >> 4), (uint32_t)swz(wc * 64 + (lane & 15), 4 + (lane >> 4))};
   gemm_pingpong_q4<BM, 2048>(lds, M / BK, lane, wr, acc, issue_a, bload, bconv, boff);
-  gateup_store<BM>(acc, ti, wv, tc, wr, wc, lane, hact, ldh);
+  gateup_store<P::FA, 4>(acc, ti, wv, 2 * tc + (wc >> 1), tc * 128 + wc * 32, wr, lane, hact, ldh);
 }
 
 __global__ __launch_bounds__(THREADS, 1) void k_prefill_gateup_q4(const uint16_t* __restrict__ x, int M, Plan p,
-                                                                  int expert_sel, int x2_only, int n_cu,
+                                                                  int expert_sel, int x2_only,
                                                                   int n_ctiles, WeightView wv_r, WeightView wv_s,
-                                                                  uint16_t* __restrict__ hact, int ldh_r, long hact_s, int ldh_s) {
+                                                                  uint16_t* __restrict__ hact_r, int ldh_r, long hact_s, int ldh_s) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  int tc;
-  TileInfo ti;
-  if (!block_tile(p, expert_sel, x2_only, n_ctiles, (wv_s.n_chunks + 1) / 2, n_cu, 1, tc, ti)) return;
-  const WeightView wv = ti.sh ? wv_s : wv_r;
-  const int ldh = ti.sh ? ldh_s : ldh_r;
-  hact += ti.sh ? hact_s : 0;
-  if (!storage_index(wv, ti.e, ti.se)) return;
-#define SI_CALL_GU(BMV) gateup_body_q4<BMV>(x, M, p, tc, ti, wv, hact, ldh, lds)
-  SI_PICK_BODY_2PASS(ti, SI_CALL_GU);
+  const int n_ctiles_s = (wv_s.n_chunks + 1) / 2;
+  const TileQueues tq = tile_queues(p, expert_sel, x2_only, n_ctiles, n_ctiles_s, true);
+  run_items(tq, p.queue, p.queue + N_XCD * QUEUE_STRIDE, lds, [&](int q, int item, auto take) {
+    int tc, half, halves;
+    TileInfo ti;
+    item_tile(tq, p, expert_sel, x2_only, q, item, n_ctiles, tc, ti, half, halves);
+    const WeightView wv = ti.sh ? wv_s : wv_r;
+    const int ldh = ti.sh ? ldh_s : ldh_r;
+    uint16_t* hact = hact_r + (ti.sh ? hact_s : 0);
+    if (!storage_index(wv, ti.e, ti.se) || (halves == 2 && !half_rows(ti, half))) return take();
+#define SI_CALL_GU(BMV) gateup_body_q4<BMV>(x, scalar_of_item(M), p, tc, ti, wv, hact, ldh, lds)
+    SI_PICK_BODY_2PASS(ti, SI_CALL_GU);
 #undef SI_CALL_GU
+    take();
+  });
 }
 
 template <int BM>
-__device__ __forceinline__ void down_body_q4(const uint16_t* __restrict__ hact, int ldh, int M, int inner, const TileInfo& ti,
-                                             int n_ntiles, int n_split, const WeightView& wv, float* __restrict__ yp,
-                                             size_t slab_stride, int accumulate, unsigned char* lds) {
+__device__ __forceinline__ void down_body_q4(const uint16_t* __restrict__ hact, int ldh, int M, const DownRange& dr, const TileInfo& ti,
+                                             const WeightView& wv, float* __restrict__ yp, size_t slab_stride, int accumulate,
+                                             unsigned char* lds) {
   using P = PingPong<BM, 0>;
-  const int nt = inner % n_ntiles, split = inner / n_ntiles;
-  const int c_begin = (int)((long)wv.n_chunks * split / n_split), c_end = (int)((long)wv.n_chunks * (split + 1) / n_split);
+  const int c_begin = dr.c_begin, c_end = dr.c_end;
   if (c_begin >= c_end && accumulate) return;
-  const int tid = threadIdx.x, lane = tid % WAVE, w = __builtin_amdgcn_readfirstlane(tid / WAVE);  // wave index, known to be uniform
+  const int tid = thread_of_item(), lane = tid % WAVE, w = __builtin_amdgcn_readfirstlane(tid / WAVE);  // wave index, known to be uniform
   const int wr = w >> 2, wc = w & 3;
-  const int n0 = nt * BN;
+  const int n0 = dr.nt * BN;
   const unsigned char* ebase = reinterpret_cast<const unsigned char*>(wv.base + (size_t)ti.se * wv.expert_stride);
-  float* out = yp + (size_t)split * slab_stride;
+  float* out = yp + (size_t)dr.split * slab_stride;
 
   const int lrow = lane >> 3, lpp = lane & 7;
   uint32_t a_src[P::ALD];  // byte offsets from hact
@@ -883,7 +1091,7 @@ __device__ __forceinline__ void down_body_q4(const uint16_t* __restrict__ hact, 
     const uint32_t b0 = SI_BOFF_K8(wc * 64 + (lane & 15), lane >> 4);
     const uint32_t boff[2] = {b0, b0 + 4 * BN * 16};
     gemm_pingpong_q4<BM, 256>(lds, c_end - c_begin, lane, wr, acc, issue_a, bload, bconv, boff);
-    down_store<BM>(acc, ti, n0, wr, wc, lane, M, out, accumulate);
+    down_store<P::FA, 4>(acc, ti, n0 + wc * 64, wr, lane, M, out, accumulate);
   } else {
     for (int i = tid; i < BM * BN; i += THREADS) {
       const int row = ti.row0 + i / BN, m = n0 + i % BN;
@@ -892,22 +1100,28 @@ __device__ __forceinline__ void down_body_q4(const uint16_t* __restrict__ hact, 
   }
 }
 
-__global__ __launch_bounds__(THREADS, 1) void k_prefill_down_q4(const uint16_t* __restrict__ hact, int ldh_r, int M, Plan p,
-                                                                int expert_sel, int x2_only, int n_cu,
+__global__ __launch_bounds__(THREADS, 1) void k_prefill_down_q4(const uint16_t* __restrict__ hact_r, int ldh_r, int M, Plan p,
+                                                                int expert_sel, int x2_only,
                                                                 int n_ntiles, int split_r, WeightView wv_r, WeightView wv_s,
                                                                 int ldh_s, long hact_s, int split_s, float* __restrict__ yp,
                                                                 size_t slab_stride, int accumulate) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  int inner;
-  TileInfo ti;
-  if (!block_tile(p, expert_sel, x2_only, n_ntiles * split_r, wv_s.n_chunks ? n_ntiles * split_s : 0, n_cu, 0, inner, ti)) return;
-  const WeightView wv = ti.sh ? wv_s : wv_r;
-  const int ldh = ti.sh ? ldh_s : ldh_r, n_split = ti.sh ? split_s : split_r;
-  hact += ti.sh ? hact_s : 0;
-  if (!storage_index(wv, ti.e, ti.se)) return;
-#define SI_CALL_DN(BMV) down_body_q4<BMV>(hact, ldh, M, inner, ti, n_ntiles, n_split, wv, yp, slab_stride, accumulate, lds)
-  SI_PICK_BODY_2PASS(ti, SI_CALL_DN);
+  const int n_in_r = n_ntiles * split_r, n_in_s = wv_s.n_chunks ? n_ntiles * split_s : 0;
+  const TileQueues tq = tile_queues(p, expert_sel, x2_only, n_in_r, n_in_s, false);
+  run_items(tq, p.queue + N_XCD * QUEUE_STRIDE, p.queue, lds, [&](int q, int item, auto take) {
+    int inner, half, halves;
+    TileInfo ti;
+    item_tile(tq, p, expert_sel, x2_only, q, item, n_in_r, inner, ti, half, halves);
+    const WeightView wv = ti.sh ? wv_s : wv_r;
+    const int ldh = ti.sh ? ldh_s : ldh_r, n_split = ti.sh ? split_s : split_r;
+    const uint16_t* hact = hact_r + (ti.sh ? hact_s : 0);
+    const DownRange dr = down_range(inner, n_ntiles, n_split, wv.n_chunks);
+    if (!storage_index(wv, ti.e, ti.se) || (halves == 2 && !half_rows(ti, half))) return take();
+#define SI_CALL_DN(BMV) down_body_q4<BMV>(hact, ldh, scalar_of_item(M), dr, ti, wv, yp, slab_stride, accumulate, lds)
+    SI_PICK_BODY_2PASS(ti, SI_CALL_DN);
 #undef SI_CALL_DN
+    take();
+  });
 }
 
 __global__ __launch_bounds__(256) void k_prefill_combine(const float* __restrict__ yp, size_t slab_stride, int n_split, int split_s,
@@ -952,27 +1166,12 @@ __global__ void k_fill_zero(float* __restrict__ p, size_t n, size_t slab_stride)
 
 }  // namespace
 
-// compute units of the current device (a round of the tail split)
-static int cu_count() {
-  static int n = [] {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0)
-      v = 256;
-    return v;
-  }();
-  return n;
-}
-
-// grid of a launch over at most n_tiles logical ids: room for the XCD ranges (rounded up to 8) and for the
-// second blocks of a split tail (at most half a round)
-static int grid_blocks(int n_tiles) { return (n_tiles + 7) / 8 * 8 + 8 + cu_count() / 2 + 8; }
-
 static hipError_t ensure_lds_attr() {
   static hipError_t st = [] {
     const void* kernels[] = {(const void*)k_prefill_gateup, (const void*)k_prefill_down, (const void*)k_prefill_gateup_q4,
                              (const void*)k_prefill_down_q4};
     for (const void* k : kernels) {
-      hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, KERNEL_LDS);
+      hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, KERNEL_LDS + NEXT_LDS);
       if (e != hipSuccess) return e;
       // The main loops count their own vector-memory operations (wait_vmcnt<N> against PingPong<>::younger): a
       // register spill would add scratch loads and stores to that count and let a barrier pass before a tile has
@@ -994,13 +1193,12 @@ hipError_t launch_prefill_gateup(const uint16_t* x, int M, const Plan& plan, int
   hipError_t e = ensure_lds_attr();
   if (e != hipSuccess) return e;
   const int n_ctiles = (wv.n_chunks + 1) / 2;
-  const int total = grid_blocks(n_row_tiles * n_ctiles) + (sp.row_tiles * ((sp.wv.n_chunks + 1) / 2) + 7) / 8 * 8;
   if (wv.q4)
-    hipLaunchKernelGGL(k_prefill_gateup_q4, dim3(total), dim3(THREADS), KERNEL_LDS, stream, x, M, plan, expert_sel, x2_only,
-                       cu_count(), n_ctiles, wv, sp.wv, hact, ldh, sp.hact, sp.ldh);
+    hipLaunchKernelGGL(k_prefill_gateup_q4, dim3(N_XCD * XCD_CU), dim3(THREADS), KERNEL_LDS + NEXT_LDS, stream, x, M, plan, expert_sel, x2_only,
+                       n_ctiles, wv, sp.wv, hact, ldh, sp.hact, sp.ldh);
   else
-    hipLaunchKernelGGL(k_prefill_gateup, dim3(total), dim3(THREADS), KERNEL_LDS, stream, x, M, plan, expert_sel, x2_only,
-                       cu_count(), n_ctiles, wv, sp.wv, hact, ldh, sp.hact, sp.ldh);
+    hipLaunchKernelGGL(k_prefill_gateup, dim3(N_XCD * XCD_CU), dim3(THREADS), KERNEL_LDS + NEXT_LDS, stream, x, M, plan, expert_sel, x2_only,
+                       n_ctiles, wv, sp.wv, hact, ldh, sp.hact, sp.ldh);
   return hipGetLastError();
 }
 
@@ -1011,13 +1209,12 @@ hipError_t launch_prefill_down(const uint16_t* hact, int ldh, int M, const Plan&
   hipError_t e = ensure_lds_attr();
   if (e != hipSuccess) return e;
   const int n_ntiles = (M + BN - 1) / BN;
-  const int total = grid_blocks(n_row_tiles * n_ntiles * n_split) + (sp.wv.n_chunks ? (sp.row_tiles * n_ntiles * sp.split + 7) / 8 * 8 : 0);
   if (wv.q4)
-    hipLaunchKernelGGL(k_prefill_down_q4, dim3(total), dim3(THREADS), KERNEL_LDS, stream, hact, ldh, M, plan, expert_sel,
-                       x2_only, cu_count(), n_ntiles, n_split, wv, sp.wv, sp.ldh, sp.hact, sp.split, yp, slab_stride, accumulate);
+    hipLaunchKernelGGL(k_prefill_down_q4, dim3(N_XCD * XCD_CU), dim3(THREADS), KERNEL_LDS + NEXT_LDS, stream, hact, ldh, M, plan, expert_sel,
+                       x2_only, n_ntiles, n_split, wv, sp.wv, sp.ldh, sp.hact, sp.split, yp, slab_stride, accumulate);
   else
-    hipLaunchKernelGGL(k_prefill_down, dim3(total), dim3(THREADS), KERNEL_LDS, stream, hact, ldh, M, plan, expert_sel,
-                       x2_only, cu_count(), n_ntiles, n_split, wv, sp.wv, sp.ldh, sp.hact, sp.split, yp, slab_stride, accumulate);
+    hipLaunchKernelGGL(k_prefill_down, dim3(N_XCD * XCD_CU), dim3(THREADS), KERNEL_LDS + NEXT_LDS, stream, hact, ldh, M, plan, expert_sel,
+                       x2_only, n_ntiles, n_split, wv, sp.wv, sp.ldh, sp.hact, sp.split, yp, slab_stride, accumulate);
   return hipGetLastError();
 }
 

@@ -35,7 +35,7 @@ struct AssignLds {
   int tot1[MAX_EXPERTS + 2];    // of those, pairs of X1 tokens
   int base[MAX_EXPERTS + 2];    // pairs before this block's, then before the current pass
   int off[MAX_EXPERTS + 3];     // exclusive prefix of tot
-  int tile[2][MAX_EXPERTS + 3]; // exclusive prefixes of the row tiles (all rows, X2 rows)
+  int tile[4][MAX_EXPERTS + 3]; // exclusive prefixes over the routed experts: spill tiles, other row tiles; the same of the X2 rows
   int touch[MAX_EXPERTS + 3];   // exclusive prefix of "has pairs"
   int multi[2];                 // some routed expert has more than one row tile
   int wcnt[ROUTE_WAVES][MAX_EXPERTS];
@@ -92,20 +92,16 @@ __device__ __forceinline__ void assign_body(AssignLds& s, int T, int E, int k, i
   __syncthreads();
   if (wv == 0) wave_scan(EX, lane, s.off, [&](int e) { return s.tot[e]; });
   if (first_block) {
-    if (wv == 1) wave_scan(EX, lane, s.tile[0], [&](int e) {
-      const int n = n_row_tiles(s.tot[e]);
-      if (n > 1 && e < E) s.multi[0] = 1;
-      return n;
+    if (wv < 4) wave_scan(E, lane, s.tile[wv], [&](int e) {
+      const int rows = s.tot[e] - (wv >= 2 ? s.tot1[e] : 0), n = n_row_tiles(rows), spill = has_spill_tile(rows);
+      if (n > 1) s.multi[wv / 2] = 1;
+      return wv % 2 ? n - spill : spill;
     });
-    if (wv == 2) wave_scan(EX, lane, s.tile[1], [&](int e) {
-      const int n = n_row_tiles(s.tot[e] - s.tot1[e]);
-      if (n > 1 && e < E) s.multi[1] = 1;
-      return n;
-    });
-    if (wv == 3) wave_scan(EX, lane, s.touch, [&](int e) { return s.tot[e] > 0 ? 1 : 0; });
+    if (wv == 4) wave_scan(EX, lane, s.touch, [&](int e) { return s.tot[e] > 0 ? 1 : 0; });
   }
   __syncthreads();
   if (first_block) {
+    if (p.queue && tid < 2 * 8) p.queue[tid * QUEUE_STRIDE] = 0;
     for (int e = tid; e < EX; e += ROUTE_THREADS) {
       if (p.count) p.count[e] = s.tot[e];
       if (p.count1) p.count1[e] = s.tot1[e];
@@ -115,23 +111,29 @@ __device__ __forceinline__ void assign_body(AssignLds& s, int T, int E, int k, i
         if (u.count) u.count[e] = s.tot[e];
         if (u.off) u.off[e] = s.off[e];
       }
-      if (p.tile_e) {
-        int n0 = s.tile[0][e + 1] - s.tile[0][e];
-        for (int r = 0; r < n0; ++r) { p.tile_e[s.tile[0][e] + r] = e; p.tile_r[s.tile[0][e] + r] = r; }
-      }
-      if (p.tile_e_x2) {
-        int n1 = s.tile[1][e + 1] - s.tile[1][e];
-        for (int r = 0; r < n1; ++r) { p.tile_e_x2[s.tile[1][e] + r] = e; p.tile_r_x2[s.tile[1][e] + r] = r; }
-      }
     }
+    if (p.tile_e)
+      for (int i = tid; i < 4 * E; i += ROUTE_THREADS) {
+        const int l = i / E, e = i % E, n = s.tile[l][e + 1] - s.tile[l][e];
+        const int pos = s.tile[l][e] + (l % 2 ? s.tile[l - 1][E] : 0);            // the spill tiles are listed first
+        const int r0 = l % 2 ? 0 : s.tile[l + 1][e + 1] - s.tile[l + 1][e];        // ... and each is the last of its expert
+        int32_t *te = l < 2 ? p.tile_e : p.tile_e_x2, *tr = l < 2 ? p.tile_r : p.tile_r_x2;
+        for (int r = 0; r < n; ++r) {
+          te[pos + r] = e + n * (TILE_E_MASK + 1);
+          tr[pos + r] = r0 + r;
+        }
+        if (e == 0 && l % 2) {
+          // (of the routed experts only: the shared one, entry E, is found through its offset)
+          int32_t* nt = p.n_tiles + (l < 2 ? 0 : 3);
+          nt[0] = s.tile[l - 1][E] + s.tile[l][E];
+          nt[1] = s.tile[l - 1][E];
+          nt[2] = !s.multi[l / 2];
+        }
+      }
     if (tid == 0) {
       if (p.off) p.off[EX] = s.off[EX];
       if (u.off) u.off[E] = s.off[E];
       if (p.n_touched) *p.n_touched = s.touch[EX];
-      // the tiles of the routed experts only (the shared expert, entry E, is found through its offset)
-      if (p.n_tiles) *p.n_tiles = s.tile[0][E];
-      if (p.n_tiles_x2) *p.n_tiles_x2 = s.tile[1][E];
-      if (p.tile_flags) *p.tile_flags = (s.multi[0] ? 0 : 1) | (s.multi[1] ? 0 : 2);
     }
   }
   // stable positions: pairs in ascending q, ROUTE_THREADS at a time
@@ -185,6 +187,7 @@ __global__ __launch_bounds__(ROUTE_THREADS) void k_assign(int T, int E, int k, i
 // A dense layer (one expert, weight 1): every table is known without looking at anything.
 __global__ __launch_bounds__(256) void k_dense_assign(int T, int n_x1, Plan p, RouteOut u) {
   const int t = blockIdx.x * 256 + threadIdx.x;
+  if (p.queue && t < 2 * 8) p.queue[t * QUEUE_STRIDE] = 0;
   if (t < T) {
     p.idx[t] = 0; p.w[t] = 1.f;
     if (p.perm) p.perm[t] = t;
@@ -195,18 +198,12 @@ __global__ __launch_bounds__(256) void k_dense_assign(int T, int n_x1, Plan p, R
     if (u.perm) u.perm[t] = t;
     if (u.inv) u.inv[t] = t;
   }
-  const int nt = n_row_tiles(T), nt2 = n_row_tiles(T - n_x1);
-  if (p.tile_e && t < nt) { p.tile_e[t] = 0; p.tile_r[t] = t; }
-  if (p.tile_e_x2 && t < nt2) { p.tile_e_x2[t] = 0; p.tile_r_x2[t] = t; }
   if (t == 0) {
     if (p.count) p.count[0] = T;
     if (p.count1) p.count1[0] = n_x1;
     if (p.off) { p.off[0] = 0; p.off[1] = T; }
     if (p.touched) p.touched[0] = 0;
     if (p.n_touched) *p.n_touched = 1;
-    if (p.n_tiles) *p.n_tiles = nt;
-    if (p.n_tiles_x2) *p.n_tiles_x2 = nt2;
-    if (p.tile_flags) *p.tile_flags = (nt <= 1 ? 1 : 0) | (nt2 <= 1 ? 2 : 0);
     if (u.count) u.count[0] = T;
     if (u.off) { u.off[0] = 0; u.off[1] = T; }
   }

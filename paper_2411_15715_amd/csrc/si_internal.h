@@ -19,11 +19,12 @@ constexpr int MAX_EXPERTS = 256;      // routed experts (a shared expert adds on
 constexpr int ROUTE_THREADS = 1024;   // block size of the assignment kernel
 constexpr int TILE_ROWS = 256;        // rows per row tile of the prefill GEMMs (the last tile of an expert: see n_row_tiles)
 constexpr int MAX_KSPLIT = 4;         // k-splits (output slabs) of the prefill down projection
+constexpr int QUEUE_STRIDE = 32;      // integers between the counters of the tile queues (128 bytes)
 constexpr int DOWN_SLOTS = 32;        // j-splits of the decode down projection per part
 
 // Row tiles of an expert (or of its X2 rows) with `rows` rows.  The GEMM kernels run, per tile, the body
-// instantiated for the rows the tile really has (64, 128, 192, 256 or 320): a block streams its weight tile whatever
-// the number of rows, so an expert with 140 rows gets one 192-row block, not two blocks of 128.
+// instantiated for the rows the tile really has (a multiple of 32): a block streams its weight tile whatever
+// the number of rows, so an expert with 140 rows gets one 160-row block, not two blocks.
 // A tile costs nearly the same whether it holds 10 rows or 256 (it streams the same weights, and its ring of LDS
 // stages is latency bound when the rows are few: measured, 128 extra tiles of 5 rows cost a 2048-tile GEMM as much
 // as 128 extra tiles of 256), so a remainder of at most TILE_ROWS_SPILL rows rides with the last full tile instead
@@ -33,6 +34,9 @@ constexpr int TILE_ROWS_SPILL = 64;  // the last tile of an expert also takes up
 inline SI_HD int n_row_tiles(int rows) {
   return rows <= 0 ? 0 : rows <= TILE_ROWS ? 1 : (rows - TILE_ROWS_SPILL + TILE_ROWS - 1) / TILE_ROWS;
 }
+// the last of them has more than TILE_ROWS rows
+inline SI_HD int has_spill_tile(int rows) { return rows > n_row_tiles(rows) * TILE_ROWS ? 1 : 0; }
+constexpr int TILE_E_MASK = 511;  // tile_e: expert in the low bits, tiles of the group above
 
 // Device-side result of the token assignment plus the launch tables derived from it.
 // Expert tables have EX = E + (shared ? 1 : 0) entries; the shared expert is entry E and owns the
@@ -48,13 +52,14 @@ struct Plan {
   int32_t* row_token;  // [T*k + T] token of each expert-sorted row
   int32_t* touched;    // [EX] experts with count > 0, ascending
   int32_t* n_touched;  // [1]
-  int32_t* tile_e;     // [max_tiles] expert of each row tile (all rows)
-  int32_t* tile_r;     // [max_tiles] index of the tile inside its expert
-  int32_t* n_tiles;    // [1] row tiles of the routed experts (the shared expert's follow in the table)
+  // Row tiles of the routed experts (all rows): the spill tiles, then the others, either by expert.  The tiles of an expert in
+  // one of the two are a group: expert | tiles of the group * 512, and the index of the tile in its expert
+  int32_t* tile_e;     // [max_tiles]
+  int32_t* tile_r;
+  int32_t* n_tiles;    // [6] row tiles, of those spill tiles, no routed expert has more than one; the same for the X2 rows
   int32_t* tile_e_x2;  // the same for the X2 rows only (CG')
   int32_t* tile_r_x2;
-  int32_t* n_tiles_x2;  // [1]
-  int32_t* tile_flags;  // [1] bit 0: no routed expert has more than one row tile; bit 1: the same for the X2 rows
+  int32_t* queue;      // [2][8 * QUEUE_STRIDE] tiles taken per XCD by the running FC1 launch / FC2 launch of the prompt phase
   int32_t n_routed;    // E: the tables of a launch over "all experts" cover entries < n_routed only (the shared expert's
                        // weights live in their own buffer: a view of their own in the same launch, or one of its own)
 };
