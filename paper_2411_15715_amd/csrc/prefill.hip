@@ -24,6 +24,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 #define SI_LPTR(p) ((void __attribute__((address_space(3)))*)(p))
 
@@ -32,7 +33,7 @@ constexpr int THREADS = 512;
 constexpr int BN = 256;  // B rows per tile: 128 hidden columns (gate+up) or 256 output columns
 constexpr int BK = 64;
 constexpr int B_BYTES = BN * BK * 2;  // 32 KB
-constexpr int KERNEL_LDS = 156 * 1024;  // the largest body
+constexpr int KERNEL_LDS = 160 * 1024 - 16;  // the largest body
 constexpr int NEXT_LDS = 16;            // after it: the block's next item (run_items)
 
 // z / (1 + exp(-z)), the division by one residual step on the reciprocal instruction, whose own error is up to 1 ulp and whose
@@ -270,10 +271,11 @@ __device__ __forceinline__ void run_items(const TileQueues& tq, int32_t* head, i
   }
 }
 
-// the rows of half a tile; false: none (of few rows the first half takes all)
+// the rows of half a tile; false: none (of few rows the first half takes all; 4-bit, dense 7424 x 8128, 114 tokens: cut 141 us,
+// whole 163)
 __device__ __forceinline__ bool half_rows(TileInfo& ti, int half) {
   const int rows = ti.row_end - ti.row0;
-  if (rows <= 128) return half == 0;
+  if (rows <= 64) return half == 0;
   const int hs = ((rows + 1) / 2 + 31) / 32 * 32;
   ti.row0 += half * hs;
   ti.row_end = min(ti.row_end, ti.row0 + hs);
@@ -474,148 +476,165 @@ __device__ __forceinline__ void gemm_pingpong(unsigned char* lds, int nk, int la
   if (!PONG || wr == 0) block_barrier();  // the second group's last slot
 }
 
-// (4-bit bodies)
-template <int BM, int BL = 4> struct PingPong {  // BL: direct-to-LDS loads of B per wave and k-tile (0: B travels through registers)
-  static constexpr int NST = BM >= 192 ? 2 : 3;     // LDS stages
-  static constexpr int STAGE = BM * 128 + B_BYTES;  // bytes per stage
-  static constexpr int LDS = NST * STAGE;           // 120, 144, 112, 128, 144 KB for BM = 64, 128, 192, 256, 320
-  static constexpr int FA = BM / 32;                // A fragments (16 rows each) per wave
-  static constexpr int ALD = BM / 64;               // A load instructions (8 rows each) per wave and k-tile
-  static constexpr int NP = (ALD + 1) / 2;          // phases per k-tile
-  static constexpr int LPW = ALD + BL;              // direct-to-LDS load instructions per wave and k-tile
-  static constexpr int aloads(int p) { return ALD - 2 * p < 2 ? ALD - 2 * p : 2; }
-  static constexpr int loads(int p) { return aloads(p) + (p == 0 ? BL : 0); }
-  // loads of a wave that may still be in flight when the data of the phase after phase q of tile `it` must have landed:
-  // those issued later than it, in the order (tile, phase region), when `rem` tiles follow tile `it`
-  static constexpr int younger(int q, int rem) {
-    int n = 0;
-    if (q < NP - 1) {
-      for (int p = q + 2; p < NP; ++p) n += loads(p);
-      for (int t = 1; t < NST && t <= rem; ++t) n += LPW;
-    } else {
-      if (rem >= 1) for (int p = 1; p < NP; ++p) n += loads(p);
-      for (int t = 2; t < NST && t <= rem; ++t) n += LPW;
+// ---------------------------------------------------------------------------------------------
+// The same loop for weights in the 4-bit storage form.  The codes of a B tile and their scales travel to LDS by direct loads
+// like A, NQ tiles ahead, every wave its own 1/8 (lane: 16 bytes of codes, i.e. 32 weights of one row or column, and the
+// aligned word that holds their scale).  A wave reads them back into registers and writes them as bf16((code - 8) * scale)
+// into the B stage that both groups have just read, the stage of tile it + 2: the conversion is vector work in the slots of the
+// matrix instructions, 2 between each two of them, so that the memory slots are those of the bf16 loop.  (Before, codes
+// came in registers by inline loads and were converted in the memory slots; 777 tokens over 8 experts of 14336: 668 -> 605 us;
+// dense 4096 x 28672, 32 / 128 / 192 / 256 / 1024 tokens: 164 / 215 / 246 / 264 / 695 -> 143 / 192 / 215 / 236 / 644, of that the
+// vector work of the conversion about a tenth; with bf16 weights 243 / 569 for the last two.)
+// Two phases (more than 128 rows): pieces 0 and 1 of tile it + 2 in the last slot of tile it, 2 and 3 in the first of it + 1; one
+// phase: all four after the barrier.  A k-tile of 64 is one scale group of either projection.
+// ---------------------------------------------------------------------------------------------
+template <int FAV> struct RingQ {
+  static constexpr int FA = FAV;
+  static constexpr int NJ = 4;
+  static constexpr int BM = 32 * FA;
+  static constexpr int NP = FA <= 4 ? 1 : 2;
+  static constexpr int NA = FA <= 4 ? 3 : 2;                // LDS stages of A
+  static constexpr int NB = 2;                              // of converted B
+  static constexpr int NQ = 3;                              // of codes
+  static constexpr int AHEAD = NQ + 2;                      // codes of tile it + AHEAD replace those of tile it + 2
+  static constexpr int A_STAGE = BM * 128;
+  static constexpr int Q_WAVE = 1024 + 256;                 // codes and scales of a wave
+  static constexpr int Q_STAGE = 8 * Q_WAVE;
+  static constexpr int B_OFF = NA * A_STAGE, Q_OFF = B_OFF + NB * B_BYTES;
+  static constexpr int LDS = Q_OFF + NQ * Q_STAGE;
+  static constexpr int R = AHEAD;
+  static constexpr int frags(int p) { return NP == 1 ? FA : p == 0 ? (FA + 1) / 2 : FA / 2; }
+  static constexpr int frag0(int p) { return p == 0 ? 0 : frag0(p - 1) + frags(p - 1); }
+  static constexpr int aloads(int p) { return (frags(p) + 1) / 2; }
+  static constexpr int aload0(int p) { return p == 0 ? 0 : aload0(p - 1) + aloads(p - 1); }
+  static constexpr int ALD = aload0(NP - 1) + aloads(NP - 1);
+  static constexpr int phase_of(int i) { int p = 0; while (i >= aload0(p) + aloads(p)) ++p; return p; }
+  static constexpr bool half(int i) { return frags(phase_of(i)) % 2 == 1 && i == aload0(phase_of(i)) + aloads(phase_of(i)) - 1; }
+  // as Ring::younger_at; needed after phase q: the A rows of the next phase, and the codes where that phase reads them.  The
+  // codes' loads of a phase are issued after its wait.
+  static constexpr int younger_at(int it, int q, int rem) {
+    const int nk = it + 1 + rem, steps = it * NP + q;
+    int pos = 0, last = 0;
+    bool any = false;
+    const int next_it = q < NP - 1 ? it : it + 1, next_q = q < NP - 1 ? q + 1 : 0;
+    auto codes = [&](int t) { if (t < nk) { pos += 2; if (next_q == NP - 1 && t == next_it + 2) { last = pos; any = true; } } };
+    auto a = [&](int t, int p) { if (t < nk) { pos += aloads(p); if (t == next_it && p == next_q) { last = pos; any = true; } } };
+    for (int t = 0; t < NQ; ++t) codes(t);
+    for (int t = 0; t < NA; ++t)
+      for (int p = 0; p < NP; ++p) a(t, p);
+    for (int t = NQ; t < AHEAD; ++t) codes(t);
+    for (int s = 0; s <= steps; ++s) {
+      const int t = s / NP, p = s % NP;
+      if (p == 0) { if (t > 0) a(t - 1 + NA, NP - 1); }
+      else a(t + NA, p - 1);
+      if (p == NP - 1 && s < steps) codes(t + AHEAD);
     }
-    if (rem >= NST) for (int p = 0; p < q; ++p) n += loads(p);
+    return any ? pos - last : pos;
+  }
+  static constexpr int younger(int q, int rem) {
+    int n = 63;
+    for (int it = 0; it < 2 * R + 2; ++it) { const int y = younger_at(it, q, rem); n = y < n ? y : n; }
     return n;
   }
-  static_assert(LDS <= KERNEL_LDS && (NST + 1) * LPW < 64, "ring does not fit");
+  static_assert(LDS <= KERNEL_LDS, "ring does not fit");
 };
-
-// first LDS row of the 8 rows that wave w's i-th A load of a k-tile fills (region p = i / 2 of both row groups)
-template <int BM> __device__ inline int pp_a_row(int w, int i) {
-  using P = PingPong<BM>;
-  const int p = i >> 1;
-  if (P::ALD - 2 * p >= 2) {
-    const int u = w * 2 + (i & 1);
-    return (u >> 3) * (BM / 2) + p * 64 + (u & 7) * 8;
-  }
-  return (w >> 2) * (BM / 2) + p * 64 + (w & 3) * 8;
-}
-
-// P: PingPong; X: register loads of B that are younger than what is waited for as well
-template <int R, class P, int Q, int X> __device__ __forceinline__ void pp_wait(int rem) {
-  if constexpr (R == 0) {
-    wait_vmcnt<P::younger(Q, 0) + X>();
-  } else {
-    if (rem >= R) wait_vmcnt<P::younger(Q, R) + X>();
-    else pp_wait<R - 1, P, Q, X>(rem);
-  }
-}
-
-// register loads and the dependency tie used by the loops whose B operand travels through registers
-__device__ inline void gload_b128(u32x4& q, const void* p) {
-  asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(q) : "v"(p) : "memory");
-}
-__device__ inline void gload_u16(uint32_t& z, const void* p) {
-  asm volatile("global_load_ushort %0, %1, off" : "=v"(z) : "v"(p) : "memory");
-}
-
-struct Q4Regs { u32x4 q; uint32_t z; };  // codes and scale of one lane's share of a B tile
-constexpr int Q4_GL = 2;                 // register loads of a Q4Regs
 
 // 16-byte LDS store the compiler does not see as one: with a direct-to-LDS load in flight it would otherwise wait
 // for ALL vector-memory operations (vmcnt(0)) before any LDS store it cannot prove disjoint from the load's
 // target, which would drain the ring every iteration.  Disjointness is by construction here (the stage written is
-// not the target of any load in flight), and completion is covered by the loop's own lgkmcnt(0) before each barrier.
+// not the target of any load), and completion is covered by the loop's own lgkmcnt(0) before each barrier.
 __device__ inline void lds_store_b128(unsigned char* p, const u32x4& v) {
   const uint32_t a = (uint32_t)(uintptr_t)SI_LPTR(p);
   asm volatile("ds_write_b128 %0, %1" ::"v"(a), "v"(v) : "memory");
 }
 
-// Eight 4-bit codes (as two words of four byte-sized codes each: `lo` holds elements a0 a1 a2 a3 in its bytes
-// 0..3 for the byte order given by the caller) -> bf16((code - 8) * scale), exact product, one rounding.
-// s8 = -8 * scale.
-__device__ inline uint32_t q4_pair(uint32_t bytes, int b0, int b1, float sc, float s8) {
-  // (the compiler turns byte extraction + conversion into one v_cvt_f32_ubyteN)
-  const float c0 = (float)((bytes >> (8 * b0)) & 0xffu), c1 = (float)((bytes >> (8 * b1)) & 0xffu);
-  return pack_bf16(__builtin_fmaf(c0, sc, s8), __builtin_fmaf(c1, sc, s8));
+// direct global -> LDS load of 4 bytes per lane
+__device__ inline void load_lds4(const void* base, uint32_t off, unsigned char* l) {
+  typedef const unsigned char __attribute__((address_space(1))) gchar;
+  asm volatile("" : "+s"(base));
+  __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)((gchar*)base + off), SI_LPTR(l), 4, 0, 0);
 }
 
-// The same loop for weights in the 4-bit storage form.  The A operand arrives by direct global->LDS loads as above;
-// the B operand cannot (it has to be turned into bf16 on the way), so every lane fetches 16 bytes of codes (32 weights)
-// and their group scale into registers, and turns them into four 16-byte pieces of bf16((code - 8) * scale) that it
-// writes into the B part of a stage.  A k-tile of 64 is one scale group of either projection.
-// A wave converts B of tile it+1 in the memory slots of tile it, four pieces over its phases, while its partner on the
-// SIMD issues matrix instructions; the registers that frees are refilled in the last phase with tile it+3 (two register
-// sets, the loop unrolled by two, so that no fetched register is copied while its load is in flight).
-// Order of a wave's vector-memory operations, which the wait counts rely on: per phase its A loads, and in the last phase
-// of a tile, after them, the Q4_GL register loads (always issued, tile index clamped).  The register loads are inline
-// assembly and their waits explicit: with direct-to-LDS loads in flight the compiler's own wait before the first use
-// of a loaded register is vmcnt(0), which would drain the ring every iteration; bready ties the registers to the wait.
-//   bload(kt, regs), bconv(stage, regs, i): fetch / convert-and-store piece i
-template <int BM, int BJ, class IA, class BL, class BC>
-__device__ __forceinline__ void gemm_pingpong_q4(unsigned char* lds, int nk, int lane, int wr, f32x4 (&acc)[BM / 32][4],
-                                                 IA issue_a, BL bload, BC bconv, const uint32_t (&boff)[2]) {
-  using P = PingPong<BM, 0>;
-  constexpr int FP = P::ALD >= 2 ? 4 : 2;  // fragments of a phase
-  // Bodies of up to 128 rows: one barrier per k-tile, as in gemm_pingpong; here the conversion makes the memory slot the
-  // longer one up to 128 rows (12 experts of 3200 columns, d_model 5632, top-6, 62 tokens: 326 -> 268 us; dense
-  // 5376 x 1472, 89 tokens: 118 -> 112; the 192- and 256-row bodies keep the two groups).
-  constexpr bool PONG = BM > 128;
-  bf16x8 fa[FP][2], fb[4][2];
-  const uint32_t aoff[2] = {(uint32_t)swz(wr * (BM / 2) + (lane & 15), lane >> 4), (uint32_t)swz(wr * (BM / 2) + (lane & 15), 4 + (lane >> 4))};
-  auto bready = [](Q4Regs& r) { asm volatile("" : "+v"(r.q), "+v"(r.z)::"memory"); };
-  auto issue = [&](auto pc, int stage, int kt) {
-    constexpr int p = decltype(pc)::value;
+// The 8 codes of a word as (c - 8) * scale in fp32, exact (scales below 2^117): f[2i], f[2i + 1] of nibbles i, i + 4.  A nibble
+// inserted into 0x6400 is the fp16 value 1024 + c at bit 0 and 1024 + 16 c at bit 4, which one mixed multiply-add turns into
+// the product: 13 instructions and 4 for the rounding to bf16 (21 with c - 8 formed first, 617 against 605 us for 777 tokens
+// over 8 experts of 14336; 23 by byte conversions).
+struct ScaledCodes {
+  uint32_t lo = 0x000F000Fu, hi = 0x00F000F0u, magic = 0x64006400u;
+  __device__ __forceinline__ void hide() { asm volatile("" : "+v"(lo), "+v"(hi), "+s"(magic)); }  // (one and-or instruction each)
+  __device__ __forceinline__ void operator()(uint32_t w, float s, float (&f)[8]) const {
+    const float s16 = s * 0.0625f, c1 = s * -1032.f, c2 = s * -72.f;
+    const uint32_t w8 = w >> 8;
+    const f16x2 a = __builtin_bit_cast(f16x2, (w & lo) | magic), b = __builtin_bit_cast(f16x2, (w & hi) | magic);
+    const f16x2 c = __builtin_bit_cast(f16x2, (w8 & lo) | magic), d = __builtin_bit_cast(f16x2, (w8 & hi) | magic);
 #pragma unroll
-    for (int i = 0; i < P::aloads(p); ++i) issue_a(2 * p + i, stage, kt);
+    for (int h = 0; h < 2; ++h) {
+      f[h] = __builtin_fmaf((float)a[h], s, c1);
+      f[2 + h] = __builtin_fmaf((float)b[h], s16, c2);
+      f[4 + h] = __builtin_fmaf((float)c[h], s, c1);
+      f[6 + h] = __builtin_fmaf((float)d[h], s16, c2);
+    }
+  }
+};
+
+//   issue_a as above;  issue_q(slot, kt): the two loads of the wave's codes and scales;  scale(word, kt): the lane's scale;
+//   conv(stage, codes word, scale, i): convert and store piece i
+template <class P, int BJ, class IA, class IQ, class SC, class CV>
+__device__ __forceinline__ void gemm_pingpong_q4(unsigned char* lds, int nk, int w, int lane, int wr, f32x4 (&acc)[P::FA][4],
+                                                 IA issue_a, IQ issue_q, SC scale, CV conv, const uint32_t (&boff)[2]) {
+  constexpr int FP = P::frags(0);
+  constexpr bool PONG = P::NP > 1;
+  bf16x8 fa[FP][2], fb[4][2];
+  const uint32_t aoff[2] = {(uint32_t)swz(wr * 16 * P::FA + (lane & 15), lane >> 4), (uint32_t)swz(wr * 16 * P::FA + (lane & 15), 4 + (lane >> 4))};
+  auto b_stage = [&](int stage) { return lds + P::B_OFF + stage * B_BYTES; };
+  auto q_slot = [&](int slot) { return lds + P::Q_OFF + slot * P::Q_STAGE + w * P::Q_WAVE; };
+  auto issue_region = [&](auto pc, int stage, int kt) {
+    constexpr int p = decltype(pc)::value;
+    unroll<P::aloads(p)>([&](auto i) { issue_a(std::integral_constant<int, P::aload0(p) + decltype(i)::value>{}, lds + stage * P::A_STAGE, kt); });
   };
-  auto phase = [&](auto qc, int it, int st, Q4Regs& rg) {
+  u32x4 rq = {0u, 0u, 0u, 0u};
+  float sc = 0.f;
+  auto read_codes = [&](int slot, int kt) {
+    const unsigned char* s = q_slot(slot);
+    rq = *reinterpret_cast<const u32x4*>(s + lane * 16);
+    sc = scale(*reinterpret_cast<const uint32_t*>(s + 1024 + lane * 4), kt);
+  };
+  // sq: slot of the codes of tile it + 2
+  auto phase = [&](auto qc, int it, int sta, int stb, int sq) {
     constexpr int q = decltype(qc)::value;
-    constexpr int nf = 2 * P::aloads(q);
-    constexpr int XB = Q4_GL * ((q + 1) % P::NP == P::NP - 1 ? P::NST - 1 : P::NST);  // register loads younger than the A region waited for
-    constexpr int NB = P::ALD + P::aloads(P::NP - 1) + Q4_GL;           // operations younger than the codes of tile it+1
-    const unsigned char* sa = lds + st * P::STAGE;
-    const int nst = st + 1 == P::NST ? 0 : st + 1;
+    constexpr int nf = P::frags(q), f0 = P::frag0(q);
+    const unsigned char *sa = lds + sta * P::A_STAGE, *sb = b_stage(stb);
     if constexpr (q == 0) {
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-          fb[j][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(sa + boff[ks] + (BM * 128 + j * BJ)));
+        for (int j = 0; j < 4; ++j) fb[j][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(sb + boff[ks] + j * BJ));
     }
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-      for (int i = 0; i < nf; ++i)
-        fa[i][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(sa + aoff[ks] + (q * 64 + i * 16) * 128));
+      for (int i = 0; i < nf; ++i) fa[i][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(sa + aoff[ks] + (f0 + i) * 2048));
+    if constexpr (q == P::NP - 1) read_codes(sq, it + 2);
     if constexpr (q == 0) {
-      if (it > 0 && it - 1 + P::NST < nk) issue(std::integral_constant<int, P::NP - 1>{}, st == 0 ? P::NST - 1 : st - 1, it - 1 + P::NST);
-      // (near the end, where A loads are no longer issued, the A part of the count is dropped)
-      if (it - 1 + P::NST < nk) wait_vmcnt<NB>(); else wait_vmcnt<Q4_GL>();
-      bready(rg);
+      if (it > 0 && it - 1 + P::NA < nk) issue_region(std::integral_constant<int, P::NP - 1>{}, sta == 0 ? P::NA - 1 : sta - 1, it - 1 + P::NA);
     } else {
-      if (it + P::NST < nk) issue(std::integral_constant<int, q - 1>{}, st, it + P::NST);
+      if (it + P::NA < nk) issue_region(std::integral_constant<int, q - 1>{}, sta, it + P::NA);
     }
-#pragma unroll
-    for (int i = 4 * q / P::NP; i < 4 * (q + 1) / P::NP; ++i) bconv(nst, rg, i);
-    if constexpr (q == P::NP - 1) bload(min(it + 3, nk - 1), rg);
-    pp_wait<P::NST, P, q, XB>(nk - 1 - it);
+    ring_wait<P::R, P, q>(nk - 1 - it);
     wait_lgkmcnt0();
+    if constexpr (q == P::NP - 1)
+      if (it + P::AHEAD < nk) issue_q(q_slot(sq), it + P::AHEAD);
     __builtin_amdgcn_sched_barrier(0);
     block_barrier();
     __builtin_amdgcn_sched_barrier(0);
+    // (past the last tile stale codes are converted into a stage that nobody reads any more)
+    if constexpr (P::NP == 1) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) conv(b_stage(stb), rq[i], sc, i);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) conv(b_stage(q == 0 ? stb ^ 1 : stb), rq[q == 0 ? i + 2 : i], sc, q == 0 ? i + 2 : i);
+    }
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
@@ -623,8 +642,13 @@ __device__ __forceinline__ void gemm_pingpong_q4(unsigned char* lds, int nk, int
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
           const int j = (i & 1) ? 3 - jj : jj;
-          acc[q * 4 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][ks], fa[i][ks], acc[q * 4 + i][j], 0, 0, 0);
+          acc[f0 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][ks], fa[i][ks], acc[f0 + i][j], 0, 0, 0);
         }
+#pragma unroll
+    for (int i = 0; i < nf * 8; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one matrix instruction,
+      __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // two vector instructions
+    }
     if constexpr (PONG) {
       __builtin_amdgcn_sched_barrier(0);
       block_barrier();
@@ -632,47 +656,39 @@ __device__ __forceinline__ void gemm_pingpong_q4(unsigned char* lds, int nk, int
     }
   };
 #pragma unroll
-  for (int i = 0; i < BM / 32; ++i)
+  for (int i = 0; i < P::FA; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  using C0 = std::integral_constant<int, 0>;
-  using C1 = std::integral_constant<int, 1>;
-  Q4Regs ra, rb;
 #pragma unroll
-  for (int t = 0; t < P::NST; ++t)
-    if (t < nk) {
-      issue(C0{}, t, t);
-      if constexpr (P::NP > 1) issue(C1{}, t, t);
-    }
-  Q4Regs r0;
-  bload(0, r0);
-  bload(min(1, nk - 1), ra);
-  bload(min(2, nk - 1), rb);
+  for (int t = 0; t < P::NQ; ++t)
+    if (t < nk) issue_q(q_slot(t), t);
+#pragma unroll
+  for (int t = 0; t < P::NA; ++t)
+    if (t < nk) unroll<P::NP>([&](auto p) { issue_region(p, t, t); });
   wait_vmcnt<0>();
-  bready(r0);
-  bready(ra);
-  bready(rb);
+  // B of tiles 0 and 1; with two phases the second half of tile 1 follows in the first slot
+  read_codes(0, 0);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) bconv(0, r0, i);
+  for (int i = 0; i < 4; ++i) conv(b_stage(0), rq[i], sc, i);
+  read_codes(1, 1);
+#pragma unroll
+  for (int i = 0; i < (P::NP == 1 ? 4 : 2); ++i) conv(b_stage(1), rq[i], sc, i);
   wait_lgkmcnt0();
+#pragma unroll
+  for (int t = P::NQ; t < P::AHEAD; ++t)
+    if (t < nk) issue_q(q_slot(t - P::NQ), t);
   block_barrier();
   __builtin_amdgcn_sched_barrier(0);
   if (PONG && wr == 1) block_barrier();
   __builtin_amdgcn_sched_barrier(0);
-  int st = 0;
-  auto tile = [&](int it, Q4Regs& rg) {
-    phase(C0{}, it, st, rg);
-    if constexpr (P::NP > 1) phase(C1{}, it, st, rg);
-    st = st + 1 == P::NST ? 0 : st + 1;
-  };
-  for (int it = 0; it < nk; it += 2) {
-    tile(it, ra);
-    if (it + 1 < nk) tile(it + 1, rb);
+  int sta = 0, stb = 0, sq = 2;
+  for (int it = 0; it < nk; ++it) {
+    unroll<P::NP>([&](auto q) { phase(q, it, sta, stb, sq); });
+    sta = sta + 1 == P::NA ? 0 : sta + 1;
+    stb ^= 1;
+    sq = sq + 1 == P::NQ ? 0 : sq + 1;
   }
   if (!PONG || wr == 0) block_barrier();  // the second group's last slot
-  wait_vmcnt<0>();  // the clamped fetches past the last tile
-  bready(ra);
-  bready(rb);
 }
 
 // Epilogue of FC1: SiLU(gate) * up of the wave's 32 hidden columns -> bf16 Hact.  The loader puts the hidden columns of a
@@ -725,8 +741,6 @@ __device__ __forceinline__ void down_store(const f32x4 (&acc)[FA][NJ], const Til
     }
   }
 }
-
-#define SI_BOFF_K8(col, pc) (((pc) * BN + (col)) * 16)
 
 // ---------------------------------------------------------------------------------------------
 // FC1 + SwiGLU.  Tile: BM rows x 128 hidden columns (two chunks).  B rows in LDS are ordered so
@@ -812,19 +826,27 @@ constexpr int CUT_COLUMNS_ROWS = 160;
     case 4: CALL(4, 2); break;                         \
     default: CALL(5, 2); break;                        \
   }
-// The 4-bit bodies stop at 256 rows (their B operand passes through registers, which leaves no room for a fifth
-// A fragment): the rows a last tile holds beyond 256 take a second pass of the same block.  No wave still reads
-// the LDS ring when a body returns (its last barrier follows every fragment read), so the next pass may refill it.
+// The 4-bit bodies stop at 256 rows (they have no registers for more fragments of A): the rows a last tile holds beyond 256
+// take a second pass of the same block.  No wave still reads the LDS rings when a body returns (its last barrier follows
+// every fragment read; what a wave still writes are its own rows of a stage of B), so the next pass may refill them.
 #define SI_PICK_BODY_2PASS(ti, CALL)                                  \
   for (const int row_end_all_ = (ti).row_end;;) {                     \
     (ti).row_end = min(row_end_all_, (ti).row0 + TILE_ROWS);          \
-    const int rows_ = (ti).row_end - (ti).row0;                       \
-    if (rows_ <= 64) CALL(64);                                        \
-    else if (rows_ <= 128) CALL(128);                                 \
-    else if (rows_ <= 192) CALL(192);                                 \
-    else CALL(256);                                                   \
-    if ((ti).row_end >= row_end_all_) break;                          \
+    const bool more_ = (ti).row_end < row_end_all_;                   \
+    auto take_ = [&]() { if (!more_) take(); };                       \
+    switch (((ti).row_end - (ti).row0 + 31) / 32) {                   \
+      case 1: CALL(1); break;                                         \
+      case 2: CALL(2); break;                                         \
+      case 3: CALL(3); break;                                         \
+      case 4: CALL(4); break;                                         \
+      case 5: CALL(5); break;                                         \
+      case 6: CALL(6); break;                                         \
+      case 7: CALL(7); break;                                         \
+      default: CALL(8); break;                                        \
+    }                                                                 \
+    if (!more_) break;                                                \
     (ti).row0 = (ti).row_end;                                         \
+    (ti).row_end = row_end_all_;                                      \
   }
 
 __global__ __launch_bounds__(THREADS, 1) void k_prefill_gateup(const uint16_t* __restrict__ x, int M, Plan p,
@@ -962,56 +984,51 @@ __global__ __launch_bounds__(THREADS, 1) void k_prefill_down(const uint16_t* __r
 // The same two GEMMs on weights in the 4-bit storage form (chunk layout in cc_worker.h), converted on the way
 // into the B stage.  Tiles, LDS layouts, fragment reads, matrix instructions and epilogues are those above.
 // ---------------------------------------------------------------------------------------------
-template <int BM>
+template <class P, class Take>
 __device__ __forceinline__ void gateup_body_q4(const uint16_t* __restrict__ x, int M, const Plan& p, int tc, const TileInfo& ti,
-                                               const WeightView& wv, uint16_t* __restrict__ hact, int ldh,
-                                               unsigned char* lds) {
-  using P = PingPong<BM, 0>;
+                                               const WeightView& wv, uint16_t* __restrict__ hact, int ldh, unsigned char* lds, Take take) {
   const int tid = thread_of_item(), lane = tid % WAVE, w = __builtin_amdgcn_readfirstlane(tid / WAVE);  // wave index, known to be uniform
   const int wr = w >> 2, wc = w & 3;
   const unsigned char* ebase = reinterpret_cast<const unsigned char*>(wv.base + (size_t)ti.se * wv.expert_stride);
 
   const int lrow = lane >> 3, lpp = lane & 7;
   uint32_t a_src[P::ALD];  // byte offsets from x
-#pragma unroll
-  for (int i = 0; i < P::ALD; ++i) {
-    const int lr = pp_a_row<BM>(w, i) + lrow;
+  unroll<P::ALD>([&](auto i) {
+    const int lr = ring_a_row<P, i>(w) + lrow;
     int row = ti.row0 + lr;
     row = row < ti.row_end ? row : ti.row_end - 1;
     a_src[i] = ((uint32_t)(ti.row_t0 >= 0 ? row - ti.row_t0 : p.row_token[row]) * (uint32_t)M + ((lpp ^ ((lr >> 1) & 7)) * 8)) * 2;
-  }
-  auto issue_a = [&](int i, int stage, int kt) {
-    load_lds16(x + kt * BK, a_src[i], lds + stage * P::STAGE + pp_a_row<BM>(w, i) * 128);
+  });
+  auto issue_a = [&](auto i, unsigned char* stage, int kt) {
+    if (!P::half(i) || lane < 32) load_lds16(x + kt * BK, a_src[i], stage + ring_a_row<P, i>(w) * 128);
   };
   // B: wave w fills LDS rows [32 w, 32 w + 32) = (chunk 2*tc + w/4, gate (w even) or up block, columns
   // ((w/2)%2)*32 + gu_col(row) of the chunk); lane = (row lane/2, k-half lane%2): the 32 weights of its half row are
   // 16 bytes of codes, i.e. the pieces 4*(lane%2) .. +3 of the LDS row
-  const int chunk_rel = min(2 * tc + (w >> 2), wv.n_chunks - 1);
+  const int chunk_rel = __builtin_amdgcn_readfirstlane(min(2 * tc + (w >> 2), wv.n_chunks - 1));
   const unsigned char* cb = ebase + (size_t)(wv.chunk0 + chunk_rel) * q4_chunk_u16(M) * 2;
+  const unsigned char *codes = cb + q4_off_codes(w & 1, M), *scales = cb + q4_off_scales(w & 1, M);
   const int jc = ((w >> 1) & 1) * 32 + gu_col(lane >> 1), kh = lane & 1;
-  const unsigned char* qrow = cb + q4_off_codes(w & 1, M) + (size_t)jc * (M / 2) + kh * 16;
-  const uint16_t* zrow = reinterpret_cast<const uint16_t*>(cb + q4_off_scales(w & 1, M)) + (size_t)jc * (M / 64);
-  const int brow = w * 32 + (lane >> 1);
-  const int bsw = (brow >> 1) & 7;
-  auto bload = [&](int kt, Q4Regs& r) {
-    gload_b128(r.q, qrow + (size_t)kt * 32);
-    gload_u16(r.z, zrow + kt);
+  uint32_t q_lane = (uint32_t)(jc * (M / 2) + kh * 16);
+  const uint32_t z_row = (uint32_t)(jc * (M / 64));  // index of the row's first scale
+  auto issue_q = [&](unsigned char* slot, int kt) {
+    load_lds16(codes + kt * 32, q_lane, slot);
+    load_lds4(scales, (z_row + kt) / 2 * 4, slot + 1024);
   };
-  // word i of the lane's codes = elements 8i .. 8i+7 of its half row; even nibbles hold elements 0 4 1 5, odd
-  // nibbles 2 6 3 7 (cc_worker.h)
-  auto bconv = [&](int stage, const Q4Regs& r, int i) {
-    const float sc = __uint_as_float(r.z << 16), s8 = -8.f * sc;
-    const uint32_t wd = r.q[i], ev = wd & 0x0f0f0f0fu, od = (wd >> 4) & 0x0f0f0f0fu;
-    u32x4 o;
-    o.x = q4_pair(ev, 0, 2, sc, s8);
-    o.y = q4_pair(od, 0, 2, sc, s8);
-    o.z = q4_pair(ev, 1, 3, sc, s8);
-    o.w = q4_pair(od, 1, 3, sc, s8);
-    lds_store_b128(lds + stage * P::STAGE + BM * 128 + brow * 128 + (((kh * 4 + i) ^ bsw) << 4), o);
+  auto scale = [&](uint32_t word, int kt) { return __uint_as_float((z_row + kt) & 1 ? word & 0xffff0000u : word << 16); };
+  const uint32_t brow = (uint32_t)(w * 32 + (lane >> 1)), b_dst = brow * 128 + (((kh * 4) ^ ((brow >> 1) & 7)) << 4);
+  ScaledCodes codes_of;
+  codes_of.hide();
+  // a word holds elements 8i .. 8i+7 of the half row: nibbles p and p + 4 are elements 2p, 2p + 1 (cc_worker.h)
+  auto conv = [&](unsigned char* stage, uint32_t word, float sc, int i) {
+    float f[8];
+    codes_of(word, sc, f);
+    lds_store_b128(stage + (b_dst ^ (i << 4)), u32x4{pack_bf16(f[0], f[1]), pack_bf16(f[2], f[3]), pack_bf16(f[4], f[5]), pack_bf16(f[6], f[7])});
   };
   f32x4 acc[P::FA][4];
   const uint32_t boff[2] = {(uint32_t)swz(wc * 64 + (lane & 15), lane >> 4), (uint32_t)swz(wc * 64 + (lane & 15), 4 + (lane >> 4))};
-  gemm_pingpong_q4<BM, 2048>(lds, M / BK, lane, wr, acc, issue_a, bload, bconv, boff);
+  gemm_pingpong_q4<P, 2048>(lds, M / BK, w, lane, wr, acc, issue_a, issue_q, scale, conv, boff);
+  take();
   gateup_store<P::FA, 4>(acc, ti, wv, 2 * tc + (wc >> 1), tc * 128 + wc * 32, wr, lane, hact, ldh);
 }
 
@@ -1030,20 +1047,18 @@ __global__ __launch_bounds__(THREADS, 1) void k_prefill_gateup_q4(const uint16_t
     const int ldh = ti.sh ? ldh_s : ldh_r;
     uint16_t* hact = hact_r + (ti.sh ? hact_s : 0);
     if (!storage_index(wv, ti.e, ti.se) || (halves == 2 && !half_rows(ti, half))) return take();
-#define SI_CALL_GU(BMV) gateup_body_q4<BMV>(x, scalar_of_item(M), p, tc, ti, wv, hact, ldh, lds)
-    SI_PICK_BODY_2PASS(ti, SI_CALL_GU);
+#define SI_CALL_GU(FAV) gateup_body_q4<RingQ<FAV>>(x, scalar_of_item(M), p, tc, ti, wv, hact, ldh, lds, take_)
+    SI_PICK_BODY_2PASS(ti, SI_CALL_GU)
 #undef SI_CALL_GU
-    take();
   });
 }
 
-template <int BM>
+template <class P, class Take>
 __device__ __forceinline__ void down_body_q4(const uint16_t* __restrict__ hact, int ldh, int M, const DownRange& dr, const TileInfo& ti,
                                              const WeightView& wv, float* __restrict__ yp, size_t slab_stride, int accumulate,
-                                             unsigned char* lds) {
-  using P = PingPong<BM, 0>;
+                                             unsigned char* lds, Take take) {
   const int c_begin = dr.c_begin, c_end = dr.c_end;
-  if (c_begin >= c_end && accumulate) return;
+  if (c_begin >= c_end && accumulate) return take();
   const int tid = thread_of_item(), lane = tid % WAVE, w = __builtin_amdgcn_readfirstlane(tid / WAVE);  // wave index, known to be uniform
   const int wr = w >> 2, wc = w & 3;
   const int n0 = dr.nt * BN;
@@ -1052,48 +1067,47 @@ __device__ __forceinline__ void down_body_q4(const uint16_t* __restrict__ hact, 
 
   const int lrow = lane >> 3, lpp = lane & 7;
   uint32_t a_src[P::ALD];  // byte offsets from hact
-#pragma unroll
-  for (int i = 0; i < P::ALD; ++i) {
-    const int lr = pp_a_row<BM>(w, i) + lrow;
+  unroll<P::ALD>([&](auto i) {
+    const int lr = ring_a_row<P, i>(w) + lrow;
     int row = ti.row0 + lr;
     row = row < ti.row_end ? row : ti.row_end - 1;
     a_src[i] = ((uint32_t)row * (uint32_t)ldh + wv.col0 + ((lpp ^ ((lr >> 1) & 7)) * 8)) * 2;
-  }
-  auto issue_a = [&](int i, int stage, int kt) {
-    load_lds16(hact + (c_begin + kt) * CHUNK_J, a_src[i], lds + stage * P::STAGE + pp_a_row<BM>(w, i) * 128);
+  });
+  auto issue_a = [&](auto i, unsigned char* stage, int kt) {
+    if (!P::half(i) || lane < 32) load_lds16(hact + (c_begin + kt) * CHUNK_J, a_src[i], stage + ring_a_row<P, i>(w) * 128);
   };
   // B: thread = (output column n0 + (w%4)*64 + lane, j-half w/4): its 16 bytes of codes are the 32 hidden columns
   // of the half for that output column, i.e. the pieces 4*half .. +3 of the column in the [piece][column] B stage
   const int NW = ntile_width(M);
   const int half = w >> 2, col = (w & 3) * 64 + lane;
   const int n = min(n0 + col, M - 1);
-  const size_t qoff = q4_off_codes(2, M) + (((size_t)(n / NW) * 2 + half) * NW + (n % NW)) * 16;
-  const size_t zoff = q4_off_scales(2, M) + (size_t)n * 2;
+  uint32_t q_lane = (uint32_t)(((n / NW) * 2 + half) * NW + (n & (NW - 1))) * 16;  // NW is a power of two
   const size_t cbytes = q4_chunk_u16(M) * 2;
-  auto bload = [&](int kt, Q4Regs& r) {
-    const unsigned char* cb = ebase + (size_t)(wv.chunk0 + c_begin + kt) * cbytes;
-    gload_b128(r.q, cb + qoff);
-    gload_u16(r.z, cb + zoff);
+  const unsigned char* cb0 = ebase + (size_t)(wv.chunk0 + c_begin) * cbytes;
+  auto issue_q = [&](unsigned char* slot, int kt) {
+    const unsigned char* cb = cb0 + (size_t)kt * cbytes;
+    load_lds16(cb + q4_off_codes(2, M), q_lane, slot);
+    load_lds4(cb + q4_off_scales(2, M), (uint32_t)n / 2 * 4, slot + 1024);
   };
-  // word i = hidden columns 8i .. 8i+7 of the half; even nibbles hold elements 0 1 2 3, odd nibbles 4 5 6 7
-  auto bconv = [&](int stage, const Q4Regs& r, int i) {
-    const float sc = __uint_as_float(r.z << 16), s8 = -8.f * sc;
-    const uint32_t wd = r.q[i], ev = wd & 0x0f0f0f0fu, od = (wd >> 4) & 0x0f0f0f0fu;
-    u32x4 o;
-    o.x = q4_pair(ev, 0, 1, sc, s8);
-    o.y = q4_pair(ev, 2, 3, sc, s8);
-    o.z = q4_pair(od, 0, 1, sc, s8);
-    o.w = q4_pair(od, 2, 3, sc, s8);
-    lds_store_b128(lds + stage * P::STAGE + BM * 128 + ((half * 4 + i) * BN + col) * 16, o);
+  auto scale = [&](uint32_t word, int) { return __uint_as_float(n & 1 ? word & 0xffff0000u : word << 16); };
+  ScaledCodes codes_of;
+  codes_of.hide();
+  // a word holds hidden columns 8i .. 8i+7 of the half: nibbles p and p + 4 are elements (0, 2), (4, 6), (1, 3), (5, 7) (cc_worker.h)
+  auto conv = [&](unsigned char* stage, uint32_t word, float sc, int i) {
+    float f[8];
+    codes_of(word, sc, f);
+    lds_store_b128(stage + ((half * 4 + i) * BN + col) * 16, u32x4{pack_bf16(f[0], f[4]), pack_bf16(f[1], f[5]), pack_bf16(f[2], f[6]), pack_bf16(f[3], f[7])});
   };
   if (c_begin < c_end) {
     f32x4 acc[P::FA][4];
-    const uint32_t b0 = SI_BOFF_K8(wc * 64 + (lane & 15), lane >> 4);
+    const uint32_t b0 = ((lane >> 4) * BN + wc * 64 + (lane & 15)) * 16;
     const uint32_t boff[2] = {b0, b0 + 4 * BN * 16};
-    gemm_pingpong_q4<BM, 256>(lds, c_end - c_begin, lane, wr, acc, issue_a, bload, bconv, boff);
+    gemm_pingpong_q4<P, 256>(lds, c_end - c_begin, w, lane, wr, acc, issue_a, issue_q, scale, conv, boff);
+    take();
     down_store<P::FA, 4>(acc, ti, n0 + wc * 64, wr, lane, M, out, accumulate);
   } else {
-    for (int i = tid; i < BM * BN; i += THREADS) {
+    take();
+    for (int i = tid; i < P::BM * BN; i += THREADS) {
       const int row = ti.row0 + i / BN, m = n0 + i % BN;
       if (row < ti.row_end && m < M) out[(size_t)row * M + m] = 0.f;
     }
@@ -1117,10 +1131,9 @@ __global__ __launch_bounds__(THREADS, 1) void k_prefill_down_q4(const uint16_t* 
     const uint16_t* hact = hact_r + (ti.sh ? hact_s : 0);
     const DownRange dr = down_range(inner, n_ntiles, n_split, wv.n_chunks);
     if (!storage_index(wv, ti.e, ti.se) || (halves == 2 && !half_rows(ti, half))) return take();
-#define SI_CALL_DN(BMV) down_body_q4<BMV>(hact, ldh, scalar_of_item(M), dr, ti, wv, yp, slab_stride, accumulate, lds)
-    SI_PICK_BODY_2PASS(ti, SI_CALL_DN);
+#define SI_CALL_DN(FAV) down_body_q4<RingQ<FAV>>(hact, ldh, scalar_of_item(M), dr, ti, wv, yp, slab_stride, accumulate, lds, take_)
+    SI_PICK_BODY_2PASS(ti, SI_CALL_DN)
 #undef SI_CALL_DN
-    take();
   });
 }
 

@@ -7,6 +7,7 @@ import pytest
 import paper_2411_15715_amd as si
 import synth
 from gpu_helpers import GpuLayer, assert_parity
+from test_gpu_q4 import Q4Layer
 
 pytestmark = pytest.mark.gpu
 
@@ -60,5 +61,23 @@ def test_experts_of_unequal_rows(oracle, E, k, T, d_ff, d_ff_shared, n_g):
         for n in (n_g, n_g, 0):
             print("unequal E=%d T=%d n_g=%d" % (E, T, n), flush=True)
             assert_parity(L.forward(xp, lg, mode=si.SI_PREFILL, n_g=n), yo)
+    finally:
+        L.close()
+
+
+@pytest.mark.parametrize("d_model,d_ff", [(64, 320), (192, 768), (576, 1024), (1024, 2112)])
+def test_every_body_q4(oracle, d_model, d_ff):
+    """4-bit bodies, with 1 to 16 k-tiles (odd numbers of scale groups per row among them); codes and scales as in earnest."""
+    cfg = synth.scaled(synth.CONFIGS["llama2_70b"], d_model=d_model, d_ff=d_ff, seed=40 + d_model)
+    wq = synth.make_weights_q4(cfg)
+    for key in ("z_gate", "z_up", "z_down"):
+        wq[key] = (wq[key] & 0xFF80) | 0x20  # scales of three significant bits: a weight has at most 7 and is a bfloat16
+    xp = synth.make_tokens(cfg, 600)
+    yo = oracle.layer_forward_q4(xp, wq)
+    L = Q4Layer(cfg, wq, (1.0, 0.0, 0.0), max_tokens=600)
+    try:
+        for T in [b + d for b in range(32, 257, 32) for d in (-1, 0, 1)] + [300, 320, 560, 576, 600]:
+            print("4-bit body M=%d H=%d T=%d" % (d_model, d_ff, T), flush=True)
+            assert_parity(L.forward(xp[:T], None, mode=si.SI_PREFILL), yo[:T])
     finally:
         L.close()
