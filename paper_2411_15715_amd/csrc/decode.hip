@@ -139,14 +139,16 @@ __global__ __launch_bounds__(GU_THREADS, 4) void k_decode_gateup(const uint16_t*
   constexpr int X_EARLY_MAX = 4;  // 16-byte pieces per thread: d_model <= 8192
   u32x4 x_reg[X_EARLY_MAX];
   bool x_early = false;
-  if constexpr (FUSED != 0) {
+  if constexpr (TB == 1) {
     // with a single token every row is token 0
-    x_early = TB == 1 && fr.T == 1 && M / 8 <= X_EARLY_MAX * GU_THREADS;
+    x_early = (FUSED ? fr.T : p.dense_T) == 1 && M / 8 <= X_EARLY_MAX * GU_THREADS;
     if (x_early) {
 #pragma unroll
       for (int i = 0; i < X_EARLY_MAX; ++i)
         if ((int)threadIdx.x + i * GU_THREADS < M / 8) x_reg[i] = reinterpret_cast<const u32x4*>(x)[threadIdx.x + i * GU_THREADS];
     }
+  }
+  if constexpr (FUSED != 0) {
     BlockRoute& br = s_br;
     block_route(fr, br, p, blockIdx.x == 0 && blockIdx.y == 0);
     if (slot < 0) {
@@ -154,7 +156,7 @@ __global__ __launch_bounds__(GU_THREADS, 4) void k_decode_gateup(const uint16_t*
       r0 = fr.T * fr.k;
       r1 = r0 + fr.T;
     } else if (expert_sel >= 0) {
-      // one given expert: the routed expert of a dense layer (every pair is its row)
+      // one given expert: the only routed one (every pair is its row)
       e = expert_sel;
       r0 = 0;
       r1 = fr.T * fr.k;
@@ -219,7 +221,7 @@ __global__ __launch_bounds__(GU_THREADS, 4) void k_decode_gateup(const uint16_t*
       constexpr int XB = 4;
       int tok[TB];
 #pragma unroll
-      for (int tb = 0; tb < TB; ++tb) tok[tb] = __builtin_amdgcn_readfirstlane(row_token[rb + min(tb, nt - 1)]);
+      for (int tb = 0; tb < TB; ++tb) tok[tb] = __builtin_amdgcn_readfirstlane(!FUSED && p.dense_T ? rb + min(tb, nt - 1) : row_token[rb + min(tb, nt - 1)]);
       for (int i0 = tid; i0 < nt * M8; i0 += XB * GU_THREADS) {
         u32x4 v[XB];
 #pragma unroll
@@ -374,7 +376,7 @@ __global__ __launch_bounds__(64) void k_decode_combine(DecodeCombineArgs a, Plan
   for (int s = 0; s < n_terms; ++s) {
     int row;
     float wgt;
-    if (s < a.k) { row = p.inv[t * a.k + s]; wgt = p.w[t * a.k + s]; }
+    if (s < a.k) { row = row_of_pair(p, t * a.k + s); wgt = weight_of_pair(p, t * a.k + s); }
     else { row = a.T * a.k + t; wgt = 1.f; }
     const int n_part[3] = {s < a.k ? a.n_slots_gg : a.s_slots_gg, s < a.k ? a.n_slots_cg : a.s_slots_cg,
                            is_x2 ? (s < a.k ? a.n_slots_cc : a.s_slots_cc) : 0};

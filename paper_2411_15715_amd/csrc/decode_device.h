@@ -18,8 +18,8 @@ __device__ inline bool block_rows(const Plan& p, int expert_sel, int x2_only, in
     e = p.touched[slot];
     if (e >= p.n_routed) return false;
   }
-  r0 = p.off[e] + (x2_only ? p.count1[e] : 0);
-  r1 = p.off[e + 1];
+  r0 = row_begin(p, e, x2_only);
+  r1 = row_end(p, e);
   return r1 > r0;
 }
 

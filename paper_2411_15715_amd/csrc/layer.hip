@@ -210,6 +210,7 @@ struct si_layer {
   // device workspaces
   char* d_plan = nullptr;
   Plan plan{};
+  bool queue_dirty = false;     // a call ended before its merge: the tile queues of the prompt phase are to be cleared first
   int max_tiles = 0;
   float* d_h = nullptr;       // decode activations [rows_dec][ldh]
   int ldh_dec = 0, rows_dec = 0;
@@ -573,6 +574,7 @@ int create_impl(const si_layer_desc_t* desc, const WeightSource& src, const uint
     L->plan.n_tiles = b + o_nt + 4;
     L->plan.n_routed = E;
     L->plan.queue = b + (o_q + 31) / 32 * 32;
+    HIP_OR_DESTROY(hipMemset(L->plan.queue, 0, (size_t)2 * 8 * QUEUE_STRIDE * 4));  // (afterwards every call leaves them clear)
     L->plan.tile_e = b + o_te; L->plan.tile_r = b + o_tr; L->plan.tile_e_x2 = b + o_te2; L->plan.tile_r_x2 = b + o_tr2;
   }
   const int T_dec = std::min(T, SI_DECODE_MAX_T);
@@ -889,6 +891,7 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
       if (L->cc_inflight) { cc_pool_wait(L->pool); L->cc_inflight = false; }
       L->pre_n = 0;
       L->in_staged = 0;
+      L->queue_dirty = true;
     }
   } guard{L};
   L->ev_used = 0;
@@ -914,9 +917,13 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
   // reading tens of megabytes of weights (Section III-C: with few tokens the launch time rivals the compute time),
   // so the assignment is derived inside the first gate/up launch instead of by a kernel of its own.
   const bool resident_only = !any_cg && !need_cgp && !need_cc && !L->placed && !L->q4 && L->ch_gg > 0;
-  bool fuse_route = path == SI_DECODE && resident_only && T <= FUSED_ROUTE_MAX_T && T * k <= FUSED_ROUTE_MAX_PAIRS;
+  // A dense layer needs no assignment at all: its tables are only written for a caller who asks for them.
+  const bool dense = E == 1 && !L->has_shared, asked = u.idx || u.w || u.count || u.off || u.perm || u.inv;
+  L->plan.dense_T = dense ? T : 0;
+  L->plan.dense_x1 = n_x1;
+  bool fuse_route = path == SI_DECODE && resident_only && !dense && T <= FUSED_ROUTE_MAX_T && T * k <= FUSED_ROUTE_MAX_PAIRS;
   FusedRoute fr{E > 1 ? logits_dev : nullptr, T, E, k, L->has_shared, n_x1, u};
-  if (!fuse_route) {
+  if (!fuse_route && (!dense || asked)) {
     SegScope sc(L, stream, 0);
     hipError_t e = launch_route(E > 1 ? logits_dev : nullptr, T, E, k, L->has_shared, n_g, L->plan, u, stream);
     if (e != hipSuccess) return fail(SI_EHIP, "route launch failed: %s", hipGetErrorString(e));
@@ -929,7 +936,12 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
     const size_t x_bytes = need_cc ? (size_t)n_x1 * M * 2 : 0;
     const bool x_copy = x_bytes > HANDOFF_DIRECT_BYTES;
     if (x_copy) HIP_TRY(hipMemcpyAsync(L->hx, x, x_bytes, hipMemcpyDeviceToHost, stream));
-    HIP_TRY(launch_handoff(L->plan, x, x_copy ? 0 : x_bytes, need_cc ? T * k : 0, EX, L->hx, L->hidx, L->hw, L->hcount, stream));
+    if (dense) {  // (known here; the workers of the call before have ended)
+      for (int t = 0; t < T; ++t) { L->hidx[t] = 0; L->hw[t] = 1.f; }
+      L->hcount[0] = T;
+      L->hcount[1] = n_x1;
+    }
+    HIP_TRY(launch_handoff(L->plan, x, x_copy ? 0 : x_bytes, need_cc && !dense ? T * k : 0, dense ? 0 : EX, L->hx, L->hidx, L->hw, L->hcount, stream));
     HIP_TRY(hipEventRecord(L->ev_host, stream));
   } else if (E == 1) {
     st.n_touched = EX;
@@ -1033,6 +1045,12 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
     int rc;
     if (path == SI_PREFILL) {
       SegScope sc(L, stream, SI_K_FILL);
+      if (L->queue_dirty) {
+        K_TRY(launch_fill_zero(reinterpret_cast<float*>(L->plan.queue), (size_t)2 * 8 * QUEUE_STRIDE, 1, 0, stream));
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        HIP_TRY(hipStreamIsCapturing(stream, &cs));
+        L->queue_dirty = cs != hipStreamCaptureStatusNone;  // (a recorded launch has cleared nothing yet)
+      }
       if (L->ch_gg == 0 || L->placed) K_TRY(launch_fill_zero(L->d_yp, (size_t)T * k * M, split_call, L->yp_slab, stream));
       if (L->has_shared && L->sch_gg == 0)
         K_TRY(launch_fill_zero(L->d_yp + (size_t)T * k * M, (size_t)T * M, split_s, L->yp_slab, stream));

@@ -168,7 +168,9 @@ __device__ __forceinline__ TileQueues tile_queues(const Plan& p, int expert_sel,
   t.rows0 = n_inner_s ? n_row_tiles(table(p.off, p.n_routed + 1) - table(p.off, p.n_routed)) : 0;
   int multi, n;
   if (expert_sel >= 0) {
-    const int rows = table(p.off, expert_sel + 1) - table(p.off, expert_sel) - (x2_only ? table(p.count1, expert_sel) : 0), last = rows & (TILE_ROWS - 1);
+    const int rows = p.dense_T ? p.dense_T - (x2_only ? p.dense_x1 : 0)
+                               : table(p.off, expert_sel + 1) - table(p.off, expert_sel) - (x2_only ? table(p.count1, expert_sel) : 0);
+    const int last = rows & (TILE_ROWS - 1);
     n = n_row_tiles(rows);
     multi = n > 1;
     t.rows1 = has_spill_tile(rows) ? 1 : multi && last && last <= SHORT_ROWS ? n - 1 : 0;
@@ -208,7 +210,8 @@ __device__ __forceinline__ void item_tile(const TileQueues& tq, const Plan& p, i
     if (list == 1) r0 = first;
     else in_group += first * n_inner;
   }
-  const int off = table(p.off, ti.e), start = off + (x2_only ? table(p.count1, ti.e) : 0), rows = table(p.off, ti.e + 1) - start, n = n_row_tiles(rows);
+  const int off = p.dense_T ? 0 : table(p.off, ti.e), start = off + (!x2_only ? 0 : p.dense_T ? p.dense_x1 : table(p.count1, ti.e));
+  const int rows = (p.dense_T ? p.dense_T : table(p.off, ti.e + 1)) - start, n = n_row_tiles(rows);
   // one expert: the spill tile (list 1) or the short last tile (list 2) is the last one
   if (expert_sel >= 0 && (has_spill_tile(rows) ? list == 1 : list == 2)) r0 = n - size;
   inner = small_div(in_group, size, rem);
@@ -1142,11 +1145,13 @@ __global__ __launch_bounds__(256) void k_prefill_combine(const float* __restrict
                                                          int has_shared, Plan p, float* __restrict__ y) {
   const int t = blockIdx.y;
   const int m4 = blockIdx.x * 256 + threadIdx.x;
+  // (the launch before has cleared one queue and used the other)
+  if (t == 0 && blockIdx.x == 0 && threadIdx.x < 2 * N_XCD) p.queue[threadIdx.x * QUEUE_STRIDE] = 0;
   if (m4 * 4 >= M) return;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int s = 0; s < k; ++s) {
-    const float wgt = p.w[t * k + s];
-    const float* row = yp + (size_t)p.inv[t * k + s] * M;
+    const float wgt = weight_of_pair(p, t * k + s);
+    const float* row = yp + (size_t)row_of_pair(p, t * k + s) * M;
     float4 v = reinterpret_cast<const float4*>(row)[m4];
     for (int q = 1; q < n_split; ++q) {
       const float4 v2 = reinterpret_cast<const float4*>(row + (size_t)q * slab_stride)[m4];

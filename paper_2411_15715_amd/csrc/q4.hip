@@ -130,7 +130,7 @@ __global__ __launch_bounds__(QGU_THREADS, 4) void k_decode_gateup_q4(const uint1
 #pragma unroll
       for (int b = 0; b < XB; ++b) {
         const int i = min(i0 + b * QGU_THREADS, nt * M8 - 1), t = i / M8;
-        v[b] = reinterpret_cast<const u32x4*>(x + (size_t)p.row_token[rb + t] * M)[i - t * M8];
+        v[b] = reinterpret_cast<const u32x4*>(x + (size_t)token_of_row(p, rb + t) * M)[i - t * M8];
       }
 #pragma unroll
       for (int b = 0; b < XB; ++b) {
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(256) void k_dequant_q4(const uint16_t* __restrict__
     de = e;
     if (e >= p.n_routed) return;
   }
-  if (p.off[e + 1] - p.off[e] - (x2_only ? p.count1[e] : 0) <= 0) return;  // no rows: nobody reads these weights
+  if (row_end(p, e) - row_begin(p, e, x2_only) <= 0) return;  // no rows: nobody reads these weights
   const int se = e_map ? e_map[e] : e;
   if (se < 0) return;
   const int c = blockIdx.x / 24, sec = (blockIdx.x % 24) / 8, oct = blockIdx.x % 8;

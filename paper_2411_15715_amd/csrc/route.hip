@@ -101,7 +101,6 @@ __device__ __forceinline__ void assign_body(AssignLds& s, int T, int E, int k, i
   }
   __syncthreads();
   if (first_block) {
-    if (p.queue && tid < 2 * 8) p.queue[tid * QUEUE_STRIDE] = 0;
     for (int e = tid; e < EX; e += ROUTE_THREADS) {
       if (p.count) p.count[e] = s.tot[e];
       if (p.count1) p.count1[e] = s.tot1[e];
@@ -184,10 +183,10 @@ __global__ __launch_bounds__(ROUTE_THREADS) void k_assign(int T, int E, int k, i
   assign_body(s, T, E, k, has_shared, n_x1, p, u, q0, min(q0 + span, T * k), blockIdx.x == 0);
 }
 
-// A dense layer (one expert, weight 1): every table is known without looking at anything.
+// A dense layer (one expert, weight 1): every table is known without looking at anything.  Launched only for a caller who asks
+// for them: the kernels of the call know them too (Plan::dense_T).
 __global__ __launch_bounds__(256) void k_dense_assign(int T, int n_x1, Plan p, RouteOut u) {
   const int t = blockIdx.x * 256 + threadIdx.x;
-  if (p.queue && t < 2 * 8) p.queue[t * QUEUE_STRIDE] = 0;
   if (t < T) {
     p.idx[t] = 0; p.w[t] = 1.f;
     if (p.perm) p.perm[t] = t;
@@ -253,6 +252,7 @@ __global__ __launch_bounds__(256) void k_handoff(Plan p, const uint4* __restrict
 hipError_t launch_handoff(const Plan& plan, const uint16_t* x, size_t x_bytes, int n_pairs, int EX, uint16_t* hx, int32_t* hidx,
                           float* hw, int32_t* hcount, hipStream_t stream) {
   const int n16 = (int)(x_bytes / 16), n = std::max(std::max(n16, n_pairs), EX);
+  if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(k_handoff, dim3((n + 255) / 256), dim3(256), 0, stream, plan, reinterpret_cast<const uint4*>(x),
                      reinterpret_cast<uint4*>(hx), n16, n_pairs, EX, hidx, hw, hcount);
   return hipGetLastError();

@@ -60,6 +60,9 @@ struct Plan {
   int32_t* tile_e_x2;  // the same for the X2 rows only (CG')
   int32_t* tile_r_x2;
   int32_t* queue;      // [2][8 * QUEUE_STRIDE] tiles taken per XCD by the running FC1 launch / FC2 launch of the prompt phase
+  // A dense layer (one expert, no shared one) of T = dense_T tokens, dense_x1 of them X1: every entry above is known (one group
+  // of rows 0 .. T-1 in token order, weight 1) and nothing has written or reads the tables.  0: the tables hold.
+  int32_t dense_T, dense_x1;
   int32_t n_routed;    // E: the tables of a launch over "all experts" cover entries < n_routed only (the shared expert's
                        // weights live in their own buffer: a view of their own in the same launch, or one of its own)
 };
@@ -91,6 +94,15 @@ struct WeightView {
 };
 
 #if defined(__HIPCC__)
+// first row of expert e (of its X2 rows), row after its last, token of a row, row and weight of pair q
+__device__ inline int row_begin(const Plan& p, int e, int x2_only) {
+  return p.dense_T ? (x2_only ? p.dense_x1 : 0) : p.off[e] + (x2_only ? p.count1[e] : 0);
+}
+__device__ inline int row_end(const Plan& p, int e) { return p.dense_T ? p.dense_T : p.off[e + 1]; }
+__device__ inline int token_of_row(const Plan& p, int row) { return p.dense_T ? row : p.row_token[row]; }
+__device__ inline int row_of_pair(const Plan& p, int q) { return p.dense_T ? q : p.inv[q]; }
+__device__ inline float weight_of_pair(const Plan& p, int q) { return p.dense_T ? 1.f : p.w[q]; }
+
 // storage index of expert e for this launch; false when the launch has nothing for the expert
 __device__ inline bool storage_index(const WeightView& wv, int e, int& se) {
   se = wv.e_map ? wv.e_map[e] : e;
