@@ -186,6 +186,7 @@ struct si_layer {
   uint16_t* h_shared = nullptr; // pinned [sch_cc + sch_cg] chunks
   int n_stage = 0, stage_chunks = 0;
   std::vector<uint16_t*> d_stage;
+  uint16_t* d_direct = nullptr;  // device: a small piece on its way through the caller's stream
   std::vector<hipEvent_t> ev_ready, ev_free;
   std::vector<char> slot_used;
   long piece_counter = 0;
@@ -396,7 +397,7 @@ void si_layer_destroy(si_layer_t* L) {
   if (L->ev_t0) (void)hipEventDestroy(L->ev_t0);
   if (L->ev_t1) (void)hipEventDestroy(L->ev_t1);
   if (L->copy_stream) (void)hipStreamDestroy(L->copy_stream);
-  void* dev[] = {L->d_gg, L->d_sgg, L->d_plan, L->d_h, L->d_part, L->d_hact, L->d_yp, L->d_ycc, L->d_deq, L->d_emap};
+  void* dev[] = {L->d_gg, L->d_sgg, L->d_plan, L->d_h, L->d_part, L->d_hact, L->d_yp, L->d_ycc, L->d_deq, L->d_emap, L->d_direct};
   for (void* p : dev) if (p) (void)hipFree(p);
   void* pin[] = {L->h_routed, L->h_shared, L->hx, L->hidx, L->hw, L->hcount, L->hycc};
   for (void* p : pin) if (p) (void)hipHostFree(p);
@@ -406,6 +407,26 @@ void si_layer_destroy(si_layer_t* L) {
 }  // extern "C"
 
 namespace {
+
+// Generation phase: small pieces are copied by a kernel on the caller's stream, which reads the pinned memory over the link at
+// the rate of the copy engine (54 GB/s), in front of the kernels that use it.  A copy on the copy stream is bracketed by two waits
+// between streams, which hold a short call up by longer than the copy takes: 0.4 MB, 256 x 704, 4 tokens, 40/30/30: 94 -> 51 us; dense,
+// one piece of 2.3 / 6.9 / 13.8 / 27 / 54 MB: 156 / 267 / 362 / 584 / 1146 -> 78 / 165 / 293 / 532 / 1021 us.  What the copy stream does
+// better is to overlap: with the resident part (limited to 10 us here), and with the kernels of the piece before, in calls of
+// several experts (16 of them: 20 pieces of 2 MB 590 -> 577 us, of 4 MB 968 -> 955, of 8 MB 1841 -> 1898).
+constexpr size_t DIRECT_COPY_BYTES = (size_t)32 << 20, DIRECT_COPY_BYTES_MOE = (size_t)4 << 20, DIRECT_RESIDENT_BYTES = (size_t)64 << 20;
+
+__global__ __launch_bounds__(256) void k_copy_piece(const uint4* __restrict__ src, uint4* __restrict__ dst, int n) {
+  constexpr int U = 4;
+  for (int i0 = blockIdx.x * 256 + threadIdx.x; i0 < n; i0 += gridDim.x * 256 * U) {
+    uint4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = src[min(i0 + u * (int)gridDim.x * 256, n - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i0 + u * (int)gridDim.x * 256 < n) dst[i0 + u * gridDim.x * 256] = v[u];
+  }
+}
 
 // Staging ring (Stream-C) and host workers, sized independently of the slicing rates so that a layer can be
 // re-sliced without touching them: a decode piece must hold whole down-projection slots of the largest part an
@@ -420,6 +441,10 @@ int setup_staging(si_layer* L) {
     L->ev_ready.assign(L->n_stage, nullptr);
     L->ev_free.assign(L->n_stage, nullptr);
     L->slot_used.assign(L->n_stage, 0);
+    {
+      int rc = dev_alloc(&L->d_direct, std::min((L->E > 1 ? DIRECT_COPY_BYTES_MOE : DIRECT_COPY_BYTES) / 2, (size_t)std::max(L->H, L->Hs) / CHUNK_J * L->ce));
+      if (rc) return rc;
+    }
     for (int i = 0; i < L->n_stage; ++i) {
       int rc = dev_alloc(&L->d_stage[i], (size_t)L->stage_chunks * L->ce);
       if (rc) return rc;
@@ -800,6 +825,11 @@ int cps_resident(int ch, bool single_expert, int M, int n_e) {
   return std::min(cps, ceil_div(ch, std::min(DOWN_SLOTS, ceil_div(single_expert ? 1024 : 512, per_slot))));
 }
 
+// The same for the streamed parts of the routed bf16 experts, which a launch takes one at a time: a part of few chunks, whose copy
+// takes less than the launches around it, as many slots as it has chunks (192 columns of d_model 256: one block of 3 chunks
+// took 11.7 us); a larger one hides behind the link.
+int cps_streamed(int ch, bool single_expert, int M) { return ch <= 8 ? 1 : cps_of(ch, single_expert, M); }
+
 // Rows handed to the host and its results are moved by kernels up to this size, above by the copy engine (whose start
 // costs as much as some 256 KB on the link).
 constexpr size_t HANDOFF_DIRECT_BYTES = 256 << 10;
@@ -820,7 +850,7 @@ int prefetch_cg(si_layer* N, int path) {
   if (!dense && !shared) return SI_OK;
   HIP_TRY(hipSetDevice(N->device));
   const int n_cg = dense ? N->ch_cg : N->sch_cg, n_cc = dense ? N->ch_cc : N->sch_cc;
-  const int piece_max = piece_chunks(N, path, cps_of(n_cg, true, N->M));
+  const int piece_max = piece_chunks(N, path, dense && !N->q4 ? cps_streamed(n_cg, true, N->M) : cps_of(n_cg, true, N->M));
   const uint16_t* hbase = dense ? N->h_routed : N->h_shared;
   N->pre_segs.clear();
   N->pre_ev_used = 0;
@@ -954,8 +984,8 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
   // (whole-expert placement: every routed expert has H/64 chunks wherever it lives)
   const bool one = E == 1;
   const int cps_gg = L->placed ? cps_of(L->H / CHUNK_J, one, M) : L->q4 ? cps_of(L->ch_gg, one, M) : cps_resident(L->ch_gg, one, M, k),
-            cps_cg = cps_of(L->placed ? L->H / CHUNK_J : L->ch_cg, one, M),
-            cps_cc = cps_of(L->placed ? L->H / CHUNK_J : L->ch_cc, one, M);
+            cps_cg = L->placed || L->q4 ? cps_of(L->placed ? L->H / CHUNK_J : L->ch_cg, one, M) : cps_streamed(L->ch_cg, one, M),
+            cps_cc = L->placed || L->q4 ? cps_of(L->placed ? L->H / CHUNK_J : L->ch_cc, one, M) : cps_streamed(L->ch_cc, one, M);
   const int scps_gg = cps_of(L->sch_gg, true, M), scps_cg = cps_of(L->sch_cg, true, M), scps_cc = cps_of(L->sch_cc, true, M);
   const size_t slot_stride = (size_t)L->rows_dec * M;
   // k-splits of the prefill down projection: enough blocks to fill 256 CUs when there are few row tiles
@@ -1111,6 +1141,8 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
 
   // ---- CG and CG' parts: copy (Stream-C) double-buffered against compute (Stream-D)
   if (any_cg || need_cgp) {
+    const size_t resident = ((size_t)std::min(E, T * k) * L->ch_gg + L->sch_gg) * ce * 2;  // (at most)
+    const size_t direct_max = resident > DIRECT_RESIDENT_BYTES ? 0 : E > 1 ? DIRECT_COPY_BYTES_MOE : DIRECT_COPY_BYTES;
     const bool shared_first = L->pre_n > 0 && L->pre_shared;  // its first pieces are already in the ring
     for (int ei = 0; ei < EX; ++ei) {
       const int e = !shared_first ? ei : ei == 0 ? E : ei - 1;
@@ -1127,8 +1159,26 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
         const int piece_max = piece_chunks(L, path, cps);
         for (int c = 0; c < pn; c += piece_max) {
           const int n = std::min(piece_max, pn - c);
+          const size_t bytes = (size_t)n * ce * 2;
+          const bool ahead = part == 1 && sh == L->pre_shared && c / piece_max < L->pre_n;
+          if (path == SI_DECODE && !ahead && bytes <= direct_max) {
+            {
+              SegScope sc(L, stream, SEG_COPY);
+              const int n16 = (int)(bytes / 16);
+              hipLaunchKernelGGL(k_copy_piece, dim3(std::min(256, (n16 + 255) / 256)), dim3(256), 0, stream,
+                                 reinterpret_cast<const uint4*>(hbase + (size_t)(pc0 + c) * ce), reinterpret_cast<uint4*>(L->d_direct), n16);
+              HIP_TRY(hipGetLastError());
+            }
+            L->in_staged = 1;
+            int rc = run_part(L->d_direct, 0, sh ? 0 : e, sh, 0, n, (pc0 + c) * CHUNK_J, part, c, x2_only, false, no_ws);
+            L->in_staged = 0;
+            if (rc) return rc;
+            st.bytes_streamed += (double)bytes;
+            st.n_copies++;
+            continue;
+          }
           int slot;
-          if (part == 1 && sh == L->pre_shared && c / piece_max < L->pre_n) {
+          if (ahead) {
             slot = L->pre_slot[c / piece_max];  // already on its way (prefetched after the previous layer's copies)
           } else {
             slot = (int)(L->piece_counter++ % L->n_stage);
