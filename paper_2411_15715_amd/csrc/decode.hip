@@ -25,12 +25,6 @@ constexpr int DN_THREADS = 256;
 __device__ inline float bf_lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ inline float bf_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
 
-__device__ inline float wave_sum(float v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, WAVE);
-  return v;
-}
-
 // Token assignment of a few tokens inside a block (FusedRoute): the same result as route.hip's kernels, derived
 // by every block for itself.  Pairs q = t*k + s in ascending order; the expert-sorted row of pair q is the number of
 // pairs with a smaller expert plus the number of earlier pairs with the same expert (stable), which for at most
@@ -282,16 +276,22 @@ __global__ __launch_bounds__(GU_THREADS, 4) void k_decode_gateup(const uint16_t*
         fma_step(c);
       }
     }
+    // column j of row tb: gate and up sums side by side in two lane rows (wave_sums)
 #pragma unroll
-    for (int j = 0; j < GU_JPW; ++j)
+    for (int tb = 0; tb < TB; ++tb) {
+      float v[2 * GU_JPW];
 #pragma unroll
-      for (int tb = 0; tb < TB; ++tb) {
-        if (tb < nt) {
-          float g = wave_sum(ag[j][tb]);
-          float u = wave_sum(au[j][tb]);
-          if (lane == 0) h[(size_t)(rb + tb) * ldh + jcol + j] = silu_f(g) * u;
+      for (int j = 0; j < GU_JPW; ++j) { v[2 * j] = ag[j][tb]; v[2 * j + 1] = au[j][tb]; }
+      wave_sums(v);
+      if (tb < nt) {
+#pragma unroll
+        for (int g = 0; g < GU_JPW / 2; ++g) {
+          // lanes 0, 16: gate of columns 2g, 2g + 1; lanes 32, 48: up
+          const float u = __uint_as_float(__builtin_amdgcn_permlane32_swap(__float_as_uint(v[g]), __float_as_uint(v[g]), false, false)[1]);
+          if (lane == 0 || lane == 16) h[(size_t)(rb + tb) * ldh + jcol + 2 * g + (lane >> 4)] = silu_f(v[g]) * u;
         }
       }
+    }
   }
 }
 
@@ -364,40 +364,57 @@ __global__ __launch_bounds__(DN_THREADS, 5) void k_decode_down(const float* __re
   }
 }
 
-// One thread per 4 output columns of one token.  The slot partials of a row are independent loads
-// (issued together, then summed in slot order, so the result is deterministic).
-__global__ __launch_bounds__(64) void k_decode_combine(DecodeCombineArgs a, Plan p, float* __restrict__ y) {
-  const int t = blockIdx.y;
-  const int m4 = blockIdx.x * 64 + threadIdx.x;
-  if (m4 * 4 >= a.M) return;
-  const bool is_x2 = t >= a.n_x1;
+// One lane per 4 output columns of one token, one wave per term (a routed expert of the token, the shared one), up to
+// MERGE_WAVES at a time; the first wave then adds the terms in their order.  The slot partials of a row are independent loads
+// (issued together, then summed in slot order, so the result is deterministic).  With the terms one after the other in one wave the
+// merge of 4 tokens, 8 + 1 terms of 5 slots took 10.4 us, now 6.7 us.
+constexpr int MERGE_WAVES = 8;
+__global__ __launch_bounds__(64 * MERGE_WAVES) void k_decode_combine(DecodeCombineArgs a, Plan p, float* __restrict__ y) {
+  __shared__ float4 s_term[MERGE_WAVES][64];
+  __shared__ float s_w[MERGE_WAVES];
+  const int t = blockIdx.y, lane = threadIdx.x % 64, wid = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), n_waves = blockDim.x / 64;
+  const int m4 = blockIdx.x * 64 + lane;
+  const bool in = m4 * 4 < a.M, is_x2 = t >= a.n_x1;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   const int n_terms = a.k + (a.has_shared ? 1 : 0);
-  for (int s = 0; s < n_terms; ++s) {
-    int row;
-    float wgt;
-    if (s < a.k) { row = row_of_pair(p, t * a.k + s); wgt = weight_of_pair(p, t * a.k + s); }
-    else { row = a.T * a.k + t; wgt = 1.f; }
-    const int n_part[3] = {s < a.k ? a.n_slots_gg : a.s_slots_gg, s < a.k ? a.n_slots_cg : a.s_slots_cg,
-                           is_x2 ? (s < a.k ? a.n_slots_cc : a.s_slots_cc) : 0};
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int s0 = 0; s0 < n_terms; s0 += n_waves) {
+    const int s = s0 + wid;
+    if (s < n_terms) {
+      const int row = s < a.k ? row_of_pair(p, t * a.k + s) : a.T * a.k + t;
+      const float wgt = s < a.k ? weight_of_pair(p, t * a.k + s) : 1.f;
+      const int n_part[3] = {s < a.k ? a.n_slots_gg : a.s_slots_gg, s < a.k ? a.n_slots_cg : a.s_slots_cg,
+                             is_x2 ? (s < a.k ? a.n_slots_cc : a.s_slots_cc) : 0};
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (in) {
 #pragma unroll
-    for (int part = 0; part < 3; ++part) {
-      const float* base = a.part + (size_t)(part * DOWN_SLOTS) * a.slot_stride + (size_t)row * a.M;
-      // eight slots at a time: their loads are issued together, then added in slot order
-      for (int q0 = 0; q0 < n_part[part]; q0 += 8) {
-        float4 tmp[8];
+        for (int part = 0; part < 3; ++part) {
+          const float* base = a.part + (size_t)(part * DOWN_SLOTS) * a.slot_stride + (size_t)row * a.M;
+          // eight slots at a time: their loads are issued together, then added in slot order
+          for (int q0 = 0; q0 < n_part[part]; q0 += 8) {
+            float4 tmp[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q)
-          tmp[q] = q0 + q < n_part[part] ? reinterpret_cast<const float4*>(base + (size_t)(q0 + q) * a.slot_stride)[m4]
-                                         : make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int q = 0; q < 8; ++q)
+              tmp[q] = q0 + q < n_part[part] ? reinterpret_cast<const float4*>(base + (size_t)(q0 + q) * a.slot_stride)[m4]
+                                             : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-        for (int q = 0; q < 8; ++q) { v.x += tmp[q].x; v.y += tmp[q].y; v.z += tmp[q].z; v.w += tmp[q].w; }
+            for (int q = 0; q < 8; ++q) { v.x += tmp[q].x; v.y += tmp[q].y; v.z += tmp[q].z; v.w += tmp[q].w; }
+          }
+        }
       }
+      s_term[wid][lane] = v;
+      if (lane == 0) s_w[wid] = wgt;
     }
-    acc.x = fmaf(wgt, v.x, acc.x); acc.y = fmaf(wgt, v.y, acc.y);
-    acc.z = fmaf(wgt, v.z, acc.z); acc.w = fmaf(wgt, v.w, acc.w);
+    __syncthreads();
+    if (wid == 0)
+      for (int i = 0; i < min(n_waves, n_terms - s0); ++i) {
+        const float4 v = s_term[i][lane];
+        const float wgt = s_w[i];
+        acc.x = fmaf(wgt, v.x, acc.x); acc.y = fmaf(wgt, v.y, acc.y);
+        acc.z = fmaf(wgt, v.z, acc.z); acc.w = fmaf(wgt, v.w, acc.w);
+      }
+    if (s0 + n_waves < n_terms) __syncthreads();
   }
+  if (wid != 0 || !in) return;
   if (!is_x2 && a.ycc) {
     const float4 c = reinterpret_cast<const float4*>(a.ycc + (size_t)t * a.M)[m4];
     acc.x += c.x; acc.y += c.y; acc.z += c.z; acc.w += c.w;
@@ -456,7 +473,8 @@ hipError_t launch_decode_down(const float* h, int ldh, int M, const Plan& plan, 
 hipError_t launch_decode_combine(const DecodeCombineArgs& a, const Plan& plan, float* y, hipStream_t stream) {
   if (a.T <= 0) return hipSuccess;
   dim3 grid((a.M / 4 + 63) / 64, a.T);
-  hipLaunchKernelGGL(k_decode_combine, grid, dim3(64), 0, stream, a, plan, y);
+  const int waves = std::min(MERGE_WAVES, a.k + (a.has_shared ? 1 : 0));
+  hipLaunchKernelGGL(k_decode_combine, grid, dim3(64 * waves), 0, stream, a, plan, y);
   return hipGetLastError();
 }
 

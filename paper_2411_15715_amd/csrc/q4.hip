@@ -174,18 +174,14 @@ __global__ __launch_bounds__(QGU_THREADS, 4) void k_decode_gateup_q4(const uint1
 #pragma unroll
     for (int i = 0; i < QU; ++i)
       if (u0 + i < n_units) use(i, u0 + i);
-    // sum over the 16 pieces; then lanes 0..3 hold the tokens of columns 0..3
+    // sum over the 16 pieces; then lanes 0..3 (gate; 32..35 up) and 16..19 hold the tokens 2g and 2g + 1 of columns 0..3
+    float v[8] = {tg[0], tu[0], tg[1], tu[1], tg[2], tu[2], tg[3], tu[3]};
+    wave_sums<8, 4>(v);
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int d = 4; d < WAVE; d <<= 1) {
-        tg[r] += __shfl_xor(tg[r], d, WAVE);
-        tu[r] += __shfl_xor(tu[r], d, WAVE);
-      }
-    if (lane < 4) {
-#pragma unroll
-      for (int t = 0; t < QGU_TB; ++t)
-        if (t < nt) h[(size_t)(rb + t) * ldh + wv.col0 + (bx / blocks_per_chunk) * CHUNK_J + jj0 + j] = silu_f(tg[t]) * tu[t];
+    for (int g = 0; g < 2; ++g) {
+      const float u = __uint_as_float(__builtin_amdgcn_permlane32_swap(__float_as_uint(v[g]), __float_as_uint(v[g]), false, false)[1]);
+      const int t = 2 * g + (lane >> 4);
+      if ((lane & 15) < 4 && lane < 32 && t < nt) h[(size_t)(rb + t) * ldh + wv.col0 + (bx / blocks_per_chunk) * CHUNK_J + jj0 + j] = silu_f(v[g]) * u;
     }
   }
 }
