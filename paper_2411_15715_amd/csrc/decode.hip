@@ -27,8 +27,7 @@ __device__ inline float bf_hi(uint32_t u) { return __uint_as_float(u & 0xffff000
 
 // Token assignment of a few tokens inside a block (FusedRoute): the same result as route.hip's kernels, derived
 // by every block for itself.  Pairs q = t*k + s in ascending order; the expert-sorted row of pair q is the number of
-// pairs with a smaller expert plus the number of earlier pairs with the same expert (stable), which for at most
-// FUSED_ROUTE_MAX_PAIRS pairs is a loop over all pairs per thread.
+// pairs with a smaller expert plus the number of earlier pairs with the same expert (stable): FewPairs, in one wave.
 struct BlockRoute {
   int32_t idx[FUSED_ROUTE_MAX_PAIRS];
   float w[FUSED_ROUTE_MAX_PAIRS];
@@ -38,43 +37,39 @@ struct BlockRoute {
   int32_t t_off[FUSED_ROUTE_MAX_PAIRS];      // first row of each touched expert
   int32_t t_cnt[FUSED_ROUTE_MAX_PAIRS];
   int32_t n_touched;
-  float sel[FUSED_ROUTE_MAX_T][MAX_EXPERTS];
 };
 
 __device__ inline void block_route(const FusedRoute& fr, BlockRoute& br, const Plan& p, bool write_tables) {
   const int tid = threadIdx.x, lane = tid % WAVE, wid = tid / WAVE;
   const int T = fr.T, E = fr.E, k = fr.k, n_pairs = T * k;
   if (fr.logits) {
-    if (wid < T) topk_token(fr.logits + (size_t)wid * E, E, k, lane, br.idx + wid * k, br.w + wid * k, br.sel[wid]);
+    if (wid < T) topk_token(fr.logits + (size_t)wid * E, E, k, lane, [&](int s, int ex, float w) { br.idx[wid * k + s] = ex; br.w[wid * k + s] = w; });
   } else if (tid < n_pairs) {
     br.idx[tid] = 0;
     br.w[tid] = 1.f;
   }
-  if (tid == 0) br.n_touched = 0;
   __syncthreads();
-  int e = -1, row = 0, cnt = 0, first = 0;
-  if (tid < n_pairs) {
-    e = br.idx[tid];
-    first = 1;
-    for (int q = 0; q < n_pairs; ++q) {
-      const int eq = br.idx[q];
-      row += (eq < e) || (eq == e && q < tid);
-      cnt += eq == e;
-      if (eq == e && q < tid) first = 0;
+  if (wid == 0) {
+    const bool valid = lane < n_pairs;
+    const int e = valid ? br.idx[lane] : 0;
+    const FewPairs few(e, valid);
+    const unsigned long long lt = (1ull << lane) - 1;
+    unsigned long long own, own_first;
+    const int row = few.below(e, few.all, own) + __popcll(own & lt);
+    const bool first = valid && (own & lt) == 0;  // the first pair of its expert writes the expert's entries
+    const unsigned long long firsts = __ballot(first);
+    const int slot = few.below(e, firsts, own_first);
+    if (valid) {
+      br.row[lane] = row;
+      br.row_token[row] = lane / k;
     }
-    br.row[tid] = first;  // (reused as the flag "first pair of its expert" for the next step)
-    br.row_token[row] = tid / k;
-  }
-  if (fr.has_shared && tid < T) br.row_token[n_pairs + tid] = tid;
-  __syncthreads();
-  if (first) {
-    // slot of this expert in the ascending list of touched experts = distinct smaller experts
-    int slot = 0;
-    for (int q = 0; q < n_pairs; ++q) slot += br.row[q] && br.idx[q] < e;
-    br.t_expert[slot] = e;
-    br.t_off[slot] = row;
-    br.t_cnt[slot] = cnt;
-    atomicAdd(&br.n_touched, 1);
+    if (first) {
+      br.t_expert[slot] = e;
+      br.t_off[slot] = row;
+      br.t_cnt[slot] = __popcll(own);
+    }
+    if (fr.has_shared && lane < T) br.row_token[n_pairs + lane] = lane;
+    if (lane == 0) br.n_touched = __popcll(firsts);
   }
   __syncthreads();
   if (!write_tables) return;
@@ -82,7 +77,7 @@ __device__ inline void block_route(const FusedRoute& fr, BlockRoute& br, const P
   const RouteOut& u = fr.user;
   const int EX = E + (fr.has_shared ? 1 : 0);
   if (tid < n_pairs) {
-    const int q = tid;
+    const int q = tid, e = br.idx[q], row = br.row[q];
     p.idx[q] = e; p.w[q] = br.w[q];
     p.perm[row] = q; p.inv[q] = row;
     if (u.idx) u.idx[q] = e;
@@ -91,15 +86,15 @@ __device__ inline void block_route(const FusedRoute& fr, BlockRoute& br, const P
     if (u.inv) u.inv[q] = row;
   }
   for (int r = tid; r < n_pairs + (fr.has_shared ? T : 0); r += GU_THREADS) p.row_token[r] = br.row_token[r];
+  const FewPairs few(lane < n_pairs ? br.idx[lane] : 0, lane < n_pairs);
+  const unsigned long long x1 = __ballot(lane < fr.n_x1 * k);
   for (int ex = tid; ex <= EX; ex += GU_THREADS) {
     int c = 0, c1 = 0, o = 0;
     if (ex < E) {
-      for (int q = 0; q < n_pairs; ++q) {
-        const int eq = br.idx[q];
-        c += eq == ex;
-        c1 += eq == ex && q / k < fr.n_x1;
-        o += eq < ex;
-      }
+      unsigned long long own;
+      o = few.below(ex, few.all, own);
+      c = __popcll(own);
+      c1 = __popcll(own & x1);
     } else if (ex == E && fr.has_shared) {
       c = T; c1 = fr.n_x1; o = n_pairs;
     } else {
