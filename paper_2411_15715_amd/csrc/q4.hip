@@ -65,6 +65,13 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 constexpr int QU = 2;      // units (512 codes per row; 2 KB of gate and up codes per wave) in flight, refilled as they are consumed
                            // (3 and 4 units: 62 and 67 us instead of 55, the registers cost waves)
 constexpr int QGU_TB = 4;  // tokens per pass over the weights
+// LDS of a block: scales [2][32][M / 64], x [tb][2 M bytes], rows of both PADded (the 4 tokens of 4 pieces then cover all banks).  At
+// M = 8192 and 4 tokens the padding would leave one block per compute unit (8192 x 28672: 70 us); without it there are two, and the
+// 16-byte words of a 64-byte piece of x are kept in an order of the token's own, so that 4 tokens of 2 pieces cover all banks: 58.6 us.
+// (Not for all: computing that order costs the smaller calls 0.5 us of 53.)
+constexpr size_t QGU_LDS = 80 * 1024;
+constexpr size_t gateup_lds(int tb, int M, bool pad) { return (size_t)2 * QGU_JPB * (M / 64 + 2 * pad) * 2 + (size_t)tb * (2 * M + 16 * pad); }
+template <bool PAD>
 __global__ __launch_bounds__(QGU_THREADS, 4) void k_decode_gateup_q4(const uint16_t* __restrict__ x, int M, Plan p,
                                                                      int expert_sel, int x2_only, WeightView wv_r, WeightView wv_s,
                                                                      int shared_y, float* __restrict__ h, int ldh, int tb) {
@@ -85,7 +92,7 @@ __global__ __launch_bounds__(QGU_THREADS, 4) void k_decode_gateup_q4(const uint1
   const unsigned char* gq = cb + q4_off_codes(0, M) + (size_t)(jj0 + j) * (M / 2);
   const unsigned char* uq = cb + q4_off_codes(1, M) + (size_t)(jj0 + j) * (M / 2);
   const int n_pieces = M / 32, n_units = (n_pieces + 15) / 16;
-  const int MG = M / 64, GS = MG + 2, xstride = 2 * M + 16;     // (padded: the 4 tokens of 4 pieces then cover all banks)
+  const int MG = M / 64, GS = MG + 2 * PAD, xstride = 2 * M + 16 * PAD;
   uint16_t* s_sc = reinterpret_cast<uint16_t*>(s_q);           // [2][32][GS]
   unsigned char* s_x = s_q + 2 * QGU_JPB * GS * 2;             // [tb][xstride]
   uint32_t mask = 0x000F000Fu, magic = 0x43004300u, m136 = 0xC308C308u;  // (m136: two bf16 values -136)
@@ -135,12 +142,13 @@ __global__ __launch_bounds__(QGU_THREADS, 4) void k_decode_gateup_q4(const uint1
 #pragma unroll
       for (int b = 0; b < XB; ++b) {
         const int i = i0 + b * QGU_THREADS, t = i / M8, c = i - t * M8;
-        if (i < nt * M8) *reinterpret_cast<u32x4*>(s_x + t * xstride + c * 16) = v[b];
+        if (i < nt * M8) *reinterpret_cast<u32x4*>(s_x + t * xstride + (PAD ? c : c ^ (t & 3)) * 16) = v[b];
       }
     }
     __syncthreads();
     // operand rows past the last token repeat it, their results are not read
-    const unsigned char* xrow = s_x + min(j, nt - 1) * xstride;
+    const int xt = min(j, nt - 1);
+    const unsigned char* xrow = s_x + xt * xstride;
     f32x4 tg = {0.f, 0.f, 0.f, 0.f}, tu = tg;
     auto use = [&](int i, int u) {
       const int pp = min(u * 16 + pc, n_pieces - 1);
@@ -149,7 +157,7 @@ __global__ __launch_bounds__(QGU_THREADS, 4) void k_decode_gateup_q4(const uint1
       f32x4 ag = {0.f, 0.f, 0.f, 0.f}, au = ag, as = ag;
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
-        const u32x4 xv = *reinterpret_cast<const u32x4*>(xp + w * 16);
+        const u32x4 xv = *reinterpret_cast<const u32x4*>(xp + (PAD ? w : w ^ xt) * 16);
         const u32x4 cg = expand_codes(wg[i][w], mask, magic), cu = expand_codes(wu[i][w], mask, magic);
 #pragma unroll
         for (int f = 0; f < 2; ++f) {
@@ -401,13 +409,12 @@ __global__ __launch_bounds__(256) void k_dequant_q4(const uint16_t* __restrict__
   }
 }
 
-size_t gateup_lds(int tb, int M) { return (size_t)2 * QGU_JPB * (M / 64 + 2) * 2 + (size_t)tb * (2 * M + 16); }
 size_t down_lds(int tb, int cps) { return (size_t)tb * 3 * (2 * cps * CHUNK_J + 16) + (size_t)cps * tb * 4; }
 constexpr size_t Q4_LDS = 81 * 1024;  // two blocks per compute unit
 
 hipError_t ensure_q4_lds() {
   static hipError_t st = [] {
-    const void* kernels[] = {(const void*)k_decode_gateup_q4, (const void*)k_decode_down_q4};
+    const void* kernels[] = {(const void*)k_decode_gateup_q4<true>, (const void*)k_decode_gateup_q4<false>, (const void*)k_decode_down_q4};
     for (const void* k : kernels) {
       const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)Q4_LDS);
       if (e != hipSuccess) return e;
@@ -425,8 +432,9 @@ hipError_t launch_decode_gateup_q4(const uint16_t* x, int M, const Plan& plan, i
   if (hipError_t e = ensure_q4_lds(); e != hipSuccess) return e;
   const int shared_y = (ws.n_chunks + wv.n_chunks - 1) / wv.n_chunks;
   dim3 grid(wv.n_chunks * (CHUNK_J / QGU_JPB), shared_y + (expert_sel >= 0 ? 1 : max_touched));
-  const int tb = std::max(1, std::min(tb_hint, QGU_TB));  // (80 KB of LDS at most: two blocks per CU)
-  hipLaunchKernelGGL(k_decode_gateup_q4, grid, dim3(QGU_THREADS), gateup_lds(tb, M), stream, x, M, plan, expert_sel, x2_only, wv, ws, shared_y, h, ldh, tb);
+  const int tb = std::max(1, std::min(tb_hint, QGU_TB));
+  const bool pad = gateup_lds(tb, M, true) <= QGU_LDS;
+  hipLaunchKernelGGL(pad ? k_decode_gateup_q4<true> : k_decode_gateup_q4<false>, grid, dim3(QGU_THREADS), gateup_lds(tb, M, pad), stream, x, M, plan, expert_sel, x2_only, wv, ws, shared_y, h, ldh, tb);
   return hipGetLastError();
 }
 
