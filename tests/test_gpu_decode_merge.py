@@ -28,3 +28,20 @@ def test_merge_terms(oracle, d_model, k, d_ff_shared, place):
             assert_parity(L.forward(xb, lg, mode=si.SI_DECODE), yo, tol=1e-4 if place[2] == 0 else 1e-3)
     finally:
         L.close()
+
+
+@pytest.mark.parametrize("k,d_ff_shared", [(1, 0), (3, 512), (4, 0), (5, 512), (9, 128)])
+def test_prompt_merge_terms(oracle, k, d_ff_shared):
+    """The prompt-phase merge, four terms at a time, over one to four slabs of each kind; bf16 activations: the usual tolerance."""
+    cfg = synth.scaled(synth.CONFIGS["qwen_moe"], d_model=320, d_ff=512, d_ff_shared=d_ff_shared, n_experts=12, top_k=k, seed=60 + k)
+    w = synth.make_weights(cfg)
+    L = GpuLayer(cfg, w, (1.0, 0.0, 0.0), max_tokens=64)
+    try:
+        for T in (3, 64):
+            xp = synth.make_tokens(cfg, T)
+            lg = synth.make_router_logits(cfg, xp)
+            sh = (w["s_gate"], w["s_up"], w["s_down"]) if d_ff_shared else None
+            yo = oracle.layer_forward(xp, w["w_gate"], w["w_up"], w["w_down"], logits=lg, top_k=k, shared=sh)
+            assert_parity(L.forward(xp, lg, mode=si.SI_PREFILL), yo)
+    finally:
+        L.close()
