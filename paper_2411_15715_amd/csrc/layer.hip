@@ -144,11 +144,16 @@ struct WeightSource {
       repack_chunks_q4(qg + qo, qu + qo, qd + qo, zg + zo, zu + zo, zd + zdo, M, c, c + 1, dst);
     }
   }
+  bool wide_scales(int E, int H, int Hs, int M) const;
 };
 
 void parallel_for(int n, int n_threads, const std::function<void(int)>& fn) {
   if (n <= 0) return;
   n_threads = std::max(1, std::min(n_threads, n));
+  if (n_threads == 1) {
+    for (int j = 0; j < n; ++j) fn(j);
+    return;
+  }
   std::atomic<int> next{0};
   std::vector<std::thread> th;
   for (int i = 0; i < n_threads; ++i)
@@ -162,6 +167,21 @@ void parallel_for(int n, int n_threads, const std::function<void(int)>& fn) {
   for (auto& t : th) t.join();
 }
 
+// some scale is 2^117 or more, infinite or NaN
+bool WeightSource::wide_scales(int E, int H, int Hs, int M) const {
+  struct { const uint16_t* z; size_t n; } arrays[6] = {{zg, (size_t)E * H * (M / 64)},  {zu, (size_t)E * H * (M / 64)},  {zd, (size_t)E * (H / 64) * M},
+                                                       {szg, (size_t)Hs * (M / 64)}, {szu, (size_t)Hs * (M / 64)}, {szd, (size_t)(Hs / 64) * M}};
+  constexpr size_t SPAN = 1 << 20;
+  std::atomic<bool> wide{false};
+  for (const auto& a : arrays)
+    parallel_for((int)((a.n + SPAN - 1) / SPAN), (int)std::min(16u, std::max(1u, std::thread::hardware_concurrency())), [&](int i) {
+      uint16_t most = 0;
+      for (size_t q = i * SPAN; q < std::min(a.n, (i + 1) * SPAN); ++q) most = std::max<uint16_t>(most, a.z[q] & 0x7fff);
+      if (most >= Q4_WIDE_BITS) wide = true;
+    });
+  return wide;
+}
+
 }  // namespace
 
 struct si_layer {
@@ -170,7 +190,7 @@ struct si_layer {
   int n_gg = 0, n_cg = 0, n_cc = 0, s_gg = 0, s_cg = 0, s_cc = 0;          // columns
   int ch_gg = 0, ch_cg = 0, ch_cc = 0, sch_gg = 0, sch_cg = 0, sch_cc = 0;  // chunks
   size_t ce = 0;                                                            // uint16 units per chunk
-  int q4 = 0;                                                               // 4-bit storage form
+  int q4 = 0;                                                               // 4-bit storage form (as WeightView::q4)
   // whole-expert placement: place[e] in {0 GG, 1 CG, 2 CC}; every routed expert keeps all its H/64 chunks in one
   // place.  ch_gg / ch_cg / ch_cc then hold H/64 when any expert is placed there (else 0), so that everything
   // sized from them (staging, slots, workers) stays valid; per-expert counts come from e_chunks().
@@ -505,7 +525,7 @@ int create_impl(const si_layer_desc_t* desc, const WeightSource& src, const uint
     L->ch_gg = n_place[0] ? Hch : 0; L->ch_cg = n_place[1] ? Hch : 0; L->ch_cc = n_place[2] ? Hch : 0;
     L->n_gg = L->ch_gg * CHUNK_J; L->n_cg = L->ch_cg * CHUNK_J; L->n_cc = L->ch_cc * CHUNK_J;
   }
-  L->q4 = src.q4 ? 1 : 0;
+  L->q4 = !src.q4 ? 0 : src.wide_scales(L->E, L->H, L->Hs, L->M) ? Q4_WIDE : 1;
   L->ce = src.q4 ? q4_chunk_u16(L->M) : chunk_elems(L->M);
   const int M = L->M, E = L->E, k = L->k, T = L->max_T;
   const size_t ce = L->ce;

@@ -558,24 +558,32 @@ __device__ inline void load_lds4(const void* base, uint32_t off, unsigned char* 
   __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)((gchar*)base + off), SI_LPTR(l), 4, 0, 0);
 }
 
-// The 8 codes of a word as (c - 8) * scale in fp32, exact (scales below 2^117): f[2i], f[2i + 1] of nibbles i, i + 4.  A nibble
-// inserted into 0x6400 is the fp16 value 1024 + c at bit 0 and 1024 + 16 c at bit 4, which one mixed multiply-add turns into
-// the product: 13 instructions and 4 for the rounding to bf16 (21 with c - 8 formed first, 617 against 605 us for 777 tokens
-// over 8 experts of 14336; 23 by byte conversions).
-struct ScaledCodes {
+// The 8 codes of a word as (c - 8) * scale in fp32, exact: f[2i], f[2i + 1] of nibbles i, i + 4.  A nibble inserted into 0x6400 is
+// the fp16 value 1024 + c at bit 0 and 1024 + 16 c at bit 4, which one mixed multiply-add turns into the product: 13 instructions
+// and 4 for the rounding to bf16 (21 with c formed first, 617 against 605 us for 777 tokens over 8 experts of 14336; 23 by byte
+// conversions).  1032 times a scale of 2^117 or more may overflow: WIDE forms c first, and c * scale - 8 scale is good to 2^125.
+// A layer that holds such a scale takes the WIDE kernels (WeightView::q4), whose results are the same.
+template <bool WIDE> struct ScaledCodes {
   uint32_t lo = 0x000F000Fu, hi = 0x00F000F0u, magic = 0x64006400u;
   __device__ __forceinline__ void hide() { asm volatile("" : "+v"(lo), "+v"(hi), "+s"(magic)); }  // (one and-or instruction each)
   __device__ __forceinline__ void operator()(uint32_t w, float s, float (&f)[8]) const {
-    const float s16 = s * 0.0625f, c1 = s * -1032.f, c2 = s * -72.f;
+    const float s_hi = WIDE ? s : s * 0.0625f, c_lo = s * (WIDE ? -8.f : -1032.f), c_hi = s * (WIDE ? -8.f : -72.f);
     const uint32_t w8 = w >> 8;
-    const f16x2 a = __builtin_bit_cast(f16x2, (w & lo) | magic), b = __builtin_bit_cast(f16x2, (w & hi) | magic);
-    const f16x2 c = __builtin_bit_cast(f16x2, (w8 & lo) | magic), d = __builtin_bit_cast(f16x2, (w8 & hi) | magic);
+    f16x2 a = __builtin_bit_cast(f16x2, (w & lo) | magic), b = __builtin_bit_cast(f16x2, (w & hi) | magic);
+    f16x2 c = __builtin_bit_cast(f16x2, (w8 & lo) | magic), d = __builtin_bit_cast(f16x2, (w8 & hi) | magic);
+    if constexpr (WIDE) {
+      const f16x2 base = {(_Float16)1024.f, (_Float16)1024.f}, sixteenth = {(_Float16)0.0625f, (_Float16)0.0625f};
+      a -= base;
+      b = (b - base) * sixteenth;
+      c -= base;
+      d = (d - base) * sixteenth;
+    }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      f[h] = __builtin_fmaf((float)a[h], s, c1);
-      f[2 + h] = __builtin_fmaf((float)b[h], s16, c2);
-      f[4 + h] = __builtin_fmaf((float)c[h], s, c1);
-      f[6 + h] = __builtin_fmaf((float)d[h], s16, c2);
+      f[h] = __builtin_fmaf((float)a[h], s, c_lo);
+      f[2 + h] = __builtin_fmaf((float)b[h], s_hi, c_hi);
+      f[4 + h] = __builtin_fmaf((float)c[h], s, c_lo);
+      f[6 + h] = __builtin_fmaf((float)d[h], s_hi, c_hi);
     }
   }
 };
@@ -992,7 +1000,7 @@ __global__ __launch_bounds__(THREADS, 1) void k_prefill_down(const uint16_t* __r
 // The same two GEMMs on weights in the 4-bit storage form (chunk layout in cc_worker.h), converted on the way
 // into the B stage.  Tiles, LDS layouts, fragment reads, matrix instructions and epilogues are those above.
 // ---------------------------------------------------------------------------------------------
-template <class P, class Take>
+template <class P, bool WIDE, class Take>
 __device__ __forceinline__ void gateup_body_q4(const uint16_t* __restrict__ x, int M, const Plan& p, int tc, const TileInfo& ti,
                                                const WeightView& wv, uint16_t* __restrict__ hact, int ldh, unsigned char* lds, Take take) {
   const int tid = thread_of_item(), lane = tid % WAVE, w = __builtin_amdgcn_readfirstlane(tid / WAVE);  // wave index, known to be uniform
@@ -1025,7 +1033,7 @@ __device__ __forceinline__ void gateup_body_q4(const uint16_t* __restrict__ x, i
   };
   auto scale = [&](uint32_t word, int kt) { return __uint_as_float((z_row + kt) & 1 ? word & 0xffff0000u : word << 16); };
   const uint32_t brow = (uint32_t)(w * 32 + (lane >> 1)), b_dst = brow * 128 + (((kh * 4) ^ ((brow >> 1) & 7)) << 4);
-  ScaledCodes codes_of;
+  ScaledCodes<WIDE> codes_of;
   codes_of.hide();
   // a word holds elements 8i .. 8i+7 of the half row: nibbles p and p + 4 are elements 2p, 2p + 1 (cc_worker.h)
   auto conv = [&](unsigned char* stage, uint32_t word, float sc, int i) {
@@ -1040,6 +1048,7 @@ __device__ __forceinline__ void gateup_body_q4(const uint16_t* __restrict__ x, i
   gateup_store<P::FA, 4>(acc, ti, wv, 2 * tc + (wc >> 1), tc * 128 + wc * 32, wr, lane, hact, ldh);
 }
 
+template <bool WIDE>
 __global__ __launch_bounds__(THREADS, 1) void k_prefill_gateup_q4(const uint16_t* __restrict__ x, int M, Plan p,
                                                                   int expert_sel, int x2_only,
                                                                   int n_ctiles, WeightView wv_r, WeightView wv_s,
@@ -1055,13 +1064,13 @@ __global__ __launch_bounds__(THREADS, 1) void k_prefill_gateup_q4(const uint16_t
     const int ldh = ti.sh ? ldh_s : ldh_r;
     uint16_t* hact = hact_r + (ti.sh ? hact_s : 0);
     if (!storage_index(wv, ti.e, ti.se) || (halves == 2 && !half_rows(ti, half))) return take();
-#define SI_CALL_GU(FAV) gateup_body_q4<RingQ<FAV>>(x, scalar_of_item(M), p, tc, ti, wv, hact, ldh, lds, take_)
+#define SI_CALL_GU(FAV) gateup_body_q4<RingQ<FAV>, WIDE>(x, scalar_of_item(M), p, tc, ti, wv, hact, ldh, lds, take_)
     SI_PICK_BODY_2PASS(ti, SI_CALL_GU)
 #undef SI_CALL_GU
   });
 }
 
-template <class P, class Take>
+template <class P, bool WIDE, class Take>
 __device__ __forceinline__ void down_body_q4(const uint16_t* __restrict__ hact, int ldh, int M, const DownRange& dr, const TileInfo& ti,
                                              const WeightView& wv, float* __restrict__ yp, size_t slab_stride, int accumulate,
                                              unsigned char* lds, Take take) {
@@ -1098,7 +1107,7 @@ __device__ __forceinline__ void down_body_q4(const uint16_t* __restrict__ hact, 
     load_lds4(cb + q4_off_scales(2, M), (uint32_t)n / 2 * 4, slot + 1024);
   };
   auto scale = [&](uint32_t word, int) { return __uint_as_float(n & 1 ? word & 0xffff0000u : word << 16); };
-  ScaledCodes codes_of;
+  ScaledCodes<WIDE> codes_of;
   codes_of.hide();
   // a word holds hidden columns 8i .. 8i+7 of the half: nibbles p and p + 4 are elements (0, 2), (4, 6), (1, 3), (5, 7) (cc_worker.h)
   auto conv = [&](unsigned char* stage, uint32_t word, float sc, int i) {
@@ -1122,6 +1131,7 @@ __device__ __forceinline__ void down_body_q4(const uint16_t* __restrict__ hact, 
   }
 }
 
+template <bool WIDE>
 __global__ __launch_bounds__(THREADS, 1) void k_prefill_down_q4(const uint16_t* __restrict__ hact_r, int ldh_r, int M, Plan p,
                                                                 int expert_sel, int x2_only,
                                                                 int n_ntiles, int split_r, WeightView wv_r, WeightView wv_s,
@@ -1139,7 +1149,7 @@ __global__ __launch_bounds__(THREADS, 1) void k_prefill_down_q4(const uint16_t* 
     const uint16_t* hact = hact_r + (ti.sh ? hact_s : 0);
     const DownRange dr = down_range(inner, n_ntiles, n_split, wv.n_chunks);
     if (!storage_index(wv, ti.e, ti.se) || (halves == 2 && !half_rows(ti, half))) return take();
-#define SI_CALL_DN(FAV) down_body_q4<RingQ<FAV>>(hact, ldh, scalar_of_item(M), dr, ti, wv, yp, slab_stride, accumulate, lds, take_)
+#define SI_CALL_DN(FAV) down_body_q4<RingQ<FAV>, WIDE>(hact, ldh, scalar_of_item(M), dr, ti, wv, yp, slab_stride, accumulate, lds, take_)
     SI_PICK_BODY_2PASS(ti, SI_CALL_DN)
 #undef SI_CALL_DN
   });
@@ -1214,8 +1224,8 @@ __global__ void k_fill_zero(float* __restrict__ p, size_t n, size_t slab_stride)
 
 static hipError_t ensure_lds_attr() {
   static hipError_t st = [] {
-    const void* kernels[] = {(const void*)k_prefill_gateup, (const void*)k_prefill_down, (const void*)k_prefill_gateup_q4,
-                             (const void*)k_prefill_down_q4};
+    const void* kernels[] = {(const void*)k_prefill_gateup, (const void*)k_prefill_down, (const void*)k_prefill_gateup_q4<false>,
+                             (const void*)k_prefill_down_q4<false>, (const void*)k_prefill_gateup_q4<true>, (const void*)k_prefill_down_q4<true>};
     for (const void* k : kernels) {
       hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, KERNEL_LDS + NEXT_LDS);
       if (e != hipSuccess) return e;
@@ -1240,7 +1250,7 @@ hipError_t launch_prefill_gateup(const uint16_t* x, int M, const Plan& plan, int
   if (e != hipSuccess) return e;
   const int n_ctiles = (wv.n_chunks + 1) / 2;
   if (wv.q4)
-    hipLaunchKernelGGL(k_prefill_gateup_q4, dim3(N_XCD * XCD_CU), dim3(THREADS), KERNEL_LDS + NEXT_LDS, stream, x, M, plan, expert_sel, x2_only,
+    hipLaunchKernelGGL(wv.q4 == Q4_WIDE ? k_prefill_gateup_q4<true> : k_prefill_gateup_q4<false>, dim3(N_XCD * XCD_CU), dim3(THREADS), KERNEL_LDS + NEXT_LDS, stream, x, M, plan, expert_sel, x2_only,
                        n_ctiles, wv, sp.wv, hact, ldh, sp.hact, sp.ldh);
   else
     hipLaunchKernelGGL(k_prefill_gateup, dim3(N_XCD * XCD_CU), dim3(THREADS), KERNEL_LDS + NEXT_LDS, stream, x, M, plan, expert_sel, x2_only,
@@ -1256,7 +1266,7 @@ hipError_t launch_prefill_down(const uint16_t* hact, int ldh, int M, const Plan&
   if (e != hipSuccess) return e;
   const int n_ntiles = (M + BN - 1) / BN;
   if (wv.q4)
-    hipLaunchKernelGGL(k_prefill_down_q4, dim3(N_XCD * XCD_CU), dim3(THREADS), KERNEL_LDS + NEXT_LDS, stream, hact, ldh, M, plan, expert_sel,
+    hipLaunchKernelGGL(wv.q4 == Q4_WIDE ? k_prefill_down_q4<true> : k_prefill_down_q4<false>, dim3(N_XCD * XCD_CU), dim3(THREADS), KERNEL_LDS + NEXT_LDS, stream, hact, ldh, M, plan, expert_sel,
                        x2_only, n_ntiles, n_split, wv, sp.wv, sp.ldh, sp.hact, sp.split, yp, slab_stride, accumulate);
   else
     hipLaunchKernelGGL(k_prefill_down, dim3(N_XCD * XCD_CU), dim3(THREADS), KERNEL_LDS + NEXT_LDS, stream, hact, ldh, M, plan, expert_sel,

@@ -81,6 +81,9 @@ hipError_t launch_route(const float* logits, int T, int E, int k, int has_shared
 hipError_t launch_handoff(const Plan& plan, const uint16_t* x, size_t x_bytes, int n_pairs, int EX, uint16_t* hx, int32_t* hidx,
                           float* hw, int32_t* hcount, hipStream_t stream);
 
+constexpr int Q4_WIDE = 2;
+constexpr int Q4_WIDE_BITS = (127 + 117) << 7;  // bf16 bits of 2^117 (also below those of infinity and NaN)
+
 // Description of the weights one kernel launch works on.
 struct WeightView {
   const uint16_t* base;   // chunk-major storage
@@ -88,7 +91,8 @@ struct WeightView {
   int chunk0;             // first chunk (relative to base / expert) to process
   int n_chunks;           // number of chunks to process
   int col0;               // hidden column (within the expert) of chunk0: indexes h / Hact columns
-  int q4;                 // chunks are in the 4-bit storage form (cc_worker.h); strides still in uint16 units
+  int q4;                 // chunks are in the 4-bit storage form (cc_worker.h); strides still in uint16 units.  Q4_WIDE: with a
+                          // scale of 2^117 or more in the layer
   const int32_t* e_map;   // device [experts] or null: storage index of expert e inside `base` (-1: the expert has
                           // no weights in this storage and the launch skips it); null = expert e is at index e
 };
