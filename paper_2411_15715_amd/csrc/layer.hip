@@ -450,36 +450,47 @@ __global__ __launch_bounds__(256) void k_copy_piece(const uint4* __restrict__ sr
 
 // Staging ring (Stream-C) and host workers, sized independently of the slicing rates so that a layer can be
 // re-sliced without touching them: a decode piece must hold whole down-projection slots of the largest part an
-// expert could have (all of its chunks).
+// expert could have (all of its chunks).  The layer gets the ring whole or not at all.
 int setup_staging(si_layer* L) {
-  if (L->d_stage.empty()) {
-    const size_t stage_bytes = (size_t)(L->desc.stage_mib == 0 ? 256 : L->desc.stage_mib) << 20;
-    const int sc = (int)std::max<size_t>(1, stage_bytes / (L->ce * 2));
-    const int cps_max = std::max({ceil_div(L->H / CHUNK_J, 16), ceil_div(L->Hs / CHUNK_J, 16), 8});  // the largest cps_of() can return
-    L->stage_chunks = std::max(sc, cps_max);
-    L->d_stage.assign(L->n_stage, nullptr);
-    L->ev_ready.assign(L->n_stage, nullptr);
-    L->ev_free.assign(L->n_stage, nullptr);
-    L->slot_used.assign(L->n_stage, 0);
-    {
-      int rc = dev_alloc(&L->d_direct, std::min((L->E > 1 ? DIRECT_COPY_BYTES_MOE : DIRECT_COPY_BYTES) / 2, (size_t)std::max(L->H, L->Hs) / CHUNK_J * L->ce));
-      if (rc) return rc;
-    }
+  if (!L->d_stage.empty()) return SI_OK;
+  const size_t stage_bytes = (size_t)(L->desc.stage_mib == 0 ? 256 : L->desc.stage_mib) << 20;
+  const int sc = (int)std::max<size_t>(1, stage_bytes / (L->ce * 2));
+  const int cps_max = std::max({ceil_div(L->H / CHUNK_J, 16), ceil_div(L->Hs / CHUNK_J, 16), 8});  // the largest cps_of() can return
+  const int chunks = std::max(sc, cps_max);
+  std::vector<uint16_t*> stage(L->n_stage, nullptr);
+  std::vector<hipEvent_t> ready(L->n_stage, nullptr), freed(L->n_stage, nullptr);
+  uint16_t* direct = nullptr;
+  auto allocate = [&]() -> int {
+    int rc = dev_alloc(&direct, std::min((L->E > 1 ? DIRECT_COPY_BYTES_MOE : DIRECT_COPY_BYTES) / 2, (size_t)std::max(L->H, L->Hs) / CHUNK_J * L->ce));
+    if (rc) return rc;
     for (int i = 0; i < L->n_stage; ++i) {
-      int rc = dev_alloc(&L->d_stage[i], (size_t)L->stage_chunks * L->ce);
+      rc = dev_alloc(&stage[i], (size_t)chunks * L->ce);
       if (rc) return rc;
-      HIP_TRY(hipEventCreateWithFlags(&L->ev_ready[i], hipEventDisableTiming));
-      HIP_TRY(hipEventCreateWithFlags(&L->ev_free[i], hipEventDisableTiming));
+      HIP_TRY(hipEventCreateWithFlags(&ready[i], hipEventDisableTiming));
+      HIP_TRY(hipEventCreateWithFlags(&freed[i], hipEventDisableTiming));
     }
+    return SI_OK;
+  };
+  if (const int rc = allocate()) {
+    if (direct) (void)hipFree(direct);
+    for (auto p : stage) if (p) (void)hipFree(p);
+    for (auto e : ready) if (e) (void)hipEventDestroy(e);
+    for (auto e : freed) if (e) (void)hipEventDestroy(e);
+    return rc;
   }
+  L->stage_chunks = chunks;
+  L->d_direct = direct;
+  L->slot_used.assign(L->n_stage, 0);
+  L->ev_ready = std::move(ready);
+  L->ev_free = std::move(freed);
+  L->d_stage = std::move(stage);
   return SI_OK;
 }
 
 int setup_pool(si_layer* L) {
-  if (!L->pool && L->ch_cc + L->sch_cc > 0) {
-    const int hw_threads = (int)std::max(1u, std::thread::hardware_concurrency());
-    L->pool = cc_pool_create(L->desc.cc_threads == 0 ? std::min(16, hw_threads) : L->desc.cc_threads);
-  }
+  if (L->pool) return SI_OK;
+  const int hw_threads = (int)std::max(1u, std::thread::hardware_concurrency());
+  L->pool = cc_pool_create(L->desc.cc_threads == 0 ? std::min(16, hw_threads) : L->desc.cc_threads);
   return SI_OK;
 }
 
@@ -657,7 +668,7 @@ int create_impl(const si_layer_desc_t* desc, const WeightSource& src, const uint
   TRY_OR_DESTROY(pin_alloc(&L->hw, n_pairs));
   TRY_OR_DESTROY(pin_alloc(&L->hcount, (size_t)2 * L->EX));
   TRY_OR_DESTROY(pin_alloc(&L->hycc, (size_t)T * M));
-  TRY_OR_DESTROY(setup_pool(L));
+  if (L->ch_cc + L->sch_cc > 0) TRY_OR_DESTROY(setup_pool(L));
   HIP_OR_DESTROY(hipDeviceSynchronize());
   *out = L;
   return SI_OK;
@@ -768,12 +779,12 @@ int si_layer_resplit(si_layer_t* L, float r_gg, float r_cg, float r_cc) {
   }
   L->pre_n = 0;
   L->pre_slot.clear();
-  if (L->ch_cc + L->ch_cg + L->sch_cc + L->sch_cg > 0) {
-    const int rc2 = setup_staging(L);
-    if (rc2) return rc2;
-  }
-  const int rc3 = setup_pool(L);
-  return rc ? rc : rc3;
+  // (after the moves, which have given the old buffers back; until these exist, forward calls that need them are refused)
+  if (L->ch_cc + L->ch_cg + L->sch_cc + L->sch_cg > 0)
+    if (const int rc2 = setup_staging(L)) return rc2;
+  if (L->ch_cc + L->sch_cc > 0)
+    if (const int rc3 = setup_pool(L)) return rc3;
+  return rc;
 }
 
 int si_layer_split_info(const si_layer_t* L, int32_t* n_gg, int32_t* n_cg, int32_t* n_cc, int32_t* s_gg, int32_t* s_cg, int32_t* s_cc) {
@@ -864,7 +875,7 @@ int piece_chunks(const si_layer* L, int path, int cps) {
 // layer: its shared expert, which every token uses (which routed experts are streamed is known only after the
 // assignment); the forward call then takes the shared expert first, while the ring still holds the pieces.
 int prefetch_cg(si_layer* N, int path) {
-  if (N->pre_n > 0) return SI_OK;
+  if (N->pre_n > 0 || N->d_stage.empty()) return SI_OK;
   const bool dense = N->E == 1 && !N->has_shared && N->ch_cg > 0;
   const bool shared = N->E > 1 && N->has_shared && N->sch_cg > 0 && !N->placed;
   if (!dense && !shared) return SI_OK;
@@ -930,6 +941,8 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
   const bool need_cgp = any_cc && n_g > 0;   // CG': CC weights on the GPU for X2
   const bool need_counts = (any_cg || need_cgp) && E > 1;  // which experts to stream
   const bool need_sync = need_cc || need_counts;
+  if (((any_cg || need_cgp) && L->d_stage.empty()) || (need_cc && !L->pool))
+    return fail(SI_EHIP, "the layer has host parts but no staging buffers or workers: its re-slicing ran out of memory; re-slice it again");
   const auto wall0 = std::chrono::steady_clock::now();
 
   // Whatever way the call ends, nothing of it may outlive it on the host: on an error return the host workers are

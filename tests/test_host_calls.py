@@ -1,0 +1,110 @@
+"""The library's host logic on a stand-in for the HIP runtime (hip_stub.c: device memory is host memory, kernels are not run): which
+allocations, copies and launches a call makes, and what is left of a layer after a call that fails half-way.  Each test runs in
+a process of its own, which loads the stand-in before the library."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROLOGUE = """
+import ctypes, sys
+sys.path.insert(0, %r)
+stub = ctypes.CDLL(%r, mode=ctypes.RTLD_GLOBAL)
+stub.hip_stub_log.restype = ctypes.c_char_p
+import numpy as np
+import paper_2411_15715_amd as si
+
+def log():
+    out = stub.hip_stub_log().decode().splitlines()
+    stub.hip_stub_clear()
+    return out
+
+def calls(lines, *names):
+    return [l for l in lines if l.split()[0] in names]
+
+def layer(M, H, split, E=1, k=1, Hs=0, max_tokens=64, **kw):
+    w = [np.zeros((E, H, M), np.uint16) for _ in range(3)]
+    s = tuple(np.zeros((Hs, M), np.uint16) for _ in range(3)) if Hs else None
+    return si.si_layer_create(M, H, E, k, *w, *split, max_tokens, d_ff_shared=Hs, shared=s, **kw)
+
+def forward(h, M, T, E=1, n_g=0, mode=si.SI_AUTO):
+    x, y, lg = np.zeros((T, M), np.uint16), np.zeros((T, M), np.float32), np.zeros((T, E), np.float32)
+    stub.hip_stub_rows(T, T - n_g)
+    si.si_layer_forward(h, x.ctypes.data, lg.ctypes.data if E > 1 else None, T, n_g, mode, y.ctypes.data, stream=0)
+
+def attempt(f, *a, **kw):
+    try:
+        f(*a, **kw)
+        return si.SI_OK
+    except si.ScheInferError as e:
+        return e.code
+"""
+
+
+@pytest.fixture(scope="session")
+def host(tmp_path_factory):
+    d = tmp_path_factory.mktemp("hip_stub")
+    so = str(d / "hip_stub.so")
+    subprocess.run(["gcc", "-O1", "-fPIC", "-shared", "-Wall", "-Wextra", "-Werror", "-o", so, os.path.join(ROOT, "tests", "hip_stub.c")], check=True)
+
+    def run(script):
+        r = subprocess.run([sys.executable, "-c", PROLOGUE % (ROOT, so) + textwrap.dedent(script)], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, "exit code %d\n%s\n%s" % (r.returncode, r.stdout[-2000:], r.stderr[-4000:])
+        return r.stdout
+
+    return run
+
+
+@pytest.mark.parametrize("call", ["hipMalloc", "hipHostMalloc", "hipEventCreateWithFlags"])
+def test_resplit_that_runs_out_of_memory_leaves_a_whole_layer(host, call):
+    """Every allocation of a re-slicing that gives a resident layer its first host parts fails once.  Calls on the layer then either work
+    or are refused, and the same re-slicing works when it is tried again; no copy or launch ever names a null buffer."""
+    out = host("""
+    def run(h):
+        codes = [attempt(forward, h, 256, 4, n_g=n_g, mode=mode) for mode in (si.SI_DECODE, si.SI_PREFILL) for n_g in (0, 4)]
+        lines = log()
+        copies = calls(lines, "k_copy_piece", "hipMemcpyAsync")
+        assert not any("(nil) ->" in l or "-> (nil)" in l for l in copies), copies
+        return codes, copies
+
+    n_failed = 0
+    for nth in range(1, 12):
+        h = layer(256, 704, (1.0, 0.0, 0.0))
+        stub.hip_stub_fail(b"%s", nth)
+        rc = attempt(si.si_layer_resplit, h, 0.4, 0.3, 0.3)
+        stub.hip_stub_fail(b"", 0)
+        n_failed += rc != si.SI_OK
+        if rc != si.SI_OK:
+            assert rc in (si.SI_ENOMEM, si.SI_EHIP), rc
+            resident = si.si_layer_split_info(h)["n_gg"] == 704
+            codes, _ = run(h)
+            assert codes == [si.SI_OK if resident else si.SI_EHIP] * 4, (nth, codes)
+            si.si_layer_resplit(h, 0.4, 0.3, 0.3)
+        codes, copies = run(h)
+        assert codes == [si.SI_OK] * 4 and copies, (codes, copies)
+        si.si_layer_destroy(h)
+    print(n_failed)
+    """ % call)
+    assert int(out) >= 1
+
+
+def test_prefetch_to_a_layer_without_staging_buffers(host):
+    """A stack whose second layer ran out of memory while it was re-sliced: the first layer's call does not copy ahead for it, the
+    second's is refused."""
+    host("""
+    a, b = layer(256, 704, (0.4, 0.6, 0.0)), layer(256, 704, (1.0, 0.0, 0.0))
+    stub.hip_stub_fail(b"hipMalloc", 3)
+    assert attempt(si.si_layer_resplit, b, 0.4, 0.6, 0.0) == si.SI_ENOMEM
+    S = si.si_stack_create([a, b])
+    x, y = np.zeros((4, 256), np.uint16), np.zeros((4, 256), np.float32)
+    log()
+    args = (S, x.ctypes.data, None, 4, 0, si.SI_AUTO, y.ctypes.data)
+    assert attempt(si.si_stack_forward, *args, prefetch=1, stream=0) == si.SI_EHIP
+    assert not any("(nil) ->" in l or "-> (nil)" in l for l in log())
+    si.si_layer_resplit(b, 0.4, 0.6, 0.0)
+    si.si_stack_forward(*args, prefetch=1, stream=0)
+    """)
