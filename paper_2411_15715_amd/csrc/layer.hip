@@ -52,10 +52,14 @@ int si::set_error(int code, const char* fmt, ...) {
 
 namespace {
 
+// (the runtime keeps an error until it is asked for: left there, the next call's launch check would report it again)
 #define HIP_TRY(expr)                                                                           \
   do {                                                                                          \
     hipError_t _e = (expr);                                                                     \
-    if (_e != hipSuccess) return fail(SI_EHIP, "%s failed: %s", #expr, hipGetErrorString(_e));  \
+    if (_e != hipSuccess) {                                                                     \
+      (void)hipGetLastError();                                                                  \
+      return fail(SI_EHIP, "%s failed: %s", #expr, hipGetErrorString(_e));                      \
+    }                                                                                           \
   } while (0)
 
 struct Seg { hipEvent_t a, b; int kind; int staged; };  // kind: SI_K_* kernel class, or SEG_COPY
@@ -556,7 +560,7 @@ int create_impl(const si_layer_desc_t* desc, const WeightSource& src, const uint
   }
 
 #define TRY_OR_DESTROY(expr) do { int _rc = (expr); if (_rc) { si_layer_destroy(L); return _rc; } } while (0)
-#define HIP_OR_DESTROY(expr) do { hipError_t _e = (expr); if (_e != hipSuccess) { fail(SI_EHIP, "%s failed: %s", #expr, hipGetErrorString(_e)); si_layer_destroy(L); return SI_EHIP; } } while (0)
+#define HIP_OR_DESTROY(expr) do { hipError_t _e = (expr); if (_e != hipSuccess) { (void)hipGetLastError(); fail(SI_EHIP, "%s failed: %s", #expr, hipGetErrorString(_e)); si_layer_destroy(L); return SI_EHIP; } } while (0)
 
   // ---- placement: GG -> device, CC | CG -> pinned host (CG' aliases the CC range)
   TRY_OR_DESTROY(dev_alloc(&L->d_gg, gg_experts * L->ch_gg * ce));

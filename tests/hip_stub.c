@@ -14,7 +14,7 @@ static char log_text[LOG_BYTES];
 static size_t log_at;
 static char fail_name[64];
 static long fail_nth;
-static int capturing, rows_all, rows_x1;
+static int capturing, rows_all, rows_x1, last_error;
 static struct { const void* host; char name[64]; } kernels[256];
 static int n_kernels;
 static struct { dim3 grid, block; size_t shared; void* stream; } config;
@@ -35,6 +35,7 @@ static int call(const char* name, const char* fmt, ...) {
     va_end(ap);
     log_at += snprintf(log_text + log_at, 64, "%s\n", failed ? " FAILED" : "");
   }
+  if (failed) last_error = FAIL_CODE;
   return failed ? FAIL_CODE : 0;
 }
 
@@ -120,5 +121,5 @@ int hipDeviceGetAttribute(int* v, int a, int d) { (void)a; (void)d; *v = 256; re
 int hipFuncSetAttribute(const void* f, int a, int v) { (void)f; (void)a; (void)v; return 0; }
 int hipFuncGetAttributes(void* a, const void* f) { (void)a; (void)f; return 0; } /* (the library passes zeros) */
 int hipGetSymbolAddress(void** p, const void* s) { (void)s; *p = NULL; return FAIL_CODE; }
-int hipGetLastError(void) { return 0; }
+int hipGetLastError(void) { const int e = last_error; last_error = 0; return e; }
 const char* hipGetErrorString(int e) { return e ? "made to fail" : "no error"; }
