@@ -1112,11 +1112,14 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
     int rc;
     if (path == SI_PREFILL) {
       SegScope sc(L, stream, SI_K_FILL);
-      if (L->queue_dirty) {
+      // The tile queues are clear unless a call has ended between FC1 and its merge.  A recorded call clears them by itself: what
+      // happens to the layer between the recording and a replay is not known to either.  (A runtime that does not say whether it
+      // records counts as one that does: clearing is never wrong.)
+      hipStreamCaptureStatus cs = hipStreamCaptureStatusActive;
+      if (hipStreamIsCapturing(stream, &cs) != hipSuccess) { (void)hipGetLastError(); cs = hipStreamCaptureStatusActive; }
+      if (L->queue_dirty || cs != hipStreamCaptureStatusNone) {
         K_TRY(launch_fill_zero(reinterpret_cast<float*>(L->plan.queue), (size_t)2 * 8 * QUEUE_STRIDE, 1, 0, stream));
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        HIP_TRY(hipStreamIsCapturing(stream, &cs));
-        L->queue_dirty = cs != hipStreamCaptureStatusNone;  // (a recorded launch has cleared nothing yet)
+        if (cs == hipStreamCaptureStatusNone) L->queue_dirty = false;  // (a recorded launch has cleared nothing yet)
       }
       if (L->ch_gg == 0 || L->placed) K_TRY(launch_fill_zero(L->d_yp, (size_t)T * k * M, split_call, L->yp_slab, stream));
       if (L->has_shared && L->sch_gg == 0)

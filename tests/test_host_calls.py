@@ -108,3 +108,52 @@ def test_prefetch_to_a_layer_without_staging_buffers(host):
     si.si_layer_resplit(b, 0.4, 0.6, 0.0)
     si.si_stack_forward(*args, prefetch=1, stream=0)
     """)
+
+
+@pytest.mark.parametrize("failing", ["k_prefill_down", "k_prefill_combine"])
+def test_tile_queues_after_a_call_that_failed(host, failing):
+    """A prompt call that ends between FC1 and its merge leaves the tile counters as FC1 or FC2 left them: the next call clears them
+    before its FC1 launch, once; a decode call in between does not."""
+    host("""
+    h = layer(256, 704, (1.0, 0.0, 0.0))
+    def prompt():
+        stub.hip_stub_clear()
+        rc = attempt(forward, h, 256, 64, mode=si.SI_PREFILL)
+        return rc, [l.split()[0] for l in calls(log(), "k_fill_zero", "k_prefill_gateup", "k_prefill_down", "k_prefill_combine")]
+    usual = (si.SI_OK, ["k_prefill_gateup", "k_prefill_down", "k_prefill_combine"])
+    prompt()
+    assert prompt() == usual
+    stub.hip_stub_fail(b"%s", 1)
+    assert prompt()[0] == si.SI_EHIP
+    forward(h, 256, 4)
+    assert prompt() == (si.SI_OK, ["k_fill_zero"] + usual[1])
+    assert prompt() == usual
+    """ % failing)
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(E=4, k=2), dict(E=4, k=2, Hs=256)])
+def test_a_recorded_prompt_call_clears_its_tile_queues(host, kw):
+    """A graph may be replayed after a call that failed, which no host flag tells it: every recorded prompt call clears the counters
+    itself, before FC1, whatever state the layer is in, and leaves what the host knows of them alone."""
+    host("""
+    kw = %r
+    h = layer(256, 704, (1.0, 0.0, 0.0), **kw)
+    def prompt(capturing):
+        stub.hip_stub_clear()
+        stub.hip_stub_capturing(capturing)
+        rc = attempt(forward, h, 256, 64, E=kw.get("E", 1), mode=si.SI_PREFILL)
+        stub.hip_stub_capturing(0)
+        names = [l.split()[0] for l in calls(log(), "k_fill_zero", "k_prefill_gateup")]
+        assert names[-1] == "k_prefill_gateup" or rc
+        return rc, len(names) - 1
+    prompt(0)
+    assert prompt(0) == (si.SI_OK, 0)
+    assert prompt(1) == (si.SI_OK, 1)
+    assert prompt(1) == (si.SI_OK, 1)
+    assert prompt(0) == (si.SI_OK, 0)
+    stub.hip_stub_fail(b"k_prefill_down", 1)
+    prompt(0)
+    assert prompt(1) == (si.SI_OK, 1)
+    assert prompt(0) == (si.SI_OK, 1)
+    assert prompt(0) == (si.SI_OK, 0)
+    """ % kw)
