@@ -210,7 +210,8 @@ struct si_layer {
   uint16_t* h_shared = nullptr; // pinned [sch_cc + sch_cg] chunks
   int n_stage = 0, stage_chunks = 0;
   std::vector<uint16_t*> d_stage;
-  uint16_t* d_direct = nullptr;  // device: a small piece on its way through the caller's stream
+  uint16_t* d_direct = nullptr;  // device: a small part on its way through the caller's stream
+  size_t direct_bytes = 0;
   std::vector<hipEvent_t> ev_ready, ev_free;
   std::vector<char> slot_used;
   long piece_counter = 0;
@@ -432,13 +433,21 @@ void si_layer_destroy(si_layer_t* L) {
 
 namespace {
 
-// Generation phase: small pieces are copied by a kernel on the caller's stream, which reads the pinned memory over the link at
-// the rate of the copy engine (54 GB/s), in front of the kernels that use it.  A copy on the copy stream is bracketed by two waits
-// between streams, which hold a short call up by longer than the copy takes: 0.4 MB, 256 x 704, 4 tokens, 40/30/30: 94 -> 51 us; dense,
-// one piece of 2.3 / 6.9 / 13.8 / 27 / 54 MB: 156 / 267 / 362 / 584 / 1146 -> 78 / 165 / 293 / 532 / 1021 us.  What the copy stream does
-// better is to overlap: with the resident part (limited to 10 us here), and with the kernels of the piece before, in calls of
-// several experts (16 of them: 20 pieces of 2 MB 590 -> 577 us, of 4 MB 968 -> 955, of 8 MB 1841 -> 1898).
-constexpr size_t DIRECT_COPY_BYTES = (size_t)32 << 20, DIRECT_COPY_BYTES_MOE = (size_t)4 << 20, DIRECT_RESIDENT_BYTES = (size_t)64 << 20;
+// Generation phase: small streamed parts may be copied by a kernel on the caller's stream, which reads the pinned memory over the
+// link at the rate of the copy engine (54 GB/s), in front of the kernels that use them: whole, as one piece.  A copy on the copy stream is
+// bracketed by two waits between streams, 7 to 12 us; what it does better is to overlap with kernels.  So the kernel copies where there
+// is little to overlap with or little to copy, always beside at most 10 us of resident work:
+//  * parts of a dense layer whose host computes a share, and so waits in every call: up to 32 MB.  A host share of an eighth, 3 MB of
+//    d_model 1024 / 4096 / 8192, 4 tokens: 102 / 153 / 208 us in the ring, 93 / 137 / 194 by the kernel; 25 MB 566 / 575 / 572 and 548 / 549 / 552.
+//  * other parts, up to 8 MB of a dense layer, 4 MB of several experts, while their kernels, which the copy of the next part or call
+//    would hide, take less than the waits: by rows x d_model.  Several experts: per part the ring is slower by (us) 9 / 6 / 5 / 2 for 1 / 2 /
+//    4 / 8 rows of d_model 1024, by 6 / 1 / -2 / -9 of 2048, 1 / -8 / -19 / -39 of 8192 (parts of 0.4 to 3 MB); by size, 16 experts, 20 parts
+//    of 4 MB 968 -> 955 us, of 8 MB 1841 -> 1898.  Dense without a host share, in a row (such calls run ahead on the copy stream) /
+//    alone, ring and kernel: 3 MB of d_model 1024, 2 tokens 89 / 104 and 81 / 92; 6 MB of 4096, 1 token 142 / 162 and 137 / 149; 13 MB
+//    243 / 274 and 253 / 264; 3 MB of 8192, 4 tokens 88 / 126 and 116 / 127.
+constexpr size_t DIRECT_COPY_BYTES_WAITING = (size_t)32 << 20, DIRECT_COPY_BYTES_DENSE = (size_t)8 << 20, DIRECT_COPY_BYTES_MOE = (size_t)4 << 20;
+constexpr size_t DIRECT_RESIDENT_BYTES = (size_t)64 << 20;
+constexpr int DIRECT_ROWS_X_MODEL = 6144;
 
 __global__ __launch_bounds__(256) void k_copy_piece(const uint4* __restrict__ src, uint4* __restrict__ dst, int n) {
   constexpr int U = 4;
@@ -463,12 +472,9 @@ int setup_staging(si_layer* L) {
   const int chunks = std::max(sc, cps_max);
   std::vector<uint16_t*> stage(L->n_stage, nullptr);
   std::vector<hipEvent_t> ready(L->n_stage, nullptr), freed(L->n_stage, nullptr);
-  uint16_t* direct = nullptr;
   auto allocate = [&]() -> int {
-    int rc = dev_alloc(&direct, std::min((L->E > 1 ? DIRECT_COPY_BYTES_MOE : DIRECT_COPY_BYTES) / 2, (size_t)std::max(L->H, L->Hs) / CHUNK_J * L->ce));
-    if (rc) return rc;
     for (int i = 0; i < L->n_stage; ++i) {
-      rc = dev_alloc(&stage[i], (size_t)chunks * L->ce);
+      const int rc = dev_alloc(&stage[i], (size_t)chunks * L->ce);
       if (rc) return rc;
       HIP_TRY(hipEventCreateWithFlags(&ready[i], hipEventDisableTiming));
       HIP_TRY(hipEventCreateWithFlags(&freed[i], hipEventDisableTiming));
@@ -476,19 +482,44 @@ int setup_staging(si_layer* L) {
     return SI_OK;
   };
   if (const int rc = allocate()) {
-    if (direct) (void)hipFree(direct);
     for (auto p : stage) if (p) (void)hipFree(p);
     for (auto e : ready) if (e) (void)hipEventDestroy(e);
     for (auto e : freed) if (e) (void)hipEventDestroy(e);
     return rc;
   }
   L->stage_chunks = chunks;
-  L->d_direct = direct;
   L->slot_used.assign(L->n_stage, 0);
   L->ev_ready = std::move(ready);
   L->ev_free = std::move(freed);
   L->d_stage = std::move(stage);
   return SI_OK;
+}
+
+// Resident weights that a call of `pairs` (token, expert) pairs reads, at most.
+size_t resident_bytes(const si_layer* L, int pairs) {
+  return ((size_t)std::min(L->E, pairs) * L->ch_gg + L->sch_gg) * L->ce * 2;
+}
+// Largest part that may be copied by the kernel (0: none): `rows` rows of it are used, `pairs` pairs in the call, for a share of
+// which the host waits or not.
+size_t direct_limit(const si_layer* L, int rows, int pairs, bool waits) {
+  if (resident_bytes(L, pairs) > DIRECT_RESIDENT_BYTES) return 0;
+  if (L->EX == 1 && waits) return DIRECT_COPY_BYTES_WAITING;
+  return rows * L->M > DIRECT_ROWS_X_MODEL ? 0 : L->EX == 1 ? DIRECT_COPY_BYTES_DENSE : DIRECT_COPY_BYTES_MOE;
+}
+
+// The buffer of these copies, as large as the largest part (of a layer whose calls may be recorded, piece) that may need it at the
+// present rates.  Without it (none may, or there is no memory for it) every part goes through the ring.  Nothing of the layer may be in
+// flight.
+void setup_direct(si_layer* L) {
+  size_t need = 0;
+  for (const int n : {L->ch_cg, L->ch_cc, L->sch_cg, L->sch_cc}) {
+    const size_t part = (size_t)n * L->ce * 2, piece = (size_t)std::min(n, L->stage_chunks) * L->ce * 2;
+    if (part <= direct_limit(L, 1, L->k, L->ch_cc + L->sch_cc > 0)) need = std::max(need, part);
+    if (L->E == 1 && piece <= DIRECT_COPY_BYTES_WAITING && resident_bytes(L, 1) <= DIRECT_RESIDENT_BYTES) need = std::max(need, piece);
+  }
+  if (need <= L->direct_bytes) return;
+  if (L->d_direct) (void)hipFree(L->d_direct);
+  L->direct_bytes = dev_alloc(&L->d_direct, need / 2) == SI_OK ? need : 0;
 }
 
 int setup_pool(si_layer* L) {
@@ -610,7 +641,10 @@ int create_impl(const si_layer_desc_t* desc, const WeightSource& src, const uint
   // ---- staging ring for CG / CG' copies (Stream-C)
   L->n_stage = desc->n_stage == 0 ? 2 : desc->n_stage;
   const bool any_host = hch + shch > 0;
-  if (any_host) TRY_OR_DESTROY(setup_staging(L));
+  if (any_host) {
+    TRY_OR_DESTROY(setup_staging(L));
+    setup_direct(L);
+  }
   HIP_OR_DESTROY(hipStreamCreateWithFlags(&L->copy_stream, hipStreamNonBlocking));
   L->own_copy_stream = L->copy_stream;
   HIP_OR_DESTROY(hipEventCreateWithFlags(&L->ev_host, hipEventDisableTiming));
@@ -786,6 +820,7 @@ int si_layer_resplit(si_layer_t* L, float r_gg, float r_cg, float r_cc) {
   // (after the moves, which have given the old buffers back; until these exist, forward calls that need them are refused)
   if (L->ch_cc + L->ch_cg + L->sch_cc + L->sch_cg > 0)
     if (const int rc2 = setup_staging(L)) return rc2;
+  setup_direct(L);
   if (L->ch_cc + L->sch_cc > 0)
     if (const int rc3 = setup_pool(L)) return rc3;
   return rc;
@@ -1181,8 +1216,10 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
 
   // ---- CG and CG' parts: copy (Stream-C) double-buffered against compute (Stream-D)
   if (any_cg || need_cgp) {
-    const size_t resident = ((size_t)std::min(E, T * k) * L->ch_gg + L->sch_gg) * ce * 2;  // (at most)
-    const size_t direct_max = resident > DIRECT_RESIDENT_BYTES ? 0 : E > 1 ? DIRECT_COPY_BYTES_MOE : DIRECT_COPY_BYTES;
+    // A call that waits for nothing may be recorded; copies on the copy stream cannot be part of that.
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (path == SI_DECODE && !need_sync && hipStreamIsCapturing(stream, &cs) != hipSuccess) (void)hipGetLastError();
+    const bool recording = cs == hipStreamCaptureStatusActive;
     const bool shared_first = L->pre_n > 0 && L->pre_shared;  // its first pieces are already in the ring
     for (int ei = 0; ei < EX; ++ei) {
       const int e = !shared_first ? ei : ei == 0 ? E : ei - 1;
@@ -1197,14 +1234,17 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
         const int pc0 = part == 2 ? 0 : n_cc_e, pn = part == 2 ? n_cc_e : n_cg_e;
         const int cps = sh ? (part == 2 ? scps_cc : scps_cg) : (part == 2 ? cps_cc : cps_cg);
         const int piece_max = piece_chunks(L, path, cps);
-        for (int c = 0; c < pn; c += piece_max) {
-          const int n = std::min(piece_max, pn - c);
-          const size_t bytes = (size_t)n * ce * 2;
-          const bool ahead = part == 1 && sh == L->pre_shared && c / piece_max < L->pre_n;
-          if (path == SI_DECODE && !ahead && bytes <= direct_max) {
+        const int n_ahead = part == 1 && sh == L->pre_shared ? L->pre_n : 0;
+        const size_t chunk_bytes = ce * 2, by_size = direct_limit(L, x2_only ? rows_x2(e) : rows_all(e), T * k, need_cc);
+        const bool whole = pn * chunk_bytes <= std::min(by_size, L->direct_bytes);
+        const bool by_kernel = path == SI_DECODE && n_ahead == 0 && (whole || (recording && std::min(pn, piece_max) * chunk_bytes <= L->direct_bytes));
+        const int piece_len = by_kernel && whole ? pn : piece_max;
+        for (int c = 0; c < pn; c += piece_len) {
+          const int n = std::min(piece_len, pn - c);
+          if (by_kernel) {
             {
               SegScope sc(L, stream, SEG_COPY);
-              const int n16 = (int)(bytes / 16);
+              const int n16 = (int)(n * chunk_bytes / 16);
               hipLaunchKernelGGL(k_copy_piece, dim3(std::min(256, (n16 + 255) / 256)), dim3(256), 0, stream,
                                  reinterpret_cast<const uint4*>(hbase + (size_t)(pc0 + c) * ce), reinterpret_cast<uint4*>(L->d_direct), n16);
               HIP_TRY(hipGetLastError());
@@ -1213,12 +1253,12 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
             int rc = run_part(L->d_direct, 0, sh ? 0 : e, sh, 0, n, (pc0 + c) * CHUNK_J, part, c, x2_only, false, no_ws);
             L->in_staged = 0;
             if (rc) return rc;
-            st.bytes_streamed += (double)bytes;
+            st.bytes_streamed += (double)(n * chunk_bytes);
             st.n_copies++;
             continue;
           }
           int slot;
-          if (ahead) {
+          if (c / piece_max < n_ahead) {
             slot = L->pre_slot[c / piece_max];  // already on its way (prefetched after the previous layer's copies)
           } else {
             slot = (int)(L->piece_counter++ % L->n_stage);

@@ -157,3 +157,124 @@ def test_a_recorded_prompt_call_clears_its_tile_queues(host, kw):
     assert prompt(0) == (si.SI_OK, 1)
     assert prompt(0) == (si.SI_OK, 0)
     """ % kw)
+
+
+def test_which_parts_a_kernel_copies(host):
+    """Generation calls: a dense layer's parts of up to 32 MB where the host computes a share, of up to 8 MB without, of several
+    experts 4 MB, both with few rows, each whole whatever the size of a staging buffer.  All else uses the ring, in pieces: larger parts to their last piece, many rows, calls
+    beside a large resident part.  Chunks of 64 columns of d_model 4096 are 1.5 MB."""
+    host("""
+    def run(M, chunks, cg, cc=0, stage_mib=0, T=1, E=1, k=1, Hs=0, n_g=0, n_stage=0, mode=si.SI_DECODE):
+        split = ((chunks - cg - cc) / chunks, cg / chunks, cc / chunks)
+        h = layer(M, 64 * chunks, split, E=E, k=k, Hs=Hs, stage_mib=stage_mib, n_stage=n_stage)
+        log()
+        forward(h, M, T, E=E, n_g=n_g, mode=mode)
+        lines = log()
+        si.si_layer_destroy(h)
+        return len(calls(lines, "k_copy_piece")), len(calls(lines, "hipMemcpyAsync"))
+    # dense, a host part
+    assert run(4096, 24, 21, 1) == (1, 0)                       # 31.5 MB
+    assert run(4096, 24, 21, 1, stage_mib=16) == (1, 0)         # ... in one piece
+    assert run(4096, 24, 22, 1) == (0, 1)                       # 33 MB
+    assert run(4096, 24, 22, 1, stage_mib=16) == (0, 3)         # ... pieces of 10, 10 and 2 chunks
+    assert run(4096, 64, 61, 1, stage_mib=16, n_stage=4) == (0, 8)  # whole slots of 8 chunks
+    assert run(4096, 24, 10, 10, T=4, n_g=2) == (2, 0)          # CG and CG'
+    assert run(4096, 48, 1, 1) == (0, 1)                        # resident part of 69 MB
+    assert run(4096, 24, 21, 1, mode=si.SI_PREFILL) == (0, 1)
+    # dense without a host share, and several experts (every one has T rows here): by the part's size, by rows x d_model
+    assert run(4096, 24, 2) == (1, 0)                           # 3 MB
+    assert run(4096, 24, 5) == (1, 0)                           # 7.5 MB
+    assert run(4096, 24, 6) == (0, 1)                           # 9 MB
+    assert run(4096, 24, 2, T=2) == (0, 1)
+    assert run(4096, 24, 2, 2, T=1, n_g=1) == (2, 0)            # CG' takes the host's share
+    assert run(4096, 24, 6, 2, T=1, n_g=1) == (1, 1)
+    assert run(4096, 8, 2, E=8, k=2, stage_mib=1) == (8, 0)
+    assert run(4096, 8, 3, E=8, k=2) == (0, 8)
+    assert run(4096, 8, 2, E=8, k=2, T=2) == (0, 8)
+    assert run(1024, 8, 2, E=8, k=2, T=6) == (8, 0)
+    assert run(1024, 8, 2, E=8, k=2, T=7) == (0, 8)
+    assert run(1024, 8, 2, 2, E=8, k=2, T=7, n_g=1) == (8, 8)   # CG of 7 rows, CG' of 1
+    assert run(8192, 8, 1, E=8, k=2) == (0, 8)
+    assert run(1024, 8, 2, E=1, Hs=512) == (2, 0)
+    """)
+
+
+def test_the_buffer_of_direct_copies_is_allocated_where_it_can_be_used(host):
+    host("""
+    def sizes(M, chunks, cg, cc=0, stage_mib=64, E=1, k=1):
+        log()
+        h = layer(M, 64 * chunks, ((chunks - cg - cc) / chunks, cg / chunks, cc / chunks), E=E, k=k, stage_mib=stage_mib)
+        used = [int(l.split()[1]) // (384 * M) for l in calls(log(), "hipMalloc")]  # in chunks
+        ring = max(8, (stage_mib << 20) // (384 * M))
+        at = used.index(ring, 0 if chunks == cg + cc else 1)
+        assert used[at:at + 2] == [ring] * 2, used
+        return h, used[at + 2]
+    assert sizes(4096, 24, 9, 11)[1] == 11           # the larger part
+    assert sizes(4096, 24, 10)[1] == 10              # nothing on the host: a recorded call
+    assert sizes(4096, 64, 60, stage_mib=16)[1] == 10  # ... in pieces
+    assert sizes(4096, 64, 30, 31)[1] == 0           # more than 32 MB
+    assert sizes(4096, 48, 1, 1)[1] == 0             # beside 69 MB
+    assert sizes(4096, 8, 2, E=8, k=2)[1] == 2
+    assert sizes(4096, 8, 3, E=8, k=2)[1] == 0       # more than 4 MB
+    assert sizes(8192, 8, 1, E=8, k=2)[1] == 0       # one row is too many
+    # no memory for it: the layer streams through the ring, and a later re-slicing tries again
+    stub.hip_stub_fail(b"hipMalloc", 4)
+    h = layer(4096, 64 * 24, (4 / 24, 9 / 24, 11 / 24), stage_mib=1)
+    log()
+    forward(h, 4096, 1)
+    lines = log()
+    assert not calls(lines, "k_copy_piece") and len(calls(lines, "hipMemcpyAsync")) == 2, lines  # (pieces of 8 chunks at most)
+    si.si_layer_resplit(h, 6 / 24, 7 / 24, 11 / 24)
+    log()
+    forward(h, 4096, 1)
+    copies = calls(log(), "k_copy_piece", "hipMemcpyAsync")
+    assert len(copies) == 1 and copies[0].startswith("k_copy_piece") and "(nil)" not in copies[0].split(" on ")[0], copies
+    """)
+
+
+@pytest.mark.parametrize("dense", [True, False])
+def test_pieces_copied_ahead_stay_in_the_ring(host, dense):
+    """A part whose first pieces were copied ahead after the layer before comes from the ring altogether, though it is small."""
+    host("""
+    kw = dict(stage_mib=1) if %r else dict(E=4, k=2, Hs=960)
+    E = kw.get("E", 1)
+    layers = [layer(256, 960, (2 / 15, 12 / 15, 1 / 15), **kw) for _ in range(2)]
+    S = si.si_stack_create(layers)
+    x, y, lg = np.zeros((4, 256), np.uint16), np.zeros((4, 256), np.float32), np.zeros((4, 4), np.float32)
+    stub.hip_stub_rows(4, 4)
+    per_call = []
+    for prefetch in (0, 1):
+        log()
+        si.si_stack_forward(S, x.ctypes.data, [lg.ctypes.data] * 2 if E > 1 else None, 4, 0, si.SI_DECODE, y.ctypes.data, prefetch=prefetch, stream=0)
+        lines = log()
+        per_call.append((len(calls(lines, "k_copy_piece")), len(calls(lines, "hipMemcpyAsync"))))
+    n = E if E > 1 else 0
+    # 12 chunks of 96 KB; ring pieces of 10 chunks (1 MiB) or all
+    assert per_call[0] == (2 * (n + 1), 0), per_call
+    assert per_call[1] == (2 * n + 1, 2 if E == 1 else 1), per_call
+    """ % dense)
+
+
+def test_recorded_calls_stay_off_the_copy_stream(host):
+    """A generation call of a dense layer without a host share can be recorded while its pieces fit the kernel's buffer, whatever its
+    rows: nothing of it is on the copy stream.  Larger pieces are not made to fit."""
+    host("""
+    def run(M, chunks, cg, T=1, stage_mib=0, n_g=0, cc=0):
+        h = layer(M, 64 * chunks, ((chunks - cg - cc) / chunks, cg / chunks, cc / chunks), stage_mib=stage_mib)
+        out = []
+        for capturing in (0, 1, 0):
+            stub.hip_stub_capturing(capturing)
+            log()
+            forward(h, M, T, n_g=n_g, mode=si.SI_DECODE)
+            lines = log()
+            stub.hip_stub_capturing(0)
+            out.append((len(calls(lines, "k_copy_piece")), len(calls(lines, "hipMemcpyAsync")), len(calls(lines, "hipStreamWaitEvent"))))
+        si.si_layer_destroy(h)
+        assert out[0][:2] == out[2][:2], out
+        return out[0][:2], out[1]
+    assert run(1024, 16, 8, T=8) == ((0, 1), (1, 0, 0))
+    assert run(4096, 24, 21, T=16) == ((0, 1), (1, 0, 0))
+    assert run(4096, 64, 60, stage_mib=16) == ((0, 8), (8, 0, 0))
+    assert run(4096, 24, 10, cc=10, T=2, n_g=2) == ((0, 2), (2, 0, 0))
+    assert run(4096, 24, 22)[1][:2] == (0, 1)
+    """)
