@@ -236,7 +236,7 @@ struct si_layer {
   // device workspaces
   char* d_plan = nullptr;
   Plan plan{};
-  bool queue_dirty = false;     // a call ended before its merge: the tile queues of the prompt phase are to be cleared first
+  bool queue_dirty = true;      // the tile queues of the prompt phase are to be cleared first: new, or a call ended before its merge
   int max_tiles = 0;
   float* d_h = nullptr;       // decode activations [rows_dec][ldh]
   int ldh_dec = 0, rows_dec = 0;
@@ -668,7 +668,6 @@ int create_impl(const si_layer_desc_t* desc, const WeightSource& src, const uint
     L->plan.n_tiles = b + o_nt + 4;
     L->plan.n_routed = E;
     L->plan.queue = b + (o_q + 31) / 32 * 32;
-    HIP_OR_DESTROY(hipMemset(L->plan.queue, 0, (size_t)2 * 8 * QUEUE_STRIDE * 4));  // (afterwards every call leaves them clear)
     L->plan.tile_e = b + o_te; L->plan.tile_r = b + o_tr; L->plan.tile_e_x2 = b + o_te2; L->plan.tile_r_x2 = b + o_tr2;
   }
   const int T_dec = std::min(T, SI_DECODE_MAX_T);

@@ -278,3 +278,17 @@ def test_recorded_calls_stay_off_the_copy_stream(host):
     assert run(4096, 24, 10, cc=10, T=2, n_g=2) == ((0, 2), (2, 0, 0))
     assert run(4096, 24, 22)[1][:2] == (0, 1)
     """)
+
+
+def test_a_new_layer_has_its_tile_queues_cleared_by_its_first_prompt_call(host):
+    """Creation does not touch the counters; the first prompt call clears them before FC1, generation calls before it do not."""
+    host("""
+    h = layer(256, 704, (1.0, 0.0, 0.0))
+    assert not calls(log(), "hipMemset", "k_fill_zero")
+    forward(h, 256, 4)
+    assert not calls(log(), "hipMemset", "k_fill_zero")
+    for n in (1, 0):
+        forward(h, 256, 64, mode=si.SI_PREFILL)
+        names = [l.split()[0] for l in calls(log(), "hipMemset", "k_fill_zero", "k_prefill_gateup")]
+        assert names == ["k_fill_zero"] * n + ["k_prefill_gateup"], names
+    """)
