@@ -556,7 +556,9 @@ class CcPool {
   bool force_generic_ = std::getenv("SI_CC_GENERIC") != nullptr;  // run the portable loops even where AVX-512 exists (tests)
   // Jobs up to this size (hidden columns x d_model x (rows + 1)) are run by the thread that waits for them: waking 16 workers takes
   // 25 to 40 us.  In place / by the workers, us: 192 x 256, 4 rows (245 K) 10 / 30; 256 x 256, 4 rows (328 K) 16 / 32; 384 x 512, 1 row
-  // (393 K) 26 / 37; 384 x 512, 4 rows (983 K) 41 / 45; 384 x 1024, 1 row (786 K) 49 / 44.  (The portable loops are 2 to 4 times slower.)
+  // (393 K) 26 / 37; 384 x 512, 4 rows (983 K) 41 / 45; 384 x 1024, 1 row (786 K) 49 / 44.  4-bit shares: 256 x 256, 4 rows (320 K) 24 / 52;
+  // 128 x 1024, 4 rows (640 K) 40 / 67; 384 x 512, 4 rows (960 K) 63 / 66; 384 x 1024, 4 rows (1920 K) 117 / 83.  The portable loops, with
+  // their quarter of it: 128 x 256, 4 rows (160 K) 19 / 42, 4-bit 20 / 55; 384 x 512, 1 row (384 K) 59 / 48, 4-bit 61 / 47.
   static constexpr size_t IN_PLACE_WORK = 640 << 10;
   size_t work_ = 0;
   bool in_place_ = false;
