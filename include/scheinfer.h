@@ -240,7 +240,9 @@ int si_layer_forward(si_layer_t* layer, const void* x_dev, const float* logits_d
 /*
  * Token assignment alone (Section II-A: the gating function assigns tokens to experts): top-k on
  * the raw logits (ties -> lower expert index), softmax over the k selected logits, per-expert
- * histogram, exclusive prefix sum and the stable expert-sorted permutation.
+ * histogram, exclusive prefix sum and the stable expert-sorted permutation.  A logit that is NaN comes before +infinity if
+ * its sign bit is clear and after -infinity if it is set (NaN among themselves by their bits), for every E: k different experts
+ * are chosen whatever the logits are; the weights of a token that chose a NaN are NaN.
  * logits_dev DEVICE f32 [T][E]; out: device pointers (any may be NULL); 1 <= k <= E <= 256.
  */
 int si_route(const float* logits_dev, int32_t T, int32_t E, int32_t k, const si_routing_out_t* out,
