@@ -653,7 +653,7 @@ int create_impl(const si_layer_desc_t* desc, const WeightSource& src, const uint
 
   // ---- workspaces
   const size_t n_pairs = (size_t)T * k, n_rows = n_pairs + (L->has_shared ? T : 0);
-  L->max_tiles = (int)(n_rows / 64) + L->EX + 2;  // row-tile tables for the smallest tile (64 rows)
+  L->max_tiles = (int)(n_rows / 64) + L->EX + 2;  // (more than n_row_tiles() can give)
   {
     size_t ints = 0;
     auto take = [&](size_t n) { size_t o = ints; ints += (n + 3) / 4 * 4; return o; };
@@ -1124,7 +1124,7 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
         }
         const int ldh = ns * CHUNK_J, ldh_s = ws.n_chunks * CHUNK_J;
         // (the activations of the T*k routed rows, then those of the shared expert's rows)
-        const SharedPart sp{ws, n_row_tiles(T), ldh_s, (long)T * k * (ldh - ldh_s), split_s};
+        const SharedPart sp{ws, ldh_s, (long)T * k * (ldh - ldh_s), split_s};
         {
           SegScope sc(L, stream, SI_K_PREFILL_GATEUP);
           K_TRY(launch_prefill_gateup(x, M, L->plan, esel, x2_only, n_rt, wg, L->d_hact, ldh, sp, stream));

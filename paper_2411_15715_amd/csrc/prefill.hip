@@ -8,7 +8,8 @@
 // Both GEMMs: one 512-thread block (8 waves, 2 per SIMD) per compute unit, which takes tile after tile of BM x 256 outputs
 // (TileQueues), BK = 64, rings of LDS stages filled by direct global->LDS loads (global_load_lds_dwordx4, no VGPR staging), wave
 // tile (BM/2) x 64.  A row tile holds up to 256 rows, the last one of an expert up to 320 (si_internal.h: n_row_tiles);
-// the block runs the body instantiated for the next multiple of 32 rows that covers the tile's (4-bit: 64, 128, 192 or 256).
+// the block runs the body instantiated for the next multiple of 32 rows that covers the tile's (4-bit: up to 256, the rows beyond in
+// a second pass).
 // The main loop is a ping-pong of two wave groups on v_mfma_f32_16x16x32_bf16 (gemm_pingpong; gemm_pingpong_q4 converts
 // 4-bit weights on their way into LDS).
 // LDS rows hold 64 contraction elements (128 bytes); the 16-byte piece c of row r sits at piece
@@ -1229,7 +1230,7 @@ static hipError_t ensure_lds_attr() {
     for (const void* k : kernels) {
       hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, KERNEL_LDS + NEXT_LDS);
       if (e != hipSuccess) return e;
-      // The main loops count their own vector-memory operations (wait_vmcnt<N> against PingPong<>::younger): a
+      // The main loops count their own vector-memory operations (wait_vmcnt<N> against Ring::younger): a
       // register spill would add scratch loads and stores to that count and let a barrier pass before a tile has
       // landed.  A build whose GEMM kernels use scratch memory is refused here instead of computing wrong results.
       hipFuncAttributes fa{};

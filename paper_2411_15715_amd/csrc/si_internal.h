@@ -123,7 +123,7 @@ __device__ inline bool storage_index(const WeightView& wv, int e, int& se) {
 // Token assignment folded into the first gate/up launch of a generation-phase call with few tokens (the launch of a
 // separate assignment kernel costs as much as reading tens of megabytes): every block derives the assignment of
 // the <= FUSED_ROUTE_MAX_T tokens itself and finds its expert from it; block (0, 0) also writes the tables that the
-// later launches of the call and the caller read.  logits == nullptr: dense layer (one expert, weight 1).
+// later launches of the call and the caller read.  logits == nullptr: one routed expert, weight 1 (beside a shared one).
 constexpr int FUSED_ROUTE_MAX_T = 4;
 constexpr int FUSED_ROUTE_MAX_PAIRS = 8;
 struct FusedRoute {
@@ -154,13 +154,12 @@ hipError_t launch_decode_combine(const DecodeCombineArgs& a, const Plan& plan, f
 // The shared expert's part of a launch that covers it along with the routed experts (wv.n_chunks == 0: it does not).
 struct SharedPart {
   WeightView wv;
-  int row_tiles;  // of its T rows
   int ldh;        // its activations: row r (an expert-sorted row index) at Hact + hact + r * ldh
   long hact;
   int split;      // k-splits of its down projection
 };
 // Hact[row][c] (bf16) for c in [0, 64*n_chunks): SwiGLU of the gate/up products (MFMA, fp32 acc).
-// n_row_tiles: (an upper bound on) the row tiles of the launch, for the grid; the kernels find the real ones
+// n_row_tiles: (an upper bound on) the row tiles of the launch: with 0 there is none; the kernels find the real ones
 hipError_t launch_prefill_gateup(const uint16_t* x, int M, const Plan& plan, int expert_sel, int x2_only,
                                  int n_row_tiles, const WeightView& wv, uint16_t* hact, int ldh, const SharedPart& sp,
                                  hipStream_t stream);
