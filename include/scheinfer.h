@@ -108,15 +108,16 @@ typedef struct {
 
 typedef struct {
   float total_ms;     /* first enqueue to last kernel, on the caller's stream */
-  float copy_ms;      /* busy time of the host->device weight copies (Stream-C) */
+  float copy_ms;      /* busy time of the host->device weight copies (Stream-C, or a kernel on the caller's stream) */
   float gpu_ms;       /* sum of kernel time on the compute stream (Stream-D), incl. waits on copies excluded */
-  float cc_ms;        /* host wall time of the CC workers (Stream-A) */
+  float cc_ms;        /* host wall time of the CC part (Stream-A), from its start to its end: the workers', or the calling
+                         thread's where it computes a small share itself once everything else is enqueued */
   float route_ms;     /* token-assignment kernels */
   double bytes_streamed;  /* CG (+CG') weight bytes copied host->device */
   double bytes_gg;        /* GG weight bytes read by the kernels (algorithmic) */
   double bytes_cc;        /* CC weight bytes read by the host workers (algorithmic) */
   float overlap;
-  int32_t n_copies;   /* number of staged pieces */
+  int32_t n_copies;   /* number of streamed pieces */
   int32_t n_touched;  /* experts with at least one token (-1 if not known on the host) */
   int32_t path;       /* SI_DECODE or SI_PREFILL actually taken */
   float kernel_ms[SI_K_COUNT];         /* summed HIP-event time of each kernel class (SI_K_*) */

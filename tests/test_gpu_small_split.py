@@ -1,6 +1,7 @@
-"""Small calls of split layers on both sides of their dispatch lines, against the oracle: pieces that a kernel copies in the
-caller's stream (dense up to 32 MB, several experts up to 4 MB) or the copy stream does, a host share that the calling thread
-runs itself or the workers do, streamed parts of up to 8 chunks (a slot each) and more; calls in a row on one layer."""
+"""Small calls of split layers on both sides of their dispatch lines, against the oracle: parts that a kernel copies in the
+caller's stream (dense up to 32 MB where the host computes a share, else up to 8 MB, of several experts up to 4 MB, both with few
+rows) or the copy stream does, a host share that the calling thread runs itself or the workers do, streamed parts of up to 8
+chunks (a slot each) and more; calls in a row on one layer."""
 import pytest
 
 import paper_2411_15715_amd as si
@@ -31,16 +32,17 @@ def test_small_split(oracle, E, k, d_model, d_ff, split):
         L.close()
 
 
-def test_one_piece_sizes(oracle):
-    """One dense piece just below and just above 32 MB (chunks of 1.5 MB), the resident part small."""
-    cfg = synth.scaled(synth.CONFIGS["llama2_70b"], d_model=4096, d_ff=1536, seed=5)
+@pytest.mark.parametrize("chunks,cg,cc,T", [(24, 21, 1, 3), (24, 22, 1, 3), (12, 5, 0, 1), (12, 6, 0, 1), (12, 5, 0, 2)])
+def test_one_part_sizes(oracle, chunks, cg, cc, T):
+    """One dense part (chunks of 1.5 MB) just below and just above 32 MB beside a host share; just below and just above 8 MB without one, and
+    below with a row too many."""
+    cfg = synth.scaled(synth.CONFIGS["llama2_70b"], d_model=4096, d_ff=64 * chunks, seed=5)
     w = synth.make_weights(cfg)
-    x = synth.make_tokens(cfg, 3)
+    x = synth.make_tokens(cfg, T)
     yo = oracle.layer_forward(x, w["w_gate"], w["w_up"], w["w_down"])
-    for chunks in (21, 22):
-        L = GpuLayer(cfg, w, ((24 - chunks) / 24, chunks / 24, 0.0), max_tokens=3)
-        try:
-            for _ in range(2):
-                assert_parity(L.forward(x, None), yo, tol=1e-4)
-        finally:
-            L.close()
+    L = GpuLayer(cfg, w, ((chunks - cg - cc) / chunks, cg / chunks, cc / chunks), max_tokens=3)
+    try:
+        for _ in range(3):
+            assert_parity(L.forward(x, None), yo, tol=1e-3 if cc else 1e-4)
+    finally:
+        L.close()
