@@ -292,3 +292,40 @@ def test_a_new_layer_has_its_tile_queues_cleared_by_its_first_prompt_call(host):
         names = [l.split()[0] for l in calls(log(), "hipMemset", "k_fill_zero", "k_prefill_gateup")]
         assert names == ["k_fill_zero"] * n + ["k_prefill_gateup"], names
     """)
+
+
+@pytest.mark.parametrize("M,H,split,kw", [(1024, 1920, (0.2, 0.6, 0.2), dict(stage_mib=1)), (256, 704, (0.4, 0.3, 0.3), dict(E=4, k=2, Hs=640)),
+                                          (256, 704, (0.4, 0.6, 0.0), dict()), (256, 704, (1.0, 0.0, 0.0), dict(E=4, k=2))])
+def test_a_call_after_one_that_failed_anywhere(host, M, H, split, kw):
+    """Every copy, event and launch of a call fails once.  The call reports it, and the next one succeeds with the launches and copies of
+    an undisturbed call (a prompt call with the clearing of the tile queues before them)."""
+    out = host("""
+    M, H, split, kw = %r, %r, %r, %r
+    E = kw.get("E", 1)
+    names = ["hipMemcpyAsync", "hipEventRecord", "hipStreamWaitEvent", "hipEventSynchronize", "k_copy_piece", "k_handoff", "k_decode_gateup", "k_decode_down",
+             "k_decode_combine", "k_prefill_gateup", "k_prefill_down", "k_prefill_combine", "k_topk", "k_assign", "k_route_few", "k_route_small"]
+    n = 0
+    for mode, T, n_g in ((si.SI_DECODE, 4, 0), (si.SI_DECODE, 4, 2), (si.SI_PREFILL, 40, 0), (si.SI_PREFILL, 40, 20)):
+        h = layer(M, H, split, **kw)
+        def call():
+            log()
+            rc = attempt(forward, h, M, T, E=E, n_g=n_g, mode=mode)
+            return rc, [l.split()[0] + " FAILED" * l.endswith("FAILED") for l in log()]
+        for _ in range(3):
+            rc, clean = call()
+            assert rc == si.SI_OK, si.si_last_error()
+        for name in names:
+            for nth in range(1, clean.count(name) + 1):
+                stub.hip_stub_fail(name.encode(), nth)
+                rc, lines = call()
+                assert rc == si.SI_EHIP and name + " FAILED" in lines, (mode, name, nth, rc)
+                rc, lines = call()
+                if mode == si.SI_PREFILL:
+                    assert lines.count("k_fill_zero") == clean.count("k_fill_zero") + 1
+                    lines.remove("k_fill_zero")
+                assert rc == si.SI_OK and lines == clean, (mode, name, nth, rc, lines, clean)
+                n += 1
+        si.si_layer_destroy(h)
+    print(n)
+    """ % (M, H, split, kw))
+    assert int(out) > 10
