@@ -10,8 +10,8 @@
 // tile (BM/2) x 64.  A row tile holds up to 256 rows, the last one of an expert up to 320 (si_internal.h: n_row_tiles);
 // the block runs the body instantiated for the next multiple of 32 rows that covers the tile's (4-bit: up to 256, the rows beyond in
 // a second pass).
-// The main loop is a ping-pong of two wave groups on v_mfma_f32_16x16x32_bf16 (gemm_pingpong; gemm_pingpong_q4 converts
-// 4-bit weights on their way into LDS).
+// The main loop is a ping-pong of two wave groups on v_mfma_f32_16x16x32_bf16 (gemm_pingpong; gemm_q4 converts 4-bit weights
+// in the registers of the wave that multiplies them).
 // LDS rows hold 64 contraction elements (128 bytes); the 16-byte piece c of row r sits at piece
 // c ^ ((r >> 1) & 7): gfx950's LDS has 64 banks, so 16 consecutive rows x 16 bytes must cover 256
 // distinct bytes of bank space for the 128-bit MFMA operand reads to be conflict free (measured:
@@ -491,6 +491,7 @@ __device__ __forceinline__ void gemm_pingpong(unsigned char* lds, int nk, int la
 // vector work of the conversion about a tenth; with bf16 weights 243 / 569 for the last two.)
 // Two phases (more than 128 rows): pieces 0 and 1 of tile it + 2 in the last slot of tile it, 2 and 3 in the first of it + 1; one
 // phase: all four after the barrier.  A k-tile of 64 is one scale group of either projection.
+// Layers that hold a scale of 2^117 or more (WeightView::q4) run it still; all others gemm_q4 below, which is 1.05 to 1.6 times as fast.
 // ---------------------------------------------------------------------------------------------
 template <int FAV> struct RingQ {
   static constexpr int FA = FAV;
@@ -563,7 +564,7 @@ __device__ inline void load_lds4(const void* base, uint32_t off, unsigned char* 
 // the fp16 value 1024 + c at bit 0 and 1024 + 16 c at bit 4, which one mixed multiply-add turns into the product: 13 instructions
 // and 4 for the rounding to bf16 (21 with c formed first, 617 against 605 us for 777 tokens over 8 experts of 14336; 23 by byte
 // conversions).  1032 times a scale of 2^117 or more may overflow: WIDE forms c first, and c * scale - 8 scale is good to 2^125.
-// A layer that holds such a scale takes the WIDE kernels (WeightView::q4), whose results are the same.
+// A layer that holds such a scale takes kernels of its own (WeightView::q4: k_prefill_*_q4), whose results are the same.
 template <bool WIDE> struct ScaledCodes {
   uint32_t lo = 0x000F000Fu, hi = 0x00F000F0u, magic = 0x64006400u;
   __device__ __forceinline__ void hide() { asm volatile("" : "+v"(lo), "+v"(hi), "+s"(magic)); }  // (one and-or instruction each)
@@ -708,6 +709,230 @@ __device__ __forceinline__ void gemm_pingpong_q4(unsigned char* lds, int nk, int
   block_barrier();
 }
 
+// ---------------------------------------------------------------------------------------------
+// 4-bit weights, converted in the registers of the wave that multiplies them.  The 8 waves of a block own 32 B rows each and all
+// rows of the tile (wave tile (32 FA) x 32), so that no converted weight is shared: the codes of a wave and their scales travel to LDS
+// by direct loads, some k-tiles ahead, into slots that only this wave reads; a lane reads the two words of each of its two B
+// fragments, and while tile `it` is multiplied they become its operand registers for tile it + 1 (two sets).  The order of the
+// products and sums is that of the bf16 loop.  A is read from LDS by all eight waves (256 bytes a clock: a quarter to a half of the
+// matrix cycles).  The two wave groups take turns as in gemm_pingpong.
+// What bounded the loop before it (weights converted into a B stage in LDS): the slots of the loads, 18 LDS reads in the longer
+// ones, and the address unit.  A direct load takes the CU's address unit 17 cycles where its lanes cover runs of 128 bytes, 32 with runs of 64 and 62 with
+// runs of 32 bytes, also when only 4 bytes a lane are loaded (measured); the codes and scales of FC1, rows of 32 and 2 bytes a k-tile, took 1000
+// cycles of 2000.  Hence blocks of four k-tiles for FC1, of which a row is 128 bytes and its scales are one load.
+// What bounds it now: few rows: the instructions of a slot (one in 4 to 8 cycles and wave: 81 vector and 26 scalar ones a k-tile; with
+// the places in a block known at run time only, 80 scalar ones, 44 instead of 40 us below); many: the matrix cores at 0.6, two slots a
+// phase of 450 matrix cycles with 47 vector instructions beside them and 80 cycles for the barriers.
+// Measured, FC1 of a dense 4096 x 32768 layer (256 tiles), us before -> now: 24 rows 61.6 -> 39.8, 48 67.3 -> 47.7, 112 81.6 -> 64.6, 144 91.8
+// -> 76.3, 208 107.5 -> 93.8, 240 113.1 -> 107.7; calls: 777 tokens over 8 experts of 14336 577 -> 508; 35 drawn 4-bit shapes 1.03 to 1.60.
+// Tried: one barrier per k-tile without turns (24 rows 51, 112 76, 208 104); half of the conversion in the slots of the loads (57, 80, 100:
+// it then waits for the LDS reads); five fragments of rows and more in one phase (208 rows 113).
+// ---------------------------------------------------------------------------------------------
+// KB: k-tiles of a block of codes (4 for FC1, whose rows then are read 128 bytes at a time; 1 for FC2)
+template <int FAV, int KBV> struct RingQR {
+  static constexpr int FA = FAV, RF = 2 * FAV;              // row fragments of a wave: all of the tile
+  static constexpr int BM = 32 * FA;
+  static constexpr int NP = FA <= 4 ? 1 : FA <= 7 ? 2 : 3;  // phases per k-tile (fewer: no registers left for the rows of one)
+  static constexpr int KB = KBV;
+  static constexpr int A_STAGE = BM * 128;
+  static constexpr int Q_CODES = KB * 1024;                 // codes of a wave in a block, then their scales
+  static constexpr int Q_WAVE = Q_CODES + (KB == 1 ? 256 : 512);
+  static constexpr int Q_STAGE = 8 * Q_WAVE;
+  // LDS stages of A, blocks of codes, parts of a block (1 KB) that are issued in one k-tile
+  static constexpr int NA = KB == 1 ? (FA >= 8 ? 3 : FA >= 6 ? 4 : FA >= 4 ? 5 : FA == 3 ? 6 : 8)
+                                    : (FA >= 8 ? 2 : FA >= 6 ? 3 : FA == 5 ? 4 : FA == 4 ? 3 : FA == 3 ? 4 : FA == 2 ? 6 : 8);
+  static constexpr int NB_ROOM = (KERNEL_LDS - NA * A_STAGE) / Q_STAGE, NB_MAX = KB == 1 ? 8 : 3;
+  static constexpr int NB = NB_ROOM < NB_MAX ? NB_ROOM : NB_MAX;
+  static constexpr int PP = KB > 1 && NB == 2 ? 2 : 1;
+  static constexpr int Q_OFF = NA * A_STAGE;
+  static constexpr int LDS = Q_OFF + NB * Q_STAGE;
+  static constexpr int R = NA > (NB - 1) * KB + 1 ? NA : (NB - 1) * KB + 1;
+  static constexpr int frags(int p) { return RF / NP + (p < RF % NP ? 1 : 0); }
+  static constexpr int frag0(int p) { return p == 0 ? 0 : frag0(p - 1) + frags(p - 1); }
+  // direct-to-LDS loads of A per wave for a phase's rows, 8 rows each (where the waves are more than the rows need, the last rows are
+  // loaded more than once)
+  static constexpr int aloads(int p) { return (frags(p) + 3) / 4; }
+  static constexpr int aload0(int p) { return p == 0 ? 0 : aload0(p - 1) + aloads(p - 1); }
+  static constexpr int ALD = aload0(NP - 1) + aloads(NP - 1);
+  static constexpr int phase_of(int i) { int p = 0; while (i >= aload0(p) + aloads(p)) ++p; return p; }
+  // word j = 2 f + s of the codes (fragment f, k-step s) is converted in phase
+  static constexpr int conv_phase(int j) { return j * NP / 4; }
+  static constexpr int convs(int p) { int n = 0; for (int j = 0; j < 4; ++j) n += conv_phase(j) == p; return n; }
+  // loads of a block that are issued in the k-tile in front of the u-th of another one: parts u PP .. + PP - 1, with the first the scales
+  static constexpr int qloads(int u) { return (u * PP < KB ? PP : 0) + (u == 0 ? 1 : 0); }
+  // Loads of a wave that may still be in flight when the rows of the phase after phase q of tile `it`, and after the last phase the
+  // codes of tile it + 2, must have landed, with `rem` tiles after tile `it`: those issued after them.  The order of issue is the loop's.
+  static constexpr int younger_at(int it, int q, int rem) {
+    const int nk = it + 1 + rem;
+    int pos = 0, last = 0;
+    const int ni = q < NP - 1 ? it : it + 1, nq = q < NP - 1 ? q + 1 : 0;
+    auto a = [&](int t, int p) { if (t < nk) { pos += aloads(p); if (t == ni && p == nq) last = pos; } };
+    auto codes = [&](int b, int n) { if (b * KB < nk) { pos += n; if (n > 0 && q == NP - 1 && it + 2 < nk && b == (it + 2) / KB) last = pos; } };
+    for (int t = 0; t < (NA > NB - 1 ? NA : NB - 1); ++t) {
+      if (t < NB - 1) codes(t, KB + 1);
+      if (t < NA) for (int p = 0; p < NP; ++p) a(t, p);
+    }
+    codes(NB - 1, qloads(0));
+    for (int s = 0; s <= it * NP + q; ++s) {
+      const int t = s / NP, p = s % NP;
+      if (p > 0) a(t + NA, p - 1);
+      else if (t > 0) a(t - 1 + NA, NP - 1);
+      if (p == 0 && s < it * NP + q) codes((t + 1) / KB + NB - 1, qloads((t + 1) % KB));
+    }
+    return last ? pos - last : 63;
+  }
+  static constexpr int younger(int q, int rem) {
+    int n = 63;
+    for (int it = 0; it < 2 * R + 2 * KB; ++it) { const int y = younger_at(it, q, rem); n = y < n ? y : n; }
+    return n;
+  }
+  // the same for the codes of tiles 0 and 1 and the rows of tile 0, which are waited for before the loop
+  static constexpr int younger_first() {
+    int pos = 0, last = 0;
+    for (int t = 0; t < (NA > NB - 1 ? NA : NB - 1); ++t) {
+      if (t < NB - 1) { pos += KB + 1; if (t <= 1 / KB) last = pos; }
+      if (t < NA) { pos += ALD; if (t == 0) last = pos; }
+    }
+    return pos + qloads(0) - last;
+  }
+  static_assert(LDS <= KERNEL_LDS && NB >= (KB == 1 ? 3 : 2) && NA >= 2, "ring does not fit");
+};
+// first LDS row of the rows that wave w's i-th A load of a k-tile fills
+template <class P, int I> __device__ __forceinline__ int qr_a_row(int w) {
+  constexpr int p = P::phase_of(I), first = (I - P::aload0(p)) * 8, n = P::frags(p) * 2;
+  return P::frag0(p) * 16 + 8 * (first + 8 <= n ? first + w : min(first + w, n - 1));
+}
+
+//   issue_a(i, stage, kt): wave's i-th A load of tile kt;  issue_q(slot, block, part): the load of a part of a block's codes, with part 0
+//   that of its scales;  read(slot, u, f, words): the two words of codes of the lane's fragment f of the block's u-th tile, and
+//   their scale as the result;  conv(word, scale): 8 codes -> operand registers
+template <class P, class IA, class IQ, class RD, class CV>
+__device__ __forceinline__ void gemm_q4(unsigned char* lds, int nk, int w, int lane, f32x4 (&acc)[P::RF][2], IA issue_a, IQ issue_q, RD read, CV conv) {
+  const int wr = w >> 2;
+  const uint32_t aoff[2] = {(uint32_t)swz(lane & 15, lane >> 4), (uint32_t)swz(lane & 15, 4 + (lane >> 4))};
+  // (stages and slots are byte offsets)
+  unsigned char* const q_lds = lds + P::Q_OFF + w * P::Q_WAVE;
+  auto issue_rows = [&](auto pc, int stage, int kt) {
+    constexpr int p = decltype(pc)::value;
+    unroll<P::aloads(p)>([&](auto i) { issue_a(std::integral_constant<int, P::aload0(p) + decltype(i)::value>{}, lds + stage, kt); });
+  };
+  bf16x8 fa[P::frags(0)][2];
+  u32x4 fb[2][2][2];  // [set][fragment][k-step]
+  uint32_t wq[2][2];
+  float sc[2];
+  auto read_codes = [&](int slot, int u) {
+#pragma unroll
+    for (int f = 0; f < 2; ++f) sc[f] = read(q_lds + slot, u, f, wq[f]);
+  };
+  auto issue_parts = [&](int slot, int block, int u) {
+#pragma unroll
+    for (int i = 0; i < P::PP; ++i)
+      if (P::PP * P::KB == 1 || u * P::PP < P::KB) issue_q(q_lds + slot, block, u * P::PP + i);
+  };
+  int sta = 0, stp = (P::NA - 1) * P::A_STAGE;  // stage of the rows of tile it, and of the tile before
+  int b = 0, sq = 0, sp = (P::NB - 1) * P::Q_STAGE;  // the block that holds the codes of tile it + 1, its slot, that of the block before
+  auto next_block = [&]() {
+    ++b;
+    sp = sq;
+    sq = sq == (P::NB - 1) * P::Q_STAGE ? 0 : sq + P::Q_STAGE;
+  };
+  // steady: at least R more tiles follow;  u: the place of tile it + 1 in its block
+  auto phase = [&](auto qc, auto setc, auto steady, int it, int u) {
+    constexpr int q = decltype(qc)::value, set = decltype(setc)::value, nf = P::frags(q), f0 = P::frag0(q);
+    constexpr bool ST = decltype(steady)::value;
+    const unsigned char* sa = lds + sta;
+    if constexpr (q == 0) read_codes(sq, u);  // of tile it + 1 (past the last tile stale ones, for operands that nobody uses)
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int i = 0; i < nf; ++i) fa[i][s] = as_bf16x8(*reinterpret_cast<const u32x4*>(sa + aoff[s] + (f0 + i) * 2048));
+    // refill the rows that both groups have read: those of the previous phase
+    if constexpr (q == 0) {
+      if (ST ? it > 0 : it > 0 && it - 1 + P::NA < nk) issue_rows(std::integral_constant<int, P::NP - 1>{}, stp, it - 1 + P::NA);
+    } else {
+      if (ST || it + P::NA < nk) issue_rows(std::integral_constant<int, q - 1>{}, sta, it + P::NA);
+    }
+    if constexpr (ST) wait_vmcnt<P::younger(q, P::R)>();
+    else ring_wait<P::R, P, q>(nk - 1 - it);
+    wait_lgkmcnt0();
+    if constexpr (q == 0)
+      if (ST || (b + P::NB - 1) * P::KB < nk) issue_parts(sp, b + P::NB - 1, u);
+    __builtin_amdgcn_sched_barrier(0);
+    block_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (P::conv_phase(j) == q) fb[set ^ 1][j >> 1][j & 1] = conv(wq[j >> 1][j & 1], sc[j >> 1]);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int i = 0; i < nf; ++i)
+#pragma unroll
+        for (int ff = 0; ff < 2; ++ff) {
+          const int f = (i & 1) ? 1 - ff : ff;
+          acc[f0 + i][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(fb[set][f][s]), fa[i][s], acc[f0 + i][f], 0, 0, 0);
+        }
+    // (kept here: what only the next tile uses would otherwise be formed in front of it)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (P::conv_phase(j) == q) asm volatile("" : "+v"(fb[set ^ 1][j >> 1][j & 1]));
+    constexpr int nm = nf * 4, nv = (P::convs(q) * 20 + nm - 1) / nm;
+#pragma unroll
+    for (int i = 0; i < nm; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one matrix instruction,
+      __builtin_amdgcn_sched_group_barrier(0x002, nv, 0);  // the vector instructions of its share
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    block_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int i = 0; i < P::RF; ++i)
+#pragma unroll
+    for (int f = 0; f < 2; ++f) acc[i][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < (P::NA > P::NB - 1 ? P::NA : P::NB - 1); ++t) {
+    if (t < P::NB - 1 && t * P::KB < nk)
+#pragma unroll
+      for (int i = 0; i < P::KB; ++i) issue_q(q_lds + t * P::Q_STAGE, t, i);
+    if (t < P::NA && t < nk) unroll<P::NP>([&](auto p) { issue_rows(p, t * P::A_STAGE, t); });
+  }
+  if ((P::NB - 1) * P::KB < nk) issue_parts((P::NB - 1) * P::Q_STAGE, P::NB - 1, 0);
+  if (nk >= P::R) wait_vmcnt<P::younger_first()>();
+  else wait_vmcnt<0>();
+  read_codes(0, 0);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) fb[0][j >> 1][j & 1] = conv(wq[j >> 1][j & 1], sc[j >> 1]);
+  wait_lgkmcnt0();
+  block_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  if (wr == 1) block_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  // (the places of the tiles in their blocks and the register sets of their operands are known in the unrolled loop)
+  constexpr int U = P::KB == 1 ? 2 : P::KB;
+  const std::integral_constant<int, 0> set0;
+  auto next_stage = [&]() {
+    stp = sta;
+    sta = sta == (P::NA - 1) * P::A_STAGE ? 0 : sta + P::A_STAGE;
+  };
+  int it = 0;
+  for (; it + U - 1 + P::R < nk; it += U)
+    unroll<U>([&](auto kc) {
+      constexpr int k = decltype(kc)::value, u = (k + 1) % P::KB;
+      if (u == 0) next_block();
+      unroll<P::NP>([&](auto q) { phase(q, std::integral_constant<int, k & 1>{}, std::true_type{}, it + k, u); });
+      next_stage();
+    });
+  for (int u = 0; it < nk; ++it) {
+    if (++u == P::KB) { u = 0; next_block(); }
+    unroll<P::NP>([&](auto q) { phase(q, set0, std::false_type{}, it, u); });
+    next_stage();
+#pragma unroll
+    for (int j = 0; j < 4; ++j) fb[0][j >> 1][j & 1] = fb[1][j >> 1][j & 1];
+  }
+  if (wr == 0) block_barrier();  // the second group's last slot
+}
+
 // Epilogue of FC1: SiLU(gate) * up of the wave's 32 hidden columns -> bf16 Hact.  The loader puts the hidden columns of a
 // wave into LDS in an order (gu_col) that leaves 8 adjacent columns in a lane, for one 16-byte store per fragment row: with
 // the plain order, 2-byte stores and a full division this epilogue was 1180 vector instructions per wave, 5 us of a tile.
@@ -845,7 +1070,8 @@ constexpr int CUT_COLUMNS_ROWS = 160;
   }
 // The 4-bit bodies stop at 256 rows (they have no registers for more fragments of A): the rows a last tile holds beyond 256
 // take a second pass of the same block.  When a body returns no wave still reads the LDS rings (its last barrier follows every
-// fragment read) or has a store to them on its way (gemm_pingpong_q4 waits), so the next pass may refill them.
+// fragment read; gemm_q4's last reads of codes are of slots of the wave itself and are not used) or has a store to them on its way
+// (gemm_pingpong_q4 waits), so the next pass may refill them.
 #define SI_PICK_BODY_2PASS(ti, CALL)                                  \
   for (const int row_end_all_ = (ti).row_end;;) {                     \
     (ti).row_end = min(row_end_all_, (ti).row0 + TILE_ROWS);          \
@@ -1001,7 +1227,7 @@ __global__ __launch_bounds__(THREADS, 1) void k_prefill_down(const uint16_t* __r
 // The same two GEMMs on weights in the 4-bit storage form (chunk layout in cc_worker.h), converted on the way
 // into the B stage.  Tiles, LDS layouts, fragment reads, matrix instructions and epilogues are those above.
 // ---------------------------------------------------------------------------------------------
-template <class P, bool WIDE, class Take>
+template <class P, class Take>
 __device__ __forceinline__ void gateup_body_q4(const uint16_t* __restrict__ x, int M, const Plan& p, int tc, const TileInfo& ti,
                                                const WeightView& wv, uint16_t* __restrict__ hact, int ldh, unsigned char* lds, Take take) {
   const int tid = thread_of_item(), lane = tid % WAVE, w = __builtin_amdgcn_readfirstlane(tid / WAVE);  // wave index, known to be uniform
@@ -1034,7 +1260,7 @@ __device__ __forceinline__ void gateup_body_q4(const uint16_t* __restrict__ x, i
   };
   auto scale = [&](uint32_t word, int kt) { return __uint_as_float((z_row + kt) & 1 ? word & 0xffff0000u : word << 16); };
   const uint32_t brow = (uint32_t)(w * 32 + (lane >> 1)), b_dst = brow * 128 + (((kh * 4) ^ ((brow >> 1) & 7)) << 4);
-  ScaledCodes<WIDE> codes_of;
+  ScaledCodes<true> codes_of;
   codes_of.hide();
   // a word holds elements 8i .. 8i+7 of the half row: nibbles p and p + 4 are elements 2p, 2p + 1 (cc_worker.h)
   auto conv = [&](unsigned char* stage, uint32_t word, float sc, int i) {
@@ -1049,7 +1275,6 @@ __device__ __forceinline__ void gateup_body_q4(const uint16_t* __restrict__ x, i
   gateup_store<P::FA, 4>(acc, ti, wv, 2 * tc + (wc >> 1), tc * 128 + wc * 32, wr, lane, hact, ldh);
 }
 
-template <bool WIDE>
 __global__ __launch_bounds__(THREADS, 1) void k_prefill_gateup_q4(const uint16_t* __restrict__ x, int M, Plan p,
                                                                   int expert_sel, int x2_only,
                                                                   int n_ctiles, WeightView wv_r, WeightView wv_s,
@@ -1065,13 +1290,13 @@ __global__ __launch_bounds__(THREADS, 1) void k_prefill_gateup_q4(const uint16_t
     const int ldh = ti.sh ? ldh_s : ldh_r;
     uint16_t* hact = hact_r + (ti.sh ? hact_s : 0);
     if (!storage_index(wv, ti.e, ti.se) || (halves == 2 && !half_rows(ti, half))) return take();
-#define SI_CALL_GU(FAV) gateup_body_q4<RingQ<FAV>, WIDE>(x, scalar_of_item(M), p, tc, ti, wv, hact, ldh, lds, take_)
+#define SI_CALL_GU(FAV) gateup_body_q4<RingQ<FAV>>(x, scalar_of_item(M), p, tc, ti, wv, hact, ldh, lds, take_)
     SI_PICK_BODY_2PASS(ti, SI_CALL_GU)
 #undef SI_CALL_GU
   });
 }
 
-template <class P, bool WIDE, class Take>
+template <class P, class Take>
 __device__ __forceinline__ void down_body_q4(const uint16_t* __restrict__ hact, int ldh, int M, const DownRange& dr, const TileInfo& ti,
                                              const WeightView& wv, float* __restrict__ yp, size_t slab_stride, int accumulate,
                                              unsigned char* lds, Take take) {
@@ -1108,7 +1333,7 @@ __device__ __forceinline__ void down_body_q4(const uint16_t* __restrict__ hact, 
     load_lds4(cb + q4_off_scales(2, M), (uint32_t)n / 2 * 4, slot + 1024);
   };
   auto scale = [&](uint32_t word, int) { return __uint_as_float(n & 1 ? word & 0xffff0000u : word << 16); };
-  ScaledCodes<WIDE> codes_of;
+  ScaledCodes<true> codes_of;
   codes_of.hide();
   // a word holds hidden columns 8i .. 8i+7 of the half: nibbles p and p + 4 are elements (0, 2), (4, 6), (1, 3), (5, 7) (cc_worker.h)
   auto conv = [&](unsigned char* stage, uint32_t word, float sc, int i) {
@@ -1132,7 +1357,6 @@ __device__ __forceinline__ void down_body_q4(const uint16_t* __restrict__ hact, 
   }
 }
 
-template <bool WIDE>
 __global__ __launch_bounds__(THREADS, 1) void k_prefill_down_q4(const uint16_t* __restrict__ hact_r, int ldh_r, int M, Plan p,
                                                                 int expert_sel, int x2_only,
                                                                 int n_ntiles, int split_r, WeightView wv_r, WeightView wv_s,
@@ -1150,7 +1374,170 @@ __global__ __launch_bounds__(THREADS, 1) void k_prefill_down_q4(const uint16_t* 
     const uint16_t* hact = hact_r + (ti.sh ? hact_s : 0);
     const DownRange dr = down_range(inner, n_ntiles, n_split, wv.n_chunks);
     if (!storage_index(wv, ti.e, ti.se) || (halves == 2 && !half_rows(ti, half))) return take();
-#define SI_CALL_DN(FAV) down_body_q4<RingQ<FAV>, WIDE>(hact, ldh, scalar_of_item(M), dr, ti, wv, yp, slab_stride, accumulate, lds, take_)
+#define SI_CALL_DN(FAV) down_body_q4<RingQ<FAV>>(hact, ldh, scalar_of_item(M), dr, ti, wv, yp, slab_stride, accumulate, lds, take_)
+    SI_PICK_BODY_2PASS(ti, SI_CALL_DN)
+#undef SI_CALL_DN
+  });
+}
+
+// the bodies on gemm_q4 (above: on gemm_pingpong_q4, for layers with a scale of 2^117 or more)
+template <class P, class Take>
+__device__ __forceinline__ void gateup_body_qr(const uint16_t* __restrict__ x, int M, const Plan& p, int tc, const TileInfo& ti,
+                                               const WeightView& wv, uint16_t* __restrict__ hact, int ldh, unsigned char* lds, Take take) {
+  const int tid = thread_of_item(), lane = tid % WAVE, w = __builtin_amdgcn_readfirstlane(tid / WAVE);  // wave index, known to be uniform
+  const unsigned char* ebase = reinterpret_cast<const unsigned char*>(wv.base + (size_t)ti.se * wv.expert_stride);
+
+  const int lrow = lane >> 3, lpp = lane & 7;
+  uint32_t a_src[P::ALD];  // byte offsets from x
+  unroll<P::ALD>([&](auto i) {
+    const int lr = qr_a_row<P, i>(w) + lrow;
+    int row = ti.row0 + lr;
+    row = row < ti.row_end ? row : ti.row_end - 1;
+    a_src[i] = ((uint32_t)(ti.row_t0 >= 0 ? row - ti.row_t0 : p.row_token[row]) * (uint32_t)M + ((lpp ^ ((lr >> 1) & 7)) * 8)) * 2;
+  });
+  auto issue_a = [&](auto i, unsigned char* stage, int kt) {
+    load_lds16(x + kt * BK, a_src[i], stage + qr_a_row<P, i>(w) * 128);
+  };
+  // B: wave w owns the hidden columns 16 (w % 4) .. + 15 of chunk 2 * tc + w / 4: rows 0 .. 15 of its 32 are their gate rows (fragment 0),
+  // 16 .. 31 their up rows.  A part of a block is 128 bytes, four k-tiles, of 8 rows; the 16-byte piece c of row r sits at piece
+  // c ^ ((r >> 1) & 7) of its 128 bytes in LDS.
+  const int chunk = 2 * tc + (w >> 2), chunk_rel = __builtin_amdgcn_readfirstlane(min(chunk, wv.n_chunks - 1));
+  const unsigned char* cb = ebase + (size_t)(wv.chunk0 + chunk_rel) * q4_chunk_u16(M) * 2;
+  const int j0 = (w & 3) * 16, MG = M / 64;
+  const unsigned char *codes = cb + q4_off_codes(0, M) + (size_t)j0 * (M / 2), *scales = cb + q4_off_scales(0, M);
+  const uint32_t up_codes = (uint32_t)(q4_off_codes(1, M) - q4_off_codes(0, M)), up_scales = (uint32_t)(q4_off_scales(1, M) - q4_off_scales(0, M));
+  // even parts hold rows 0 .. 7 of the 16 gate / up rows, odd ones 8 .. 15
+  const uint32_t q_even = (uint32_t)(lrow * (M / 2) + ((lpp ^ (lrow >> 1)) * 16)), q_odd = (uint32_t)((8 + lrow) * (M / 2) + ((lpp ^ (4 + (lrow >> 1))) * 16));
+  // scales of a block: 16 bytes of lane = row (0 .. 31), from the aligned word that holds the first
+  const uint32_t z_row = (uint32_t)((j0 + (lane & 15)) * MG), z_lane = ((lane >> 4) & 1) * up_scales;
+  auto issue_q = [&](unsigned char* slot, int block, int part) {
+    uint32_t off = (part & 1) ? q_odd : q_even;
+    load_lds16(codes + ((part & 2) ? up_codes : 0u) + block * 128, off, slot + part * 1024);
+    if (part == 0 && lane < 32) {
+      uint32_t z = z_lane + (z_row + block * 4) / 2 * 4;
+      load_lds16(scales, z, slot + P::Q_CODES);
+    }
+  };
+  const int n = lane & 15;
+  const uint32_t q_rd = (uint32_t)(n * 128 + (((n >> 1) & 7) << 4) + (lane >> 4) * 4), s_rd = (uint32_t)(P::Q_CODES + n * 16 + ((((j0 + n) * MG) & 1) << 1));
+  auto read = [&](const unsigned char* slot, int u, int f, uint32_t (&words)[2]) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) words[s] = *reinterpret_cast<const uint32_t*>(slot + (q_rd ^ (uint32_t)((2 * u + s) << 4)) + f * 2048);
+    return __uint_as_float((uint32_t)*reinterpret_cast<const uint16_t*>(slot + s_rd + u * 2 + f * 256) << 16);
+  };
+  ScaledCodes<false> codes_of;
+  codes_of.hide();
+  auto conv = [&](uint32_t word, float sc) {
+    float f[8];
+    codes_of(word, sc, f);
+    return u32x4{pack_bf16(f[0], f[1]), pack_bf16(f[2], f[3]), pack_bf16(f[4], f[5]), pack_bf16(f[6], f[7])};
+  };
+  f32x4 acc[P::RF][2];
+  gemm_q4<P>(lds, M / BK, w, lane, acc, issue_a, issue_q, read, conv);
+  take();
+  gateup_store<P::RF, 2>(acc, ti, wv, chunk, tc * 128 + w * 16, 0, lane, hact, ldh);
+}
+
+template <class P, class Take>
+__device__ __forceinline__ void down_body_qr(const uint16_t* __restrict__ hact, int ldh, int M, const DownRange& dr, const TileInfo& ti,
+                                             const WeightView& wv, float* __restrict__ yp, size_t slab_stride, int accumulate,
+                                             unsigned char* lds, Take take) {
+  const int c_begin = dr.c_begin, c_end = dr.c_end;
+  if (c_begin >= c_end && accumulate) return take();
+  const int tid = thread_of_item(), lane = tid % WAVE, w = __builtin_amdgcn_readfirstlane(tid / WAVE);  // wave index, known to be uniform
+  const int n0 = dr.nt * BN;
+  const unsigned char* ebase = reinterpret_cast<const unsigned char*>(wv.base + (size_t)ti.se * wv.expert_stride);
+  float* out = yp + (size_t)dr.split * slab_stride;
+
+  const int lrow = lane >> 3, lpp = lane & 7;
+  uint32_t a_src[P::ALD];  // byte offsets from hact
+  unroll<P::ALD>([&](auto i) {
+    const int lr = qr_a_row<P, i>(w) + lrow;
+    int row = ti.row0 + lr;
+    row = row < ti.row_end ? row : ti.row_end - 1;
+    a_src[i] = ((uint32_t)row * (uint32_t)ldh + wv.col0 + ((lpp ^ ((lr >> 1) & 7)) * 8)) * 2;
+  });
+  auto issue_a = [&](auto i, unsigned char* stage, int kt) {
+    load_lds16(hact + (c_begin + kt) * CHUNK_J, a_src[i], stage + qr_a_row<P, i>(w) * 128);
+  };
+  // B: wave w owns the output columns n0 + 32 w .. + 31.  A block is one chunk: 16 bytes, 32 hidden columns, of lane = (column lane % 32,
+  // j-half lane / 32), and the words of the columns' scales
+  const int NW = ntile_width(M);
+  const int nl = min(n0 + w * 32 + (lane & 31), M - 1);
+  uint32_t q_lane = (uint32_t)(((nl / NW) * 2 + (lane >> 5)) * NW + (nl & (NW - 1))) * 16;  // NW is a power of two
+  const size_t cbytes = q4_chunk_u16(M) * 2;
+  const unsigned char* cb0 = ebase + (size_t)(wv.chunk0 + c_begin) * cbytes;
+  auto issue_q = [&](unsigned char* slot, int block, int) {
+    const unsigned char* cb = cb0 + (size_t)block * cbytes;
+    load_lds16(cb + q4_off_codes(2, M), q_lane, slot);
+    load_lds4(cb + q4_off_scales(2, M), (uint32_t)nl / 2 * 4, slot + P::Q_CODES);
+  };
+  const uint32_t q_rd = (uint32_t)((lane & 15) * 16 + (lane >> 4) * 4), s_rd = (uint32_t)(P::Q_CODES + (lane & 15) * 4 + (lane & 1) * 2);
+  auto read = [&](const unsigned char* slot, int, int f, uint32_t (&words)[2]) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) words[s] = *reinterpret_cast<const uint32_t*>(slot + q_rd + f * 256 + s * 512);
+    return __uint_as_float((uint32_t)*reinterpret_cast<const uint16_t*>(slot + s_rd + f * 64) << 16);
+  };
+  ScaledCodes<false> codes_of;
+  codes_of.hide();
+  auto conv = [&](uint32_t word, float sc) {
+    float f[8];
+    codes_of(word, sc, f);
+    return u32x4{pack_bf16(f[0], f[4]), pack_bf16(f[1], f[5]), pack_bf16(f[2], f[6]), pack_bf16(f[3], f[7])};
+  };
+  if (c_begin < c_end) {
+    f32x4 acc[P::RF][2];
+    gemm_q4<P>(lds, c_end - c_begin, w, lane, acc, issue_a, issue_q, read, conv);
+    take();
+    down_store<P::RF, 2>(acc, ti, n0 + w * 32, 0, lane, M, out, accumulate);
+  } else {
+    take();
+    for (int i = tid; i < P::BM * BN; i += THREADS) {
+      const int row = ti.row0 + i / BN, m = n0 + i % BN;
+      if (row < ti.row_end && m < M) out[(size_t)row * M + m] = 0.f;
+    }
+  }
+}
+
+__global__ __launch_bounds__(THREADS, 1) void k_prefill_gateup_qr(const uint16_t* __restrict__ x, int M, Plan p,
+                                                                  int expert_sel, int x2_only,
+                                                                  int n_ctiles, WeightView wv_r, WeightView wv_s,
+                                                                  uint16_t* __restrict__ hact_r, int ldh_r, long hact_s, int ldh_s) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  const int n_ctiles_s = (wv_s.n_chunks + 1) / 2;
+  const TileQueues tq = tile_queues(p, expert_sel, x2_only, n_ctiles, n_ctiles_s, true);
+  run_items(tq, p.queue, p.queue + N_XCD * QUEUE_STRIDE, lds, [&](int q, int item, auto take) {
+    int tc, half, halves;
+    TileInfo ti;
+    item_tile(tq, p, expert_sel, x2_only, q, item, n_ctiles, tc, ti, half, halves);
+    const WeightView wv = ti.sh ? wv_s : wv_r;
+    const int ldh = ti.sh ? ldh_s : ldh_r;
+    uint16_t* hact = hact_r + (ti.sh ? hact_s : 0);
+    if (!storage_index(wv, ti.e, ti.se) || (halves == 2 && !half_rows(ti, half))) return take();
+#define SI_CALL_GU(FAV) gateup_body_qr<RingQR<FAV, 4>>(x, scalar_of_item(M), p, tc, ti, wv, hact, ldh, lds, take_)
+    SI_PICK_BODY_2PASS(ti, SI_CALL_GU)
+#undef SI_CALL_GU
+  });
+}
+
+__global__ __launch_bounds__(THREADS, 1) void k_prefill_down_qr(const uint16_t* __restrict__ hact_r, int ldh_r, int M, Plan p,
+                                                                int expert_sel, int x2_only,
+                                                                int n_ntiles, int split_r, WeightView wv_r, WeightView wv_s,
+                                                                int ldh_s, long hact_s, int split_s, float* __restrict__ yp,
+                                                                size_t slab_stride, int accumulate) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  const int n_in_r = n_ntiles * split_r, n_in_s = wv_s.n_chunks ? n_ntiles * split_s : 0;
+  const TileQueues tq = tile_queues(p, expert_sel, x2_only, n_in_r, n_in_s, false);
+  run_items(tq, p.queue + N_XCD * QUEUE_STRIDE, p.queue, lds, [&](int q, int item, auto take) {
+    int inner, half, halves;
+    TileInfo ti;
+    item_tile(tq, p, expert_sel, x2_only, q, item, n_in_r, inner, ti, half, halves);
+    const WeightView wv = ti.sh ? wv_s : wv_r;
+    const int ldh = ti.sh ? ldh_s : ldh_r, n_split = ti.sh ? split_s : split_r;
+    const uint16_t* hact = hact_r + (ti.sh ? hact_s : 0);
+    const DownRange dr = down_range(inner, n_ntiles, n_split, wv.n_chunks);
+    if (!storage_index(wv, ti.e, ti.se) || (halves == 2 && !half_rows(ti, half))) return take();
+#define SI_CALL_DN(FAV) down_body_qr<RingQR<FAV, 1>>(hact, ldh, scalar_of_item(M), dr, ti, wv, yp, slab_stride, accumulate, lds, take_)
     SI_PICK_BODY_2PASS(ti, SI_CALL_DN)
 #undef SI_CALL_DN
   });
@@ -1225,8 +1612,8 @@ __global__ void k_fill_zero(float* __restrict__ p, size_t n, size_t slab_stride)
 
 static hipError_t ensure_lds_attr() {
   static hipError_t st = [] {
-    const void* kernels[] = {(const void*)k_prefill_gateup, (const void*)k_prefill_down, (const void*)k_prefill_gateup_q4<false>,
-                             (const void*)k_prefill_down_q4<false>, (const void*)k_prefill_gateup_q4<true>, (const void*)k_prefill_down_q4<true>};
+    const void* kernels[] = {(const void*)k_prefill_gateup, (const void*)k_prefill_down, (const void*)k_prefill_gateup_qr,
+                             (const void*)k_prefill_down_qr, (const void*)k_prefill_gateup_q4, (const void*)k_prefill_down_q4};
     for (const void* k : kernels) {
       hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, KERNEL_LDS + NEXT_LDS);
       if (e != hipSuccess) return e;
@@ -1251,7 +1638,7 @@ hipError_t launch_prefill_gateup(const uint16_t* x, int M, const Plan& plan, int
   if (e != hipSuccess) return e;
   const int n_ctiles = (wv.n_chunks + 1) / 2;
   if (wv.q4)
-    hipLaunchKernelGGL(wv.q4 == Q4_WIDE ? k_prefill_gateup_q4<true> : k_prefill_gateup_q4<false>, dim3(N_XCD * XCD_CU), dim3(THREADS), KERNEL_LDS + NEXT_LDS, stream, x, M, plan, expert_sel, x2_only,
+    hipLaunchKernelGGL(wv.q4 == Q4_WIDE ? k_prefill_gateup_q4 : k_prefill_gateup_qr, dim3(N_XCD * XCD_CU), dim3(THREADS), KERNEL_LDS + NEXT_LDS, stream, x, M, plan, expert_sel, x2_only,
                        n_ctiles, wv, sp.wv, hact, ldh, sp.hact, sp.ldh);
   else
     hipLaunchKernelGGL(k_prefill_gateup, dim3(N_XCD * XCD_CU), dim3(THREADS), KERNEL_LDS + NEXT_LDS, stream, x, M, plan, expert_sel, x2_only,
@@ -1267,7 +1654,7 @@ hipError_t launch_prefill_down(const uint16_t* hact, int ldh, int M, const Plan&
   if (e != hipSuccess) return e;
   const int n_ntiles = (M + BN - 1) / BN;
   if (wv.q4)
-    hipLaunchKernelGGL(wv.q4 == Q4_WIDE ? k_prefill_down_q4<true> : k_prefill_down_q4<false>, dim3(N_XCD * XCD_CU), dim3(THREADS), KERNEL_LDS + NEXT_LDS, stream, hact, ldh, M, plan, expert_sel,
+    hipLaunchKernelGGL(wv.q4 == Q4_WIDE ? k_prefill_down_q4 : k_prefill_down_qr, dim3(N_XCD * XCD_CU), dim3(THREADS), KERNEL_LDS + NEXT_LDS, stream, hact, ldh, M, plan, expert_sel,
                        x2_only, n_ntiles, n_split, wv, sp.wv, sp.ldh, sp.hact, sp.split, yp, slab_stride, accumulate);
   else
     hipLaunchKernelGGL(k_prefill_down, dim3(N_XCD * XCD_CU), dim3(THREADS), KERNEL_LDS + NEXT_LDS, stream, hact, ldh, M, plan, expert_sel,
