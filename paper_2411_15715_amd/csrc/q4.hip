@@ -194,6 +194,155 @@ __global__ __launch_bounds__(QGU_THREADS, 4) void k_decode_gateup_q4(const uint1
   }
 }
 
+// The same for a launch over one expert whose rows are long (d_model > 6656), with the contraction split over the waves of a block: a wave
+// keeps its 2 units of x (up to 4 tokens) and their -136 sum(x) in registers over all groups (4 columns) of the block, so that neither takes
+// LDS or instructions per group; the partial sums of the waves meet in LDS at the end and are added in their order, which is the same for
+// every launch.  The groups are dealt equally to two blocks per compute unit: k_decode_gateup_q4 with 28672 columns of d_model 8192 is 896
+// blocks of 66 KB, 1.75 rounds, of which each stages 49 KB of x; with 1408 columns it is 44 blocks.
+// Dense layers, call before -> now (us): 8192 x 28672, 3 tokens 81.0 -> 75.7 (gate/up 53.8 -> 46.2, 5.4 TB/s); 8192 x 14336, 4 tokens 48.9 -> 45.8; 8192 x
+// 5632, 1 token 27.4 -> 24.8; 8192 x 1408, 4 tokens 25.2 -> 17.9; 7168 x 14336 equal, 7168 x 5632, 1 token 25.9 -> 23.8.  Shorter rows lose by it, as the
+// waves' shares get uneven and x in LDS is small: 5120 x 14336, 4 tokens (10 units on 8 waves) 35.3 -> 38.2, 4096 x 14336 equal, 1024 x 5632
+// 13.2 -> 14.7; so do launches over several experts (16 of 4864 x 3264, 8 tokens 45.2 -> 51.7: a block's share ends inside an expert and
+// starts over with the next one's x and scales).
+constexpr int QGS_WAVES = 8, QGS_THREADS = QGS_WAVES * WAVE, QGS_BLOCKS = 512;
+constexpr int QGS_UNITS = 14;          // from so many units (of 16) up
+constexpr int QGS_MAX_M = 8192;
+constexpr size_t QGS_LDS = 78 * 1024;  // two blocks per compute unit
+// (193 to 256 blocks of the other kernel are one good round of it, and but for the longest rows nothing is gained: 6720 x 7168, 4 tokens
+// 27.3 -> 29.0, 7424 x 7168 30.0 -> 30.4, 8192 x 8192 33.5 -> 32.3; 192 blocks: 6720 x 6144, 1 / 4 tokens 25.4 -> 23.6 / 26.5 -> 26.3)
+constexpr bool gateup_split(int M, int n_chunks) {
+  const int n_units = (M / 32 + 15) / 16, blocks = n_chunks * (CHUNK_J / QGU_JPB);
+  return M <= QGS_MAX_M && n_units >= QGS_UNITS && (n_units == 2 * QGS_WAVES || blocks <= 192 || blocks > 256);
+}
+// LDS of a block per group: scales [2][4][M / 64 + 2], partial sums [waves][2][4 tokens][4]
+constexpr size_t gateup_group_lds(int M) { return (size_t)16 * (M / 64 + 2) + 128 * QGS_WAVES; }
+__global__ __launch_bounds__(QGS_THREADS, 4) void k_decode_gateup_q4_split(const uint16_t* __restrict__ x, int M, Plan p, int expert_sel,
+                                                                           int x2_only, WeightView wv, int lds_groups,
+                                                                           float* __restrict__ h, int ldh) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char s_q[];
+  constexpr int GROUPS = CHUNK_J / 4;  // of a chunk
+  constexpr int KU = 2;                // units of x of a wave
+  const int tid = threadIdx.x, lane = tid % WAVE, w0 = __builtin_amdgcn_readfirstlane(tid / WAVE), j = lane & 3, pc = lane >> 2;
+  int e, r0, r1, se;
+  if (!block_rows(p, expert_sel, x2_only, 0, e, r0, r1)) return;
+  if (!storage_index(wv, e, se)) return;
+  const unsigned char* cb0 = reinterpret_cast<const unsigned char*>(wv.base + (size_t)se * wv.expert_stride + (size_t)wv.chunk0 * q4_chunk_u16(M));
+  const size_t cbytes = q4_chunk_u16(M) * 2;
+  const int n_pieces = M / 32, n_units = (n_pieces + 15) / 16;
+  const int MG = M / 64, GS = MG + 2;
+  uint16_t* s_sc = reinterpret_cast<uint16_t*>(s_q);                           // [2][lds_groups * 4][GS]
+  float* s_p = reinterpret_cast<float*>(s_q + (size_t)16 * lds_groups * GS);  // [waves][lds_groups][2][4 tokens][4]
+  uint32_t mask = 0x000F000Fu, magic = 0x43004300u, m136 = 0xC308C308u;  // (m136: two bf16 values -136)
+  asm volatile("" : "+v"(mask), "+s"(magic), "+v"(m136));  // kept out of the optimiser's sight (see expand_codes)
+  const s16x4 neg136 = __builtin_bit_cast(s16x4, (u32x2{m136, m136}));
+
+  // an equal share of the groups for every block, in stretches that LDS holds
+  const long long ng = wv.n_chunks * GROUPS;
+  const int hi = (int)(ng * (blockIdx.x + 1) / gridDim.x);
+  for (int g0 = (int)(ng * blockIdx.x / gridDim.x), n_g; g0 < hi; g0 += n_g) {
+    n_g = min(hi - g0, lds_groups);
+    // the lane's pieces of the wave's units w0 and w0 + 8
+    uint32_t off[KU], sidx[KU];  // bytes from the group's first gate code; its scale (past the row: a zero beside the row's scales)
+    const int n_mine = (n_units - w0 + QGS_WAVES - 1) / QGS_WAVES;
+#pragma unroll
+    for (int i = 0; i < KU; ++i) {
+      const int q = (w0 + QGS_WAVES * i) * 16 + pc;
+      off[i] = (uint32_t)(j * (M / 2) + min(q, n_pieces - 1) * 16);  // (a piece past the row is fetched from its end and not used)
+      sidx[i] = q < n_pieces ? q >> 1 : MG;
+    }
+    const uint32_t up = (uint32_t)(q4_off_codes(1, M) - q4_off_codes(0, M));
+    u32x4 wg[KU], wu[KU];
+    auto fetch = [&](int i, int gl) {  // unit i of group gl of the stretch
+      const int g = g0 + gl;
+      const unsigned char* base = cb0 + (size_t)(g / GROUPS) * cbytes + q4_off_codes(0, M) + (size_t)(g % GROUPS) * (2 * M);
+      wg[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + off[i]));
+      wu[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + up + off[i]));
+    };
+    auto fetch_first = [&]() {
+#pragma unroll
+      for (int i = 0; i < KU; ++i)
+        if (i < n_mine) fetch(i, 0);
+    };
+    fetch_first();
+    __syncthreads();  // (the stretch before is done with LDS)
+    // the scales of a group's 4 rows are contiguous: 4 per load (4 * MG of them)
+    for (int i = tid; i < 2 * n_g * MG; i += QGS_THREADS) {
+      const int f = i >= n_g * MG, k = f ? i - n_g * MG : i, gl = k / MG, pos = (k - gl * MG) * 4, g = g0 + gl;
+      const u32x2 v = *reinterpret_cast<const u32x2*>(cb0 + (size_t)(g / GROUPS) * cbytes + q4_off_scales(f, M) + ((size_t)(g % GROUPS) * 4 * MG + pos) * 2);
+      int r = pos / MG, c = pos - r * MG;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        s_sc[((f * lds_groups + gl) * 4 + r) * GS + c] = (uint16_t)(v[q >> 1] >> (16 * (q & 1)));
+        if (++c == MG) { c = 0; ++r; }
+      }
+    }
+    for (int i = tid; i < 8 * n_g; i += QGS_THREADS) s_sc[((i & 1) * lds_groups * 4 + (i >> 1)) * GS + MG] = 0;
+    for (int rb = r0; rb < r1; rb += QGU_TB) {
+      const int nt = min(QGU_TB, r1 - rb);
+      // operand rows past the last token repeat it, their results are not read
+      const uint16_t* xrow = x + (size_t)token_of_row(p, rb + min(j, nt - 1)) * M;
+      if (rb != r0) fetch_first();
+      u32x4 xv[KU][4];
+      f32x4 as[KU];
+#pragma unroll
+      for (int i = 0; i < KU; ++i) {
+#pragma unroll
+        for (int w = 0; w < 4; ++w) xv[i][w] = reinterpret_cast<const u32x4*>(xrow + (off[i] - j * (M / 2)) * 2)[w];
+        as[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+#pragma unroll
+          for (int f = 0; f < 2; ++f)
+            as[i] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(s16x4, (u32x2{xv[i][w][2 * f], xv[i][w][2 * f + 1]})), neg136, as[i], 0, 0, 0);
+      }
+      __syncthreads();  // the scales are in LDS, and the sums of the rows before have been taken from it
+      for (int gl = 0; gl < n_g; ++gl) {
+        const uint16_t* sc = s_sc + (gl * 4 + j) * GS;
+        f32x4 tg = {0.f, 0.f, 0.f, 0.f}, tu = tg;
+#pragma unroll
+        for (int i = 0; i < KU; ++i)
+          if (i < n_mine) {
+            f32x4 ag = {0.f, 0.f, 0.f, 0.f}, au = ag;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+              const u32x4 cg = expand_codes(wg[i][w], mask, magic), cu = expand_codes(wu[i][w], mask, magic);
+#pragma unroll
+              for (int f = 0; f < 2; ++f) {
+                const s16x4 xa = __builtin_bit_cast(s16x4, (u32x2{xv[i][w][2 * f], xv[i][w][2 * f + 1]}));
+                ag = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(xa, __builtin_bit_cast(s16x4, (u32x2{cg[2 * f], cg[2 * f + 1]})), ag, 0, 0, 0);
+                au = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(xa, __builtin_bit_cast(s16x4, (u32x2{cu[2 * f], cu[2 * f + 1]})), au, 0, 0, 0);
+              }
+            }
+            if (gl + 1 < n_g) fetch(i, gl + 1);
+            const float sg = bf16_f32(sc[sidx[i]]), su = bf16_f32(sc[lds_groups * 4 * GS + sidx[i]]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) { tg[r] = fmaf(sg, ag[r] + as[i][r], tg[r]); tu[r] = fmaf(su, au[r] + as[i][r], tu[r]); }
+          }
+        // sum over the 16 pieces; then lanes 0..3 (gate; 32..35 up) and 16..19 hold the tokens 2g and 2g + 1 of columns 0..3
+        float v[8] = {tg[0], tu[0], tg[1], tu[1], tg[2], tu[2], tg[3], tu[3]};
+        wave_sums<8, 4>(v);
+        if ((lane & 15) < 4) {
+          float* d = s_p + ((w0 * lds_groups + gl) * 2 + (lane >> 5)) * 16 + ((lane >> 4) & 1) * 4 + j;
+#pragma unroll
+          for (int g = 0; g < 2; ++g) d[8 * g] = v[g];
+        }
+      }
+      __syncthreads();
+      for (int i = tid; i < n_g * 4 * nt; i += QGS_THREADS) {
+        const int c = i & 3, t = (i >> 2) % nt, gl = (i >> 2) / nt, g = g0 + gl;
+        float vg = 0.f, vu = 0.f;
+#pragma unroll
+        for (int w = 0; w < QGS_WAVES; ++w) {
+          const float* s = s_p + (w * lds_groups + gl) * 32 + t * 4 + c;
+          vg += s[0];
+          vu += s[16];
+        }
+        h[(size_t)(rb + t) * ldh + wv.col0 + g * 4 + c] = silu_f(vg) * vu;
+      }
+    }
+  }
+}
+
 // 8 codes as the fp16 values c - 8 (exact), in the order of expand_codes.  A nibble inserted into 0x6400 is 1024 + c at bit 0
 // and 1024 + 16 c at bit 4, which a packed addition and a packed multiply-add turn into c - 8.
 struct SignedCodes {
@@ -414,7 +563,7 @@ constexpr size_t Q4_LDS = 81 * 1024;  // two blocks per compute unit
 
 hipError_t ensure_q4_lds() {
   static hipError_t st = [] {
-    const void* kernels[] = {(const void*)k_decode_gateup_q4<true>, (const void*)k_decode_gateup_q4<false>, (const void*)k_decode_down_q4};
+    const void* kernels[] = {(const void*)k_decode_gateup_q4<true>, (const void*)k_decode_gateup_q4<false>, (const void*)k_decode_gateup_q4_split, (const void*)k_decode_down_q4};
     for (const void* k : kernels) {
       const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)Q4_LDS);
       if (e != hipSuccess) return e;
@@ -430,6 +579,13 @@ hipError_t launch_decode_gateup_q4(const uint16_t* x, int M, const Plan& plan, i
                                    int max_touched, const WeightView& wv, const WeightView& ws, float* h, int ldh, hipStream_t stream) {
   if (wv.n_chunks <= 0) return hipSuccess;
   if (hipError_t e = ensure_q4_lds(); e != hipSuccess) return e;
+  if (expert_sel >= 0 && ws.n_chunks == 0 && gateup_split(M, wv.n_chunks)) {
+    const int ng = wv.n_chunks * (CHUNK_J / 4), blocks = std::min(QGS_BLOCKS, ng);
+    const int groups = std::min((ng + blocks - 1) / blocks, (int)(QGS_LDS / gateup_group_lds(M)));
+    hipLaunchKernelGGL(k_decode_gateup_q4_split, dim3(blocks), dim3(QGS_THREADS), groups * gateup_group_lds(M), stream, x, M, plan, expert_sel, x2_only, wv,
+                       groups, h, ldh);
+    return hipGetLastError();
+  }
   const int shared_y = (ws.n_chunks + wv.n_chunks - 1) / wv.n_chunks;
   dim3 grid(wv.n_chunks * (CHUNK_J / QGU_JPB), shared_y + (expert_sel >= 0 ? 1 : max_touched));
   const int tb = std::max(1, std::min(tb_hint, QGU_TB));
