@@ -105,10 +105,10 @@ __device__ inline void block_route(const FusedRoute& fr, BlockRoute& br, const P
     if (ex < E) { if (u.count) u.count[ex] = c; }
     if (ex <= E) { if (u.off) u.off[ex] = ex < E ? o : n_pairs; }
   }
-  if (tid < br.n_touched) p.touched[tid] = br.t_expert[tid];
+  if (tid < br.n_touched) p.touched[tid] = make_int4(br.t_expert[tid], br.t_off[tid], br.t_off[tid] + br.t_cnt[tid], 0);
   if (tid == 0) {
     int nt = br.n_touched;
-    if (fr.has_shared) p.touched[nt++] = E;  // the shared expert always has rows
+    if (fr.has_shared) p.touched[nt++] = make_int4(E, n_pairs, n_pairs + T, 0);  // the shared expert always has rows
     *p.n_touched = nt;
   }
 }

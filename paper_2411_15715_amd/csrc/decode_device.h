@@ -44,9 +44,16 @@ __device__ inline bool block_rows(const Plan& p, int expert_sel, int x2_only, in
   } else if (expert_sel >= 0) {
     e = expert_sel;
   } else {
-    if (slot >= *p.n_touched) return false;
-    e = p.touched[slot];
-    if (e >= p.n_routed) return false;
+    // one trip to memory for the expert and its rows: the number of experts, their indices and their offsets one after the other
+    // were three, before the first weight could be asked for.  (slot < entries of the table: the grid has no more)
+    const int32_t* rec = reinterpret_cast<const int32_t*>(p.touched);
+    const int n = table(p.n_touched, 0);
+    e = table(rec, 4 * slot);
+    r0 = table(rec, 4 * slot + 1);
+    r1 = table(rec, 4 * slot + 2);
+    if (slot >= n || e >= p.n_routed) return false;
+    if (x2_only) r0 += table(p.count1, e);
+    return r1 > r0;
   }
   r0 = row_begin(p, e, x2_only);
   r1 = row_end(p, e);

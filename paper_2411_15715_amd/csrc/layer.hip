@@ -658,13 +658,13 @@ int create_impl(const si_layer_desc_t* desc, const WeightSource& src, const uint
     size_t ints = 0;
     auto take = [&](size_t n) { size_t o = ints; ints += (n + 3) / 4 * 4; return o; };
     size_t o_idx = take(n_pairs), o_w = take(n_pairs), o_count = take(L->EX), o_off = take(L->EX + 1), o_count1 = take(L->EX),
-           o_perm = take(n_pairs), o_inv = take(n_pairs), o_rt = take(n_rows), o_touched = take(L->EX), o_nt = take(12),
+           o_perm = take(n_pairs), o_inv = take(n_pairs), o_rt = take(n_rows), o_touched = take(4 * (size_t)L->EX), o_nt = take(12),
            o_te = take(L->max_tiles), o_tr = take(L->max_tiles), o_te2 = take(L->max_tiles), o_tr2 = take(L->max_tiles), o_q = take(31 + 2 * 8 * QUEUE_STRIDE);
     TRY_OR_DESTROY(dev_alloc(&L->d_plan, ints * 4));
     int32_t* b = reinterpret_cast<int32_t*>(L->d_plan);
     L->plan.idx = b + o_idx; L->plan.w = reinterpret_cast<float*>(b + o_w); L->plan.count = b + o_count;
     L->plan.off = b + o_off; L->plan.count1 = b + o_count1; L->plan.perm = b + o_perm; L->plan.inv = b + o_inv;
-    L->plan.row_token = b + o_rt; L->plan.touched = b + o_touched; L->plan.n_touched = b + o_nt;
+    L->plan.row_token = b + o_rt; L->plan.touched = reinterpret_cast<int4*>(b + o_touched); L->plan.n_touched = b + o_nt;
     L->plan.n_tiles = b + o_nt + 4;
     L->plan.n_routed = E;
     L->plan.queue = b + (o_q + 31) / 32 * 32;

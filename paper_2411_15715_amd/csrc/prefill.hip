@@ -70,13 +70,6 @@ __device__ __forceinline__ int scalar_of_item(int v) {
   return v;
 }
 
-// Entry i (uniform) of a table that kernels before this one wrote, as a scalar load.  (Left to the compiler, which has to assume
-// that the stores of earlier tiles reach it, it is a vector load and a wait for all of them.)
-__device__ __forceinline__ int table(const int32_t* t, int i) {
-  typedef const int32_t __attribute__((address_space(4))) constant_t;
-  return ((constant_t*)(uintptr_t)t)[i];
-}
-
 // direct global -> LDS load of 16 bytes per lane: uniform base (scalar registers) + 32-bit byte offset of the lane
 __device__ inline void load_lds16(const void* base, uint32_t& off, unsigned char* l) {
   typedef const unsigned char __attribute__((address_space(1))) gchar;

@@ -106,7 +106,7 @@ __device__ __forceinline__ void assign_body(AssignLds& s, int T, int E, int k, i
       if (p.count) p.count[e] = s.tot[e];
       if (p.count1) p.count1[e] = s.tot1[e];
       if (p.off) p.off[e] = s.off[e];
-      if (p.touched && s.tot[e] > 0) p.touched[s.touch[e]] = e;
+      if (p.touched && s.tot[e] > 0) p.touched[s.touch[e]] = make_int4(e, s.off[e], s.off[e] + s.tot[e], 0);
       if (e < E) {
         if (u.count) u.count[e] = s.tot[e];
         if (u.off) u.off[e] = s.off[e];
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(256) void k_dense_assign(int T, int n_x1, Plan p, R
     if (p.count) p.count[0] = T;
     if (p.count1) p.count1[0] = n_x1;
     if (p.off) { p.off[0] = 0; p.off[1] = T; }
-    if (p.touched) p.touched[0] = 0;
+    if (p.touched) p.touched[0] = make_int4(0, 0, T, 0);
     if (p.n_touched) *p.n_touched = 1;
     if (u.count) u.count[0] = T;
     if (u.off) { u.off[0] = 0; u.off[1] = T; }
@@ -262,7 +262,10 @@ __global__ __launch_bounds__(ROUTE_THREADS) void k_route_few(const float* __rest
       if (routed && u.count) u.count[ex] = c;
       if (routed && u.off) u.off[ex] = off;
     }
-    if (p.touched && t_in) p.touched[n_touched + __popcll(mt & lt)] = ex;
+    if (p.touched && t_in) {
+      const int off = routed ? below : n_pairs;
+      p.touched[n_touched + __popcll(mt & lt)] = make_int4(ex, off, off + c, 0);
+    }
     if (p.tile_e) {
       if (r_in) { const int i = n_tiles + __popcll(mr & lt); p.tile_e[i] = ex + TILE_E_MASK + 1; p.tile_r[i] = 0; }
       if (x2_in) { const int i = n_x2 + __popcll(mx & lt); p.tile_e_x2[i] = ex + TILE_E_MASK + 1; p.tile_r_x2[i] = 0; }

@@ -50,7 +50,7 @@ struct Plan {
   int32_t* perm;       // [T*k]
   int32_t* inv;        // [T*k]
   int32_t* row_token;  // [T*k + T] token of each expert-sorted row
-  int32_t* touched;    // [EX] experts with count > 0, ascending
+  int4* touched;       // [EX] experts with count > 0, ascending: expert, first row, row after its last, 0
   int32_t* n_touched;  // [1]
   // Row tiles of the routed experts (all rows): the spill tiles, then the others, either by expert.  The tiles of an expert in
   // one of the two are a group: expert | tiles of the group * 512, and the index of the tile in its expert
@@ -98,6 +98,13 @@ struct WeightView {
 };
 
 #if defined(__HIPCC__)
+// Entry i (uniform) of a table that kernels before this one wrote, as a scalar load.  (Left to the compiler, which has to assume
+// that the stores of the kernel reach it, it is a vector load and a wait for all of them.)
+__device__ __forceinline__ int table(const int32_t* t, int i) {
+  typedef const int32_t __attribute__((address_space(4))) constant_t;
+  return ((constant_t*)(uintptr_t)t)[i];
+}
+
 // first row of expert e (of its X2 rows), row after its last, token of a row, row and weight of pair q
 __device__ inline int row_begin(const Plan& p, int e, int x2_only) {
   return p.dense_T ? (x2_only ? p.dense_x1 : 0) : p.off[e] + (x2_only ? p.count1[e] : 0);
