@@ -293,14 +293,14 @@ __global__ __launch_bounds__(GU_THREADS, 4) void k_decode_gateup(const uint16_t*
 template <int TB>
 __global__ __launch_bounds__(DN_THREADS, 5) void k_decode_down(const float* __restrict__ h, int ldh, int M, Plan p,
                                                             int expert_sel, int x2_only, WeightView wv_r, WeightView wv_s,
-                                                            int shared_z, int cps_s, int slot0, int chunks_per_slot,
+                                                            int shared_z, int cps_s, int slot0_s, int slot0, int chunks_per_slot,
                                                             float* __restrict__ part, size_t slot_stride) {
   int e, r0, r1;
   // the first shared_z layers of the grid are the j-slots of the shared expert
   const int slot = (int)blockIdx.z - shared_z;
   if (!block_rows(p, expert_sel, x2_only, slot, e, r0, r1)) return;
   const WeightView wv = slot < 0 ? wv_s : wv_r;
-  if (slot < 0) chunks_per_slot = cps_s;
+  if (slot < 0) { chunks_per_slot = cps_s; slot0 = slot0_s; }
   const int s = slot < 0 ? blockIdx.z * gridDim.y + blockIdx.y : blockIdx.y;
   const int c_begin = s * chunks_per_slot;
   const int c_end = min(c_begin + chunks_per_slot, wv.n_chunks);
@@ -448,9 +448,10 @@ hipError_t launch_decode_gateup(const uint16_t* x, int M, const Plan& plan, int 
 }
 
 hipError_t launch_decode_down(const float* h, int ldh, int M, const Plan& plan, int tb_hint, int expert_sel, int x2_only,
-                              int max_touched, const WeightView& wv, const WeightView& ws, int cps_s, int slot0, int chunks_per_slot,
+                              int max_touched, const WeightView& wv, const WeightView& ws, int cps_s, int slot0_s, int slot0, int chunks_per_slot,
                               float* part, size_t slot_stride, hipStream_t stream) {
   if (wv.n_chunks <= 0) return hipSuccess;
+  if (wv.q4 && slot0_s != slot0 && ws.n_chunks) return hipErrorInvalidValue;  // (the 4-bit kernel has one first slot)
   if (wv.q4)
     return launch_decode_down_q4(h, ldh, M, plan, tb_hint, expert_sel, x2_only, max_touched, wv, ws, cps_s, slot0, chunks_per_slot,
                                  part, slot_stride, stream);
@@ -459,7 +460,7 @@ hipError_t launch_decode_down(const float* h, int ldh, int M, const Plan& plan, 
   dim3 grid((M + DN_THREADS - 1) / DN_THREADS, n_slots, shared_z + (expert_sel >= 0 ? 1 : max_touched));
   const int tb = pick_tb(tb_hint);
   size_t lds = (size_t)tb * std::max(chunks_per_slot, slots_s ? cps_s : 0) * CHUNK_J * sizeof(float);
-#define SI_DN(TBV) hipLaunchKernelGGL(k_decode_down<TBV>, grid, dim3(DN_THREADS), lds, stream, h, ldh, M, plan, expert_sel, x2_only, wv, ws, shared_z, cps_s, slot0, chunks_per_slot, part, slot_stride)
+#define SI_DN(TBV) hipLaunchKernelGGL(k_decode_down<TBV>, grid, dim3(DN_THREADS), lds, stream, h, ldh, M, plan, expert_sel, x2_only, wv, ws, shared_z, cps_s, slot0_s, slot0, chunks_per_slot, part, slot_stride)
   if (tb == 1) SI_DN(1); else if (tb == 2) SI_DN(2); else SI_DN(4);
 #undef SI_DN
   return hipGetLastError();

@@ -899,6 +899,17 @@ int cps_resident(int ch, bool single_expert, int M, int n_e) {
 // took 11.7 us); a larger one hides behind the link.
 int cps_streamed(int ch, bool single_expert, int M) { return ch <= 8 ? 1 : cps_of(ch, single_expert, M); }
 
+// Streamed parts that the generation-phase kernels read from host memory, in the launches of the resident part: of dense layers, of calls of up
+// to IN_PLACE_MAX_T tokens (one pass over the weights; the GEMVs keep enough loads in flight for the rate of the link) without CG'.
+// Against a copy by a kernel or through the ring, in launches of their own (us, calls in a row): where the host computes a share and the
+// copies would start behind the hand-off, 256 x 704 40/30/30, 4 tokens 45.7 -> 33.7; 1024 x 1472 40/30/30, 1 / 4 tokens 112 -> 91 / 129 -> 99; 2048 x 2048 40/30/30
+// (7.1 MB) 201 -> 141 / 249 -> 154; where it does not, 256 x 704 80/20/0, 1 / 4 tokens 27.5 -> 14.3 / 29.6 -> 18.9; 1024 x 1472 80/20/0 58 -> 46 / 67 -> 51.  Above the
+// lines, and beside a large resident part, parts are copied as before.  With a host share that is the worse way at any size measured (4096 x
+// 2816 40/30/30, 20 MB: 466 where in place is 379; 8192 x 5632, 83 MB: 1710 / 1526), but it is the copy schedule that the host tests hold; without
+// one the two cross near 24 MB (2048 x 2816 80/20/0, 6.9 MB 159 / 137; 4096 x 1984 50/50/0, 24.4 MB 435 / 429; 4096 x 4608 50/50/0, 57 MB 1013 / 1025).
+constexpr int IN_PLACE_MAX_T = 4;
+constexpr size_t IN_PLACE_BYTES_WAITING = (size_t)8 << 20, IN_PLACE_BYTES = (size_t)2 << 20;
+
 // Rows handed to the host and its results are moved by kernels up to this size, above by the copy engine (whose start
 // costs as much as some 256 KB on the link).
 constexpr size_t HANDOFF_DIRECT_BYTES = 256 << 10;
@@ -1074,13 +1085,19 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
   hipError_t ke = hipSuccess;
 #define K_TRY(expr) do { ke = (expr); if (ke != hipSuccess) return fail(SI_EHIP, "%s failed: %s", #expr, hipGetErrorString(ke)); } while (0)
 
+  // The streamed part of a dense layer in a call of so few tokens that each weight is read once: the generation-phase kernels read it from
+  // host memory themselves, in the launches of the resident part and before the host waits for anything.  Same sums, same slots as with a copy
+  // in between.  (Not in a stack, where the copies of consecutive layers follow each other on one stream, and not where they are timed.)
+  const bool cg_in_place = path == SI_DECODE && dense && !L->q4 && !L->placed && !L->profiling && L->ch_gg > 0 && L->ch_cg > 0 && L->copy_stream == L->own_copy_stream &&
+                           T <= IN_PLACE_MAX_T && !need_cgp && resident_bytes(L, T * k) <= DIRECT_RESIDENT_BYTES &&
+                           (size_t)L->ch_cg * ce * 2 <= (need_cc ? IN_PLACE_BYTES_WAITING : IN_PLACE_BYTES);
   // process chunks [c0, c0+n) (relative to `base`) of a part on the GPU.
   //   expert_sel < 0: all routed experts from their resident GG storage
   //   col_base: hidden column of chunk c0 within the expert;  part: 0 GG, 1 CG, 2 CC(CG')
   //   ws: the shared expert's resident part, to go into the same launches (n_chunks == 0: not)
   const WeightView no_ws{};
   auto run_part = [&](const uint16_t* base, size_t estride, int expert_sel, int is_shared, int c0, int n, int col_base,
-                      int part, int part_chunk0, int x2_only, bool first_for_rows, const WeightView& ws) -> int {
+                      int part, int part_chunk0, int x2_only, bool first_for_rows, const WeightView& ws, int ws_cps, int ws_slot) -> int {
     if (n <= 0) return SI_OK;
     WeightView wv{base, estride, c0, n, 0, L->q4, nullptr};
     if (L->placed && !is_shared) {
@@ -1101,7 +1118,7 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
         fuse_route = false;  // the tables exist from here on
       }
       SegScope sc(L, stream, SI_K_DECODE_DOWN);
-      K_TRY(launch_decode_down(L->d_h, L->ldh_dec, M, L->plan, T, esel, x2_only, max_touched, wv, ws, scps_gg,
+      K_TRY(launch_decode_down(L->d_h, L->ldh_dec, M, L->plan, T, esel, x2_only, max_touched, wv, ws, ws_cps, ws_slot,
                                part * DOWN_SLOTS + part_chunk0 / cps, cps, L->d_part, slot_stride, stream));
     } else {
       const int n_rt = esel >= 0 ? n_row_tiles(x2_only ? rows_x2(esel) : rows_all(esel)) : tiles_upper;
@@ -1171,11 +1188,17 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
     WeightView ws{};
     // (col0 as in run_part: the generation phase keeps h by the column of the expert, the prompt phase by that of the launch)
     if (joint) ws = WeightView{L->d_sgg, 0, 0, L->sch_gg, path == SI_DECODE ? (L->sch_cc + L->sch_cg) * CHUNK_J : 0, L->q4, nullptr};
-    if (E == 1) rc = run_part(L->d_gg, 0, 0, 0, 0, L->ch_gg, hch * CHUNK_J, 0, 0, 0, true, ws);
-    else rc = run_part(L->d_gg, (size_t)L->ch_gg * ce, -1, 0, 0, L->ch_gg, hch * CHUNK_J, 0, 0, 0, true, ws);
+    if (cg_in_place) ws = WeightView{L->host_base(0) + (size_t)L->ch_cc * ce, 0, 0, L->ch_cg, L->ch_cc * CHUNK_J, 0, nullptr};
+    const int ws_cps = cg_in_place ? cps_cg : scps_gg, ws_slot = cg_in_place ? DOWN_SLOTS : 0;
+    if (E == 1) rc = run_part(L->d_gg, 0, 0, 0, 0, L->ch_gg, hch * CHUNK_J, 0, 0, 0, true, ws, ws_cps, ws_slot);
+    else rc = run_part(L->d_gg, (size_t)L->ch_gg * ce, -1, 0, 0, L->ch_gg, hch * CHUNK_J, 0, 0, 0, true, ws, ws_cps, ws_slot);
+    if (cg_in_place) {
+      st.bytes_streamed += (double)L->ch_cg * ce * 2;
+      st.n_copies++;
+    }
     if (rc) return rc;
     if (L->has_shared && !joint) {
-      rc = run_part(L->d_sgg, 0, 0, 1, 0, L->sch_gg, (L->sch_cc + L->sch_cg) * CHUNK_J, 0, 0, 0, true, no_ws);
+      rc = run_part(L->d_sgg, 0, 0, 1, 0, L->sch_gg, (L->sch_cc + L->sch_cg) * CHUNK_J, 0, 0, 0, true, no_ws, 0, 0);
       if (rc) return rc;
     }
   }
@@ -1230,6 +1253,7 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
       for (int part = 1; part <= 2; ++part) {  // CG on all rows, then CG' (the CC range) on the X2 rows
         const int x2_only = part == 2;
         if (part == 2 && (!need_cgp || rows_x2(e) <= 0)) continue;
+        if (part == 1 && cg_in_place) continue;
         const int pc0 = part == 2 ? 0 : n_cc_e, pn = part == 2 ? n_cc_e : n_cg_e;
         const int cps = sh ? (part == 2 ? scps_cc : scps_cg) : (part == 2 ? cps_cc : cps_cg);
         const int piece_max = piece_chunks(L, path, cps);
@@ -1249,7 +1273,7 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
               HIP_TRY(hipGetLastError());
             }
             L->in_staged = 1;
-            int rc = run_part(L->d_direct, 0, sh ? 0 : e, sh, 0, n, (pc0 + c) * CHUNK_J, part, c, x2_only, false, no_ws);
+            int rc = run_part(L->d_direct, 0, sh ? 0 : e, sh, 0, n, (pc0 + c) * CHUNK_J, part, c, x2_only, false, no_ws, 0, part * DOWN_SLOTS);
             L->in_staged = 0;
             if (rc) return rc;
             st.bytes_streamed += (double)(n * chunk_bytes);
@@ -1271,7 +1295,7 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
           HIP_TRY(hipStreamWaitEvent(stream, L->ev_ready[slot], 0));
           {
             L->in_staged = 1;
-            int rc = run_part(L->d_stage[slot], 0, sh ? 0 : e, sh, 0, n, (pc0 + c) * CHUNK_J, part, c, x2_only, false, no_ws);
+            int rc = run_part(L->d_stage[slot], 0, sh ? 0 : e, sh, 0, n, (pc0 + c) * CHUNK_J, part, c, x2_only, false, no_ws, 0, part * DOWN_SLOTS);
             L->in_staged = 0;
             if (rc) return rc;
           }

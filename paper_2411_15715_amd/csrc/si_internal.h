@@ -151,9 +151,10 @@ struct DecodeCombineArgs {
   int T, k, M, n_x1, has_shared;
 };
 // part[slot][row][m] = sum over the j of the slot of h[row][j] * Wd[j][m]
-// (ws, cps_s: the shared expert's weights and chunks per slot, as above)
+// (ws, cps_s, slot0_s: the shared expert's weights, chunks per slot and first slot, as above.  In a launch over the one expert of a dense
+// layer ws may be another part of that expert: gate/up and down then cover both.)
 hipError_t launch_decode_down(const float* h, int ldh, int M, const Plan& plan, int tb_hint, int expert_sel, int x2_only,
-                              int max_touched, const WeightView& wv, const WeightView& ws, int cps_s, int slot0, int chunks_per_slot,
+                              int max_touched, const WeightView& wv, const WeightView& ws, int cps_s, int slot0_s, int slot0, int chunks_per_slot,
                               float* part, size_t slot_stride, hipStream_t stream);
 hipError_t launch_decode_combine(const DecodeCombineArgs& a, const Plan& plan, float* y, hipStream_t stream);
 
