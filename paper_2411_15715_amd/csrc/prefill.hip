@@ -300,8 +300,13 @@ template <int FAV, int NJV> struct Ring {
   static constexpr int BM = 32 * FA;                               // rows of the tile
   static constexpr int BNW = 64 * NJ;                              // B rows
   static constexpr int NP = FA <= 4 ? 1 : FA <= 8 ? 2 : 3;         // phases per k-tile
-  static constexpr int NA = FA <= 5 ? 3 : 2;                       // LDS stages of A
-  static constexpr int NB = FA <= 2 ? 4 : FA <= 5 ? 3 : 2;         // LDS stages of B
+  // LDS stages of A and B.  Tiles of 65 to 128 rows cut along their columns (NJ = 2) have room for a fourth, and a launch of few such tiles is
+  // bound by the loads a compute unit has in flight: calls of dense 4096 x 11008, 90 / 100 tokens 78.2 -> 73.6 / 81.2 -> 76.9 us, 128 tokens 85.8 -> 82.0.
+  // Not below, where LDS reads and the barrier of a k-tile take longer than its loads: five stages gained 1 to 5 % with 48 and 64 tokens (4096 x
+  // 8192 and x 4096) and lost 2 to 6 % with 8 and 24 (4864 x 1664 35.1 -> 37.4, 1024 x 1024 17.2 -> 17.9: the ring is full later).
+  static constexpr bool DEEP = NJ == 2 && FA >= 3 && FA <= 4;
+  static constexpr int NA = DEEP ? 4 : FA <= 5 ? 3 : 2;
+  static constexpr int NB = DEEP || FA <= 2 ? 4 : FA <= 5 ? 3 : 2;
   static constexpr int A_STAGE = BM * 128;
   static constexpr int B_STAGE = BNW * 128;
   static constexpr int B_OFF = NA * A_STAGE;
@@ -355,6 +360,13 @@ template <int FAV, int NJV> struct Ring {
     for (int it = 0; it < 2 * R + 2; ++it) { const int y = younger_at(it, q, rem); n = y < n ? y : n; }
     return n;
   }
+  // the same for the first phase of tile 0 behind the prologue of a loop of nk tiles (a k-split of FC2 may have fewer than stages; a wait for all
+  // of them there took dense 5120 x 1024, 120 tokens, from 57.7 to 58.7 us with the fourth stage)
+  static constexpr int younger_start(int nk) {
+    int n = ALD - aloads(0);
+    for (int t = 1; t < nk && t < R; ++t) n += (t < NA ? ALD : 0) + (t < NB ? BL : 0);
+    return n;
+  }
   static_assert(LDS <= KERNEL_LDS, "ring does not fit");
 };
 
@@ -378,6 +390,15 @@ template <int R, class P, int Q> __device__ __forceinline__ void ring_wait(int r
   } else {
     if (rem >= R) wait_vmcnt<P::younger(Q, R)>();
     else ring_wait<R - 1, P, Q>(rem);
+  }
+}
+
+template <int N, class P> __device__ __forceinline__ void ring_wait_start(int nk) {
+  if constexpr (N == 1) {
+    wait_vmcnt<P::younger_start(1)>();
+  } else {
+    if (nk >= N) wait_vmcnt<P::younger_start(N)>();
+    else ring_wait_start<N - 1, P>(nk);
   }
 }
 
@@ -458,8 +479,7 @@ __device__ __forceinline__ void gemm_pingpong(unsigned char* lds, int nk, int la
         if (t < P::NA) issue_region(p, t, t);
         if (p == 0 && t < P::NB) issue_b(b_stage(t), t);
       });
-  if (nk >= P::R) wait_vmcnt<P::NA * P::ALD + P::NB * P::BL - P::aloads(0) - P::BL>();  // the first region of A and B of tile 0
-  else wait_vmcnt<0>();
+  ring_wait_start<P::R, P>(nk);  // the first region of A and B of tile 0
   block_barrier();
   __builtin_amdgcn_sched_barrier(0);
   if (PONG && wr == 1) block_barrier();
