@@ -422,12 +422,12 @@ __global__ __launch_bounds__(64 * MERGE_WAVES) void k_decode_combine(DecodeCombi
 static int pick_tb(int tb_hint) { return tb_hint <= 1 ? 1 : (tb_hint <= 2 ? 2 : 4); }
 
 hipError_t launch_decode_gateup(const uint16_t* x, int M, const Plan& plan, int tb_hint, int expert_sel, int x2_only,
-                                int max_touched, const WeightView& wv, const WeightView& ws, float* h, int ldh,
+                                int max_touched, const WeightView& wv, int e_chunks, const WeightView& ws, float* h, int ldh,
                                 hipStream_t stream, const FusedRoute* fused_route) {
   if (wv.n_chunks <= 0) return hipSuccess;
   if (wv.q4) {
     if (fused_route) return hipErrorInvalidValue;  // the 4-bit kernels take the assignment from the tables
-    return launch_decode_gateup_q4(x, M, plan, tb_hint, expert_sel, x2_only, max_touched, wv, ws, h, ldh, stream);
+    return launch_decode_gateup_q4(x, M, plan, tb_hint, expert_sel, x2_only, max_touched, wv, e_chunks, ws, h, ldh, stream);
   }
   const int shared_y = (ws.n_chunks + wv.n_chunks - 1) / wv.n_chunks;
   dim3 grid(wv.n_chunks * (CHUNK_J / GU_JPB), shared_y + (expert_sel >= 0 ? 1 : max_touched));

@@ -1113,7 +1113,7 @@ int si_layer_forward(si_layer_t* L, const void* x_dev, const float* logits_dev, 
       const int cps = is_shared ? (part == 0 ? scps_gg : part == 1 ? scps_cg : scps_cc) : (part == 0 ? cps_gg : part == 1 ? cps_cg : cps_cc);
       {
         SegScope sc(L, stream, SI_K_DECODE_GATEUP);
-        K_TRY(launch_decode_gateup(x, M, L->plan, T, esel, x2_only, max_touched, wv, ws, L->d_h, L->ldh_dec, stream,
+        K_TRY(launch_decode_gateup(x, M, L->plan, T, esel, x2_only, max_touched, wv, (is_shared ? L->Hs : L->H) / CHUNK_J, ws, L->d_h, L->ldh_dec, stream,
                                    fuse_route ? &fr : nullptr));
         fuse_route = false;  // the tables exist from here on
       }

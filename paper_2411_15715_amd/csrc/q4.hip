@@ -209,9 +209,11 @@ constexpr int QGS_UNITS = 14;          // from so many units (of 16) up
 constexpr int QGS_MAX_M = 8192;
 constexpr size_t QGS_LDS = 78 * 1024;  // two blocks per compute unit
 // (193 to 256 blocks of the other kernel are one good round of it, and but for the longest rows nothing is gained: 6720 x 7168, 4 tokens
-// 27.3 -> 29.0, 7424 x 7168 30.0 -> 30.4, 8192 x 8192 33.5 -> 32.3; 192 blocks: 6720 x 6144, 1 / 4 tokens 25.4 -> 23.6 / 26.5 -> 26.3)
-constexpr bool gateup_split(int M, int n_chunks) {
-  const int n_units = (M / 32 + 15) / 16, blocks = n_chunks * (CHUNK_J / QGU_JPB);
+// 27.3 -> 29.0, 7424 x 7168 30.0 -> 30.4, 8192 x 8192 33.5 -> 32.3; 192 blocks: 6720 x 6144, 1 / 4 tokens 25.4 -> 23.6 / 26.5 -> 26.3.
+// The blocks are those of the whole expert, not of a launch over a part or a piece of one: the kernels sum a row in different orders, and
+// a result must not depend on how a streamed part is cut.  Such calls wait for their copies, 12 us a chunk, whichever kernel it is.)
+constexpr bool gateup_split(int M, int e_chunks) {
+  const int n_units = (M / 32 + 15) / 16, blocks = e_chunks * (CHUNK_J / QGU_JPB);
   return M <= QGS_MAX_M && n_units >= QGS_UNITS && (n_units == 2 * QGS_WAVES || blocks <= 192 || blocks > 256);
 }
 // LDS of a block per group: scales [2][4][M / 64 + 2], partial sums [waves][2][4 tokens][4]
@@ -576,10 +578,10 @@ hipError_t ensure_q4_lds() {
 }  // namespace
 
 hipError_t launch_decode_gateup_q4(const uint16_t* x, int M, const Plan& plan, int tb_hint, int expert_sel, int x2_only,
-                                   int max_touched, const WeightView& wv, const WeightView& ws, float* h, int ldh, hipStream_t stream) {
+                                   int max_touched, const WeightView& wv, int e_chunks, const WeightView& ws, float* h, int ldh, hipStream_t stream) {
   if (wv.n_chunks <= 0) return hipSuccess;
   if (hipError_t e = ensure_q4_lds(); e != hipSuccess) return e;
-  if (expert_sel >= 0 && ws.n_chunks == 0 && gateup_split(M, wv.n_chunks)) {
+  if (expert_sel >= 0 && ws.n_chunks == 0 && gateup_split(M, e_chunks)) {
     const int ng = wv.n_chunks * (CHUNK_J / 4), blocks = std::min(QGS_BLOCKS, ng);
     const int groups = std::min((ng + blocks - 1) / blocks, (int)(QGS_LDS / gateup_group_lds(M)));
     hipLaunchKernelGGL(k_decode_gateup_q4_split, dim3(blocks), dim3(QGS_THREADS), groups * gateup_group_lds(M), stream, x, M, plan, expert_sel, x2_only, wv,

@@ -127,6 +127,7 @@ __device__ inline bool storage_index(const WeightView& wv, int e, int& se) {
 //  x2_only: restrict to rows of X2 tokens (CG').
 //  ws: the shared expert's weights, covered by the same launch (n_chunks == 0: not); its blocks come first in the grid.
 //  tb_hint: upper bound on the rows of one expert (T); picks the tokens-per-pass instantiation (1, 2 or 4).
+//  e_chunks: chunks of an expert of wv in all its parts.  (What a launch of one part must not decide by itself: the order of the sums.)
 // Token assignment folded into the first gate/up launch of a generation-phase call with few tokens (the launch of a
 // separate assignment kernel costs as much as reading tens of megabytes): every block derives the assignment of
 // the <= FUSED_ROUTE_MAX_T tokens itself and finds its expert from it; block (0, 0) also writes the tables that the
@@ -139,7 +140,7 @@ struct FusedRoute {
   RouteOut user;
 };
 hipError_t launch_decode_gateup(const uint16_t* x, int M, const Plan& plan, int tb_hint, int expert_sel, int x2_only,
-                                int max_touched, const WeightView& wv, const WeightView& ws, float* h, int ldh,
+                                int max_touched, const WeightView& wv, int e_chunks, const WeightView& ws, float* h, int ldh,
                                 hipStream_t stream, const FusedRoute* fused_route = nullptr);
 // part[slot][row][m] = sum over the j of the slot of h[row][j] * Wd[j][m]
 // y[t][m] = sum_s w[t][s] * sum_slots part[slot][inv[t*k+s]][m] + shared rows + ycc[t][m]
@@ -185,7 +186,7 @@ hipError_t launch_fill_zero(float* p, size_t n, int n_slabs, size_t slab_stride,
 // q4.hip -------------------------------------------------------------------------------------
 // the GEMV launchers of decode.hip hand over to these when wv.q4 is set
 hipError_t launch_decode_gateup_q4(const uint16_t* x, int M, const Plan& plan, int tb_hint, int expert_sel, int x2_only,
-                                   int max_touched, const WeightView& wv, const WeightView& ws, float* h, int ldh, hipStream_t stream);
+                                   int max_touched, const WeightView& wv, int e_chunks, const WeightView& ws, float* h, int ldh, hipStream_t stream);
 hipError_t launch_decode_down_q4(const float* h, int ldh, int M, const Plan& plan, int tb_hint, int expert_sel, int x2_only,
                                  int max_touched, const WeightView& wv, const WeightView& ws, int cps_s, int slot0,
                                  int chunks_per_slot, float* part, size_t slot_stride, hipStream_t stream);

@@ -29,3 +29,21 @@ def test_split_rows(oracle, d_model, d_ff):
             assert np.array_equal(y, full[:T])  # a token's sums do not depend on its batch
     finally:
         L.close()
+
+
+@pytest.mark.parametrize("d_model,chunks", [(6720, 120), (6720, 140), (8192, 100)])
+def test_pieces_of_a_part(d_model, chunks):
+    """A streamed part in one launch and in pieces, in a layer of a size for either kernel: the same bits."""
+    cfg = synth.scaled(synth.CONFIGS["llama2_70b"], d_model=d_model, d_ff=64 * chunks, seed=chunks)
+    wq = synth.make_weights_q4(cfg)
+    xp = synth.make_tokens(cfg, 5)
+    for split in ((0.0, 1.0, 0.0), (20 / chunks, 1 - 20 / chunks, 0.0)):
+        outs = []
+        for stage_mib in (256, 16):
+            print("pieces M=%d chunks=%d stage %d MiB" % (d_model, chunks, stage_mib), flush=True)
+            L = Q4Layer(cfg, wq, split, max_tokens=8, stage_mib=stage_mib)
+            try:
+                outs.append([L.forward(xp[:T], None, mode=si.SI_DECODE) for T in (1, 5)])
+            finally:
+                L.close()
+        assert all(np.array_equal(a, b) for a, b in zip(*outs))

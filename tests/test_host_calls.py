@@ -329,3 +329,41 @@ def test_a_call_after_one_that_failed_anywhere(host, M, H, split, kw):
     print(n)
     """ % (M, H, split, kw))
     assert int(out) > 10
+
+
+def test_the_gate_up_kernel_of_a_4bit_expert_does_not_follow_the_cut_of_its_parts(host):
+    """The two 4-bit gate/up kernels sum a row in different orders: all launches over one expert's columns by itself take the same one,
+    whatever the size of the part, of a staging buffer and of the pieces.  120 chunks of d_model 6720 are 82 MB."""
+    host("""
+    def layer_q4(M, H, split, E, k, Hs, stage_mib):
+        w = {}
+        for pre, lead, h in (("", (E,), H), ("s", (), Hs)):
+            if h:
+                for n in ("gate", "up", "down"):
+                    w[pre + "q_" + n] = np.zeros(lead + (h, M // 2), np.uint8)
+                w[pre + "z_gate"], w[pre + "z_up"] = (np.zeros(lead + (h, M // 64), np.uint16) for _ in range(2))
+                w[pre + "z_down"] = np.zeros(lead + (h // 64, M), np.uint16)
+        return si.si_layer_create_q4(M, H, E, k, w, *split, 16, d_ff_shared=Hs, stage_mib=stage_mib)
+
+    def kernels(M, chunks, cg, cc=0, stage_mib=0, E=1, k=1, sh=0, T=2, n_g=0):
+        h = layer_q4(M, 64 * chunks, ((chunks - cg - cc) / chunks, cg / chunks, cc / chunks), E, k, 64 * sh, stage_mib)
+        log()
+        forward(h, M, T, E=E, n_g=n_g, mode=si.SI_DECODE)
+        names = [l.split()[0] for l in log() if l.startswith("k_decode_gateup")]
+        si.si_layer_destroy(h)
+        return set(names), len(names)
+
+    WHOLE, SPLIT = "k_decode_gateup_q4", "k_decode_gateup_q4_split"
+    # one launch or many: whole parts, pieces of 23 chunks, parts on both sides of 96 and of 128 chunks
+    for M, chunks, want in ((6720, 120, WHOLE), (6720, 140, SPLIT), (6720, 96, SPLIT), (8192, 120, SPLIT), (6592, 96, WHOLE)):
+        assert kernels(M, chunks, 0)[0] == {want}
+        for cg, cc, n_g in ((chunks, 0, 0), (chunks - 20, 0, 0), (chunks // 3, 0, 0), (chunks // 3, chunks // 3, 2)):
+            for stage_mib in (0, 16):
+                names, n = kernels(M, chunks, cg, cc, stage_mib, n_g=n_g)
+                assert names == {want} and (n > 2 or not stage_mib), (M, chunks, cg, stage_mib, names, n)
+    # the streamed experts of several, and a shared expert by itself
+    for stage_mib in (0, 16):
+        assert kernels(6720, 110, 110, stage_mib=stage_mib, E=2)[0] == {WHOLE}
+        assert kernels(6720, 24, 24, stage_mib=stage_mib, E=2, sh=110)[0] == {SPLIT, WHOLE}
+        assert kernels(6720, 24, 24, stage_mib=stage_mib, E=2, sh=48)[0] == {SPLIT}
+    """)
