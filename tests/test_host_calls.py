@@ -160,9 +160,10 @@ def test_a_recorded_prompt_call_clears_its_tile_queues(host, kw):
 
 
 def test_which_parts_a_kernel_copies(host):
-    """Generation calls: a dense layer's parts of up to 32 MB where the host computes a share, of up to 8 MB without, of several
-    experts 4 MB, both with few rows, each whole whatever the size of a staging buffer.  All else uses the ring, in pieces: larger parts to their last piece, many rows, calls
-    beside a large resident part.  Chunks of 64 columns of d_model 4096 are 1.5 MB."""
+    """Generation calls whose streamed part is not read in place (test_which_parts_are_read_in_place): a dense layer's parts of up to 32 MB where
+    the host computes a share, of up to 8 MB without, of several experts 4 MB, both with few rows, each whole whatever the size of a staging
+    buffer.  All else uses the ring, in pieces: larger parts to their last piece, many rows, calls beside a large resident part.  Chunks of 64 columns of
+    d_model 4096 are 1.5 MB."""
     host("""
     def run(M, chunks, cg, cc=0, stage_mib=0, T=1, E=1, k=1, Hs=0, n_g=0, n_stage=0, mode=si.SI_DECODE):
         split = ((chunks - cg - cc) / chunks, cg / chunks, cc / chunks)
@@ -196,6 +197,60 @@ def test_which_parts_a_kernel_copies(host):
     assert run(1024, 8, 2, 2, E=8, k=2, T=7, n_g=1) == (8, 8)   # CG of 7 rows, CG' of 1
     assert run(8192, 8, 1, E=8, k=2) == (0, 8)
     assert run(1024, 8, 2, E=1, Hs=512) == (2, 0)
+    """)
+
+
+def test_which_parts_are_read_in_place(host):
+    """Generation calls of up to four tokens: a bf16 dense layer's streamed part of up to 8 MB where the host computes a share, of up to 2 MB
+    without, beside a resident part of up to 64 MB, takes no copy and no launch of its own, recorded or not.  Not with CG' rows, in a stack, while the
+    call is timed, on the prompt path, for 4-bit weights or beside other experts.  Chunks are 96 KiB at d_model 256, 384 KiB at 1024, 768 KiB at 2048."""
+    host("""
+    def calls_of(h, f):
+        log()
+        f()
+        lines = log()
+        n = lambda *names: len(calls(lines, *names))
+        return n("k_copy_piece", "hipMemcpyAsync"), n("k_decode_gateup", "k_decode_gateup_q4"), n("k_decode_down", "k_decode_down_q4"), n("hipStreamWaitEvent")
+
+    def run(M, chunks, cg, cc=0, T=1, n_g=0, mode=si.SI_DECODE, timed=0, E=1, Hs=0):
+        h = layer(M, 64 * chunks, ((chunks - cg - cc) / chunks, cg / chunks, cc / chunks), E=E, Hs=Hs)
+        si.si_layer_set_profiling(h, timed)
+        out = calls_of(h, lambda: forward(h, M, T, E=E, n_g=n_g, mode=mode))
+        st = si.si_layer_stats(h)
+        if cg and not n_g and E == 1 and not Hs:
+            assert st["n_copies"] == 1 and st["bytes_streamed"] == cg * 384 * M, st  # one streamed piece, however it travels
+        si.si_layer_destroy(h)
+        return out
+    IN_PLACE = (0, 1, 1, 0)
+    copied = lambda out: out[:3] == (1, 2, 2)
+    for T in (1, 2, 3, 4):
+        assert run(256, 11, 3, 3, T=T) == IN_PLACE
+        assert run(256, 40, 21, T=T) == IN_PLACE            # 1.97 MB
+        assert copied(run(256, 40, 22, T=T))                # 2.06 MB
+        assert run(2048, 24, 10, 1, T=T) == IN_PLACE        # 7.5 MB and a host share
+        assert copied(run(2048, 24, 11, 1, T=T))            # 8.25 MB
+    assert copied(run(256, 11, 3, 3, T=5)) and copied(run(256, 40, 21, T=5))
+    assert run(1024, 170, 1, 1) == IN_PLACE                 # beside 63 MB
+    assert copied(run(1024, 173, 1, 1))                     # beside 64.1 MB
+    assert copied(run(256, 11, 3, 3, T=4, timed=1)) and copied(run(256, 40, 21, timed=1))
+    assert run(256, 11, 3, 3, T=4, n_g=2)[:3] == (2, 3, 3)  # CG and CG'
+    assert run(256, 11, 8, 3)[:2] == (1, 1)                 # nothing resident to share launches with
+    assert run(256, 11, 3, 3, T=4, mode=si.SI_PREFILL)[0] == 1
+    assert run(256, 11, 3, 0, E=4)[0] == 4
+    assert run(256, 11, 3, 0, Hs=704)[0] == 2
+    h = layer(256, 704, (8 / 11, 3 / 11, 0.0))
+    for capturing in (1, 0):
+        stub.hip_stub_capturing(capturing)
+        assert calls_of(h, lambda: forward(h, 256, 4, mode=si.SI_DECODE)) == IN_PLACE
+    x, y = np.zeros((4, 256), np.uint16), np.zeros((4, 256), np.float32)
+    S = si.si_stack_create([h])
+    assert copied(calls_of(h, lambda: si.si_stack_forward(S, x.ctypes.data, None, 4, 0, si.SI_DECODE, y.ctypes.data, prefetch=0, stream=0)))
+    si.si_stack_destroy(S)
+    assert calls_of(h, lambda: forward(h, 256, 4, mode=si.SI_DECODE)) == IN_PLACE
+    w = {"q_gate": np.zeros((1, 704, 128), np.uint8), "q_up": np.zeros((1, 704, 128), np.uint8), "q_down": np.zeros((1, 704, 128), np.uint8),
+         "z_gate": np.zeros((1, 704, 4), np.uint16), "z_up": np.zeros((1, 704, 4), np.uint16), "z_down": np.zeros((1, 11, 256), np.uint16)}
+    h = si.si_layer_create_q4(256, 704, 1, 1, w, 8 / 11, 3 / 11, 0.0, 8)
+    assert copied(calls_of(h, lambda: forward(h, 256, 4, mode=si.SI_DECODE)))
     """)
 
 
