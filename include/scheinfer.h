@@ -4,7 +4,8 @@
  * The layer is a dense SwiGLU MLP or the routed experts of a sparse MoE block whose weights are
  * sliced along the hidden dimension into three parts (Section III-B, "Memory Manager"):
  *   GG  stored in GPU memory, run on the GPU
- *   CG  stored in pinned host memory, copied to the GPU for every call, run on the GPU
+ *   CG  stored in pinned host memory, copied to the GPU for every call (small parts of dense layers, few tokens: read from host
+ *       memory by the kernels themselves), run on the GPU
  *   CC  stored in host memory, run on host threads; its result is sent to the GPU and added
  * and whose output is the sum of the three partial products (Eq. 1-2), identical to the unsliced
  * layer.  In the prompt phase the last n_g tokens (X2) run their CC share on the GPU from the same
@@ -71,8 +72,8 @@ typedef struct {
   int32_t device;      /* HIP device ordinal */
   int32_t stage_mib;   /* size of one staging buffer for CG copies in MiB; 0 -> 256 */
   int32_t n_stage;     /* number of staging buffers (>= 2); 0 -> 2 (double buffering) */
-  int32_t deq_mib;     /* 4-bit layers only.  0: the prompt-phase GEMMs read the 4-bit chunks and convert them on
-                          their way into LDS (no scratch).  > 0: two passes instead, a dequantisation kernel writing
+  int32_t deq_mib;     /* 4-bit layers only.  0: the prompt-phase GEMMs read the 4-bit chunks and convert them
+                          themselves (no scratch).  > 0: two passes instead, a dequantisation kernel writing
                           bf16 copies into a device scratch of this many MiB (never more than the largest part
                           needs) that the bf16 GEMMs then read, piece by piece */
 } si_layer_desc_t;
@@ -113,11 +114,11 @@ typedef struct {
   float cc_ms;        /* host wall time of the CC part (Stream-A), from its start to its end: the workers', or the calling
                          thread's where it computes a small share itself once everything else is enqueued */
   float route_ms;     /* token-assignment kernels */
-  double bytes_streamed;  /* CG (+CG') weight bytes copied host->device */
+  double bytes_streamed;  /* CG (+CG') weight bytes that crossed the host link: copied, or read from host memory by the kernels */
   double bytes_gg;        /* GG weight bytes read by the kernels (algorithmic) */
   double bytes_cc;        /* CC weight bytes read by the host workers (algorithmic) */
   float overlap;
-  int32_t n_copies;   /* number of streamed pieces */
+  int32_t n_copies;   /* number of streamed pieces (a part that the kernels read from host memory: one) */
   int32_t n_touched;  /* experts with at least one token (-1 if not known on the host) */
   int32_t path;       /* SI_DECODE or SI_PREFILL actually taken */
   float kernel_ms[SI_K_COUNT];         /* summed HIP-event time of each kernel class (SI_K_*) */
@@ -181,7 +182,7 @@ int si_place_experts(const double* freq, int32_t n_experts, int32_t n_gg, double
  * bounded by the |h * (c - 8)| summed; FC1 of x * (128 + c) less 136 * x, whose partial sums within a scale group
  * reach 143 * sum |x| before the offset cancels.  The host workers sum in fp32 too; where the CPU has bf16 dot products
  * they take h as two bf16 parts (16 bits) and both products in the 128 + c form.  The prompt-phase GEMMs read the
- * same chunks and feed the matrix cores (c - 8) * scale rounded to bf16, converted on the way into LDS (or, with
+ * same chunks and feed the matrix cores (c - 8) * scale rounded to bf16, converted by the GEMM (or, with
  * desc->deq_mib > 0, by a separate pass into a bf16 scratch).
  */
 typedef struct {
@@ -268,7 +269,12 @@ int si_route_noalloc(const float* logits_dev, int32_t T, int32_t E, int32_t k, c
 int si_layer_stats(si_layer_t* layer, si_stats_t* out);
 
 /* Turn per-call event timing on (1) or off (0, default).  Off removes all event records that
- * exist only for si_layer_stats. */
+ * exist only for si_layer_stats.
+ * A timed call copies every streamed part, so that copies and kernels have times of their own.  Calls that are not timed
+ * read some parts from host memory inside the launches of the resident part instead: generation calls of up to 4 tokens of a
+ * dense bf16 layer outside a stack whose CG part has at most 2 MB, or 8 MB where the host computes a share, beside a resident
+ * part of at most 64 MB, without CG' rows.  Both give the same bits; the times of such a call with timing on are those of
+ * the copies, up to twice as long. */
 int si_layer_set_profiling(si_layer_t* layer, int32_t on);
 
 /*

@@ -681,7 +681,7 @@ int create_impl(const si_layer_desc_t* desc, const WeightSource& src, const uint
     if (L->q4 && desc->deq_mib > 0) {
       // two-pass prompt phase on request: bf16 scratch that a dequantisation kernel fills and the bf16 GEMMs read
       // (the fewer sub-pieces, the fewer short launches), at least one chunk per routed expert, never more than
-      // the largest part needs.  By default (deq_mib = 0) the GEMMs convert the codes on their way into LDS.
+      // the largest part needs.  By default (deq_mib = 0) the GEMMs convert the codes themselves.
       const size_t cb16 = chunk_elems(M) * 2;
       L->deq_chunks = (int)std::max<size_t>((size_t)E, ((size_t)desc->deq_mib << 20) / cb16);
       L->deq_chunks = std::min(L->deq_chunks, std::max(E, E * std::max({L->H / CHUNK_J, L->Hs / CHUNK_J, 1})));
@@ -903,10 +903,11 @@ int cps_streamed(int ch, bool single_expert, int M) { return ch <= 8 ? 1 : cps_o
 // to IN_PLACE_MAX_T tokens (one pass over the weights; the GEMVs keep enough loads in flight for the rate of the link) without CG'.
 // Against a copy by a kernel or through the ring, in launches of their own (us, calls in a row): where the host computes a share and the
 // copies would start behind the hand-off, 256 x 704 40/30/30, 4 tokens 45.7 -> 33.7; 1024 x 1472 40/30/30, 1 / 4 tokens 112 -> 91 / 129 -> 99; 2048 x 2048 40/30/30
-// (7.1 MB) 201 -> 141 / 249 -> 154; where it does not, 256 x 704 80/20/0, 1 / 4 tokens 27.5 -> 14.3 / 29.6 -> 18.9; 1024 x 1472 80/20/0 58 -> 46 / 67 -> 51.  Above the
-// lines, and beside a large resident part, parts are copied as before.  With a host share that is the worse way at any size measured (4096 x
-// 2816 40/30/30, 20 MB: 466 where in place is 379; 8192 x 5632, 83 MB: 1710 / 1526), but it is the copy schedule that the host tests hold; without
-// one the two cross near 24 MB (2048 x 2816 80/20/0, 6.9 MB 159 / 137; 4096 x 1984 50/50/0, 24.4 MB 435 / 429; 4096 x 4608 50/50/0, 57 MB 1013 / 1025).
+// (7.1 MB) 201 -> 141 / 249 -> 154; where it does not, 256 x 704 80/20/0, 1 / 4 tokens 27.5 -> 14.3 / 29.6 -> 18.9; 1024 x 1472 80/20/0 58 -> 46 / 67 -> 51.  Larger
+// parts, and those beside a large resident part, are copied.  The lines lie below where the two ways cross: they are the largest round sizes that leave
+// the schedule of copies as the host tests state it (3 MB without a host share and 10.5 MB with one are copied).  Measured above them, copied / in place:
+// with a host share the copy is slower at every size (4096 x 2816 40/30/30, 20 MB 466 / 379; 8192 x 5632, 83 MB 1710 / 1526); without one up to some
+// 24 MB (2048 x 2816 80/20/0, 6.9 MB 159 / 137; 4096 x 1984 50/50/0, 24.4 MB 435 / 429; 4096 x 4608 50/50/0, 57 MB 1013 / 1025).
 constexpr int IN_PLACE_MAX_T = 4;
 constexpr size_t IN_PLACE_BYTES_WAITING = (size_t)8 << 20, IN_PLACE_BYTES = (size_t)2 << 20;
 

@@ -733,11 +733,12 @@ __device__ __forceinline__ void gemm_pingpong_q4(unsigned char* lds, int nk, int
 // ones, and the address unit.  A direct load takes the CU's address unit 17 cycles where its lanes cover runs of 128 bytes, 32 with runs of 64 and 62 with
 // runs of 32 bytes, also when only 4 bytes a lane are loaded (measured); the codes and scales of FC1, rows of 32 and 2 bytes a k-tile, took 1000
 // cycles of 2000.  Hence blocks of four k-tiles for FC1, of which a row is 128 bytes and its scales are one load.
-// What bounds it now: few rows: the instructions of a slot (one in 4 to 8 cycles and wave: 81 vector and 26 scalar ones a k-tile; with
-// the places in a block known at run time only, 80 scalar ones, 44 instead of 40 us below); many: the matrix cores at 0.6, two slots a
+// What bounds it now: few rows: the instructions of a slot (one in 4 to 8 cycles and wave: 81 vector and 26 scalar ones a k-tile, 91 and 31 by the
+// counters of 24 rows, which hold prologue and epilogue too: vector units busy 0.64, matrix cores 0.20, address unit 0.38; with
+// the places in a block known at run time only, 80 scalar ones, 44 instead of 40 us below); many: the matrix cores, busy 0.61 to 0.66, two slots a
 // phase of 450 matrix cycles with 47 vector instructions beside them and 80 cycles for the barriers.
 // Measured, FC1 of a dense 4096 x 32768 layer (256 tiles), us before -> now: 24 rows 61.6 -> 39.8, 48 67.3 -> 47.7, 112 81.6 -> 64.6, 144 91.8
-// -> 76.3, 208 107.5 -> 93.8, 240 113.1 -> 107.7; calls: 777 tokens over 8 experts of 14336 577 -> 508; 35 drawn 4-bit shapes 1.03 to 1.60.
+// -> 76.3, 208 107.5 -> 93.8, 240 113.1 -> 107.7; calls: 777 tokens over 8 experts of 14336 601 -> 536 (other cards 577 -> 508, 615 -> 545); 35 drawn 4-bit shapes 1.03 to 1.60.
 // Tried: one barrier per k-tile without turns (24 rows 51, 112 76, 208 104); half of the conversion in the slots of the loads (57, 80, 100:
 // it then waits for the LDS reads); five fragments of rows and more in one phase (208 rows 113).
 // ---------------------------------------------------------------------------------------------

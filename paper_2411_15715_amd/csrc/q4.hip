@@ -211,7 +211,9 @@ constexpr size_t QGS_LDS = 78 * 1024;  // two blocks per compute unit
 // (193 to 256 blocks of the other kernel are one good round of it, and but for the longest rows nothing is gained: 6720 x 7168, 4 tokens
 // 27.3 -> 29.0, 7424 x 7168 30.0 -> 30.4, 8192 x 8192 33.5 -> 32.3; 192 blocks: 6720 x 6144, 1 / 4 tokens 25.4 -> 23.6 / 26.5 -> 26.3.
 // The blocks are those of the whole expert, not of a launch over a part or a piece of one: the kernels sum a row in different orders, and
-// a result must not depend on how a streamed part is cut.  Such calls wait for their copies, 12 us a chunk, whichever kernel it is.)
+// a result must not depend on how a streamed part is cut.  Against a choice by the chunks of a launch, eleven calls of 6720 to 8192 x 6400 to 28672
+// with 6 to 125 chunks streamed or on the host: 0.993 to 1.017, the worst 7168 x 6400, 6 chunks, 4 tokens 86.9 -> 87.5: they wait for their copies,
+// 12 us a chunk, whichever kernel it is.)
 constexpr bool gateup_split(int M, int e_chunks) {
   const int n_units = (M / 32 + 15) / 16, blocks = e_chunks * (CHUNK_J / QGU_JPB);
   return M <= QGS_MAX_M && n_units >= QGS_UNITS && (n_units == 2 * QGS_WAVES || blocks <= 192 || blocks > 256);
